@@ -414,26 +414,49 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
               qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, R = cp.n_rows;
 
     if (dt == ax::F32) {
-        // fp32 models: one kernel per operation (the exactness configuration)
-        ax::launch_embed(dt, m->tok_emb, sv.row_tok, x, R, d_model, stream);
+        // fp32 models: five launches per layer.  The norms are folded into the GEMMs that read them; the first layer reads
+        // its rows straight from the embedding.
+        ax::GemmF32Args base{};
+        base.M = R;
+        base.eps = c.rms_eps;
+        const float* rope_cos = (const float*)(ws + L.rope_cos);
+        const float* rope_sin = (const float*)(ws + L.rope_sin);
         for (int l = 0; l < c.n_layers; ++l) {
-            ax::launch_rmsnorm(dt, x, m->norm_attn[(size_t)l], h, nullptr, R, d_model, c.rms_eps, stream);
-            { ProfScope ps(m, 0, stream);
-              ax::launch_gemm(dt, ax::EPI_STORE_F32, h, m->wqkv[(size_t)l], nullptr, qkv, R, qkv_rows, d_model, stream); }
-            ax::launch_rope_kv(dt, qkv, qb, kg, l, sv, (const float*)(ws + L.rope_cos),
-                               (const float*)(ws + L.rope_sin), c.n_q_heads, stream);
+            {
+                ax::GemmF32Args g = base;
+                g.A = l == 0 ? (const float*)m->tok_emb : x; g.a_rows = l == 0 ? sv.row_tok : nullptr;
+                g.gain = (const float*)m->norm_attn[(size_t)l]; g.W = (const float*)m->wqkv[(size_t)l];
+                g.N = qkv_rows; g.K = d_model; g.C = qkv;
+                g.rope.kv = kg; g.rope.layer = l; g.rope.n_q_heads = c.n_q_heads; g.rope.q_out = qb;
+                g.rope.row_pos = sv.row_pos; g.rope.row_slot = sv.row_slot; g.rope.cos = rope_cos; g.rope.sin = rope_sin;
+                ProfScope ps(m, 0, stream);
+                ax::launch_gemm_f32(ax::EPI_QKV, g, stream);
+            }
             { ProfScope ps(m, 1, stream);
               ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, nullptr, 1, stream); }
-            { ProfScope ps(m, 2, stream);
-              ax::launch_gemm(dt, ax::EPI_RESIDUAL, attn, m->wo[(size_t)l], nullptr, x, R, d_model, qdim, stream); }
-            ax::launch_rmsnorm(dt, x, m->norm_mlp[(size_t)l], h, nullptr, R, d_model, c.rms_eps, stream);
-            { ProfScope ps(m, 3, stream);
-              ax::launch_gemm(dt, ax::EPI_SWIGLU, h, m->w_gate[(size_t)l], m->w_up[(size_t)l], ffn, R, c.d_ff, d_model, stream); }
-            { ProfScope ps(m, 4, stream);
-              ax::launch_gemm(dt, ax::EPI_RESIDUAL, ffn, m->w_down[(size_t)l], nullptr, x, R, d_model, c.d_ff, stream); }
+            {
+                ax::GemmF32Args g = base;
+                g.A = (const float*)attn; g.W = (const float*)m->wo[(size_t)l]; g.N = d_model; g.K = qdim; g.C = x;
+                if (l == 0) { g.res = (const float*)m->tok_emb; g.res_rows = sv.row_tok; }
+                ProfScope ps(m, 2, stream);
+                ax::launch_gemm_f32(ax::EPI_RESIDUAL, g, stream);
+            }
+            {
+                ax::GemmF32Args g = base;
+                g.A = x; g.gain = (const float*)m->norm_mlp[(size_t)l]; g.W = (const float*)m->w_gate[(size_t)l];
+                g.W2 = (const float*)m->w_up[(size_t)l]; g.N = c.d_ff; g.K = d_model; g.C = (float*)ffn;
+                ProfScope ps(m, 3, stream);
+                ax::launch_gemm_f32(ax::EPI_SWIGLU, g, stream);
+            }
+            {
+                ax::GemmF32Args g = base;
+                g.A = (const float*)ffn; g.W = (const float*)m->w_down[(size_t)l]; g.N = d_model; g.K = c.d_ff; g.C = x;
+                ProfScope ps(m, 4, stream);
+                ax::launch_gemm_f32(ax::EPI_RESIDUAL, g, stream);
+            }
         }
         if (n_out > 0) {
-            ax::launch_rmsnorm(dt, x, m->final_norm, h, sv.out_rows, n_out, d_model, c.rms_eps, stream);
+            ax::launch_rmsnorm_f32(x, (const float*)m->final_norm, (float*)h, sv.out_rows, n_out, d_model, c.rms_eps, stream);
             if (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_ALL_LOGITS) {
                 ProfScope ps(m, 5, stream);
                 ax::launch_gemm(dt, ax::EPI_STORE_F32, h, m->lm_head, nullptr, out, n_out, c.vocab, d_model, stream);

@@ -2,8 +2,7 @@
 // of a sequence attend to the P cached positions and to each other; row at position p sees
 // keys 0..p (prefix caching relies on exactly this causality, paper Sec. 2.3).
 //
-//   * attn_simple_kernel: one wavefront per (row, query head), fp32 arithmetic, any head_dim
-//     up to 256 and either storage type.  It is the fp32 models' path.
+//   * attn_f32_kernel: the fp32 models' path, fp32 matrix instructions, any even head_dim up to 256.
 //   * attn_split_kernel + attn_combine_kernel: 16-bit path on the matrix cores (fp16 q, K, V and
 //     probabilities, fp32 accumulation; used by bf16-weight models).  The query rows
 //     of the G heads that share one KV head are stacked into one matrix (row = t*G + g), cut
@@ -21,87 +20,145 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float ld_f32(const float* p) { return *p; }
-__device__ __forceinline__ float ld_f32(const f16* p) { return (float)*p; }
-__device__ __forceinline__ void st_f32(float* p, float v) { *p = v; }
-__device__ __forceinline__ void st_f32(f16* p, float v) { *p = (f16)v; }
+// ------------------------------------------------------------------------------ fp32 kernel
+// fp32 models: everything on the fp32 matrix instruction (16x16x4), one block per tile of 16 stacked rows (t * G + g) and
+// KV head; its NW wavefronts take every NW-th page of 16 keys with their own online softmax and meet in LDS at the end,
+// so a call of a few rows still keeps NW chains of page loads in flight and needs no second kernel.  (A wavefront
+// per (row, query head) walking its keys 64 at a time took 137 us on a 5-row step over 512 keys; this takes 13 us.)
+//
+// S^T = K * Q^T per page: lane l supplies slot l % 16 of the page (and stacked row l % 16 of q) at channels 16 c +
+// 4 * (l / 16) .. + 3 - one float4, element j for instruction j, the same order of channels on both sides - and receives
+// the scores of keys 4 * (l / 16) .. + 3 for stacked row l % 16.  That is the B operand of O^T = V^T * P^T as it
+// stands: V pages are token-minor, so the matching A operand (channel l % 16 of a 16-channel tile, keys 4 * (l / 16) .. + 3)
+// is one float4 as well.
+//
+// HDT: 16-channel tiles the registers hold (head_dim <= 16 * HDT; channels past head_dim are zeros).
+template <int HDT, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, KVGeom kv, int layer,
+                                                           const int* __restrict__ tile_info, const int* __restrict__ bt, int Hq,
+                                                           int subs) {
+    __shared__ __attribute__((aligned(16))) f32x4 s_o[NW][HDT][64];
+    __shared__ float s_m[NW][16], s_l[NW][16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+    const int hd = kv.head_dim, Hkv = kv.n_kv_heads, G = Hq / Hkv, hk = blockIdx.y;
+    const int* ti = tile_info + (blockIdx.x / subs) * 8;         // a record covers subs tiles of 16 rows
+    const int4 ti0 = *(const int4*)ti, ti1 = *(const int4*)(ti + 4);
+    const int P = ti0.z, T = ti0.w, row0 = ti1.x, r0 = ti0.y + (int)(blockIdx.x % subs) * 16, n_stacked = T * G;
+    if (r0 >= n_stacked) return;                                 // the record's last tiles may lie past the sequence's rows
+    const int* tab = bt + ti1.y;
+    const int kv_len = P + T;
 
-__device__ __forceinline__ float wave_max(float v) {
+    const int rq = min(r0 + lr, n_stacked - 1), tq = rq / G, pos_q = P + tq;
+    const float* qrow = q + ((long long)(row0 + tq) * Hq + hk * G + rq % G) * hd;
+    const float* Kp = (const float*)kv.base + kv.plane(layer, 0, hk);
+    const float* Vp = (const float*)kv.base + kv.plane(layer, 1, hk);
+    const bool vec = (hd & 3) == 0;
+    auto load_row = [&](const float* row, int c) {               // channels 16 c + 4 lg .. + 3 of a row of hd channels
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        const int ch = c * 16 + lg * 4;
+        if (vec) {
+            if (ch < hd) v = *(const f32x4*)(row + ch);
+        } else {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ float wave_add(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// ------------------------------------------------------------------------------ simple kernel
-// grid (n_rows, Hq), 64 threads.  Keys are taken 64 at a time: lane j scores key base + j,
-// the wavefront reduces max and sum with shuffles (online softmax), then lane c accumulates
-// output channels c, c + 64, ... over the 64 keys (probabilities broadcast by shuffle).
-template <typename T, int HD_MAX>
-__global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q, T* __restrict__ out,
-                                                         KVGeom kv, int layer,
-                                                         const int* __restrict__ row_pos,
-                                                         const int* __restrict__ row_seq,
-                                                         const int* __restrict__ seq_bt,
-                                                         const int* __restrict__ bt, int Hq) {
-    constexpr int NC = HD_MAX / 64;
-    const int r = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int hd = kv.head_dim, B = kv.block_tokens;
-    const int hk = h / (Hq / kv.n_kv_heads);
-    const int pos = row_pos[r];
-    const int* tab = bt + seq_bt[row_seq[r]];
-    const T* Kp = (const T*)kv.base + kv.plane(layer, 0, hk);
-    const T* Vp = (const T*)kv.base + kv.plane(layer, 1, hk);
-    const T* qr = q + ((long long)r * Hq + h) * hd;
-    const float scale = 1.0f / sqrtf((float)hd);
-
-    __shared__ float sq[HD_MAX];
-    for (int c = lane; c < hd; c += 64) sq[c] = ld_f32(qr + c);
-    __syncthreads();
-
-    float m = -INFINITY, l = 0.f, o[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) o[i] = 0.f;
-
-    for (int base = 0; base <= pos; base += 64) {
-        const int j = base + lane;
-        float s = -INFINITY;
-        if (j <= pos) {
-            const T* kr = Kp + ((long long)tab[j / B] * B + j % B) * hd;
-            float d = 0.f;
-            for (int c = 0; c < hd; ++c) d = fmaf(sq[c], ld_f32(kr + c), d);
-            s = d * scale;
+            for (int i = 0; i < 4; ++i) if (ch + i < hd) v[i] = row[ch + i];
         }
-        const float mn = fmaxf(m, wave_max(s));            // finite: key `base` is always visible
-        const float p = (j <= pos) ? expf(s - mn) : 0.f;
-        const float alpha = expf(m - mn);                  // exp(-inf) = 0 on the first chunk
-        l = l * alpha + wave_add(p);
+        return v;
+    };
+    f32x4 qf[HDT];
 #pragma unroll
-        for (int i = 0; i < NC; ++i) o[i] *= alpha;
-        const int cnt = min(64, pos - base + 1);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pj = __shfl(p, jj, 64);
-            const int key = base + jj;
-            const T* vb = Vp + (long long)tab[key / B] * B * hd + key % B;
+    for (int c = 0; c < HDT; ++c) qf[c] = load_row(qrow, c);
+
+    const float scale = 1.0f / sqrtf((float)hd);
+    float m = -INFINITY, l = 0.f;                                // l: this lane's keys only, summed over the lanes at the end
+    f32x4 o[HDT];
 #pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                const int c = lane + 64 * i;
-                if (c < hd) o[i] = fmaf(pj, ld_f32(vb + (long long)c * B), o[i]);
-            }
+    for (int c = 0; c < HDT; ++c) o[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    const int r_last = min(r0 + 15, n_stacked - 1);
+    const int pages = (P + r_last / G + 16) >> 4;                // up to the page of the tile's last visible key
+    // (fetching the next page's operands ahead was slower, 12.9 -> 15.6 us: a wavefront has two or three pages, and the
+    // second copy of the loop body costs more instruction fetches than the loads it hides)
+    for (int pg = wave; pg < pages; pg += NW) {
+        const int blk = tab[pg], kv0 = pg * 16;
+        const float* kp = Kp + ((long long)blk * 16 + lr) * hd;
+        const float* vp = Vp + (long long)blk * 16 * hd + lg * 4;
+        f32x4 kf[HDT], vf[HDT];
+#pragma unroll
+        for (int c = 0; c < HDT; ++c) kf[c] = load_row(kp, c);
+#pragma unroll
+        for (int c = 0; c < HDT; ++c) {
+            vf[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (c * 16 + lr < hd) vf[c] = *(const f32x4*)(vp + (c * 16 + lr) * 16);
+        }
+        if (kv0 + 16 > kv_len) {                                 // slots past the sequence's end hold anything: exact zeros
+#pragma unroll
+            for (int c = 0; c < HDT; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) if (kv0 + lg * 4 + i >= kv_len) vf[c][i] = 0.f;
+        }
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};     // two chains of dependent products
+#pragma unroll
+        for (int c = 0; c < HDT; ++c) {
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][0], qf[c][0], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][1], qf[c][1], s1, 0, 0, 0);
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][2], qf[c][2], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][3], qf[c][3], s1, 0, 0, 0);
+        }
+        float mx = -INFINITY;
+        f32x4 p;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = kv0 + lg * 4 + i <= pos_q ? (s0[i] + s1[i]) * scale : -INFINITY;
+            mx = fmaxf(mx, p[i]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float mn = fmaxf(m, mx), mu = mn == -INFINITY ? 0.f : mn;  // nothing visible yet: exp(-inf) = 0 all the same
+        const float alpha = expf(m - mu);
+        l *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = expf(p[i] - mu);
+            l += p[i];
         }
         m = mn;
-    }
-    T* orow = out + ((long long)r * Hq + h) * hd;
 #pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const int c = lane + 64 * i;
-        if (c < hd) st_f32(orow + c, o[i] / l);
+        for (int c = 0; c < HDT; ++c) {
+            o[c] *= alpha;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][i], p[i], o[c], 0, 0, 0);
+        }
+    }
+
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (lg == 0) { s_m[wave][lr] = m; s_l[wave][lr] = l; }
+#pragma unroll
+    for (int c = 0; c < HDT; ++c) s_o[wave][c][lane] = o[c];
+    __syncthreads();
+    // wavefront w finishes channel tiles w, w + NW, ..: register i of lane l is channel 4 * (l / 16) + i of stacked row l % 16
+    float M = -INFINITY, L = 0.f, wt[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][lr]);       // finite: every row sees key 0
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        wt[w] = expf(s_m[w][lr] - M);
+        L += wt[w] * s_l[w][lr];
+    }
+    if (r0 + lr >= n_stacked) return;
+    float* orow = out + ((long long)(row0 + tq) * Hq + hk * G + rq % G) * hd;
+    for (int c = wave; c < HDT; c += NW) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += wt[w] * s_o[w][c][lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int ch = c * 16 + lg * 4 + i;
+            if (ch < hd) orow[ch] = v[i] / L;
+        }
     }
 }
 
@@ -765,10 +822,14 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
                       int n_q_heads, float* partials, int n_splits, hipStream_t s, long long q_lo_off,
                       long long out_lo_off) {
     if (dt == F32) {
-        dim3 grid(sv.n_rows, n_q_heads);
-        attn_simple_kernel<float, 256><<<grid, 64, 0, s>>>((const float*)q, (float*)out, kv, layer,
-                                                           sv.row_pos, sv.row_seq, sv.seq_bt, sv.bt,
-                                                           n_q_heads);
+        const int subs = 2 * sv.tile_nq, hd = kv.head_dim;      // 16-row tiles per record of 32 * tile_nq rows
+        dim3 grid(sv.n_tiles * subs, kv.n_kv_heads);
+        const float* qf = (const float*)q;
+        float* of = (float*)out;
+        // wavefronts per block: as many as the LDS record of their partial outputs (4 KB per 64 channels each) leaves room for
+        if (hd <= 64) attn_f32_kernel<4, 16><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else if (hd <= 128) attn_f32_kernel<8, 8><<<grid, 512, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else attn_f32_kernel<16, 4><<<grid, 256, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
         return;
     }
     AttnArgs a{};

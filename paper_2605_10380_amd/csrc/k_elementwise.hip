@@ -1,19 +1,10 @@
-// Small memory-bound kernels of the extend forward: embedding gather, RMSNorm, rotary + paged
-// KV append, vocabulary argmax, greedy draft acceptance, copy-on-write block copy.
+// Small memory-bound kernels of the extend forward: embedding gather, RMSNorm, vocabulary argmax, greedy draft acceptance, copy-on-write block copy.
 #include "kernels.h"
 
 namespace ax {
 
 typedef __bf16 bf16;
 typedef _Float16 f16;     // activation and KV-cache type of bf16-weight models
-
-__device__ __forceinline__ float to_f32(float v) { return v; }
-__device__ __forceinline__ float to_f32(bf16 v) { return (float)v; }
-__device__ __forceinline__ float to_f32(f16 v) { return (float)v; }
-template <typename T> __device__ __forceinline__ T from_f32(float v);
-template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ bf16 from_f32<bf16>(float v) { return (bf16)v; }  // RNE
-template <> __device__ __forceinline__ f16 from_f32<f16>(float v) { return (f16)v; }     // RNE
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -22,23 +13,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // ---------------------------------------------------------------- embedding gather
-template <typename T>
-__global__ void embed_kernel(const T* __restrict__ emb, const int* __restrict__ row_tok,
-                             float* __restrict__ x, int d) {
-    const int r = blockIdx.x;
-    const T* src = emb + (long long)row_tok[r] * d;
-    float* dst = x + (long long)r * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = to_f32(src[c]);
-}
-
-void launch_embed(DType dt, const void* emb, const int* row_tok, float* x, int n_rows, int d,
-                  hipStream_t s) {
-    if (dt == F32)
-        embed_kernel<float><<<n_rows, 256, 0, s>>>((const float*)emb, row_tok, x, d);
-    else
-        embed_kernel<bf16><<<n_rows, 256, 0, s>>>((const bf16*)emb, row_tok, x, d);
-}
-
 // Embedding gather that also prepares the first RMSNorm of bf16-weight models: the fp16 copy
 // scaled by the norm gain and the row's sum of squares (in partial 0; the other partials are
 // zeroed so that the row looks like the output of a GEMM with `nparts` column blocks).
@@ -72,15 +46,13 @@ void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, fl
 }
 
 // ---------------------------------------------------------------- RMSNorm
-// One 256-thread block per row: sum of squares in fp32 (wavefront shuffles, then LDS across the
-// four wavefronts), then x * rsqrt(mean + eps) * gain.
-template <typename TG, typename T>
-__global__ void rmsnorm_kernel(const float* __restrict__ x, const TG* __restrict__ gain,
-                               T* __restrict__ h, const int* __restrict__ rows, int d, float eps) {
+// The norm in front of an fp32 model's LM head (the others are folded into the GEMMs).  One 256-thread block per row: sum
+// of squares (wavefront shuffles, then LDS across the four wavefronts), then x * rsqrt(mean + eps) * gain.
+__global__ void rmsnorm_f32_kernel(const float* __restrict__ x, const float* __restrict__ gain, float* __restrict__ h,
+                                   const int* __restrict__ rows, int d, float eps) {
     __shared__ float part[4];
     const int i = blockIdx.x;
-    const int r = rows ? rows[i] : i;
-    const float* xr = x + (long long)r * d;
+    const float* xr = x + (long long)rows[i] * d;
     float ss = 0.f;
     for (int c = threadIdx.x; c < d; c += 256) {
         float v = xr[c];
@@ -89,66 +61,13 @@ __global__ void rmsnorm_kernel(const float* __restrict__ x, const TG* __restrict
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();
-    const float tot = part[0] + part[1] + part[2] + part[3];
-    const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-    T* hr = h + (long long)i * d;
-    for (int c = threadIdx.x; c < d; c += 256) hr[c] = from_f32<T>(xr[c] * inv * to_f32(gain[c]));
+    const float inv = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)d + eps);
+    float* hr = h + (long long)i * d;
+    for (int c = threadIdx.x; c < d; c += 256) hr[c] = xr[c] * inv * gain[c];
 }
 
-void launch_rmsnorm(DType dt, const float* x, const void* gain, void* h, const int* rows,
-                    int n_rows, int d, float eps, hipStream_t s) {
-    if (dt == F32)
-        rmsnorm_kernel<float, float><<<n_rows, 256, 0, s>>>(x, (const float*)gain, (float*)h, rows, d, eps);
-    else
-        rmsnorm_kernel<bf16, f16><<<n_rows, 256, 0, s>>>(x, (const bf16*)gain, (f16*)h, rows, d, eps);
-}
-
-// ---------------------------------------------------------------- rotary + paged KV append
-// grid (n_rows, Hq + 2*Hkv); one block per (row, head).  Pair (j, j + hd/2) is rotated by
-// the angle pos * base^(-2j/hd); cos / sin come from a host-built table [max_pos][hd/2].
-template <typename T>
-__global__ void rope_kv_kernel(const float* __restrict__ qkv, T* __restrict__ q_out, KVGeom kv,
-                               int layer, const int* __restrict__ row_pos,
-                               const int* __restrict__ row_seq, const int* __restrict__ seq_bt,
-                               const int* __restrict__ bt, const float* __restrict__ rope_cos,
-                               const float* __restrict__ rope_sin, int Hq) {
-    const int r = blockIdx.x, head = blockIdx.y;
-    const int hd = kv.head_dim, half = hd >> 1, Hkv = kv.n_kv_heads, B = kv.block_tokens;
-    const int pos = row_pos[r];
-    const float* src = qkv + (long long)r * (Hq + 2 * Hkv) * hd + (long long)head * hd;
-    T* pool = (T*)kv.base;
-    if (head < Hq + Hkv) {
-        const float* cs = rope_cos + (long long)pos * half;
-        const float* sn = rope_sin + (long long)pos * half;
-        T* dst;
-        if (head < Hq) {
-            dst = q_out + ((long long)r * Hq + head) * hd;
-        } else {
-            const int blk = bt[seq_bt[row_seq[r]] + pos / B];
-            dst = pool + kv.plane(layer, 0, head - Hq) + ((long long)blk * B + pos % B) * hd;
-        }
-        for (int j = threadIdx.x; j < half; j += blockDim.x) {
-            const float a = src[j], b = src[j + half], c = cs[j], sgn = sn[j];
-            dst[j] = from_f32<T>(a * c - b * sgn);
-            dst[j + half] = from_f32<T>(b * c + a * sgn);
-        }
-    } else {
-        const int blk = bt[seq_bt[row_seq[r]] + pos / B];
-        T* dst = pool + kv.plane(layer, 1, head - Hq - Hkv) + (long long)blk * B * hd + pos % B;
-        for (int c = threadIdx.x; c < hd; c += blockDim.x) dst[(long long)c * B] = from_f32<T>(src[c]);
-    }
-}
-
-void launch_rope_kv(DType dt, const float* qkv, void* q_out, KVGeom kv, int layer,
-                    const StepView& sv, const float* rope_cos, const float* rope_sin,
-                    int n_q_heads, hipStream_t s) {
-    dim3 grid(sv.n_rows, n_q_heads + 2 * kv.n_kv_heads);
-    if (dt == F32)
-        rope_kv_kernel<float><<<grid, 64, 0, s>>>(qkv, (float*)q_out, kv, layer, sv.row_pos, sv.row_seq,
-                                                  sv.seq_bt, sv.bt, rope_cos, rope_sin, n_q_heads);
-    else
-        rope_kv_kernel<f16><<<grid, 64, 0, s>>>(qkv, (f16*)q_out, kv, layer, sv.row_pos, sv.row_seq,
-                                                 sv.seq_bt, sv.bt, rope_cos, rope_sin, n_q_heads);
+void launch_rmsnorm_f32(const float* x, const float* gain, float* h, const int* rows, int n_rows, int d, float eps, hipStream_t s) {
+    rmsnorm_f32_kernel<<<n_rows, 256, 0, s>>>(x, gain, h, rows, d, eps);
 }
 
 // ---------------------------------------------------------------- vocabulary argmax

@@ -40,9 +40,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-void launch_gemm_f32(Epilogue epi, const float* A, const float* W, const float* W2, float* C,
-                     int M, int N, int K, hipStream_t s);
-
 __device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
 
 // 8 bf16 (one 16-byte fragment) -> 8 fp16.  A bf16 is the top half of an fp32, so each half of
@@ -1528,7 +1525,10 @@ int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 void launch_gemm(DType dt, Epilogue epi, const void* A, const void* W, const void* W2, void* C,
                  int M, int N, int K, hipStream_t s) {
     if (dt == F32) {
-        launch_gemm_f32(epi, (const float*)A, (const float*)W, (const float*)W2, (float*)C, M, N, K, s);
+        GemmF32Args g{};
+        g.A = (const float*)A; g.W = (const float*)W; g.W2 = (const float*)W2; g.C = (float*)C;
+        g.M = M; g.N = N; g.K = K;
+        launch_gemm_f32(epi, g, s);
         return;
     }
     GemmArgs g{};

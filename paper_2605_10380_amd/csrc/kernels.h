@@ -97,22 +97,29 @@ void launch_pack_weights(const void* src, void* dst, int N, int K, hipStream_t s
 void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off,
                        float* ssq, int nparts, int n_rows, int d, hipStream_t s);
 
-// x[r, :] = emb[row_tok[r], :] widened to fp32
-void launch_embed(DType dt, const void* emb, const int* row_tok, float* x, int n_rows, int d,
-                  hipStream_t s);
-// h[i, :] = rmsnorm(x[rows ? rows[i] : i, :]) * gain, written in the activation type
-void launch_rmsnorm(DType dt, const float* x, const void* gain, void* h, const int* rows,
-                    int n_rows, int d, float eps, hipStream_t s);
+// fp32 models: h[i, :] = rmsnorm(x[rows[i], :]) * gain
+void launch_rmsnorm_f32(const float* x, const float* gain, float* h, const int* rows, int n_rows, int d, float eps, hipStream_t s);
+// One GEMM of an fp32 model: C = A[M,K] * W[N,K]^T.  EPI_STORE_F32: C [M,N].  EPI_RESIDUAL: C [M,N] = res + product.
+// EPI_SWIGLU: C [M,N] = silu(A W^T) * (A W2^T).  EPI_QKV: rotary on q and k, q -> rope.q_out [M, Hq, hd], k and v -> the
+// rows' KV slots, C [M,N] = the products before the rotation; N = (Hq + 2 Hkv) * hd.
+struct GemmF32Args {
+    const float* A;                   // [rows, K]
+    const int* a_rows;                // optional gather: A row of output row m is a_rows[m]
+    const float *W, *W2;              // [N, K]; W2 only for EPI_SWIGLU
+    const float* gain;                // [K]: the A rows are RMS-normalised with this gain first; NULL = taken as they are
+    float eps;
+    int M, N, K;
+    float* C;
+    const float* res;                 // EPI_RESIDUAL: NULL = C itself (updated in place)
+    const int* res_rows;              // ... row of res that belongs to output row m (NULL = m)
+    RopeArgs rope;                    // EPI_QKV (q_out is fp32)
+};
+void launch_gemm_f32(Epilogue epi, const GemmF32Args& g, hipStream_t s);
 // C = A[M,K] * W[N,K]^T with fp32 accumulation.  A is of the activation type, W of the weight
 // type.  EPI_STORE_F32: C float [M,N].  EPI_RESIDUAL: C float [M,N] += .
 // EPI_SWIGLU: C (activation type) [M,N] = silu(A*W^T) * (A*W2^T).
 void launch_gemm(DType dt, Epilogue epi, const void* A, const void* W, const void* W2, void* C,
                  int M, int N, int K, hipStream_t s);
-// rotary on q and k heads of qkv (fp32 [n_rows, (Hq+2Hkv)*hd]); q -> q_out [n_rows, Hq, hd]
-// (activation type), k and v -> pages of `layer`.
-void launch_rope_kv(DType dt, const float* qkv, void* q_out, KVGeom kv, int layer,
-                    const StepView& sv, const float* rope_cos, const float* rope_sin,
-                    int n_q_heads, hipStream_t s);
 // Causal attention of the new rows over the paged cache (which already holds the new rows).
 // out [n_rows, Hq, hd] in the activation type.  `partials` is fp32 scratch for the split-KV
 // path (bf16 only); n_splits >= 1.

@@ -216,6 +216,26 @@ def test_single_layer_stages(torch_cuda, which, P, T):
     dm.close()
 
 
+@pytest.mark.parametrize("hd,d,F,P,T", [(18, 68, 77, 15, 2), (64, 256, 688, 31, 129), (96, 100, 203, 0, 17),
+                                        (130, 72, 64, 16, 16), (256, 64, 129, 250, 9)])
+def test_f32_model_head_dims_and_row_edges(torch_cuda, hd, d, F, P, T):
+    """fp32 kernels at the edges of their tiles: head_dim off the 4- and 16-channel grid and at its largest, K off the
+    16-wide step, rows around one and eight row tiles, caches that end on and off a page."""
+    from paper_2605_10380_amd import binding as B
+    sh = I.DecoderShape("f32-edge", 2, d, 6, 2, hd, F, 301, "f32")
+    w = I.make_weights(sh, 11)
+    toks = I.templated_prompt(sh.vocab, 11, P + T)
+    dm = B.DeviceModel(sh, w, max_pos=512, max_tokens=256, pool_tokens=1024, pool_fill=0xFF)
+    kv = dm.new_kv()
+    okv = O.KVCache(sh.n_layers, sh.n_kv_heads, sh.head_dim)
+    if P:
+        dm.extend(kv, toks[:P])
+        O.forward(sh, w, toks[:P], okv)
+    got = dm.extend(kv, toks[P:], B.AX_OUT_ALL_LOGITS).cpu().numpy().astype(np.float64)
+    assert np.abs(got - O.forward(sh, w, toks[P:], okv)).max() <= 1e-4
+    dm.close()
+
+
 def test_measured_peaks_probe(torch_cuda):
     """The machine-rate probes leave their buffer's first half untouched (the read-only stream writes
     nothing, the copy kernel fills the second half with the first) and report rates that a working
