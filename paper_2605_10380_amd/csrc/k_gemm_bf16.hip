@@ -27,68 +27,9 @@
 #include <cstdlib>
 #include <type_traits>
 
-#include "kernels.h"
+#include "gemm_device.h"
 
 namespace ax {
-
-typedef __bf16 bf16;
-typedef _Float16 f16;
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
-
-// 8 bf16 (one 16-byte fragment) -> 8 fp16.  A bf16 is the top half of an fp32, so each half of
-// a dword becomes an fp32 by a shift or a mask; bf16 has fewer significant bits than fp16, so
-// the round-toward-zero pack is exact in fp16's normal range.
-__device__ __forceinline__ f16x8 bf16x8_to_f16x8(u32x4 raw) {
-    f16x8 out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float lo = __uint_as_float(raw[i] << 16), hi = __uint_as_float(raw[i] & 0xffff0000u);
-        const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(lo, hi));
-        out[2 * i] = h[0];
-        out[2 * i + 1] = h[1];
-    }
-    return out;
-}
-__device__ __forceinline__ f16x8 load_w(const bf16* p) { return *(const f16x8*)p; }     // packed weights are already fp16
-
-// Split activations (see GemmArgs): v goes out as hi = fp16(v) and, lo_off elements further on, lo = fp16(v - hi).
-__device__ __forceinline__ void store_split(f16* p, long long lo_off, float v) {
-    const f16 hi = (f16)v;
-    *p = hi;
-    if (lo_off) p[lo_off] = (f16)(v - (float)hi);
-}
-__device__ __forceinline__ void store_split4(f16* p, long long lo_off, const float (&v)[4]) {
-    f16x4 hi, lo;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        hi[r] = (f16)v[r];
-        lo[r] = (f16)(v[r] - (float)hi[r]);
-    }
-    *(f16x4*)p = hi;
-    if (lo_off) *(f16x4*)(p + lo_off) = lo;
-}
-
-// ------------------------------------------------------------------------------ weight layout
-// bf16 weight matrices are not read as given.  ax_model_create repacks every [N, K] matrix once,
-// widening each bf16 to fp16 on the way (the round-toward-zero pack above: exact in fp16's normal
-// range; the kernels multiply on the fp16 MFMA), into panels of 16 rows; a panel is cut into chunks of 32 k, and a chunk (1 KB) is stored in
-// the order the 16x16x32 MFMA takes it: 4 k-groups of 8, inside a group the 16 rows, each with
-// its 8 consecutive k (16 bytes).  A wavefront's weight load for one MFMA step is then 1 KB of
-// contiguous memory instead of 16 pieces of 64 bytes from 16 rows - measured 7-19 % faster
-// streaming in the skinny kernels and ~1.4x in the tile kernels that feed MFMA operands straight
-// from global memory.  Element (n, k) sits at
-//     (n / 16) * 16 K  +  (k / 32) * 512  +  ((k % 32) / 8) * 128  +  (n % 16) * 8  +  k % 8.
-// N % 16 == 0 and K % 32 == 0 (guaranteed by the model configuration checks).
-__device__ __forceinline__ long long packed_row(int n, int K) { return (long long)(n >> 4) * 16 * K + (n & 15) * 8; }
-constexpr int PK_KG = 128;        // elements between k-groups of 8 inside a chunk
-constexpr int PK_CHUNK = 512;     // elements per chunk of 32 k  (so k advances by 32 -> +512: "k * 16")
 
 // out-of-place repack: one thread per 16-byte unit of the destination (coalesced writes)
 // A bf16 weight beyond fp16's range (|w| > 65504, infinities, NaNs) does not survive: `bad` reports it.
@@ -111,113 +52,6 @@ __global__ void pack_weights_kernel(const u32x4* __restrict__ src, u32x4* __rest
 
 void launch_pack_weights(const void* src, void* dst, int N, int K, hipStream_t s, int* bad) {
     pack_weights_kernel<<<2048, 256, 0, s>>>((const u32x4*)src, (u32x4*)dst, N, K, bad);
-}
-
-// 1 / rms of A rows from the column-block partial sums of x^2 their producer left behind.
-// A kernel of this size is a chain of memory round trips, so every helper here requests all
-// the partials it will need before it adds anything up: the index is clamped instead of
-// branched on (no load sits behind a branch), values past the end are dropped when summing.
-//
-// One row's partials spread over a group of G lanes (gl = lane within the group), 4 G per round.
-template <int G>
-__device__ __forceinline__ float ssq_lane_sum(const float* __restrict__ src, int nparts, int gl) {
-    float v = 0.f;
-    for (int base = 0; base < nparts; base += 4 * G) {
-        float t[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) t[u] = src[min(base + u * G + gl, nparts - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v += base + u * G + gl < nparts ? t[u] : 0.f;
-    }
-    return v;
-}
-// One row by one wavefront; every lane gets the result.
-__device__ __forceinline__ float wave_inv_rms(const float* __restrict__ ssq, int row, int nparts,
-                                              int d_norm, float eps, int lane) {
-    float v = ssq_lane_sum<64>(ssq + (long long)row * nparts, nparts, lane);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return 1.0f / sqrtf(v / (float)d_norm + eps);
-}
-
-// Block-wide: 1 / rms of `rows` A-rows into s_inv[0..rows).  Half a wavefront (32 lanes) owns a
-// row and a thread works on INV_BATCH rows at a time (a power of two up to 16): their
-// 4 x INV_BATCH loads are in flight together, so the table costs one memory round trip per
-// INV_BATCH rows of a thread (and per 128 partials of a row), not one per load.
-// The INV_BATCH per-lane sums are then added across the 32 lanes with a transposing butterfly:
-// at each stage a lane hands half of its values to its partner and keeps the other half, so the
-// batch costs INV_BATCH - 1 + (5 - log2 INV_BATCH) cross-lane exchanges instead of 5 per row and
-// ends with each row's total in its own lanes - one division and square root per thread, not one
-// per row.  (Five exchanges and a square root per row, one row after the other, were ~4 us of a
-// 128-row block's prologue.)  The caller synchronises before reading s_inv.
-template <int INV_BATCH>
-__device__ __forceinline__ void block_inv_rms(const GemmArgs& g, int first_row, int rows, float* s_inv) {
-    static_assert(INV_BATCH == 1 || INV_BATCH == 2 || INV_BATCH == 4 || INV_BATCH == 8 || INV_BATCH == 16, "power of two up to 16");
-    constexpr int LOG = INV_BATCH == 16 ? 4 : INV_BATCH == 8 ? 3 : INV_BATCH == 4 ? 2 : INV_BATCH == 2 ? 1 : 0;
-    const int hw = threadIdx.x >> 5, hl = threadIdx.x & 31, nhw = blockDim.x >> 5;
-    for (int base = 0; base < rows; base += INV_BATCH * nhw) {
-        long long src[INV_BATCH];
-        float v[INV_BATCH];
-#pragma unroll
-        for (int p = 0; p < INV_BATCH; ++p) {
-            const int gm = min(first_row + min(base + p * nhw + hw, rows - 1), g.M - 1);
-            src[p] = (long long)(g.a_rows ? g.a_rows[gm] : gm) * g.nparts;
-            v[p] = 0.f;
-        }
-        for (int q0 = 0; q0 < g.nparts; q0 += 128) {
-            float t[INV_BATCH][4];
-#pragma unroll
-            for (int p = 0; p < INV_BATCH; ++p)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) t[p][u] = g.ssq[src[p] + min(q0 + u * 32 + hl, g.nparts - 1)];
-#pragma unroll
-            for (int p = 0; p < INV_BATCH; ++p)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[p] += q0 + u * 32 + hl < g.nparts ? t[p][u] : 0.f;
-        }
-        // stage st: partner = lane ^ (16 >> st); the lane with that bit set keeps the upper half of
-        // the remaining values, so after LOG stages it holds the row whose index (within the batch)
-        // is the top LOG bits of its lane number
-#pragma unroll
-        for (int st = 0; st < LOG; ++st) {
-            const int n = INV_BATCH >> st, o = 16 >> st;
-            const bool upper = (hl & o) != 0;
-#pragma unroll
-            for (int j = 0; j < n / 2; ++j) {
-                const float send = upper ? v[j] : v[j + n / 2];
-                const float keep = upper ? v[j + n / 2] : v[j];
-                v[j] = keep + __shfl_xor(send, o, 64);
-            }
-        }
-#pragma unroll
-        for (int o = 16 >> LOG; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
-        const int r = base + (hl >> (5 - LOG)) * nhw + hw;
-        if ((hl & ((32 >> LOG) - 1)) == 0 && r < rows) s_inv[r] = 1.0f / sqrtf(v[0] / (float)g.d_norm + g.eps);
-    }
-}
-
-// The same for rows that left at most 4 partial sums behind (their producer was a K-split GEMM's
-// reduce kernel, or the embedding): four lanes per row, one load each, the rows of up to four
-// passes in flight together - cheap enough in registers to sit behind the operand loads of a
-// kernel's prologue, where its cold misses overlap theirs.
-__device__ __forceinline__ void block_inv_rms_few(const GemmArgs& g, int first_row, int rows, float* s_inv) {
-    const int p = threadIdx.x & 3, per_pass = blockDim.x >> 2;
-    for (int base = 0; base < rows; base += 4 * per_pass) {
-        float v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int gm = min(first_row + min(base + u * per_pass + (int)(threadIdx.x >> 2), rows - 1), g.M - 1);
-            v[u] = g.ssq[(long long)(g.a_rows ? g.a_rows[gm] : gm) * g.nparts + min(p, g.nparts - 1)];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float t = p < g.nparts ? v[u] : 0.f;
-            t += __shfl_xor(t, 1, 64);
-            t += __shfl_xor(t, 2, 64);
-            const int r = base + u * per_pass + (int)(threadIdx.x >> 2);
-            if (p == 0 && r < rows) s_inv[r] = 1.0f / sqrtf(t / (float)g.d_norm + g.eps);
-        }
-    }
 }
 
 // ------------------------------------------------------------------------------ tile kernel
@@ -505,7 +339,7 @@ __global__ __launch_bounds__(256) void residual_reduce_kernel(GemmArgs g) {
     }
 }
 // launches it; returns the partial sums per row it leaves
-static int launch_residual_reduce(const GemmArgs& g, hipStream_t s) {
+int launch_residual_reduce(const GemmArgs& g, hipStream_t s) {
     const int parts = (g.N + REDUCE_COLS - 1) / REDUCE_COLS;
     residual_reduce_kernel<<<dim3((unsigned)parts, (unsigned)g.M), 256, 0, s>>>(g);
     return parts;
@@ -558,6 +392,10 @@ __global__ __launch_bounds__(256) void qkv_reduce_rope_kernel(GemmArgs g) {
         dst[(long long)j * 16] = (f16)a;
         dst[(long long)(j + half) * 16] = (f16)b;
     }
+}
+
+void launch_qkv_reduce(const GemmArgs& g, hipStream_t s) {
+    qkv_reduce_rope_kernel<<<dim3((unsigned)g.M, (unsigned)((g.N / 2 + 255) / 256)), 256, 0, s>>>(g);
 }
 
 // Second half of a K-sliced SwiGLU GEMM: out[m, n] = fp16(silu(gate * inv) * (up * inv)) with gate
@@ -1262,7 +1100,7 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             gp.Cf = g.split_ws;
             const int gx = (N + 255) / 256, gy = (M + 127) / 128;
             AX_SPLIT_LAUNCH(gp.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3, 2, false), gx * gy, 256, gp, gx, gy);
-            qkv_reduce_rope_kernel<<<dim3((unsigned)M, (unsigned)((N / 2 + 255) / 256)), 256, 0, s>>>(gs);
+            launch_qkv_reduce(gs, s);
             return 0;
         }
         // A plain store GEMM writes fp32 products, a second kernel does the rms scaling, rotary
@@ -1297,7 +1135,7 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             dim3 grid((N + 127) / 128, (M + 63) / 64, ks);
             AX_SPLIT_LAUNCH(gp.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_STORE_F32, 1, 1, 2, 4), grid, 512, gp);
         }
-        qkv_reduce_rope_kernel<<<dim3((unsigned)M, (unsigned)((N / 2 + 255) / 256)), 256, 0, s>>>(gs);
+        launch_qkv_reduce(gs, s);
         return 0;
     } else if constexpr (EPI == EPI_RESIDUAL) {
         if (mid_ks > 1 && mid_cb * mid_ks >= 160) {            // (~1B width: 128 blocks, slower than the tile kernels)
@@ -1466,9 +1304,19 @@ static bool use_skinny(int epi, int M, int N, int K) {
     return !(epi == EPI_QKV || epi == EPI_SWIGLU || (epi == EPI_RESIDUAL && K >= 2 * N));
 }
 
+static const int kBlockMinM = env_int("AX_BLOCK_MIN_M", 257);
+static const int kBlockShape = env_int("AX_BLOCK_SHAPE", -1);
+static const int kBlockKs = env_int("AX_BLOCK_KS", 0);
+
 template <int EPI>
 static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
+    if (M >= kBlockMinM && !g.a_rows && N % 64 == 0) {
+        BlockPlan p = plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
+        if (kBlockShape >= 0) p.shape = kBlockShape;
+        if (kBlockKs > 0) p.ks = kBlockKs;
+        return launch_gemm_block((Epilogue)EPI, g, p, s);
+    }
     if (use_skinny(EPI, M, N, K)) {
         // wavefronts per block (= K slices): enough to keep ~2k wavefronts in flight (~4k for the SwiGLU
         // GEMM: 8 instead of 4 wavefronts per block took the ~1B verify kernel from 16.6 to 14.7 us), each with
