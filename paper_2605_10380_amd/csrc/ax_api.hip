@@ -46,7 +46,8 @@ struct TimerEvents {
 constexpr int N_SLOTS = 4;            // staging ring for per-call descriptors
 constexpr int LOGIT_ROWS = 256;       // rows per LM-head pass when only the argmax is wanted
 constexpr long long kSharedMinKeys = 2048;   // (sequences - 1) x shared keys that justify a shared-prefix pass
-constexpr int SPLIT_ITEMS = 2048;     // partial records the split attention may use (workspace size)
+constexpr int MIN_RECORDS = 2048;     // partial records the split attention may always use (workspace size)
+constexpr int MAX_RECORDS = 8192;     // ... and what it has no use for beyond (unless single slices already need more)
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 int isz(int dtype) { return ax::itemsize(dtype); }
@@ -81,7 +82,14 @@ Layout make_layout(const ax_model_config& c) {
     Layout L{};
     const size_t T = (size_t)c.max_tokens, S = (size_t)c.max_seqs, a = (size_t)isz(c.dtype);
     const int G = c.n_q_heads / c.n_kv_heads;
-    L.max_tiles = (int)((T * G + 31) / 32 + S + (T * G) / 128 + 2);     // per-sequence tiles + groups of a shared-prefix pass
+    // Partial records of the split attention: one per (q tile of 32 stacked rows, KV head, key slice).  A call
+    // whose longest sequence runs on blocks of 4 or 8 tiles pads EVERY sequence to whole blocks, so the most a
+    // call can need with one slice is (T G / 32 + 8 per sequence) tiles per KV head; the slice count is then
+    // chosen to stay inside this capacity.  Room for two passes: the per-sequence one and the shared-prefix one.
+    const size_t one_slice = ((T * G + 31) / 32 + 8 * S + 2) * (size_t)c.n_kv_heads;
+    L.max_records = std::max({(size_t)MIN_RECORDS, one_slice, std::min((size_t)MAX_RECORDS, 8 * one_slice)});
+    // tile records, or items (no more than their partial records plus one per group) and merge records; and the shared pass's items
+    L.max_tiles = (int)((T * G + 31) / 32 + S + 2 * ((T * G) / 128 + S + 2) + 2 * (L.max_records / (4 * (size_t)c.n_kv_heads)));
     L.max_bt = (c.max_pos + 15) / 16;
     L.desc_ints = 5 * T + 4 * S + S * (size_t)L.max_bt + 8 * (size_t)L.max_tiles + 32;
     size_t o = 0;
@@ -112,11 +120,6 @@ Layout make_layout(const ax_model_config& c) {
         L.q_lo = L.attn_lo = (long long)(T * qdim);
         L.ffn_lo = (long long)(T * c.d_ff);
     }
-    // Partial records of the split attention: one per (q tile of 32 stacked rows, KV head, key slice).  A call
-    // whose longest sequence runs on blocks of 4 or 8 tiles pads EVERY sequence to whole blocks, so the most a
-    // call can need with one slice is (T G / 32 + 8 per sequence) tiles per KV head; the slice count is then
-    // chosen to stay inside this capacity.  Room for two passes: the per-sequence one and the shared-prefix one.
-    L.max_records = std::max<size_t>(SPLIT_ITEMS, ((T * G + 31) / 32 + 8 * S + 2) * (size_t)c.n_kv_heads);
     L.partials = take(c.dtype == AX_BF16 ? 2 * L.max_records * ((size_t)c.head_dim * 32 + 64) * 4 : 0);
     // fp32 slabs of GEMMs that finish in a second kernel: K-slice partials of the residual GEMMs (SPLITK_MAX slabs of
     // [T, d_model]; the SwiGLU GEMM's slices take what fits) and the raw products of the QKV GEMM above 64 rows, which
@@ -180,7 +183,7 @@ struct ProfScope {                     // records a pair of events around one la
 };
 
 // Key slices of the split attention, from measurements on the ~1B and ~8B shapes: blocks of 4 q
-// tiles (long extends) run best at about two blocks per CU (2048 wavefronts); single-tile
+// tiles inside a captured graph (others: plan_items) at about two blocks per CU (2048 wavefronts); single-tile
 // wavefronts (verify steps, short extends) at about 512 wavefronts - beyond that the merge of the
 // slices costs more than the shorter key loops save.  At least two 32-key steps per slice,
 // rounded down to a power of two so that the choice (a launch dimension, hence part of a captured
@@ -199,11 +202,89 @@ int choose_splits(const ax_model* m, int items, int nq, int max_steps) {
     return p2;
 }
 
+// Work of the block attention kernel: a group of q tiles of sequence s and its key steps [lo, hi); slot >= 0: partial records.
+// Merge records: first slot and number of slices.
+struct AttnItem { int s, r0, lo, hi, slot, n; };
+
+// Cuts the q-tile groups of a call (AttnItem: lo = 0, hi = all key steps) into items of about equal length and orders them.
+// A block is one item of 4 tiles; b of them share a CU (up to 4 at head_dim 64, 3 at 128, 2 with split activations: registers), so
+// 256 b / heads items per head run at the same time.  Every cut costs partial records (8 or 16 KB a tile, written and read back by a
+// merge kernel), so groups are cut only while that fills the chip: for each b, the shortest item length for which all items still run
+// at once; the b whose length x step time + cost of the records is smallest (step times measured with b blocks on every CU).
+// More groups than run at once: whole ones for as many full rounds as there are, and the rest cut so that they fill the last
+// round (~3B, 118 groups per head for 96 places: without the cut the last 22 run alone for a third of the time).
+// `uniform` > 0: that many items per group instead (calls inside a captured graph, whose launch dimensions may not follow the
+// cache length).
+// Order: longest first (what starts last should be short); items that all run at once go to the CUs in rounds of 256 blocks, so every other
+// round is reversed - a CU's blocks then add up to about the same (~1B, 4096 rows without a prefix: a block's keys range from
+// 128 to 4096).
+void plan_items(std::vector<AttnItem>& groups, int n_heads, bool hd64, bool q_split, int uniform, size_t max_records,
+                std::vector<AttnItem>& items, std::vector<AttnItem>& merges) {
+    items.clear();
+    merges.clear();
+    static const float kStep[2][2][4] = {{{0.80f, 1.00f, 1.50f, 0.f}, {0.98f, 1.53f, 0.f, 0.f}},        // head_dim 128: plain, split q
+                                         {{0.64f, 0.85f, 1.20f, 1.56f}, {0.75f, 1.10f, 1.65f, 0.f}}};   // head_dim 64
+    const float* step = kStep[hd64][q_split];
+    const int fit = step[2] == 0.f ? 2 : step[3] == 0.f ? 3 : 4, n = (int)groups.size();
+    const long long max_slots = (long long)(max_records / ((size_t)n_heads * 4));
+    auto room = [&](int b) { return std::max(1, 256 * b / n_heads); };
+    std::stable_sort(groups.begin(), groups.end(), [](const AttnItem& a, const AttnItem& b) { return a.hi > b.hi; });
+    std::vector<int> cuts((size_t)n, 1);
+    if (uniform > 0) {
+        std::fill(cuts.begin(), cuts.end(), uniform);
+    } else if (n > room(fit)) {
+        const int rest = n % room(fit);
+        for (int k = rest ? room(fit) / rest : 1, i = n - rest; i < n && k > 1; ++i)
+            cuts[(size_t)i] = std::max(1, std::min(k, groups[(size_t)i].hi / 16));
+    } else {
+        float best = 1e30f;
+        int length = groups[0].hi;
+        for (int b = 1; b <= fit; ++b) {
+            if (n > room(b)) continue;
+            long long slots = 0;
+            auto fits = [&](int c) {                              // all items of at most c steps run at once
+                long long count = 0;
+                slots = 0;
+                for (const AttnItem& g : groups) {
+                    const int k = (g.hi + c - 1) / c;
+                    count += k;
+                    slots += k > 1 ? k : 0;
+                }
+                return count <= room(b) && slots <= max_slots;
+            };
+            int lo = std::min(groups[0].hi, 4), hi = groups[0].hi;
+            while (lo < hi) {
+                const int mid = (lo + hi) / 2;
+                if (fits(mid)) hi = mid; else lo = mid + 1;
+            }
+            (void)fits(lo);
+            const float us = lo * step[b - 1] + (slots ? 4.f + slots * n_heads * 4 * (hd64 ? 0.0021f : 0.0042f) : 0.f);
+            if (us < best) { best = us; length = lo; }
+        }
+        for (int i = 0; i < n; ++i) cuts[(size_t)i] = (groups[(size_t)i].hi + length - 1) / length;
+    }
+    int slot = 0;
+    for (int i = 0; i < n; ++i) {
+        const AttnItem& g = groups[(size_t)i];
+        int k = cuts[(size_t)i];
+        if (k > 1 && slot + k > max_slots) k = 1;
+        const int per = (g.hi + k - 1) / k;
+        if (k > 1) merges.push_back({g.s, g.r0, 0, 0, slot, k});
+        for (int q = 0; q < k; ++q) items.push_back({g.s, g.r0, std::min(q * per, g.hi), std::min((q + 1) * per, g.hi), k > 1 ? slot++ : -1, 0});
+    }
+    std::stable_sort(items.begin(), items.end(), [](const AttnItem& a, const AttnItem& b) { return a.hi - a.lo > b.hi - b.lo; });
+    const size_t round = (size_t)room(1);
+    if (items.size() <= (size_t)room(fit))
+        for (size_t at = round; at < items.size(); at += 2 * round)
+            std::reverse(items.begin() + (long)at, items.begin() + (long)std::min(items.size(), at + round));
+}
+
 // Host half of a call: validation, KV reservation (all or nothing) and the descriptor, written
 // into a pinned staging slot.  Nothing is launched here.
 struct CallPlan {
     int n = 0, n_rows = 0, n_out = 0, n_tiles = 0, tile_nq = 1, bt_total = 0, max_steps = 1, out_mode = 0, slot = 0;
     int n_tiles_shared = 0, shared_nq = 4, shared_len = 0, shared_splits = 1;   // shared-prefix attention pass (0 groups = none)
+    std::vector<AttnItem> items, merges;                                        // block-kernel calls (tile_nq 4)
     size_t o_tok = 0, o_pos = 0, o_seq = 0, o_slot = 0, o_out = 0, o_P = 0, o_T = 0, o_row0 = 0, o_bt = 0, o_tinfo = 0,
            o_tab = 0, ints = 0;
     ax_pool* pool = nullptr;
@@ -260,14 +341,13 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
     // attention q tiles (32 stacked rows).  Verify steps and short extends (<= 128 stacked rows
     // per sequence, <= 256 at head_dim 64): one tile per wavefront - measured, a wavefront that
     // carries two tiles (sharing the K/V loads) is no faster, its serial softmax chain per key step
-    // is twice as long.  Longer extends: blocks of 4 or 8 tiles that share LDS-staged K/V.  (With
+    // is twice as long.  Longer extends: blocks of 4 tiles that share LDS-staged K/V.  (With
     // 65-128 stacked rows the blocks were tried first and lost by far: a verify round at k = 16
     // of the ~1B model 1.58 -> 1.29 ms, of the ~8B model 5.0 -> 4.4 ms.)
     const int split_rows_max = c.head_dim == 64 ? 256 : 128;
-    cp.tile_nq = 1;
-    for (int s = 0; s < n; ++s) {
-        if (T_each[s] * G > split_rows_max && cp.tile_nq < 4) cp.tile_nq = 4;
-        if (T_each[s] * G >= 2048) cp.tile_nq = 8;    // 8 tiles per block: ~10 % on the ~8B shape at T = 512, none below
+    cp.tile_nq = 1;                               // (fp32 models: their kernel takes single tiles)
+    for (int s = 0; s < n && c.dtype == AX_BF16; ++s) {
+        if (T_each[s] * G > split_rows_max) cp.tile_nq = 4;
     }
     cp.n_tiles = cp.bt_total = 0;
     for (int s = 0; s < n; ++s) {
@@ -300,6 +380,21 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
             while (cp.shared_splits * 2 <= want) cp.shared_splits *= 2;
         }
     }
+    if (cp.tile_nq > 1) {
+        std::vector<AttnItem> groups;
+        int longest = 1;
+        for (int s = 0; s < n; ++s)
+            for (int r0 = 0; r0 < T_each[s] * G; r0 += 32 * cp.tile_nq) {
+                const int r_last = std::min(r0 + 32 * cp.tile_nq, T_each[s] * G) - 1;
+                groups.push_back({s, r0, 0, (int)((kvs[s]->seq.len + r_last / G + 1 + 31) / 32), -1, 0});
+                longest = std::max(longest, groups.back().hi);
+            }
+        if ((size_t)cp.n_tiles * cp.tile_nq * c.n_kv_heads > m->lay.max_records)
+            return fail(AX_ERR_UNSUPPORTED, "%d attention tile groups of %d tiles exceed the workspace's %zu partial records",
+                        cp.n_tiles, cp.tile_nq, m->lay.max_records);
+        const int uniform = graph_slot ? choose_splits(m, cp.n_tiles * c.n_kv_heads, cp.tile_nq, longest) : 0;
+        plan_items(groups, c.n_kv_heads, c.head_dim == 64, m->lay.q_lo != 0, uniform, m->lay.max_records, cp.items, cp.merges);
+    }
     cp.n_out = out_mode == AX_OUT_NONE ? 0
                : (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_LAST_ARGMAX) ? n : (int)n_rows;
     size_t at = 0;
@@ -309,7 +404,8 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
     cp.o_out = region((size_t)std::max(cp.n_out, 1)); cp.o_P = region((size_t)n); cp.o_T = region((size_t)n);
     cp.o_row0 = region((size_t)n); cp.o_bt = region((size_t)n);
     at = (at + 7) / 8 * 8;                                                   // 32-byte aligned tile records
-    cp.o_tinfo = region((size_t)(cp.n_tiles + cp.n_tiles_shared) * 8);
+    cp.o_tinfo = region(cp.tile_nq > 1 ? (cp.items.size() + cp.merges.size()) * 8
+                                       : (size_t)(cp.n_tiles + cp.n_tiles_shared * cp.shared_splits) * 8);
     cp.o_tab = region((size_t)(graph_slot ? m->lay.max_bt : cp.bt_total));   // fixed extent inside a graph
     cp.ints = at;
     if (cp.ints > m->slot_ints || cp.bt_total > n * m->lay.max_bt)
@@ -318,7 +414,7 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
     // each pass must fit the workspace region sized for it (it does for every call within max_tokens / max_seqs;
     // checked all the same, before anything is committed, because a kernel would write past the region otherwise)
     if (c.dtype == AX_BF16 &&
-        ((size_t)cp.n_tiles * cp.tile_nq * c.n_kv_heads > m->lay.max_records ||
+        ((cp.tile_nq == 1 && (size_t)cp.n_tiles * c.n_kv_heads > m->lay.max_records) ||
          (size_t)cp.n_tiles_shared * cp.shared_nq * c.n_kv_heads * cp.shared_splits > m->lay.max_records))
         return fail(AX_ERR_UNSUPPORTED, "%d attention tile groups of %d tiles exceed the workspace's %zu partial records",
                     cp.n_tiles, cp.tile_nq, m->lay.max_records);
@@ -350,7 +446,7 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         d[cp.o_row0 + s] = row;
         d[cp.o_bt + s] = tab;
         for (int32_t b : kvs[s]->seq.blocks) d[cp.o_tab + tab++] = b;
-        for (int r0 = 0; r0 < T * G; r0 += 32 * cp.tile_nq) {
+        for (int r0 = 0; r0 < T * G && cp.tile_nq == 1; r0 += 32) {
             int* ti = d + cp.o_tinfo + (size_t)tile * 8;
             ti[0] = s; ti[1] = r0; ti[2] = P[(size_t)s]; ti[3] = T; ti[4] = row; ti[5] = d[cp.o_bt + s];
             ti[6] = 0;
@@ -367,10 +463,23 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         if (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_LAST_ARGMAX) d[cp.o_out + oi++] = row - 1;
         cp.max_steps = std::max(cp.max_steps, (P[(size_t)s] + T - (cp.n_tiles_shared > 0 ? cp.shared_len : 0) + 31) / 32);
     }
-    for (int g = 0; g < cp.n_tiles_shared; ++g) {                   // the shared pass: one virtual sequence of all rows
-        int* ti = d + cp.o_tinfo + (size_t)(cp.n_tiles + g) * 8;
-        ti[0] = 0; ti[1] = g * 32 * cp.shared_nq; ti[2] = cp.shared_len; ti[3] = (int)n_rows; ti[4] = 0; ti[5] = d[cp.o_bt + 0];
-        ti[6] = cp.shared_len; ti[7] = 0;
+    for (int g = 0; g < cp.n_tiles_shared; ++g)                     // the shared pass: one virtual sequence of all rows
+        for (int i = 0; i < cp.shared_splits; ++i) {
+            const int steps = cp.shared_len / 32, per = (steps + cp.shared_splits - 1) / cp.shared_splits, at = g * cp.shared_splits + i;
+            int* ti = d + cp.o_tinfo + (size_t)(cp.n_tiles + at) * 8;
+            ti[0] = at; ti[1] = g * 32 * cp.shared_nq; ti[2] = cp.shared_len; ti[3] = (int)n_rows; ti[4] = 0; ti[5] = d[cp.o_bt + 0];
+            ti[6] = std::min((i + 1) * per, steps); ti[7] = std::min(i * per, steps);
+        }
+    for (size_t i = 0; i < cp.items.size(); ++i) {
+        const AttnItem& it = cp.items[i];
+        int* ti = d + cp.o_tinfo + i * 8;
+        ti[0] = it.slot; ti[1] = it.r0; ti[2] = P[(size_t)it.s]; ti[3] = T_each[it.s]; ti[4] = d[cp.o_row0 + it.s]; ti[5] = d[cp.o_bt + it.s];
+        ti[6] = it.hi; ti[7] = it.lo;
+    }
+    for (size_t i = 0; i < cp.merges.size(); ++i) {
+        const AttnItem& it = cp.merges[i];
+        int* ti = d + cp.o_tinfo + (cp.items.size() + i) * 8;
+        ti[0] = it.slot; ti[1] = it.r0; ti[2] = it.n; ti[3] = T_each[it.s]; ti[4] = d[cp.o_row0 + it.s]; ti[5] = ti[6] = ti[7] = 0;
     }
     return AX_OK;
 }
@@ -393,6 +502,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
     sv.seq_row0 = dev_d + cp.o_row0; sv.seq_bt = dev_d + cp.o_bt;   sv.tile_info = dev_d + cp.o_tinfo;
     sv.bt = dev_d + cp.o_tab;
     sv.n_rows = cp.n_rows; sv.n_seq = cp.n; sv.n_out = cp.n_out; sv.n_tiles = cp.n_tiles; sv.tile_nq = cp.tile_nq;
+    sv.n_items = (int)cp.items.size(); sv.n_merge = (int)cp.merges.size();
     sv.n_tiles_shared = cp.n_tiles_shared; sv.shared_nq = cp.shared_nq; sv.shared_len = cp.shared_len; sv.shared_splits = cp.shared_splits;
 
     const ax::DType dt = c.dtype == AX_F32 ? ax::F32 : ax::BF16;
@@ -593,7 +703,8 @@ ax_status run_verify_graph(ax_model* m, ax_kv* kv, const int32_t* toks, int T, v
     const ax::DType dt = m->cfg.dtype == AX_F32 ? ax::F32 : ax::BF16;
     for (auto& cw : cp.cows) ax::launch_block_copy(dt, cp.pool->geom, m->cfg.n_layers, cw.first, cw.second, stream);
     const int n_splits = choose_splits(m, cp.n_tiles * m->cfg.n_kv_heads, cp.tile_nq, cp.max_steps);
-    const uint64_t key = ((uint64_t)(uint32_t)T << 32) | (uint32_t)n_splits;
+    // (block-kernel calls: the item counts follow from T and the slice count of plan_items' uniform cut)
+    const uint64_t key = ((uint64_t)(uint32_t)T << 32) | (uint32_t)(cp.tile_nq > 1 ? (int)(cp.items.size() / (size_t)cp.n_tiles) : n_splits);
     hipGraphExec_t exec = nullptr;
     for (auto& g : m->graphs)
         if (g.key == key && g.pool_uid == cp.pool->uid) exec = g.exec;

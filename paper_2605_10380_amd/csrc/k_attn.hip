@@ -12,6 +12,7 @@
 //     the slices.  Splitting the key range is what fills 256 CUs when T is small (verify:
 //     T = 1 + k) and it is harmless when T is large.
 #include "kernels.h"
+#include "lds_copy.h"
 
 namespace ax {
 
@@ -192,12 +193,13 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
 // on steps that reach past the tile's earliest row (`diagonal`, wavefront-uniform).  v_exp_f32
 // is used directly: a result that underflows to 0 is exact enough for a probability.
 constexpr float SOFTMAX_SLACK = 8.0f;
+template <bool PAGES = false>          // key of register r: PAGES: kv0 + (r / 8) * 16 + g * 8 + r % 8 (block kernel)
 __device__ __forceinline__ bool online_softmax_step(f32x16& s, int kv0, int g, int pos_q, bool diagonal, float c,
                                                     float& m, float& l, float& alpha, f16x8 (&pb)[2]) {
     if (diagonal) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int kj = kv0 + (r >> 2) * 8 + g * 4 + (r & 3);
+            const int kj = PAGES ? kv0 + (r >> 3) * 16 + g * 8 + (r & 7) : kv0 + (r >> 2) * 8 + g * 4 + (r & 3);
             s[r] = (kj <= pos_q) ? s[r] : -INFINITY;
         }
     }
@@ -256,8 +258,7 @@ struct AttnArgs {
     long long q_lo_off, out_lo_off;   // split activations: lo parts of q / out this many elements behind (0 = not split)
     KVGeom kv;
     int layer, Hq, n_splits;
-    const int* tile_info;      // per q-tile group, 8 ints: seq, first stacked row, P, T, row0, block-table offset,
-                               // key limit (0 = none: causal bound of the rows), first key
+    const int* tile_info;      // 8 ints per q tile, item or merge record (see StepView)
     const int* bt;
     float* partials;
     // shared-prefix pass of a many-sequence call (see launch_attention); unused otherwise
@@ -431,47 +432,43 @@ __global__ __launch_bounds__(64) void attn_split_kernel(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------ MFMA block kernel
-// Long extends (many q tiles per KV head): a block of 4 wavefronts owns 4 consecutive q tiles
-// (128 stacked rows) of one KV head and one key slice.  The K/V operands of a 32-key step are
-// fetched once per block (one 16-byte chunk of K and one of V per thread and 64 channels of
-// head_dim), staged through LDS and shared by the four tiles; global loads run D steps ahead in
-// a register ring, LDS is double buffered, one barrier per step.  Everything after the operand
-// fetch is the per-wavefront online softmax of attn_split_kernel; the partial records are those
-// of a group of NQ = 4 tiles, merged by attn_combine_kernel<HD, 4>.
+// Long extends (many q tiles per KV head) and the shared-prefix pass: a block of NQ wavefronts owns NQ consecutive q tiles (32 * NQ
+// stacked rows) of one KV head and a range of key steps - one ITEM of the list the host planned (StepView::items).  The K and V pages of
+// a 32-key step are copied to LDS by the memory pipeline (no registers in between), S stages deep, one barrier per step, and
+// shared by the NQ tiles; everything after that is the per-wavefront online softmax of attn_split_kernel.  An item that
+// holds all the keys of its tiles writes the attention output itself; the others leave (O, m, l) records for
+// attn_merge_items_kernel.
 //
-// LDS layout of a stage: K rows [32 keys][HD + 8] (padded, 16-byte operand reads are conflict
-// free); V rows [2 blocks * HD channels][16 tokens in operand order + 8 pad], where operand order
-// puts tokens {0-3, 8-11, 4-7, 12-15} so that a lane's PV operand (tokens 4g..4g+3 and
-// 8+4g..8+4g+3 of its channel) is one 16-byte read.
-template <int HD, int NQ, bool QS = false>
-__global__ __launch_bounds__(64 * NQ) void attn_block_kernel(AttnArgs a) {
-    constexpr int KQ = HD / 16, DT = HD / 32, PS = HD * 32 + 64, NT = 64 * NQ;
-    constexpr int NP = QS ? 2 : 1;       // q in hi and lo parts (split activations)
-    constexpr int D = 4;                              // prefetch distance in key steps (even)
-    constexpr int KLS = HD + 8, VLS = 24;             // padded LDS row lengths (fp16 elements)
-    constexpr int TCH = 32 * HD / 8;                  // 16-byte chunks of K (and of V) per step
-    constexpr int CH = (TCH + NT - 1) / NT;           // ... per thread (threads past TCH idle)
-    __shared__ __attribute__((aligned(16))) f16 sK[2][32 * KLS];
-    __shared__ __attribute__((aligned(16))) f16 sV[2][2 * HD * VLS];
+// A key step is 32 keys = 2 pages: 4 * HD bytes of K and V each, copied in 1 KB units (wavefront w takes units w, w + NQ, ..).
+//   K: [32 keys][HD]; the 16-byte columns of a row are rotated by swz(key) (which column a lane COPIES is free to choose, where it
+//      lands is not), so that 16 keys at one column fall into all 16-byte columns of 256 bytes.
+//   V: [2 pages][HD channels][16 tokens]; the two halves of a channel's 32 bytes trade places in every other group of 8 channels.
+// The score product takes the keys in the order 0-3, 8-11, 4-7, 12-15 (of each page): then a lane ends up with the scores of
+// keys 8 g .. 8 g + 7 of both pages (g = lane / 32), and its V operand is ONE 16-byte read.
+template <int HD, int NQ, int S, bool QS = false>
+__global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(HD == 64 ? (QS ? 3 : 4) : (QS || NQ == 8 ? 2 : 3))))
+void attn_block_kernel(AttnArgs a) {
+    constexpr int KQ = HD / 16, DT = HD / 32, PS = HD * 32 + 64;
+    constexpr int NP = QS ? 2 : 1;                    // q in hi and lo parts (split activations)
+    constexpr int KB = 32 * HD * 2, STAGE = 2 * KB;   // bytes of K (and of V) per step
+    constexpr int U = STAGE / 1024, L = (U + NQ - 1) / NQ, PU = U / 4;      // copy units per step, per wavefront, per page of K or V
+    static_assert(U % NQ == 0, "whole units per wavefront");
+    __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
 
-    const AttnWork wk = attn_work();
-    const int tile = wk.tile, hk = wk.hk, split = wk.split;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ql = lane & 31, g = lane >> 5;
+    const unsigned nx = gridDim.x, total = nx * gridDim.y;
+    unsigned id = blockIdx.x + nx * blockIdx.y;       // (see attn_work: with 8 KV heads, one head per XCD)
+    if ((total & 7u) == 0) id = (id & 7u) * (total >> 3) + (id >> 3);
+    const int item = (int)(id % nx), hk = (int)(id / nx);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ql = lane & 31, g = lane >> 5;
     const int Hq = a.Hq, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
-    const int4 ti0 = *(const int4*)(a.tile_info + tile * 8), ti1 = *(const int4*)(a.tile_info + tile * 8 + 4);
-    const int r0 = ti0.y, P = ti0.z, T = ti0.w, row0 = ti1.x;
+    const int4 ti0 = *(const int4*)(a.tile_info + item * 8), ti1 = *(const int4*)(a.tile_info + item * 8 + 4);
+    const int slot = ti0.x, r0 = ti0.y, P = ti0.z, T = ti0.w, row0 = ti1.x, s_hi = ti1.z, s_lo = ti1.w;
     const int n_stacked = T * G;
     const int* tab = a.bt + ti1.y;
-    const int klimit = ti1.z;                                  // > 0: keys [0, klimit) only (shared pass)
-    const int kv_len = klimit > 0 ? klimit : P + T, last_blk = (kv_len - 1) >> 4;
+    const int kv_len = P + T, last_blk = min((kv_len - 1) >> 4, 2 * s_hi - 1);
 
-    const int r_last = min(r0 + NQ * 32 - 1, n_stacked - 1);
-    const int kv_end = klimit > 0 ? klimit : P + r_last / G + 1;
-    const int steps = (kv_end + 31) / 32;
-    const int per = (steps + a.n_splits - 1) / a.n_splits;
-    const int s_lo = split * per, s_hi = min(steps, s_lo + per);
-
-    // this wavefront's q tile
+    // this wavefront's q tile (a tile past the sequence's rows copies and synchronises with the others, nothing more)
+    const bool idle = r0 + wave * 32 >= n_stacked;
     const int rq = min(r0 + wave * 32 + ql, n_stacked - 1);
     const int tq = rq / G, gq = rq % G;
     const int pos_q = P + tq;
@@ -482,150 +479,159 @@ __global__ __launch_bounds__(64 * NQ) void attn_block_kernel(AttnArgs a) {
 #pragma unroll
         for (int kk = 0; kk < KQ; ++kk) qf[p][kk] = *(const f16x8*)(qrow + (p ? a.q_lo_off : 0) + kk * 16 + g * 8);
 
-    const f16* Kp = (const f16*)a.kv.base + a.kv.plane(a.layer, 0, hk);
-    const f16* Vp = (const f16*)a.kv.base + a.kv.plane(a.layer, 1, hk);
+    const char* Kp = (const char*)((const f16*)a.kv.base + a.kv.plane(a.layer, 0, hk));
+    const char* Vp = (const char*)((const f16*)a.kv.base + a.kv.plane(a.layer, 1, hk));
     const float c = 1.4426950408889634f / sqrtf((float)HD);
-    const int pos_tile_min = P + (r0 + wave * 32) / G;         // earliest position among this tile's rows
-    float m = -INFINITY, l = 0.f, alpha_out = 1.f;
-    f16x8 pb_out[2];
+    const int pos_tile_min = P + min(r0 + wave * 32, n_stacked - 1) / G;       // earliest and latest position among this tile's rows
+    const int pos_tile_max = P + min(r0 + wave * 32 + 31, n_stacked - 1) / G;
+    float m = -INFINITY, l = 0.f;
     f32x16 o[DT];
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
 
-    // operand chunks of this thread: K chunk i covers key (cidx / (HD/8)), columns 8*(cidx % (HD/8));
-    // V chunk i covers block (cidx / (2*HD)), channel ((cidx / 2) % HD), tokens 8*(cidx % 2)..+7.
-    // The 64 chunks of a wavefront lie inside ONE 16-token block of the step (8 or 4 whole keys of K,
-    // half or a quarter of a V block), so which of the step's two blocks a chunk belongs to is
-    // wavefront-uniform: the block ids are read out of the table register into scalars, the block's
-    // base address is scalar arithmetic, and what is left per lane is a constant offset computed once.
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    unsigned k_off[CH], v_off[CH];
-    bool k_second[CH], v_second[CH];
+    // copies: unit x < U / 2 is K (page x / PU, part x % PU of it), the others V
+    auto swz = [](int key) { return HD == 128 ? key & 15 : (key & 7) ^ ((key >> 3) & 1); };
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+    unsigned off[L];
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
-        const int cidx = min(tid + NT * i, TCH - 1), c0 = min(wave_u * 64 + NT * i, TCH - 1);
-        k_off[i] = (unsigned)(((cidx / (HD / 8)) & 15) * HD + (cidx % (HD / 8)) * 8) * 2u;      // bytes
-        v_off[i] = (unsigned)(((cidx / 2) % HD) * 16 + (cidx % 2) * 8) * 2u;
-        k_second[i] = ((c0 / (HD / 8)) >> 4) != 0;
-        v_second[i] = (c0 / (2 * HD)) != 0;
+    for (int i = 0; i < L; ++i) {
+        const int x = wave + NQ * i, part = x % PU;
+        const int unit16 = part * 64 + lane;                   // 16-byte piece within the page, as it lies in LDS
+        const int key = unit16 / (HD / 8), col = unit16 % (HD / 8), ch = unit16 >> 1, half = unit16 & 1;
+        off[i] = x < U / 2 ? (unsigned)(key * HD * 2 + (col ^ swz(key)) * 16) : (unsigned)(ch * 32 + (half ^ ((ch >> 3) & 1)) * 16);
     }
-    u32x4 rk[D][CH], rv[D][CH];
-    // keys past the end of the sequence (last step only) read slots of the last block that were never
-    // written, or the last block twice: their scores are replaced by -inf whatever they are, and
-    // process() zeroes their V operands
-    auto gload = [&](int slot, int st, int tabv, int chunk) {
-        const int rel = 2 * (st - chunk), lim = last_blk - 2 * chunk;     // table lanes of the step's two blocks
+    // page ids: lane i of tabv holds page 2 * tab_at + i, the pages of 32 steps; the next 64 are on their way in tabn
+    int tab_at = s_lo, tabv = tab[min(2 * s_lo + lane, last_blk)], tabn = tab[min(2 * s_lo + 64 + lane, last_blk)];
+    auto load_stage = [&](int buf, int st) {
+        if (st - tab_at >= 32) {
+            tab_at += 32;
+            tabv = tabn;
+            tabn = tab[min(2 * tab_at + 64 + lane, last_blk)];
+        }
+        const int rel = 2 * (st - tab_at), lim = last_blk - 2 * tab_at;       // table lanes of the step's two pages
         const int b0 = __builtin_amdgcn_readlane(tabv, min(rel, lim)), b1 = __builtin_amdgcn_readlane(tabv, min(rel + 1, lim));
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            if (TCH % NT != 0 && wave_u * 64 + NT * i >= TCH) continue;     // more threads than chunks: the rest load nothing
-            const char* kb = (const char*)(Kp + (long long)(k_second[i] ? b1 : b0) * 16 * HD);
-            const char* vb = (const char*)(Vp + (long long)(v_second[i] ? b1 : b0) * 16 * HD);
-            rk[slot][i] = *(const u32x4*)(kb + k_off[i]);
-            rv[slot][i] = *(const u32x4*)(vb + v_off[i]);
+        for (int i = 0; i < L; ++i) {
+            const int x = wave + NQ * i, page = (x / PU) & 1;
+            const char* base = (x < U / 2 ? Kp : Vp) + (long long)(page ? b1 : b0) * 16 * HD * 2;
+            copy_to_lds(base, off[i], lds0 + buf * STAGE + x * 1024);
         }
     };
-    auto lstore = [&](int slot, int buf) {
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int cidx = tid + NT * i;
-            if (TCH % NT != 0 && cidx >= TCH) continue;
-            *(u32x4*)(sK[buf] + (cidx / (HD / 8)) * KLS + (cidx % (HD / 8)) * 8) = rk[slot][i];
-            // tokens 8h..8h+3 -> operand position 4h, tokens 8h+4..8h+7 -> operand position 8 + 4h
-            const int vrow = (cidx / (2 * HD)) * HD + (cidx / 2) % HD, h = cidx % 2;
-            uint2* dst = (uint2*)(sV[buf] + vrow * VLS);
-            dst[h] = make_uint2(rv[slot][i][0], rv[slot][i][1]);
-            dst[2 + h] = make_uint2(rv[slot][i][2], rv[slot][i][3]);
-        }
-    };
-    auto process = [&](int buf, int st) {
+    // operand addresses.  Score product: MFMA row i takes key i with bits 2 and 3 swapped
+    const int key_of = (ql & 0x13) | ((ql & 4) << 1) | ((ql & 8) >> 1);
+    const unsigned k_at = key_of * HD * 2 + ((g ^ swz(key_of & 15)) * 16);     // column 2 kk + g of the row: k_at ^ (kk * 32)
+    const unsigned v_at = KB + ql * 32 + (g ^ ((ql >> 3) & 1)) * 16;
+
+    auto process = [&](const char* stg, int st) {
         const int kv0 = st * 32;
+        if (idle || kv0 > pos_tile_max) return;                // none of the tile's rows sees these keys
+        // K operands are requested four products ahead and half of the V operands before the softmax, the other half behind it (what the
+        // registers of three wavefronts per SIMD hold): left alone, the compiler keeps two reads in flight
+        f16x8 kf[4], v0[DT], v1[DT];
+        unsigned ka = k_at;
+        asm volatile("" : "+v"(ka));                         // (one xor per read instead of eight registers for the addresses)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) kf[kk] = *(const f16x8*)(stg + (ka ^ (kk * 32)));
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < KQ; ++kk) {
-            const f16x8 kf = *(const f16x8*)(sK[buf] + ql * KLS + kk * 16 + g * 8);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int p = 0; p < NP; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[p][kk], s, 0, 0, 0);
+            for (int p = 0; p < NP; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[kk & 3], qf[p][kk], s, 0, 0, 0);
+            if (kk + 4 < KQ) kf[kk & 3] = *(const f16x8*)(stg + (ka ^ ((kk + 4) * 32)));
         }
-        if (online_softmax_step(s, kv0, g, pos_q, kv0 + 31 > pos_tile_min, c, m, l, alpha_out, pb_out)) {
-            const float alpha = alpha_out;
+#pragma unroll
+        for (int d = 0; d < DT; ++d) v0[d] = *(const f16x8*)(stg + v_at + d * 1024);
+        __builtin_amdgcn_sched_barrier(0);
+        float alpha;
+        f16x8 pb[2];
+        if (online_softmax_step<true>(s, kv0, g, pos_q, kv0 + 31 > pos_tile_min, c, m, l, alpha, pb)) {
 #pragma unroll
             for (int d = 0; d < DT; ++d)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
         }
-        const f16x8* pb = pb_out;
-        const bool ragged = kv0 + 32 > kv_len;          // block-uniform: the sequence ends inside this step
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int d = 0; d < DT; ++d) {
-            f16x8 va = *(const f16x8*)(sV[buf] + (d * 32 + ql) * VLS + g * 8);
-            f16x8 vb = *(const f16x8*)(sV[buf] + (HD + d * 32 + ql) * VLS + g * 8);
-            if (ragged) {
-                // slots past the end of the sequence hold whatever the pool memory held: exact zeros instead, so
-                // that their probability of 0 cannot meet a NaN or an infinity (element i of va is token
-                // (i / 4) * 8 + 4 g + i % 4 of the step's first block, of vb the same of its second block)
+        for (int d = 0; d < DT; ++d) v1[d] = *(const f16x8*)(stg + v_at + HD * 32 + d * 1024);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int key = kv0 + (i >> 2) * 8 + g * 4 + (i & 3);
-                    if (key >= kv_len) va[i] = (f16)0.f;
-                    if (key + 16 >= kv_len) vb[i] = (f16)0.f;
-                }
-            }
-            o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, pb[0], o[d], 0, 0, 0);
-            o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, pb[1], o[d], 0, 0, 0);
-        }
+        for (int d = 0; d < DT; ++d) o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v0[d], pb[0], o[d], 0, 0, 0);
+#pragma unroll
+        for (int d = 0; d < DT; ++d) o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v1[d], pb[1], o[d], 0, 0, 0);
     };
 
-    for (int chunk = s_lo; chunk < s_hi; chunk += 32) {          // 32 steps = 64 blocks = one table load
-        const int tabv = tab[min(2 * chunk + lane, last_blk)];
-        const int c_hi = min(s_hi, chunk + 32), n = c_hi - chunk;
+    const int n = s_hi - s_lo;
 #pragma unroll
-        for (int u = 0; u < D; ++u)
-            if (u < n) gload(u, chunk + u, tabv, chunk);
-        lstore(0, 0);
-        __syncthreads();
-        int b = 0;
-        for (; b + 2 * D <= n; b += D) {                         // steady state, branch free
+    for (int u = 0; u < S - 1; ++u)
+        if (u < n) load_stage(u, s_lo + u);
+    int i = 0;
+    for (; i + 2 * S - 2 < n; i += S) {
 #pragma unroll
-            for (int u = 0; u < D; ++u) {
-                gload(u, chunk + b + u + D, tabv, chunk);
-                process(u & 1, chunk + b + u);
-                lstore((u + 1) % D, (u + 1) & 1);
+        for (int u = 0; u < S; ++u) {
+            wait_copies_and_sync<(S - 2) * L>();                 // step i + u has landed for everybody, nobody reads step i + u - 1 any more
+            load_stage((u + S - 1) % S, s_lo + i + u + S - 1);
+            process(smem + u * STAGE, s_lo + i + u);
+        }
+    }
+    for (; i < n; i += S) {
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            if (i + u >= n) break;
+            wait_copies_and_sync<0>();
+            if (i + u + S - 1 < n) load_stage((u + S - 1) % S, s_lo + i + u + S - 1);
+            const int left = kv_len - (s_lo + i + u) * 32;       // keys from the step's first one to the sequence's end
+            if (left < 32) {
+                // the sequence ends inside this step (its last one): the slots behind hold whatever the pool memory held - exact
+                // zeros instead, so that their probability of 0 cannot meet a NaN or an infinity
+                for (int x = tid; x < 2 * HD; x += 64 * NQ) {
+                    const int ch = x % HD, page = x / HD;
+                    char* at = smem + u * STAGE + KB + page * HD * 32 + ch * 32;
+                    for (int t = max(left - page * 16, 0); t < 16; ++t)
+                        *(f16*)(at + (((t >> 3) ^ ((ch >> 3) & 1)) * 16) + (t & 7) * 2) = (f16)0.f;
+                }
                 __syncthreads();
             }
-        }
-        for (; b < n; b += D) {                                  // drain
-#pragma unroll
-            for (int u = 0; u < D; ++u) {
-                const int i = b + u;
-                if (i < n) {
-                    if (i + D < n) gload(u, chunk + i + D, tabv, chunk);
-                    process(u & 1, chunk + i);
-                    if (i + 1 < n) lstore((u + 1) % D, (u + 1) & 1);
-                    __syncthreads();
-                }
-            }
+            process(smem + u * STAGE, s_lo + i + u);
         }
     }
 
     const float l_row = l + __shfl_xor(l, 32, 64);               // both halves of the row
-    if (r0 + wave * 32 + ql < n_stacked) {
-        float* part = a.partials + (((long long)(tile * Hkv + hk) * a.n_splits + split) * NQ + wave) * PS;
+    if (r0 + wave * 32 + ql >= n_stacked) return;
+    if (slot < 0) {
+        const float inv = 1.0f / l_row;
+        f16* dst = a.out + ((long long)(row0 + tq) * Hq + hk * G + gq) * HD + g * 4;
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ch = d * 32 + (r >> 2) * 8 + g * 4 + (r & 3);
-                part[ch * 32 + ql] = o[d][r];
+            for (int r = 0; r < 16; r += 4) {
+                f16x4 hi, lo;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = o[d][r + q] * inv;
+                    hi[q] = (f16)v;
+                    lo[q] = (f16)(v - (float)hi[q]);
+                }
+                *(f16x4*)(dst + d * 32 + r * 2) = hi;
+                if (a.out_lo_off) *(f16x4*)(dst + a.out_lo_off + d * 32 + r * 2) = lo;
             }
-        if (g == 0) {
-            part[HD * 32 + ql] = m;
-            part[HD * 32 + 32 + ql] = l_row;
+        return;
+    }
+    float* part = a.partials + (((long long)slot * Hkv + hk) * NQ + wave) * PS;
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int ch = d * 32 + (r >> 2) * 8 + g * 4 + (r & 3);
+            part[ch * 32 + ql] = o[d][r];
         }
+    if (g == 0) {
+        part[HD * 32 + ql] = m;
+        part[HD * 32 + 32 + ql] = l_row;
     }
 }
 
@@ -657,8 +663,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     long long sstride = 0;
     if (a.shared_splits > 0) {
         const int rc = min(r, n_stacked - 1), R = (row0 + rc / G) * G + rc % G, gsz = 32 * a.shared_nq;
-        sbase = a.shared_partials + ((long long)((R / gsz) * Hkv + hk) * a.shared_splits * a.shared_nq + (R % gsz) / 32) * PS + (R & 31);
-        sstride = (long long)a.shared_nq * PS;
+        sbase = a.shared_partials + ((long long)((R / gsz) * a.shared_splits * Hkv + hk) * a.shared_nq + (R % gsz) / 32) * PS + (R & 31);
+        sstride = (long long)Hkv * a.shared_nq * PS;
     }
     auto slice = [&](int s) { return s < own_splits ? base + s * stride : sbase + (s - own_splits) * sstride; };
 
@@ -721,14 +727,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     if (a.out_lo_off) dst[a.out_lo_off] = (f16)(res - (float)hi);
 }
 
-// Slice merge for launches with many tile records and few slices each (the block kernel's groups
-// of 4 or 8 tiles; single-tile launches over many sequences, with their shared-prefix slices).
+// Slice merge for launches with many tile records and few slices each: ITEMS - the tiles the block kernel's items cut into several
+// key ranges (records of the host's merge list: first slot, first stacked row, slices, T, first row); otherwise single-tile launches
+// over many sequences, with their shared-prefix slices.
 // One block per (group, KV head, tile): 256 threads = 32 query rows x 8 channel groups, a thread
 // owns HD/8 consecutive channels of its row and walks the slices itself, so nothing meets in
 // LDS and every load of a pass is independent.  Pass 1: the row's reference exponents of all
 // slices -> maximum.  Pass 2: weights 2^(m_s - M), weighted sums, one 16-byte (HD = 64) or
 // 32-byte store of the normalised fp16 outputs.
-template <int HD, int NQ>
+template <int HD, int NQ, bool ITEMS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     constexpr int PS = HD * 32 + 64, CPT = HD / 8, SU = 4;
     const int Hkv = a.kv.n_kv_heads, G = a.Hq / Hkv;
@@ -738,15 +745,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     const int row0 = a.tile_info[tile * 8 + 4];
     const int r = ti0.y + t * 32 + ql, n_stacked = ti0.w * G;
     if (r >= n_stacked) return;
-    const int own_splits = a.n_splits, n_splits = own_splits + a.shared_splits;
-    const float* base = a.partials + ((long long)(tile * Hkv + hk) * own_splits * NQ + t) * PS + ql;
-    const long long stride = (long long)NQ * PS;               // between slices
+    const int own_splits = ITEMS ? ti0.z : a.n_splits, n_splits = own_splits + a.shared_splits;
+    const float* base = a.partials + (ITEMS ? ((long long)ti0.x * Hkv + hk) * NQ + t : (long long)(tile * Hkv + hk) * own_splits * NQ + t) * PS + ql;
+    const long long stride = (long long)(ITEMS ? Hkv * NQ : NQ) * PS;               // between slices
     const float* sbase = nullptr;                              // the row's record in a shared-prefix pass, slice 0
     long long sstride = 0;
     if (a.shared_splits > 0) {
         const int R = (row0 + r / G) * G + r % G, gsz = 32 * a.shared_nq;
-        sbase = a.shared_partials + ((long long)((R / gsz) * Hkv + hk) * a.shared_splits * a.shared_nq + (R % gsz) / 32) * PS + (R & 31);
-        sstride = (long long)a.shared_nq * PS;
+        sbase = a.shared_partials + ((long long)((R / gsz) * a.shared_splits * Hkv + hk) * a.shared_nq + (R % gsz) / 32) * PS + (R & 31);
+        sstride = (long long)Hkv * a.shared_nq * PS;
     }
     auto slice = [&](int s) { return s < own_splits ? base + s * stride : sbase + (s - own_splits) * sstride; };
 
@@ -807,15 +814,30 @@ static void launch_attn_mfma(const AttnArgs& a, int n_groups, hipStream_t s) {
     // few records with many slices (one session): blocks of 4 channels that spread the slices over
     // threads; many records with few slices (many sessions): one block per record
     if (n_groups * a.kv.n_kv_heads >= 64 && a.n_splits + a.shared_splits <= 32)
-        attn_merge_kernel<HD, NQ><<<n_groups * a.kv.n_kv_heads * NQ, 256, 0, s>>>(a);
+        attn_merge_kernel<HD, NQ, false><<<n_groups * a.kv.n_kv_heads * NQ, 256, 0, s>>>(a);
     else
         attn_combine_kernel<HD, NQ><<<cgrid, 256, 0, s>>>(a);
 }
 
 template <int HD, int NQ>
-static void launch_attn_block(const AttnArgs& a, dim3 grid, hipStream_t s) {
-    if (a.q_lo_off) attn_block_kernel<HD, NQ, true><<<grid, 64 * NQ, 0, s>>>(a);
-    else attn_block_kernel<HD, NQ, false><<<grid, 64 * NQ, 0, s>>>(a);
+static void launch_block(const AttnArgs& a, int n_items, hipStream_t s) {
+    dim3 grid((unsigned)n_items, (unsigned)a.kv.n_kv_heads);
+    if (a.q_lo_off) attn_block_kernel<HD, NQ, 3, true><<<grid, 64 * NQ, 0, s>>>(a);
+    else attn_block_kernel<HD, NQ, 3, false><<<grid, 64 * NQ, 0, s>>>(a);
+}
+// The items of a block-kernel pass, then the tiles whose keys they cut.
+template <int NQ>
+static void launch_items(const AttnArgs& a, int n_items, int n_merge, hipStream_t s) {
+    AttnArgs mg = a;
+    mg.tile_info = a.tile_info + (size_t)n_items * 8;
+    const unsigned mgrid = (unsigned)(n_merge * a.kv.n_kv_heads * NQ);
+    if (a.kv.head_dim == 64) {
+        launch_block<64, NQ>(a, n_items, s);
+        if (n_merge) attn_merge_kernel<64, NQ, true><<<mgrid, 256, 0, s>>>(mg);
+    } else {
+        launch_block<128, NQ>(a, n_items, s);
+        if (n_merge) attn_merge_kernel<128, NQ, true><<<mgrid, 256, 0, s>>>(mg);
+    }
 }
 
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, const StepView& sv,
@@ -837,26 +859,8 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
     a.tile_info = sv.tile_info; a.bt = sv.bt; a.partials = partials;
     a.q_lo_off = q_lo_off; a.out_lo_off = out_lo_off;
     const int hd = kv.head_dim;
-    if (sv.tile_nq >= 4) {                                     // long extends: 4 or 8 tiles per block, K/V through LDS
-        dim3 grid(sv.n_tiles, kv.n_kv_heads, n_splits);
-        const unsigned mgrid = (unsigned)(sv.n_tiles * kv.n_kv_heads * sv.tile_nq);
-        if (sv.tile_nq == 4) {
-            if (hd == 64) {
-                launch_attn_block<64, 4>(a, grid, s);
-                attn_merge_kernel<64, 4><<<mgrid, 256, 0, s>>>(a);
-            } else {
-                launch_attn_block<128, 4>(a, grid, s);
-                attn_merge_kernel<128, 4><<<mgrid, 256, 0, s>>>(a);
-            }
-        } else {
-            if (hd == 64) {
-                launch_attn_block<64, 8>(a, grid, s);
-                attn_merge_kernel<64, 8><<<mgrid, 256, 0, s>>>(a);
-            } else {
-                launch_attn_block<128, 8>(a, grid, s);
-                attn_merge_kernel<128, 8><<<mgrid, 256, 0, s>>>(a);
-            }
-        }
+    if (sv.tile_nq == 4) {                                     // long extends: 4 tiles per block, K/V through LDS
+        launch_items<4>(a, sv.n_items, sv.n_merge, s);
     } else {
         if (sv.n_tiles_shared > 0) {
             // Many sequences that share a cached prefix (the same leading blocks): the keys of the
@@ -866,14 +870,9 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
             // wavefronts below start at shared_len, and the merge adds the shared pass's slices.
             AttnArgs sh = a;
             sh.tile_info = sv.tile_info + (size_t)sv.n_tiles * 8;
-            sh.n_splits = sv.shared_splits;
             sh.partials = partials + attention_partial_floats(sv.n_tiles, kv.n_kv_heads, hd, n_splits);
-            dim3 grid(sv.n_tiles_shared, kv.n_kv_heads, sv.shared_splits);
-            if (sv.shared_nq == 4) {
-                if (hd == 64) launch_attn_block<64, 4>(sh, grid, s); else launch_attn_block<128, 4>(sh, grid, s);
-            } else {
-                if (hd == 64) launch_attn_block<64, 8>(sh, grid, s); else launch_attn_block<128, 8>(sh, grid, s);
-            }
+            if (sv.shared_nq == 4) launch_items<4>(sh, sv.n_tiles_shared * sv.shared_splits, 0, s);
+            else launch_items<8>(sh, sv.n_tiles_shared * sv.shared_splits, 0, s);
             a.shared_partials = sh.partials;
             a.shared_splits = sv.shared_splits;
             a.shared_nq = sv.shared_nq;

@@ -12,23 +12,9 @@
 //   * Smaller tiles (128 x 256, 128 x 128) move 1.5x / 2x the operands per product; they are for launches that would leave CUs without a
 //     block (the planner at the end weighs tile and K-slice choices by measured step times).
 #include "gemm_device.h"
+#include "lds_copy.h"
 
 namespace ax {
-
-// The 64 lanes of a wavefront copy 64 x 16 bytes to 1 KB of LDS at `lds` (wavefront-uniform byte address): lane l's 16 bytes come from
-// base + off and land at lds + 16 l.  Written as assembly because the compiler orders every later LDS read
-// behind such a copy with a full vmcnt wait; the kernel's own waits and barriers (below) are what orders them.
-__device__ __forceinline__ void copy_to_lds(const void* base, unsigned off, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(base) : "memory");
-}
-// All but the last N copies of this wavefront have landed and its LDS reads have come back; then a barrier.  (The LDS wait is a builtin so
-// that the compiler knows about it and waits for no later read because of an earlier one.)
-template <int N>
-__device__ __forceinline__ void wait_copies_and_sync() {
-    __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0)
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N) : "memory");
-}
 
 // 16 rows' sums over 32 lanes (v[r]: this lane's share of row r) with a transposing butterfly: at each stage a lane hands half of its
 // values to its partner and keeps the other half.  Returns the total of row (lane % 32) >> 1.

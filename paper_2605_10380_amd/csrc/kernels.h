@@ -25,14 +25,19 @@ struct StepView {
     const int* seq_bt;      // [n_seq] offset of the sequence's block table inside bt
     const int* bt;          // concatenated block tables
     const int* out_rows;    // [n_out] rows that go through the LM head
-    const int* tile_info;   // [n_tiles + n_tiles_shared][8] attention q-tile groups over stacked rows (t, g):
-                            // sequence, first stacked row, P, T, first row of the sequence, block-table offset,
-                            // key limit (0 = the rows' causal bound), first key
-                            // (a group = tile_nq tiles of 32 rows; 32-byte aligned records)
-    int n_rows, n_seq, n_out, n_tiles, tile_nq;
-    // shared-prefix pass (calls with several sequences whose block tables start alike): groups of
-    // shared_nq tiles over ALL rows of the call against keys [0, shared_len); 0 groups = no such pass
-    int n_tiles_shared, shared_nq, shared_len, shared_splits;
+    // attention work, 8 ints (32 bytes, aligned) a record.  Stacked rows of a sequence: row t of query head g of a KV head is t * G + g.
+    //   tile_nq == 1 (fp32 models; verify steps and short extends): n_tiles records of one 32-row tile each -
+    //     sequence, first stacked row, P, T, first row of the sequence, block-table offset, 0, first key;
+    //     then (n_tiles_shared > 0: sequences whose block tables start alike) the items of a pass of groups of shared_nq tiles over
+    //     ALL rows of the call against keys [0, shared_len), shared_splits items per group
+    //   tile_nq == 4 (long extends): n_items ITEMS of 4 tiles and a range of key steps of 32 each -
+    //     slot of the partial records (-1: all the keys, writes the output itself), first stacked row, P, T, first row of the
+    //     sequence, block-table offset, end of the range, first step;
+    //     then n_merge records of the tiles several items share -
+    //     first slot, first stacked row, number of slots, T, first row of the sequence, 0, 0, 0
+    const int* tile_info;
+    int n_rows, n_seq, n_out, n_tiles, tile_nq, n_items, n_merge;
+    int n_tiles_shared, shared_nq, shared_len, shared_splits;      // 0 groups = no shared-prefix pass
 };
 
 enum Epilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };

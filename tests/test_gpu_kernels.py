@@ -236,6 +236,53 @@ def test_f32_model_head_dims_and_row_edges(torch_cuda, hd, d, F, P, T):
     dm.close()
 
 
+def _one_layer(torch_cuda, sh, P, T, seed, max_tokens, act_split=0):
+    """Attention output and residual stream of the last T rows of a one-layer model, and the oracle's."""
+    from paper_2605_10380_amd import binding as B
+    w = I.make_weights(sh, seed)
+    toks = I.templated_prompt(sh.vocab, seed, P + T)
+    dm = B.DeviceModel(sh, w, max_pos=P + T + 16, max_tokens=max_tokens, pool_tokens=P + T + 64, pool_fill=0xFF, act_split=act_split)
+    kv = dm.new_kv()
+    okv = O.KVCache(sh.n_layers, sh.n_kv_heads, sh.head_dim)
+    for at in range(0, P, max_tokens):
+        dm.extend(kv, toks[at:min(P, at + max_tokens)])
+        O.forward(sh, w, toks[at:min(P, at + max_tokens)], okv)
+    dm.extend(kv, toks[P:], B.AX_OUT_LAST_ARGMAX)
+    attn = np.zeros((T, sh.n_q_heads * sh.head_dim), dtype=np.float16)
+    x = np.zeros((T, sh.d_model), dtype=np.float32)
+    B.ax_dbg_read(dm.model, 3, attn)
+    B.ax_dbg_read(dm.model, 0, x)
+    tr = {}
+    O.forward(sh, w, toks[P:], okv, trace=tr)
+    dm.close()
+    return attn.astype(np.float64), tr["attn"].reshape(T, -1), x.astype(np.float64), tr["x"]
+
+
+@pytest.mark.parametrize("hd,hkv,G,P,T,split", [
+    (64, 2, 4, 0, 65, 0), (64, 2, 4, 31, 100, 0), (64, 1, 1, 0, 300, 0), (64, 8, 4, 777, 96, 0), (64, 4, 3, 1000, 130, 1),
+    (128, 2, 3, 0, 43, 0), (128, 1, 8, 500, 17, 0), (128, 8, 1, 640, 257, 0), (128, 2, 5, 33, 90, 1),
+    (64, 32, 4, 40, 1056, 0)])                                 # more groups of tiles than run at once: the rest is cut
+def test_block_attention_items(torch_cuda, hd, hkv, G, P, T, split):
+    """Attention of long extends at the edges of its tiles (32 rows), groups (128), key steps (32), pages (16) and key
+    ranges, over pool memory full of NaN patterns."""
+    sh = I.DecoderShape("attn-edge", 1, 128, hkv * G, hkv, hd, 192, 512, "bf16")
+    got, ref, x, xr = _one_layer(torch_cuda, sh, P, T, 21, max(T, 64), split)
+    assert np.abs(got - ref).max() <= 4e-3 * np.abs(ref).max()
+    assert np.abs(x - xr).max() <= 4e-3 * np.abs(xr).max()
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,F,T,split", [
+    (64, 2, 1, 64, 64, 257, 0), (192, 3, 1, 128, 320, 300, 0), (512, 8, 2, 64, 1088, 511, 0), (2048, 8, 2, 128, 2112, 385, 0),
+    (1088, 5, 5, 64, 4096, 640, 0), (320, 4, 2, 128, 448, 270, 1), (1024, 8, 4, 64, 2560, 513, 1)])
+def test_many_row_gemms(torch_cuda, d, hq, hkv, hd, F, T, split):
+    """The block GEMMs of calls with more than 256 rows: row, column and K remainders of all tile shapes, K slices (the long K of the
+    down projection against few columns), both activation layouts."""
+    sh = I.DecoderShape("gemm-edge", 1, d, hq, hkv, hd, F, 512, "bf16")
+    got, ref, x, xr = _one_layer(torch_cuda, sh, 0, T, 22, T, split)
+    assert np.abs(got - ref).max() <= 4e-3 * np.abs(ref).max()
+    assert np.abs(x - xr).max() <= 4e-3 * np.abs(xr).max()
+
+
 def test_measured_peaks_probe(torch_cuda):
     """The machine-rate probes leave their buffer's first half untouched (the read-only stream writes
     nothing, the copy kernel fills the second half with the first) and report rates that a working
