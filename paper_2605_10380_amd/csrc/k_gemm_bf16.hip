@@ -9,11 +9,12 @@
 //   * skinny kernel (M <= 16, the O projection and narrow stores to 32: verify steps, pure weight streaming): one block owns 16 output
 //     columns, its wavefronts split K, W goes HBM -> registers -> v_mfma_f32_16x16x32_f16
 //     with no LDS in the streaming loop; the per-wavefront partial sums meet in LDS.
-//   * tile kernel   (more rows): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
+//   * tile kernel   (more rows, to 256): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
 //     v_mfma_f32_32x32x16_f16, global loads several K slices ahead.
-//   * stream kernel (SwiGLU from 193-257 rows, logits from 17 rows, QKV / down projection of many rows, and - over K
-//     slices - the SwiGLU GEMM of 17-192 rows and the down projection of 129 rows up): activations through LDS,
-//     weights straight into MFMA operands.  The launcher states each crossover with the figures behind it.
+//   * stream kernel (logits from 17 rows, SwiGLU at 193-256 rows of wide matrices, and - over K slices - the SwiGLU GEMM of
+//     17-192 rows and the down projection of 129-192): activations through LDS, weights straight into MFMA operands.
+//     The launcher states each crossover with the figures behind it.
+//   * block kernel  (more than 256 rows; k_gemm_block.hip).
 //
 // RMSNorm is folded into the GEMMs around it.  The GEMM that produces the residual stream x
 // also writes a = fp16(x * gain_next) and, per row and per block of columns, a partial sum of
@@ -424,23 +425,19 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs g) {
     store_split((f16*)g.C16 + (long long)m * N + n, g.c_lo_off, silu_f(a * s_inv) * (b * s_inv));
 }
 
-// ------------------------------------------------------------------------------ stream SwiGLU kernel
-// First written for the SwiGLU gate/up GEMM of a few hundred rows.  The LDS-staged kernel above moves both operands through
-// LDS and spends more cycles there than on the matrix cores (a 32 x 64 wavefront tile reads
-// 1.5 KB of LDS per MFMA).  Here only the activation tile goes through LDS; every wavefront
+// ------------------------------------------------------------------------------ stream kernel
+// The LDS-staged kernel above moves both operands through LDS and spends more cycles there than on the matrix cores (a 32 x 64
+// wavefront tile reads 1.5 KB of LDS per MFMA).  Here only the activation tile goes through LDS; every wavefront
 // streams its own weight rows HBM/L2 -> registers -> MFMA, as the skinny kernel does.  Block = 4
 // wavefronts side by side along N, all working on the same BM = TM*32 rows; a wavefront owns 32
 // output columns, i.e. one 32-row tile each of W (gate) and W2 (up).  The weight loads run D
 // k-steps ahead in a register ring, the activation tile is double buffered in LDS, one barrier
-// per k-step of 64.  Measured against the LDS-staged kernel at M = 512 / 1024: 79 / 147 us
-// instead of 110 / 184 us (N = 8192, K = 3072), 174 / 332 instead of 246 / 410 us (N = 14336,
-// K = 4096); at M = 256 it has too few blocks per CU and loses, so it is not used there.
+// per k-step of 64.  Above 256 rows the block kernel is faster (~1B gate / up at 4096 rows: 382 -> 270 us).
 //
 // Blocks are renumbered so that the gy row tiles that share a weight tile have consecutive ids
 // on one XCD (workgroups are dealt to the 8 XCDs round robin), i.e. share that XCD's L2.
 //
-// The same kernel serves the other GEMMs of calls with thousands of rows (EPI_STORE_F32: the QKV
-// products, EPI_RESIDUAL): there a wavefront's two weight streams are two 32-row tiles of the ONE
+// EPI_STORE_F32 (logits) and EPI_RESIDUAL with NS = 2: a wavefront's two weight streams are two 32-row tiles of the ONE
 // matrix, 32 columns apart, and a block covers 256 output columns.
 //
 // NS = 1: one weight stream per wavefront (block = 128 columns), and K may be cut into g.ksplit
@@ -1041,17 +1038,12 @@ static int env_int(const char* name, int dflt) {
 static constexpr int env_int(const char*, int dflt) { return dflt; }
 #endif
 static const int kSwigluStreamMinNK = env_int("AX_SWIGLU_STREAM_MIN_NK", 0);   // measurement switch: gate/up weights (2^20) per matrix from which verify-size calls stream (0 = never)
-static const int kStreamTm = env_int("AX_STREAM_TM", 1);   // experiment knob: 0 = always 128-row blocks
 static const int kSwigluWaves = env_int("AX_SWIGLU_WAVES", 4096);   // wavefronts in flight the SwiGLU launch aims for (two weight streams per wavefront)
 static const int kLmStream = env_int("AX_LM_STREAM", 1);   // experiment knob
 static const int kSkinnyMaxM = std::min(32, env_int("AX_SKINNY_MAX_M", 32));   // experiment knob: rows up to which the skinny kernel may run
 static const int kForceNW = env_int("AX_SKINNY_NW", 0);   // experiment knob: wavefronts per block, 0 = automatic
 
 // More rows: LDS-staged tiles.
-static const int kStreamMinBlocks = env_int("AX_STREAM_MIN_BLOCKS", 128);
-static const int kStreamMinM = env_int("AX_STREAM_MIN_M", 512);   // rows from which QKV / residual GEMMs stream their weights (0 = never)
-static const int kSliceMinM = env_int("AX_SLICE_MIN_M", 257);   // rows from which the down projection may stream over K slices
-static const int kSliceStream = env_int("AX_SLICE_STREAM", 1);   // experiment knob
 static const int kMidStream = env_int("AX_MID_STREAM", 1);   // experiment knob: 0 = tile kernels for 129-192 rows
 static const int kQkvTile = env_int("AX_QKV_TILE", -1);   // experiment knobs: force 64-row (0) or 128-row (1) blocks
 static const int kResTile = env_int("AX_RES_TILE", -1);
@@ -1067,17 +1059,6 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
     const long long tiles128 = (long long)((N + 127) / 128) * ((M + 127) / 128);
     // 128-row blocks only when their row padding costs at most ~15 % more rows than 64-row blocks' (M = 144 does not qualify)
     const bool pad_ok = (long long)((M + 127) / 128) * 128 * 100 <= (long long)((M + 63) / 64) * 64 * 115;
-    // Calls with several hundred rows or more: the streaming kernel (weights straight to the MFMA
-    // operands, 128 x 256 blocks, one block per CU at a time) where its blocks fill the 256 CUs
-    // evenly - a single round of 128 or more blocks (160 for the down projection, which otherwise
-    // goes over K slices), or rounds that are at least 3/4 full - and,
-    // for the residual GEMMs, only with the long K of the down projection.  Measured against the
-    // tile kernel: ~8B QKV 94-101 -> 81 us at M = 704-768, 106 -> 88 at 1024, 326 -> 278 at 3584;
-    // ~8B down 293 -> 259 at 2048 and 558 -> 493 at 3584, ~3B down 168 -> 153 at 2048; O projections
-    // and half-empty last rounds (336 blocks) lose 5-40 % and stay with the tile kernel.
-    const long long sblocks = (long long)((N + 255) / 256) * ((M + 127) / 128), rounds = (sblocks + 255) / 256;
-    const bool stream = kStreamMinM > 0 && M >= kStreamMinM && N % 32 == 0 && sblocks >= (EPI == EPI_RESIDUAL ? 160 : kStreamMinBlocks) &&
-                        (rounds == 1 || sblocks * 4 >= rounds * 256 * 3) && (EPI != EPI_RESIDUAL || K >= 8192);
     // 129-192 rows (16 sessions verified together), residual GEMM with a long K (down projection):
     // one 160- or 192-row streaming block per 128 columns reads every weight once (64-row tiles
     // pull it three times out of L2) and K slices give the chip its ~200 blocks: ~3B down
@@ -1092,17 +1073,6 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
                 (size_t)ks * 2 * M * N * sizeof(float) <= g.split_ws_bytes)
                 mid_ks = ks;
     if constexpr (EPI == EPI_QKV) {
-        if (stream && (size_t)M * N * sizeof(float) <= g.split_ws_bytes) {
-            GemmArgs gs = g;
-            gs.ksplit = 1;
-            GemmArgs gp = gs;
-            gp.ssq = nullptr;
-            gp.Cf = g.split_ws;
-            const int gx = (N + 255) / 256, gy = (M + 127) / 128;
-            AX_SPLIT_LAUNCH(gp.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3, 2, false), gx * gy, 256, gp, gx, gy);
-            launch_qkv_reduce(gs, s);
-            return 0;
-        }
         // A plain store GEMM writes fp32 products, a second kernel does the rms scaling, rotary
         // embedding and KV append: measured faster than a fused epilogue (one head per wavefront)
         // at every size tried (M = 256 / 512, all three model shapes).  With few tiles K is cut in
@@ -1144,29 +1114,6 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             if (M <= 160) gemm_bf16_stream_kernel<EPI_RESIDUAL, 5, 3, 1, true, false><<<mid_cb * mid_ks, 256, 0, s>>>(gs, mid_cb, 1);
             else gemm_bf16_stream_kernel<EPI_RESIDUAL, 6, 3, 1, true, false><<<mid_cb * mid_ks, 256, 0, s>>>(gs, mid_cb, 1);
             return launch_residual_reduce(gs, s);
-        }
-        if (stream) {
-            const int gx = (N + 255) / 256, gy = (M + 127) / 128;
-            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_RESIDUAL, 4, 3, 2, false), gx * gy, 256, g, gx, gy);
-            return N / 32;
-        }
-        // a few hundred rows against the long K of the down projection: too few 128 x 256 blocks for
-        // the streaming kernel as it is, enough once K is cut into 2-4 slices (160-256 blocks).
-        // Against the tile kernel: ~8B 107 -> 70 us at M = 288-320, 85 -> 71 at 384, 145 -> 118 at 768, 145 -> 131 at 1024;
-        // ~3B 58 -> 50 at 512, 93 -> 78 at 1024; ~1B 57 -> 49 at 768.
-        if (kSliceStream && M >= kSliceMinM && K >= 8192 && N % 64 == 0 && g.split_ws) {
-            int ks = 1;
-            for (int c : {4, 3, 2})                        // one block per CU at a time: at most 256 blocks
-                if (ks == 1 && sblocks * c <= 256 && K % (c * 64) == 0 && K / (c * 64) >= 16 &&
-                    (size_t)c * 2 * M * N * sizeof(float) <= g.split_ws_bytes)
-                    ks = c;
-            if (ks > 1 && sblocks * ks >= (ks == 2 ? 128 : 160)) {       // two slices pay from half the CUs up (~3B at 704-768 rows: 88 -> 74 us)
-                GemmArgs gs = g;
-                gs.ksplit = ks;
-                const int gx = (N + 255) / 256, gy = (M + 127) / 128;
-                AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_RESIDUAL, 4, 3, 2, true), gx * gy * ks, 256, gs, gx, gy);
-                return launch_residual_reduce(gs, s);
-            }
         }
         // Few output tiles (M = 256 against N = 2048 is 64 tiles of 64 x 128 for 256 CUs): cut K
         // until there are ~256 blocks, each still with 8 or more k-steps; fp32 partial slabs go to
@@ -1272,7 +1219,10 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             }
             return 0;
         }
-        if (EPI == EPI_STORE_F32 && stream) {              // logits of thousands of rows
+        // last-row logits of more than 512 sequences (their rows gathered, which the block kernel does not do): 128 x 256 streaming
+        // blocks where they fill the 256 CUs evenly - a single round of 128 or more, or rounds at least 3/4 full
+        const long long sblocks = (long long)((N + 255) / 256) * ((M + 127) / 128), rounds = (sblocks + 255) / 256;
+        if (EPI == EPI_STORE_F32 && M >= 512 && N % 32 == 0 && sblocks >= 128 && (rounds == 1 || sblocks * 4 >= rounds * 256 * 3)) {
             const int gx = (N + 255) / 256, gy = (M + 127) / 128;
             AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3, 2, false), gx * gy, 256, g, gx, gy);
             return 0;
@@ -1332,32 +1282,16 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         else launch_skinny_nw<EPI, 2>(g, nw, s);
         return EPI == EPI_RESIDUAL ? N / cols : 0;
     }
-    // streaming SwiGLU kernel: from three 128-row blocks up, and with two when the matrix is wide
-    // enough for ~200 blocks (~8B shape at 193-256 rows: 118 -> 97 us; ~1B / ~3B have 128 blocks
-    // there and lose: 32 -> 52, 45 -> 68 us)
-    if (EPI == EPI_SWIGLU && (M > 256 || (M > 192 && (long long)((N + 127) / 128) * ((M + 127) / 128) >= 192))) {
-        // rows per block: 96, 128, 160 or 192.  One block runs per CU at a time, so a launch takes
-        // (rounds of 256 blocks) x (time of a block), and a block's time grows with the operand rows
-        // it pulls (its activation rows + 2 x 128 weight rows): pick the shape with the smallest
-        // product.  257 rows of the ~1B shape: 3 x 96 rows (192 blocks) instead of 3 x 128, 56 -> 45 us;
-        // 640 rows: 4 x 160 (256 blocks, one round) instead of 5 x 128 (320 blocks, two), 99 -> 65 us.
-        int tm = 4;
-        if (kStreamTm) {
-            long long best = -1;
-            for (int t : {4, 3, 5, 6}) {
-                if (g.a_lo_off != 0 && t > 4) continue;      // split activations: at most 128-row blocks
-                const long long blocks = (long long)((N + 127) / 128) * ((M + 32 * t - 1) / (32 * t));
-                const long long cost = ((blocks + 255) / 256) * (32 * t + 256) * (t >= 5 ? 115 : 100);   // the two large shapes run ~15 % below the model
-                if (best < 0 || cost < best) { best = cost; tm = t; }
-            }
-        }
-        const int gx = (N + 127) / 128, gy = (M + 32 * tm - 1) / (32 * tm);
-        switch (tm) {
-            case 3: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-            case 5: gemm_bf16_stream_kernel<EPI_SWIGLU, 5, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
-            case 6: gemm_bf16_stream_kernel<EPI_SWIGLU, 6, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
-            default: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-        }
+    // streaming SwiGLU kernel at 193-256 rows when the matrix is wide enough for ~200 blocks (~8B shape: 118 -> 97 us; ~1B / ~3B
+    // have 128 blocks there and lose: 32 -> 52, 45 -> 68 us)
+    if (EPI == EPI_SWIGLU && M > 192 && M <= 256 && (N + 127) / 128 * 2 >= 192) {
+        // Two blocks of 128 rows or three of 96.  One block runs per CU at a time, so a launch takes (rounds of 256 blocks) x (time of
+        // a block), and a block's time grows with the operand rows it pulls (its activation rows + 2 x 128 weight rows).
+        const int gx = (N + 127) / 128;
+        if ((3 * gx + 255) / 256 * (96 + 256) < (2 * gx + 255) / 256 * (128 + 256))
+            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3, 2, false), gx * 3, 256, g, gx, 3);
+        else
+            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3, 2, false), gx * 2, 256, g, gx, 2);
         return 0;
     }
     return launch_lds_tile<EPI>(g, s);
