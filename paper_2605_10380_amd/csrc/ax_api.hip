@@ -182,19 +182,24 @@ struct ProfScope {                     // records a pair of events around one la
     ~ProfScope() { if (b) (void)hipEventRecord(b, st); }
 };
 
-// Key slices of the split attention, from measurements on the ~1B and ~8B shapes: blocks of 4 q
-// tiles inside a captured graph (others: plan_items) at about two blocks per CU (2048 wavefronts); single-tile
-// wavefronts (verify steps, short extends) at about 512 wavefronts - beyond that the merge of the
-// slices costs more than the shorter key loops save.  At least two 32-key steps per slice,
-// rounded down to a power of two so that the choice (a launch dimension, hence part of a captured
-// graph) changes only when the cache length doubles.
+// Wavefronts per block of the split attention (`items` single tiles x KV heads): four, which share out a slice's key steps, where the
+// steps give every CU such a block with at least two steps per wavefront (~1B verify, 16 items of 137 steps: 843 -> 826 us);
+// else one (~1B decode, 8 items of 41 steps: 727 us against 755 on 32 blocks of four).
+int split_waves(int items, int max_steps) { return 256 / std::max(1, items) <= max_steps / 8 ? 4 : 1; }
+
+// Key slices of the split attention.  Blocks of 4 q tiles inside a captured graph (others: plan_items) run best at about two
+// blocks per CU (2048 wavefronts); single tiles (verify steps, short extends) at one block of four wavefronts per CU, or at about 512
+// blocks of one - beyond that the merge of the slices costs more than the shorter key loops save.
+// At least two 32-key steps per wavefront, rounded down to a power of two so that the choice (a launch dimension, hence
+// part of a captured graph) changes only when the cache length doubles.
 int choose_splits(const ax_model* m, int items, int nq, int max_steps) {
-    const int target = nq == 1 ? 512 : 2048;
-    int want = std::max(1, target / std::max(1, items * nq));
-    // many sequences in one call: 512 wavefronts would leave each with a long serial key loop;
-    // go up to 2048 wavefronts while a slice still has ~8 key steps
-    if (nq == 1 && max_steps / want > 8) want = std::max(want, std::min(2048 / std::max(1, items), (max_steps + 7) / 8));
-    want = std::min(want, std::max(1, max_steps / 2));
+    const int waves = nq == 1 ? split_waves(items, max_steps) : 1;
+    int want = std::max(1, (nq > 1 ? 2048 : waves == 4 ? 256 : 512) / std::max(1, items * nq));
+    // many sequences in one call: that would leave wavefronts with long serial key loops;
+    // go up to 2048 wavefronts while each still has ~8 key steps
+    if (nq == 1 && max_steps / want > 8 * waves)
+        want = std::max(want, std::min(2048 / (waves * std::max(1, items)), (max_steps + 8 * waves - 1) / (8 * waves)));
+    want = std::min(want, std::max(1, max_steps / (2 * waves)));
     const size_t cap = m->lay.max_records / ((size_t)items * nq);      // >= 1 for every call prepare_call lets through
     want = std::min(want, std::max(1, (int)cap));
     int p2 = 1;
@@ -543,7 +548,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
                 ax::launch_gemm_f32(ax::EPI_QKV, g, stream);
             }
             { ProfScope ps(m, 1, stream);
-              ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, nullptr, 1, stream); }
+              ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, nullptr, 1, 1, stream); }
             {
                 ax::GemmF32Args g = base;
                 g.A = (const float*)attn; g.W = (const float*)m->wo[(size_t)l]; g.N = d_model; g.K = qdim; g.C = x;
@@ -609,7 +614,8 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
                 (void)ax::launch_gemm_bf16(ax::EPI_QKV, g, stream);   // (its slab always fits: make_layout reserves max_tokens rows of it)
             }
             { ProfScope ps(m, 1, stream);
-              ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, (float*)(ws + L.partials), n_splits, stream, L.q_lo, L.attn_lo); }
+              ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, (float*)(ws + L.partials), n_splits,
+                                 split_waves(cp.n_tiles * c.n_kv_heads, cp.max_steps), stream, L.q_lo, L.attn_lo); }
             { ProfScope empty(m, 6, stream); }         // bracket around nothing: the cost of the two events
             {
                 ax::GemmArgs g = base;
@@ -704,7 +710,7 @@ ax_status run_verify_graph(ax_model* m, ax_kv* kv, const int32_t* toks, int T, v
     for (auto& cw : cp.cows) ax::launch_block_copy(dt, cp.pool->geom, m->cfg.n_layers, cw.first, cw.second, stream);
     const int n_splits = choose_splits(m, cp.n_tiles * m->cfg.n_kv_heads, cp.tile_nq, cp.max_steps);
     // (block-kernel calls: the item counts follow from T and the slice count of plan_items' uniform cut)
-    const uint64_t key = ((uint64_t)(uint32_t)T << 32) | (uint32_t)(cp.tile_nq > 1 ? (int)(cp.items.size() / (size_t)cp.n_tiles) : n_splits);
+    const uint64_t key = ((uint64_t)(uint32_t)T << 32) | (uint32_t)(cp.tile_nq > 1 ? (int)(cp.items.size() / (size_t)cp.n_tiles) : n_splits | split_waves(cp.n_tiles * m->cfg.n_kv_heads, cp.max_steps) << 24);
     hipGraphExec_t exec = nullptr;
     for (auto& g : m->graphs)
         if (g.key == key && g.pool_uid == cp.pool->uid) exec = g.exec;

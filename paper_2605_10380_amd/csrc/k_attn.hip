@@ -6,10 +6,10 @@
 //   * attn_split_kernel + attn_combine_kernel: 16-bit path on the matrix cores (fp16 q, K, V and
 //     probabilities, fp32 accumulation; used by bf16-weight models).  The query rows
 //     of the G heads that share one KV head are stacked into one matrix (row = t*G + g), cut
-//     into tiles of 32 rows; one wavefront owns (tile, KV head, slice of the key range), streams
-//     its K/V slice from the pages straight into MFMA operand registers, keeps an online
-//     softmax per row and writes an unnormalised partial (O, m, l); the combine kernel merges
-//     the slices.  Splitting the key range is what fills 256 CUs when T is small (verify:
+//     into tiles of 32 rows; one block of 1 or 4 wavefronts owns (tile, KV head, slice of the key range), each wavefront
+//     streams its share of the slice from the pages straight into MFMA operand registers with an online
+//     softmax per row; the block adds them up in LDS and writes an unnormalised partial (O, m, l); the combine
+//     kernel merges the slices.  Splitting the key range is what fills 256 CUs when T is small (verify:
 //     T = 1 + k) and it is harmless when T is large.
 #include "kernels.h"
 #include "lds_copy.h"
@@ -271,16 +271,22 @@ struct AttnArgs {
 // record is one 32-byte load, the block-table entries of the whole key slice are fetched by
 // one wavefront-wide load (and handed out with shuffles), and the K/V operands of step s + 1
 // are in flight while step s is multiplied.
+// NW = 4: the wavefronts of a block meet in LDS, so a wavefront's serial chain of key steps is a quarter of the slice while only one
+// partial record per slice goes to memory and through the combine kernel.  Whole steps: ~1B verify over 4352 keys 843 -> 826 us,
+// ~8B over 8704 4108 -> 4021 us, 16 ~3B sessions verified together 5359 -> 5162 us.
+// NW = 1: caches too short to give every CU such a block (~1B decode over 1301 keys: 727 us a step, 755 with NW = 4).
 // QS: q comes as hi and lo parts (split activations): the score product takes both against the same K operand.
-template <int HD, int NQ, bool QS = false>
-__global__ __launch_bounds__(64) void attn_split_kernel(AttnArgs a) {
+template <int HD, int NW, bool QS>
+__global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
     constexpr int KQ = HD / 16;          // MFMA k-steps of the score product
     constexpr int NP = QS ? 2 : 1;
     constexpr int DT = HD / 32;          // 32-channel tiles of the output
     constexpr int PS = HD * 32 + 64;     // floats of one partial: O^T [HD][32], m[32], l[32]
+    __shared__ f32x4 s_o[NW][NW > 1 ? DT * 4 : 1][64];
+    __shared__ float s_m[NW][32], s_l[NW][32];
     const AttnWork wk = attn_work();
     const int tile = wk.tile, hk = wk.hk, split = wk.split;
-    const int lane = threadIdx.x, ql = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5;
     const int Hq = a.Hq, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
     const int4 ti0 = *(const int4*)(a.tile_info + tile * 8), ti1 = *(const int4*)(a.tile_info + tile * 8 + 4);
     const int r0 = ti0.y, P = ti0.z, T = ti0.w, row0 = ti1.x;
@@ -291,44 +297,35 @@ __global__ __launch_bounds__(64) void attn_split_kernel(AttnArgs a) {
     // keys this group can see at all: up to the position of its last valid row.  (Keys past the end of the
     // sequence, reached only by its last step, re-read the last valid K row - see fetch - and their scores are
     // replaced by -inf, so K is never read from unwritten slots; V is, and process() zeroes those operands.)
-    const int r_last = min(r0 + NQ * 32 - 1, n_stacked - 1);
+    const int r_last = min(r0 + 31, n_stacked - 1);
     const int kv_end = P + r_last / G + 1;
     const int first = ti1.w >> 5;                        // first key step (keys before it belong to the shared pass)
     const int steps = (kv_end + 31) / 32;
     const int per = (steps - first + a.n_splits - 1) / a.n_splits;
-    const int s_lo = first + split * per, s_hi = min(steps, s_lo + per);
+    const int b_lo = first + split * per, b_hi = min(steps, b_lo + per);      // the block's key steps
+    const int per_w = (max(b_hi - b_lo, 0) + NW - 1) / NW;
+    const int s_lo = b_lo + wave * per_w, s_hi = min(b_hi, s_lo + per_w);     // this wavefront's (may be none)
 
-    // this lane's query rows (clamped rows compute garbage that is never written)
-    int pos_q[NQ], pos_min[NQ];          // pos_min: earliest position among the tile's rows (uniform)
-    f16x8 qf[NQ][NP][KQ];
+    // this lane's query row (clamped rows compute garbage that is never written)
+    const int rq = min(r0 + ql, n_stacked - 1), tq = rq / G;
+    const int pos_q = P + tq, pos_min = P + min(r0, n_stacked - 1) / G;       // pos_min: earliest position of the tile (uniform)
+    const f16* qrow = a.q + ((long long)(row0 + tq) * Hq + hk * G + rq % G) * HD;
+    f16x8 qf[NP][KQ];
 #pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-        const int rq = min(r0 + t * 32 + ql, n_stacked - 1);
-        const int tq = rq / G, gq = rq % G;
-        pos_q[t] = P + tq;
-        pos_min[t] = P + min(r0 + t * 32, n_stacked - 1) / G;
-        const f16* qrow = a.q + ((long long)(row0 + tq) * Hq + hk * G + gq) * HD;
+    for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-            for (int kk = 0; kk < KQ; ++kk) qf[t][p][kk] = *(const f16x8*)(qrow + (p ? a.q_lo_off : 0) + kk * 16 + g * 8);
-    }
+        for (int kk = 0; kk < KQ; ++kk) qf[p][kk] = *(const f16x8*)(qrow + (p ? a.q_lo_off : 0) + kk * 16 + g * 8);
 
     const f16* Kp = (const f16*)a.kv.base + a.kv.plane(a.layer, 0, hk);
     const f16* Vp = (const f16*)a.kv.base + a.kv.plane(a.layer, 1, hk);
 
     const float c = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
-    float m[NQ], l[NQ];
-    f32x16 o[NQ][DT];
+    float m = -INFINITY, l = 0.f;
+    f32x16 o[DT];
 #pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-        m[t] = -INFINITY;
-        l[t] = 0.f;
+    for (int d = 0; d < DT; ++d)
 #pragma unroll
-        for (int d = 0; d < DT; ++d)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[t][d][r] = 0.f;
-    }
+        for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
 
     f16x8 kf[2][KQ];                     // K / V operands of the current and the next step
     f16x4 vq[2][DT][4];
@@ -366,31 +363,28 @@ __global__ __launch_bounds__(64) void attn_split_kernel(AttnArgs a) {
                     for (int i = 0; i < 4; ++i)
                         if (kv0 + qd * 8 + g * 4 + i >= kv_len) vq[buf][d][qd][i] = (f16)0.f;
         }
+        f32x16 s;
 #pragma unroll
-        for (int t = 0; t < NQ; ++t) {
-            f32x16 s;
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        for (int kk = 0; kk < KQ; ++kk)
 #pragma unroll
-            for (int kk = 0; kk < KQ; ++kk)
+            for (int p = 0; p < NP; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[buf][kk], qf[p][kk], s, 0, 0, 0);
+        float alpha;
+        f16x8 pb[2];
+        if (online_softmax_step(s, kv0, g, pos_q, kv0 + 31 > pos_min, c, m, l, alpha, pb)) {
 #pragma unroll
-                for (int p = 0; p < NP; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[buf][kk], qf[t][p][kk], s, 0, 0, 0);
-            float alpha;
-            f16x8 pb[2];
-            if (online_softmax_step(s, kv0, g, pos_q[t], kv0 + 31 > pos_min[t], c, m[t], l[t], alpha, pb)) {
+            for (int d = 0; d < DT; ++d)
 #pragma unroll
-                for (int d = 0; d < DT; ++d)
+                for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+        }
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) o[t][d][r] *= alpha;
-            }
-#pragma unroll
-            for (int d = 0; d < DT; ++d) {
-                const f16x4 *v = vq[buf][d];
-                const f16x8 va = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
-                const f16x8 vb = {v[2][0], v[2][1], v[2][2], v[2][3], v[3][0], v[3][1], v[3][2], v[3][3]};
-                o[t][d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, pb[0], o[t][d], 0, 0, 0);
-                o[t][d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, pb[1], o[t][d], 0, 0, 0);
-            }
+        for (int d = 0; d < DT; ++d) {
+            const f16x4 *v = vq[buf][d];
+            const f16x8 va = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
+            const f16x8 vb = {v[2][0], v[2][1], v[2][2], v[2][3], v[3][0], v[3][1], v[3][2], v[3][3]};
+            o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, pb[0], o[d], 0, 0, 0);
+            o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, pb[1], o[d], 0, 0, 0);
         }
     };
 
@@ -408,26 +402,52 @@ __global__ __launch_bounds__(64) void attn_split_kernel(AttnArgs a) {
         }
     }
 
-    // partials of the group: NQ consecutive (O^T, m, l) records per (group, KV head, slice);
-    // rows past the end of the sequence are not written (and never read)
-    float l_row[NQ];
-#pragma unroll
-    for (int t = 0; t < NQ; ++t) l_row[t] = l[t] + __shfl_xor(l[t], 32, 64);    // both halves of each row
-#pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-        if (r0 + t * 32 + ql >= n_stacked) continue;
-        float* part = a.partials + (((long long)(tile * Hkv + hk) * a.n_splits + split) * NQ + t) * PS;
+    // one (O^T, m, l) record per (tile, KV head, slice); rows past the end of the sequence are not written (and never read)
+    float* part = a.partials + ((long long)(tile * Hkv + hk) * a.n_splits + split) * PS;
+    if constexpr (NW == 1) {
+        l += __shfl_xor(l, 32, 64);                              // both halves of each row
+        if (r0 + ql >= n_stacked) return;
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ch = d * 32 + (r >> 2) * 8 + g * 4 + (r & 3);
-                part[ch * 32 + ql] = o[t][d][r];
-            }
+            for (int r = 0; r < 16; ++r) part[(d * 32 + (r >> 2) * 8 + g * 4 + (r & 3)) * 32 + ql] = o[d][r];
         if (g == 0) {
-            part[HD * 32 + ql] = m[t];
-            part[HD * 32 + 32 + ql] = l_row[t];
+            part[HD * 32 + ql] = m;
+            part[HD * 32 + 32 + ql] = l;
         }
+        return;
+    }
+    // the wavefronts' sums, brought to the block's largest reference exponent, meet in LDS
+    l += __shfl_xor(l, 32, 64);                                  // both halves of each row
+    if (g == 0) s_m[wave][ql] = m;
+    __syncthreads();
+    float M = s_m[0][ql];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w][ql]);
+    const float scale = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);    // no visible key in this wavefront's steps: 0
+    if (g == 0) s_l[wave][ql] = l * scale;
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+            s_o[wave][d * 4 + (r >> 2)][lane] = (f32x4){o[d][r] * scale, o[d][r + 1] * scale, o[d][r + 2] * scale, o[d][r + 3] * scale};
+    __syncthreads();
+    if (r0 + ql >= n_stacked) return;
+#pragma unroll
+    for (int i = 0; i < DT * 4 / NW; ++i) {                      // a wavefront writes its share of the channels
+        const int e = wave * (DT * 4 / NW) + i;                             // channels (e / 4) * 32 + (e % 4) * 8 + 4 g .. + 3
+        f32x4 t = s_o[0][e][lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += s_o[w][e][lane];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part[((e >> 2) * 32 + (e & 3) * 8 + g * 4 + q) * 32 + ql] = t[q];
+    }
+    if (wave == 0 && g == 0) {
+        float t = s_l[0][ql];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += s_l[w][ql];
+        part[HD * 32 + ql] = M;
+        part[HD * 32 + 32 + ql] = t;
     }
 }
 
@@ -807,10 +827,15 @@ size_t attention_partial_floats(int n_tiles, int n_kv_heads, int head_dim, int n
 }
 
 template <int HD, int NQ>
-static void launch_attn_mfma(const AttnArgs& a, int n_groups, hipStream_t s) {
+static void launch_attn_mfma(const AttnArgs& a, int n_groups, int waves, hipStream_t s) {
     dim3 grid(n_groups, a.kv.n_kv_heads, a.n_splits), cgrid(n_groups * a.kv.n_kv_heads * NQ, HD / 4);
-    if (a.q_lo_off) attn_split_kernel<HD, NQ, true><<<grid, 64, 0, s>>>(a);
-    else attn_split_kernel<HD, NQ, false><<<grid, 64, 0, s>>>(a);
+    if (waves == 4) {
+        if (a.q_lo_off) attn_split_kernel<HD, 4, true><<<grid, 256, 0, s>>>(a);
+        else attn_split_kernel<HD, 4, false><<<grid, 256, 0, s>>>(a);
+    } else {
+        if (a.q_lo_off) attn_split_kernel<HD, 1, true><<<grid, 64, 0, s>>>(a);
+        else attn_split_kernel<HD, 1, false><<<grid, 64, 0, s>>>(a);
+    }
     // few records with many slices (one session): blocks of 4 channels that spread the slices over
     // threads; many records with few slices (many sessions): one block per record
     if (n_groups * a.kv.n_kv_heads >= 64 && a.n_splits + a.shared_splits <= 32)
@@ -841,7 +866,7 @@ static void launch_items(const AttnArgs& a, int n_items, int n_merge, hipStream_
 }
 
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, const StepView& sv,
-                      int n_q_heads, float* partials, int n_splits, hipStream_t s, long long q_lo_off,
+                      int n_q_heads, float* partials, int n_splits, int split_waves, hipStream_t s, long long q_lo_off,
                       long long out_lo_off) {
     if (dt == F32) {
         const int subs = 2 * sv.tile_nq, hd = kv.head_dim;      // 16-row tiles per record of 32 * tile_nq rows
@@ -878,7 +903,7 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
             a.shared_nq = sv.shared_nq;
             a.shared_len = sv.shared_len;
         }
-        if (hd == 64) launch_attn_mfma<64, 1>(a, sv.n_tiles, s); else launch_attn_mfma<128, 1>(a, sv.n_tiles, s);
+        if (hd == 64) launch_attn_mfma<64, 1>(a, sv.n_tiles, split_waves, s); else launch_attn_mfma<128, 1>(a, sv.n_tiles, split_waves, s);
     }
 }
 

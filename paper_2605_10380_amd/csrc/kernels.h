@@ -127,10 +127,10 @@ void launch_gemm(DType dt, Epilogue epi, const void* A, const void* W, const voi
                  int M, int N, int K, hipStream_t s);
 // Causal attention of the new rows over the paged cache (which already holds the new rows).
 // out [n_rows, Hq, hd] in the activation type.  `partials` is fp32 scratch for the split-KV
-// path (bf16 only); n_splits >= 1.
+// path (bf16 only); n_splits >= 1, split_waves 1 or 4 wavefronts per block of it.
 // q_lo_off / out_lo_off: split activations (see GemmArgs): lo parts of q read, lo parts of out written (0 = none).
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer,
-                      const StepView& sv, int n_q_heads, float* partials, int n_splits,
+                      const StepView& sv, int n_q_heads, float* partials, int n_splits, int split_waves,
                       hipStream_t s, long long q_lo_off = 0, long long out_lo_off = 0);
 // Floats of `partials` launch_attention needs for n_tiles q tiles (of 32 rows) and n_splits splits.
 size_t attention_partial_floats(int n_tiles, int n_kv_heads, int head_dim, int n_splits);

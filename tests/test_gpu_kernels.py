@@ -271,6 +271,19 @@ def test_block_attention_items(torch_cuda, hd, hkv, G, P, T, split):
     assert np.abs(x - xr).max() <= 4e-3 * np.abs(xr).max()
 
 
+@pytest.mark.parametrize("hd,hkv,G,P,T,split", [
+    (64, 8, 4, 0, 1, 0), (64, 2, 4, 31, 2, 0), (128, 8, 4, 65, 9, 0), (128, 2, 3, 290, 17, 1), (64, 1, 1, 2000, 5, 0),
+    (128, 1, 8, 1055, 16, 0), (64, 4, 8, 700, 32, 1)])
+def test_split_attention_wavefronts(torch_cuda, hd, hkv, G, P, T, split):
+    """Attention of few rows, whose blocks of four wavefronts share out a slice's key steps: fewer steps than wavefronts, steps
+    and slices that do not divide, one slice and many, over pool memory full of NaN patterns.  Bound: q, K, V and the
+    probabilities are fp16 (11 bits, 2^-11 = 4.9e-4 each), as in the other attention tests."""
+    sh = I.DecoderShape("attn-few", 1, 128, hkv * G, hkv, hd, 192, 512, "bf16")
+    got, ref, x, xr = _one_layer(torch_cuda, sh, P, T, 23, max(T, 256), split)
+    assert np.abs(got - ref).max() <= 4e-3 * np.abs(ref).max()
+    assert np.abs(x - xr).max() <= 4e-3 * np.abs(xr).max()
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,F,T,split", [
     (64, 2, 1, 64, 64, 257, 0), (192, 3, 1, 128, 320, 300, 0), (512, 8, 2, 64, 1088, 511, 0), (2048, 8, 2, 128, 2112, 385, 0),
     (1088, 5, 5, 64, 4096, 640, 0), (320, 4, 2, 128, 448, 270, 1), (1024, 8, 4, 64, 2560, 513, 1)])
