@@ -62,6 +62,32 @@ def test_bf16_gemm(torch_cuda, M, N, K, epi):
         assert np.abs(got - want).max() <= 2 ** -11 * np.abs(want).max() + 1e-6
 
 
+def test_swiglu_of_many_rows_rounds_like_few_rows(torch_cuda):
+    """Gates of three terms that together need 20 bits (exact in fp32 in any order of summation) and ups of +-1: what is left is
+    silu(gate) itself, rounded to fp16 once, and the kernels of up to 256 rows and of more must agree bit for bit (a division that
+    is not correctly rounded in one of them moves some of the 1.2 M results to the next fp16)."""
+    torch = torch_cuda
+    from paper_2605_10380_amd import binding as B
+    M, N, K = 600, 2048, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.zeros((M, K), dtype=torch.float16, device="cuda")
+    rows = torch.arange(M, device="cuda")
+    A[rows, rows % 16] = 1.0
+    A[rows, 16 + rows // 16 % 16] = 2.0 ** -6
+    A[rows, 32 + rows % 32] = 2.0 ** -12
+    W = (torch.randint(-255, 256, (N, K), generator=g, device="cuda") / 64.0).bfloat16()
+    W2 = torch.zeros((N, K), dtype=torch.bfloat16, device="cuda")
+    W2[:, :16] = torch.where(torch.rand((N, 16), generator=g, device="cuda") < 0.5, -1.0, 1.0)
+    out = torch.zeros((2, M, N), dtype=torch.float16, device="cuda")
+    torch.cuda.synchronize()
+    B.ax_dbg_gemm(B.AX_BF16, 2, A.data_ptr(), W.data_ptr(), W2.data_ptr(), out[0].data_ptr(), M, N, K)
+    for at in range(0, M, 200):
+        B.ax_dbg_gemm(B.AX_BF16, 2, A[at:].data_ptr(), W.data_ptr(), W2.data_ptr(), out[1, at:].data_ptr(), 200, N, K)
+    assert torch.isfinite(out).all()
+    differ = int((out[0].view(torch.int16) != out[1].view(torch.int16)).sum())
+    assert differ == 0, differ
+
+
 def _random_gemm_cases(n, seed=20260517):
     """Seeded shapes around the launcher's row-count crossovers (16/17, 32/33, 64/65, 128/129, 192/193, 256/257,
     512/513) with ragged column counts (multiples of 16) and K a multiple of 64: every (kernel, epilogue)
