@@ -46,8 +46,7 @@ struct TimerEvents {
 constexpr int N_SLOTS = 4;            // staging ring for per-call descriptors
 constexpr int LOGIT_ROWS = 256;       // rows per LM-head pass when only the argmax is wanted
 constexpr long long kSharedMinKeys = 2048;   // (sequences - 1) x shared keys that justify a shared-prefix pass
-constexpr int MIN_RECORDS = 2048;     // partial records the split attention may always use (workspace size)
-constexpr int MAX_RECORDS = 8192;     // ... and what it has no use for beyond (unless single slices already need more)
+constexpr int MIN_RECORDS = 2048;     // partial records a pass of the attention may always use (workspace size)
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 int isz(int dtype) { return ax::itemsize(dtype); }
@@ -65,7 +64,7 @@ struct Layout {                       // byte offsets into the workspace
     size_t rope_cos, rope_sin, desc, x, h, ssq, qkv, q, attn, ffn, partials, splitk, logits, amax_scratch,
         amax_out, result, packed, total;
     size_t desc_ints;                 // capacity of one descriptor slot
-    size_t max_records;               // split-attention partial records one pass may write (there is room for two passes)
+    size_t max_records;               // attention partial records one pass of tiles may write (there is room for two; items have both)
     int max_tiles, max_bt;
     // split activations: element offsets from the hi part of each 16-bit activation buffer to its lo part (0 = off)
     long long h_lo, q_lo, attn_lo, ffn_lo;
@@ -82,14 +81,13 @@ Layout make_layout(const ax_model_config& c) {
     Layout L{};
     const size_t T = (size_t)c.max_tokens, S = (size_t)c.max_seqs, a = (size_t)isz(c.dtype);
     const int G = c.n_q_heads / c.n_kv_heads;
-    // Partial records of the split attention: one per (q tile of 32 stacked rows, KV head, key slice).  A call
-    // whose longest sequence runs on blocks of 4 or 8 tiles pads EVERY sequence to whole blocks, so the most a
-    // call can need with one slice is (T G / 32 + 8 per sequence) tiles per KV head; the slice count is then
-    // chosen to stay inside this capacity.  Room for two passes: the per-sequence one and the shared-prefix one.
-    const size_t one_slice = ((T * G + 31) / 32 + 8 * S + 2) * (size_t)c.n_kv_heads;
-    L.max_records = std::max({(size_t)MIN_RECORDS, one_slice, std::min((size_t)MAX_RECORDS, 8 * one_slice)});
-    // tile records, or items (no more than their partial records plus one per group) and merge records; and the shared pass's items
-    L.max_tiles = (int)((T * G + 31) / 32 + S + 2 * ((T * G) / 128 + S + 2) + 2 * (L.max_records / (4 * (size_t)c.n_kv_heads)));
+    // Partial records of the attention: one per (q tile of 32 stacked rows, KV head, key slice).  The most a pass can need with
+    // one slice is (T G / 32 + 8 per sequence) tiles per KV head (groups of 4 or 8 tiles pad a sequence to whole groups); the slice
+    // counts are then chosen to stay inside this capacity.  Room for two passes: single tiles and the shared-prefix pass.  Planned
+    // items have the room of both: a call has either of the two, and items that run at once never need more than 4096 records.
+    L.max_records = std::max((size_t)MIN_RECORDS, ((T * G + 31) / 32 + 8 * S + 2) * (size_t)c.n_kv_heads);
+    // tile records and the shared pass's items; or items (a group that is not cut, or a slot each) and merge records (of two slots or more)
+    L.max_tiles = (int)((T * G + 31) / 32 + S + 2 + L.max_records / (size_t)c.n_kv_heads);
     L.max_bt = (c.max_pos + 15) / 16;
     L.desc_ints = 5 * T + 4 * S + S * (size_t)L.max_bt + 8 * (size_t)L.max_tiles + 32;
     size_t o = 0;
@@ -398,7 +396,7 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
             return fail(AX_ERR_UNSUPPORTED, "%d attention tile groups of %d tiles exceed the workspace's %zu partial records",
                         cp.n_tiles, cp.tile_nq, m->lay.max_records);
         const int uniform = graph_slot ? choose_splits(m, cp.n_tiles * c.n_kv_heads, cp.tile_nq, longest) : 0;
-        plan_items(groups, c.n_kv_heads, c.head_dim == 64, m->lay.q_lo != 0, uniform, m->lay.max_records, cp.items, cp.merges);
+        plan_items(groups, c.n_kv_heads, c.head_dim == 64, m->lay.q_lo != 0, uniform, 2 * m->lay.max_records, cp.items, cp.merges);
     }
     cp.n_out = out_mode == AX_OUT_NONE ? 0
                : (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_LAST_ARGMAX) ? n : (int)n_rows;

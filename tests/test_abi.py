@@ -60,6 +60,17 @@ def test_config_validation_without_gpu():
     assert B.ax_workspace_bytes(B.make_config(I.SHAPES["tiny"], 1024, 64)) > 0
 
 
+@pytest.mark.parametrize("name,max_pos,max_tokens,max_seqs,most", [
+    ("1b", 8192, 256, 1, 2666.5e6), ("1b", 8192, 1024, 1, 2746.0e6), ("1b", 5000, 4096, 1, 3099.5e6), ("1b", 2048, 64, 4, 2546.5e6),
+    ("3b", 8192, 1024, 1, 6780.0e6), ("3b", 8192, 256, 16, 6667.5e6), ("3b", 9000, 3520, 16, 7202.5e6),
+    ("8b", 9000, 1024, 1, 15476.5e6), ("8b", 16384, 512, 1, 15349.0e6)])
+def test_workspace_stays_the_size_callers_planned_for(name, max_pos, max_tokens, max_seqs, most):
+    """Workspace bytes of the decoder shapes.  Attention records: two passes of at most max(2048, one slice) records, which also hold
+    every set of items that runs at once (256 compute units x up to 4 blocks x 4 tiles = 4096); a capacity nothing can use once
+    made the region four times this size.  The bounds leave 1 MB for descriptors."""
+    assert 0 < B.ax_workspace_bytes(B.make_config(I.SHAPES[name], max_pos, max_tokens, max_seqs)) <= most
+
+
 def test_extend_rejects_bad_arguments_before_any_launch():
     cfg = B.make_config(I.SHAPES["tiny"], 1024, 64)
     pool = B.ax_pool_create(cfg, 0, B.ax_pool_block_bytes(cfg) * 8)
