@@ -10,7 +10,7 @@ namespace ax {
 // behind such a copy with a full vmcnt wait; the kernel's own waits and barriers (below) are what orders them.
 __device__ __forceinline__ void copy_to_lds(const void* base, unsigned off, unsigned lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(base) : "memory");
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(base) : "m0", "memory");
 }
 // All but the last N copies of this wavefront have landed and its LDS reads have come back; then a barrier.  (The LDS wait is a builtin so
 // that the compiler knows about it and waits for no later read because of an earlier one.)
