@@ -20,6 +20,10 @@ extern "C" {
 ax_status ax_dbg_gemm(int dtype, int epilogue, const void *A, const void *W, const void *W2, void *C,
                       int M, int N, int K, void *hip_stream);
 
+/* How the attention of a verify step or short extend would be launched: `items` = tiles of 32 stacked rows x KV heads, max_steps =
+ * key steps of 32 of the longest sequence.  Writes the wavefronts per block (1 or 4) and the key slices per item.  Host only. */
+ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps, int *waves, int *slices);
+
 /* The residual GEMM as a bf16-weight decoder layer runs it (O and down projections): x[M,N] (float,
  * updated in place) += A[M,K] W[N,K]^T, then a16[M,N] = fp16(x * gain[n]) and per-row partial sums
  * of x^2: ssq[m * (*n_parts) + p], p < *n_parts (written by the call; at most N / 8), whose sum

@@ -80,6 +80,7 @@ def _load():
         "ax_lut_draft": (C.c_int, [vp, i32p, i64, C.c_int, C.c_int, C.c_uint64, i64, i32p, C.POINTER(C.c_int)]),
         "ax_exspec_generate": (C.c_int, [vp, vp, vp, i32p, i64, C.c_int32, C.c_int, C.c_int, C.c_int, C.c_uint64, i32p,
                                          C.POINTER(ax_exspec_stats), vp]),
+        "ax_dbg_split_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_gemm": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, vp]),
         "ax_dbg_gemm_time": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t,
                                        C.c_int, C.POINTER(C.c_float), vp]),
@@ -374,6 +375,12 @@ def ax_exspec_generate(model: int, kv: int, lut: int, history, pending: int, max
 
 
 # ------------------------------------------------------------------ test-only entry points
+
+def ax_dbg_split_plan(cfg, items: int, max_steps: int):
+    waves, slices = C.c_int(), C.c_int()
+    _check(lib.ax_dbg_split_plan(C.byref(cfg), items, max_steps, C.byref(waves), C.byref(slices)))
+    return waves.value, slices.value
+
 
 def ax_dbg_gemm(dtype: int, epilogue: int, A: int, W: int, W2: int, Cptr: int, M: int, N: int, K: int, stream: int = 0):
     _check(lib.ax_dbg_gemm(dtype, epilogue, C.c_void_p(A), C.c_void_p(W), C.c_void_p(W2), C.c_void_p(Cptr), M, N, K,

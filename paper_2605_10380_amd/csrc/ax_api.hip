@@ -180,17 +180,18 @@ struct ProfScope {                     // records a pair of events around one la
     ~ProfScope() { if (b) (void)hipEventRecord(b, st); }
 };
 
-// Wavefronts per block of the split attention (`items` single tiles x KV heads): four, which share out a slice's key steps, where the
-// steps give every CU such a block with at least two steps per wavefront (~1B verify, 16 items of 137 steps: 843 -> 826 us);
-// else one (~1B decode, 8 items of 41 steps: 727 us against 755 on 32 blocks of four).
-int split_waves(int items, int max_steps) { return 256 / std::max(1, items) <= max_steps / 8 ? 4 : 1; }
+// Wavefronts per block of the split attention (`items` single tiles x KV heads): four, which share out a slice's key steps, where slices
+// of at least two steps per wavefront make a block for every CU (~1B verify, 16 items of 137 steps: 826 us against 843); else one (~1B
+// decode, 8 items of 41 steps: 727 us against 755 on 32 blocks of four; 48 sessions of the ~3B shape with 1 to 3 steps each,
+// 4 layers: 607 us against 632).
+int split_waves(int items, int max_steps) { return (long long)items * (max_steps / 8) >= 256 ? 4 : 1; }
 
 // Key slices of the split attention.  Blocks of 4 q tiles inside a captured graph (others: plan_items) run best at about two
 // blocks per CU (2048 wavefronts); single tiles (verify steps, short extends) at one block of four wavefronts per CU, or at about 512
 // blocks of one - beyond that the merge of the slices costs more than the shorter key loops save.
 // At least two 32-key steps per wavefront, rounded down to a power of two so that the choice (a launch dimension, hence
 // part of a captured graph) changes only when the cache length doubles.
-int choose_splits(const ax_model* m, int items, int nq, int max_steps) {
+int choose_splits(size_t max_records, int items, int nq, int max_steps) {
     const int waves = nq == 1 ? split_waves(items, max_steps) : 1;
     int want = std::max(1, (nq > 1 ? 2048 : waves == 4 ? 256 : 512) / std::max(1, items * nq));
     // many sequences in one call: that would leave wavefronts with long serial key loops;
@@ -198,7 +199,7 @@ int choose_splits(const ax_model* m, int items, int nq, int max_steps) {
     if (nq == 1 && max_steps / want > 8 * waves)
         want = std::max(want, std::min(2048 / (waves * std::max(1, items)), (max_steps + 8 * waves - 1) / (8 * waves)));
     want = std::min(want, std::max(1, max_steps / (2 * waves)));
-    const size_t cap = m->lay.max_records / ((size_t)items * nq);      // >= 1 for every call prepare_call lets through
+    const size_t cap = max_records / ((size_t)items * nq);      // >= 1 for every call prepare_call lets through
     want = std::min(want, std::max(1, (int)cap));
     int p2 = 1;
     while (p2 * 2 <= want) p2 *= 2;
@@ -395,7 +396,7 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         if ((size_t)cp.n_tiles * cp.tile_nq * c.n_kv_heads > m->lay.max_records)
             return fail(AX_ERR_UNSUPPORTED, "%d attention tile groups of %d tiles exceed the workspace's %zu partial records",
                         cp.n_tiles, cp.tile_nq, m->lay.max_records);
-        const int uniform = graph_slot ? choose_splits(m, cp.n_tiles * c.n_kv_heads, cp.tile_nq, longest) : 0;
+        const int uniform = graph_slot ? choose_splits(m->lay.max_records, cp.n_tiles * c.n_kv_heads, cp.tile_nq, longest) : 0;
         plan_items(groups, c.n_kv_heads, c.head_dim == 64, m->lay.q_lo != 0, uniform, 2 * m->lay.max_records, cp.items, cp.merges);
     }
     cp.n_out = out_mode == AX_OUT_NONE ? 0
@@ -688,7 +689,7 @@ ax_status run_extend(ax_model* m, int n, ax_kv* const* kvs, const int32_t* token
     if (st != AX_OK) return st;
     const ax::DType dt = m->cfg.dtype == AX_F32 ? ax::F32 : ax::BF16;
     for (auto& cw : cp.cows) ax::launch_block_copy(dt, cp.pool->geom, m->cfg.n_layers, cw.first, cw.second, stream);
-    const int n_splits = choose_splits(m, cp.n_tiles * m->cfg.n_kv_heads, cp.tile_nq, cp.max_steps);
+    const int n_splits = choose_splits(m->lay.max_records, cp.n_tiles * m->cfg.n_kv_heads, cp.tile_nq, cp.max_steps);
     return enqueue_call(m, cp, out, stream, n_splits, verify_k, host_result, false);
 }
 
@@ -706,7 +707,7 @@ ax_status run_verify_graph(ax_model* m, ax_kv* kv, const int32_t* toks, int T, v
     if (st != AX_OK) return st;
     const ax::DType dt = m->cfg.dtype == AX_F32 ? ax::F32 : ax::BF16;
     for (auto& cw : cp.cows) ax::launch_block_copy(dt, cp.pool->geom, m->cfg.n_layers, cw.first, cw.second, stream);
-    const int n_splits = choose_splits(m, cp.n_tiles * m->cfg.n_kv_heads, cp.tile_nq, cp.max_steps);
+    const int n_splits = choose_splits(m->lay.max_records, cp.n_tiles * m->cfg.n_kv_heads, cp.tile_nq, cp.max_steps);
     // (block-kernel calls: the item counts follow from T and the slice count of plan_items' uniform cut)
     const uint64_t key = ((uint64_t)(uint32_t)T << 32) | (uint32_t)(cp.tile_nq > 1 ? (int)(cp.items.size() / (size_t)cp.n_tiles) : n_splits | split_waves(cp.n_tiles * m->cfg.n_kv_heads, cp.max_steps) << 24);
     hipGraphExec_t exec = nullptr;
@@ -1224,6 +1225,17 @@ ax_status ax_exspec_generate(ax_model* model, ax_kv* kv, const ax_lut* lut, cons
         pending = nxt;
     }
     if (stats) *stats = st;
+    return AX_OK;
+}
+
+ax_status ax_dbg_split_plan(const ax_model_config* cfg, int items, int max_steps, int* waves, int* slices) {
+    ax_status why;
+    if (!config_ok(cfg, &why)) return fail(why, "model config rejected");
+    if (items <= 0 || max_steps <= 0 || !waves || !slices) return fail(AX_ERR_INVALID, "bad argument");
+    const size_t records = make_layout(*cfg).max_records;
+    if ((size_t)items > records) return fail(AX_ERR_INVALID, "%d items exceed the %zu records of a pass", items, records);
+    *waves = split_waves(items, max_steps);
+    *slices = choose_splits(records, items, 1, max_steps);
     return AX_OK;
 }
 

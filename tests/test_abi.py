@@ -71,6 +71,23 @@ def test_workspace_stays_the_size_callers_planned_for(name, max_pos, max_tokens,
     assert 0 < B.ax_workspace_bytes(B.make_config(I.SHAPES[name], max_pos, max_tokens, max_seqs)) <= most
 
 
+def test_split_attention_plan():
+    """Four wavefronts share out a slice only where slices of eight key steps (two each) make a block for each of the 256 compute
+    units - many items over a few steps have nothing to share out; slices of two steps per wavefront at least, a power of
+    two, and no more records than a pass has."""
+    cfg = B.make_config(I.SHAPES["3b"], 8192, 1024, 64)
+    for items in list(range(1, 40)) + [64, 96, 128, 200, 255, 256, 257, 384, 768, 1024, 2000]:
+        for steps in list(range(1, 20)) + [24, 31, 32, 41, 64, 137, 256, 273]:
+            waves, slices = B.ax_dbg_split_plan(cfg, items, steps)
+            assert waves == (4 if items * (steps // 8) >= 256 else 1), (items, steps)
+            assert slices & (slices - 1) == 0 and items * slices <= 2048 and (slices == 1 or steps >= 2 * waves * slices), (items, steps, slices)
+    assert B.ax_dbg_split_plan(cfg, 384, 3) == (1, 1)
+    assert B.ax_dbg_split_plan(cfg, 16, 137)[0] == 4 and B.ax_dbg_split_plan(cfg, 8, 41)[0] == 1
+    for items, steps in ((0, 5), (5, 0), (1 << 20, 5)):
+        with pytest.raises(B.AxError):
+            B.ax_dbg_split_plan(cfg, items, steps)
+
+
 def test_extend_rejects_bad_arguments_before_any_launch():
     cfg = B.make_config(I.SHAPES["tiny"], 1024, 64)
     pool = B.ax_pool_create(cfg, 0, B.ax_pool_block_bytes(cfg) * 8)
