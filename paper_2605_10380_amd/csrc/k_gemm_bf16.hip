@@ -1255,16 +1255,12 @@ static bool use_skinny(int epi, int M, int N, int K) {
 }
 
 static const int kBlockMinM = env_int("AX_BLOCK_MIN_M", 257);
-static const int kBlockShape = env_int("AX_BLOCK_SHAPE", -1);
-static const int kBlockKs = env_int("AX_BLOCK_KS", 0);
 
 template <int EPI>
 static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
     if (M >= kBlockMinM && !g.a_rows && N % 64 == 0) {
-        BlockPlan p = plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
-        if (kBlockShape >= 0) p.shape = kBlockShape;
-        if (kBlockKs > 0) p.ks = kBlockKs;
+        const BlockPlan p = plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
         return launch_gemm_block((Epilogue)EPI, g, p, s);
     }
     if (use_skinny(EPI, M, N, K)) {
@@ -1295,6 +1291,15 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         return 0;
     }
     return launch_lds_tile<EPI>(g, s);
+}
+
+bool gemm_block_shape(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes, int* rows, int* cols, int* slices) {
+    if (M < kBlockMinM || N % 64 != 0) return false;
+    const BlockPlan p = plan_gemm_block(epi, M, N, K, split, ws_bytes);
+    *rows = p.shape == 0 ? 256 : 128;
+    *cols = p.shape == 2 ? 128 : 256;
+    *slices = p.ks;
+    return true;
 }
 
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s) {

@@ -5,6 +5,7 @@ import glob
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2605_10380_amd import binding as B
@@ -86,6 +87,26 @@ def test_split_attention_plan():
     for items, steps in ((0, 5), (5, 0), (1 << 20, 5)):
         with pytest.raises(B.AxError):
             B.ax_dbg_split_plan(cfg, items, steps)
+
+
+def test_many_row_gemm_plans_are_launchable():
+    """Every plan names a block that is built (SwiGLU has no 128 x 128 one) and K slices that are whole, long enough, and fit the
+    scratch and the kernels that add them up."""
+    rng = np.random.default_rng(4)
+    seen = set()
+    for _ in range(4000):
+        epi, split = int(rng.integers(0, 4)), bool(rng.integers(0, 2))
+        M, N, K = int(np.exp(rng.uniform(np.log(257), np.log(6000)))), 64 * int(rng.integers(1, 260)), 64 * int(rng.integers(1, 260))
+        ws = int(rng.choice([0, M * N * 4, 3 * M * N * 4 - 1, 32 * M * N]))
+        rows, cols, slices = B.ax_dbg_gemm_plan(epi, M, N, K, split, ws)
+        if (rows, cols, slices) == (0, 0, 0):
+            continue
+        seen.add((epi, rows, cols, slices > 1))
+        assert (rows, cols) in ((256, 256), (128, 256)) + (((128, 128),) if epi != 2 else ())
+        assert 1 <= slices <= 4 and K % (32 * slices) == 0
+        assert slices == 1 or (epi in (1, 3) and K // slices >= 512 and slices * M * N * 4 <= ws)
+    assert len(seen) >= 12, seen
+    assert B.ax_dbg_gemm_plan(1, 256, 2048, 2048) == (0, 0, 0) == B.ax_dbg_gemm_plan(1, 512, 2064, 2048)
 
 
 def test_extend_rejects_bad_arguments_before_any_launch():
