@@ -24,10 +24,11 @@ ax_status ax_dbg_gemm(int dtype, int epilogue, const void *A, const void *W, con
  * key steps of 32 of the longest sequence.  Writes the wavefronts per block (1 or 4) and the key slices per item.  Host only. */
 ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps, int *waves, int *slices);
 
-/* Which tile of the many-row GEMM kernel a GEMM of M rows runs on: rows x cols operand rows of A and W per block and K slices, all 0
- * if another kernel runs.  epilogue as ax_dbg_gemm, 3 = QKV (rotary, KV append).  split: activations in hi + lo parts.
- * split_ws_bytes: scratch for K slices.  Host only. */
-ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int *rows, int *cols, int *slices);
+/* What a bf16-weight GEMM of more than 256 rows runs on: *kernel (static text) "block", "tile" or "stream", rows of A and of W per block
+ * (SwiGLU: half of the latter gate, half up) and K slices; "" and zeros for fewer rows or N not a multiple of 64.  epilogue as
+ * ax_dbg_gemm, 3 = QKV (rotary, KV append).  split: activations in hi + lo parts.  split_ws_bytes: scratch for K slices.  Host only. */
+ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char **kernel, int *rows, int *cols,
+                           int *slices);
 
 /* The residual GEMM as a bf16-weight decoder layer runs it (O and down projections): x[M,N] (float,
  * updated in place) += A[M,K] W[N,K]^T, then a16[M,N] = fp16(x * gain[n]) and per-row partial sums

@@ -81,8 +81,8 @@ def _load():
         "ax_exspec_generate": (C.c_int, [vp, vp, vp, i32p, i64, C.c_int32, C.c_int, C.c_int, C.c_int, C.c_uint64, i32p,
                                          C.POINTER(ax_exspec_stats), vp]),
         "ax_dbg_split_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
-        "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_int), C.POINTER(C.c_int),
-                                       C.POINTER(C.c_int)]),
+        "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
+                                       C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_gemm": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, vp]),
         "ax_dbg_gemm_time": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t,
                                        C.c_int, C.POINTER(C.c_float), vp]),
@@ -385,10 +385,10 @@ def ax_dbg_split_plan(cfg, items: int, max_steps: int):
 
 
 def ax_dbg_gemm_plan(epilogue: int, M: int, N: int, K: int, split: bool = False, split_ws_bytes: int = 1 << 40):
-    """(rows, cols, K slices) of the many-row GEMM kernel's block, (0, 0, 0) if another kernel runs."""
-    r, c, k = C.c_int(), C.c_int(), C.c_int()
-    _check(lib.ax_dbg_gemm_plan(epilogue, M, N, K, int(split), split_ws_bytes, C.byref(r), C.byref(c), C.byref(k)))
-    return r.value, c.value, k.value
+    """(kernel, rows, cols, K slices) of a GEMM of more than 256 rows."""
+    n, r, c, k = C.c_char_p(), C.c_int(), C.c_int(), C.c_int()
+    _check(lib.ax_dbg_gemm_plan(epilogue, M, N, K, int(split), split_ws_bytes, C.byref(n), C.byref(r), C.byref(c), C.byref(k)))
+    return n.value.decode(), r.value, c.value, k.value
 
 
 def ax_dbg_gemm(dtype: int, epilogue: int, A: int, W: int, W2: int, Cptr: int, M: int, N: int, K: int, stream: int = 0):

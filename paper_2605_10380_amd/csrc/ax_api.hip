@@ -1239,10 +1239,15 @@ ax_status ax_dbg_split_plan(const ax_model_config* cfg, int items, int max_steps
     return AX_OK;
 }
 
-ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int* rows, int* cols, int* slices) {
-    if (epilogue < 0 || epilogue > 3 || M <= 0 || N <= 0 || K <= 0 || !rows || !cols || !slices) return fail(AX_ERR_INVALID, "bad argument");
+ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char** kernel, int* rows, int* cols,
+                           int* slices) {
+    if (epilogue < 0 || epilogue > 3 || M <= 0 || N <= 0 || K <= 0 || !kernel || !rows || !cols || !slices) return fail(AX_ERR_INVALID, "bad argument");
     if (K % 64 != 0 || N % 16 != 0) return fail(AX_ERR_UNSUPPORTED, "bf16 needs K %% 64 == 0, N %% 16 == 0");
-    if (!ax::gemm_block_shape((ax::Epilogue)epilogue, M, N, K, split != 0, split_ws_bytes, rows, cols, slices)) *rows = *cols = *slices = 0;
+    const ax::GemmPlan p = ax::gemm_plan((ax::Epilogue)epilogue, M, N, K, split != 0, split_ws_bytes);
+    *kernel = p.kernel;
+    *rows = p.rows;
+    *cols = p.cols;
+    *slices = p.slices;
     return AX_OK;
 }
 

@@ -177,6 +177,7 @@ __device__ __forceinline__ void block_inv_rms_few(const GemmArgs& g, int first_r
 // Many-row GEMMs (k_gemm_block.hip): which tile shape and how many K slices, and the time the plan expects.
 struct BlockPlan { int shape, ks; float us; };
 BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
+float gemm_reduce_us(Epilogue epi, int M, int N, int ks);      // time of the kernel that adds up ks slabs (EPI_QKV, EPI_RESIDUAL)
 // a_rows must be NULL and N % 64 == 0; returns the partial sums per row it leaves, as launch_gemm_bf16.
 int launch_gemm_block(Epilogue epi, const GemmArgs& g, const BlockPlan& p, hipStream_t s);
 // Second halves of K-sliced GEMMs (k_gemm_bf16.hip): add the g.ksplit slabs of g.split_ws and run the epilogue.

@@ -1049,16 +1049,61 @@ static const int kQkvTile = env_int("AX_QKV_TILE", -1);   // experiment knobs: f
 static const int kResTile = env_int("AX_RES_TILE", -1);
 static const int kResBig = env_int("AX_RES_BIG", 256);
 static const int kQkvKs = env_int("AX_QKV_KS", 0);   // experiment knob: K slices of the QKV GEMM (1 = never split)
+// Which blocks and how many K slices the tile kernel takes for a QKV or residual GEMM (ws_bytes: room for slabs).
+// Two block shapes, both of 8 wavefronts: 64 x 128 (2 x 4 wavefronts of 32 x 32) and 128 x 128
+// (wavefront tile 64 x 32).  The larger one pulls a third fewer operand bytes per output and
+// wins wherever it still gives the chip enough blocks (measured per GEMM class below).
+struct TilePlan { bool big; int ks; };
 template <int EPI>
-static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
-    const int M = g.M, N = g.N, K = g.K;
-    // Two block shapes, both of 8 wavefronts: 64 x 128 (2 x 4 wavefronts of 32 x 32) and 128 x 128
-    // (wavefront tile 64 x 32).  The larger one pulls a third fewer operand bytes per output and
-    // wins wherever it still gives the chip enough blocks (measured per GEMM class below).
+static TilePlan plan_tile(int M, int N, int K, size_t ws_bytes) {
     const long long tiles64 = (long long)((N + 127) / 128) * ((M + 63) / 64);
     const long long tiles128 = (long long)((N + 127) / 128) * ((M + 127) / 128);
     // 128-row blocks only when their row padding costs at most ~15 % more rows than 64-row blocks' (M = 144 does not qualify)
     const bool pad_ok = (long long)((M + 127) / 128) * 128 * 100 <= (long long)((M + 63) / 64) * 64 * 115;
+    const size_t slab = (size_t)M * N * sizeof(float);
+    if constexpr (EPI == EPI_QKV) {
+        // 128-row blocks from 80 tiles up (~3B / ~8B at M = 256: 36 -> 29 / 43 -> 34 us); the ~1B shape at M = 256 has 48 such
+        // tiles and stays with 64 rows
+        const bool big = kQkvTile >= 0 ? kQkvTile > 0 : (pad_ok && tiles128 >= 80);
+        // 64-row blocks: two slices only while both fit one round of 256 blocks (more blocks than CUs run two to a
+        // CU and gain nothing from the cut: ~1B at 384 rows 26.8 -> 24.7 us, ~3B / ~8B at 320 rows 35.2 -> 32.3 / 43.0 -> 39.1 us)
+        int ks = big ? (tiles128 < 128 ? 2 : 1) : (tiles64 * 2 <= 256 ? 2 : 1);
+        // three slices where they fill the chip better than two and K divides (~3B at 193-256 rows: 80 tiles,
+        // 240 blocks instead of 160: 30.6 -> 28.8 us; four slices, 320 blocks in two rounds: 37.5 us)
+        if (big && ks == 2 && tiles128 * 3 <= 256 && K % (3 * 64) == 0 && K / (3 * 64) >= 8 && 3 * slab <= ws_bytes) ks = 3;
+        if (kQkvKs > 0) ks = kQkvKs;
+        while (ks > 1 && (K % (ks * 64) != 0 || ks * slab > ws_bytes)) ks >>= 1;
+        return {big, ks};
+    } else {
+        // Few output tiles (M = 256 against N = 2048 is 64 tiles of 64 x 128 for 256 CUs): cut K
+        // until there are ~256 blocks, each still with 8 or more k-steps; fp32 partial slabs go to
+        // the workspace and residual_reduce_kernel finishes.
+        auto slices = [&](long long tiles) {
+            int ks = 1;
+            if (!ws_bytes || N % 64 != 0) return ks;
+            // (a cut that would overshoot one round of 256 blocks is not taken once 144 or more CUs have a block:
+            // ~3B at 193-256 rows, 96 tiles: 192 blocks instead of 384, O projection 20.6 -> 18.7 us, down projection -
+            // then on 128-row blocks, 4 slices, 192 blocks - 39.1 -> 30.7 us; ~1B at 384 rows 37.5 -> 30.2 us,
+            // ~8B O projection at 384 rows 39.3 -> 31.0 us, ~3B at 144 rows 18.5 -> 16.8 us)
+            static const int fill = env_int("AX_SLICE_FILL", 144);   // measurement switch: 256 = always cut up to a full round
+            while (ks < SPLITK_MAX && tiles * ks < 256 && !(tiles * ks >= fill && tiles * ks * 2 > 256) &&
+                   K % (ks * 2 * 64) == 0 && K / (ks * 2 * 64) >= 8 && ks * 2 * slab <= ws_bytes)
+                ks *= 2;
+            return ks;
+        };
+        // 128-row blocks: when there are plenty of tiles without any cut (or more 64-row tiles than one
+        // round of two per CU), or when K is long (down projection) and at most 4 slices give ~200 blocks or more.
+        // Measured against 64-row blocks: ~8B down projection 57 -> 49 us at M = 256, 98 -> 81 at 512;
+        // ~1B at M = 256 would need 8 slices and is no faster, so it keeps 64-row blocks.
+        const int ks128 = slices(tiles128);
+        const bool big = kResTile >= 0 ? kResTile > 0 : (M > 128 && pad_ok && (tiles128 >= kResBig || tiles64 > 256 || (K >= 4096 && ks128 <= 4 && tiles128 * ks128 >= 192)));
+        return {big, big ? ks128 : slices(tiles64)};
+    }
+}
+
+template <int EPI>
+static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
+    const int M = g.M, N = g.N, K = g.K;
     // 129-192 rows (16 sessions verified together), residual GEMM with a long K (down projection):
     // one 160- or 192-row streaming block per 128 columns reads every weight once (64-row tiles
     // pull it three times out of L2) and K slices give the chip its ~200 blocks: ~3B down
@@ -1079,30 +1124,18 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
         // two slices that the second kernel adds up.
         // (The workspace holds at least one [M, N] fp32 slab - a model's layout reserves max_tokens x N of it
         // whatever the ratio of N to d_model; a caller that brings less gets nothing launched.)
-        // 128-row blocks from 80 tiles up (~3B / ~8B at M = 256: 36 -> 29 / 43 -> 34 us; M = 3584:
-        // 275 -> 221 / 443 -> 329 us); the ~1B shape at M = 256 has 48 such tiles and stays with 64 rows
-        const bool big = kQkvTile >= 0 ? kQkvTile > 0 : (pad_ok && tiles128 >= 80);
-        // 64-row blocks: two slices only while both fit one round of 256 blocks (more blocks than CUs run two to a
-        // CU and gain nothing from the cut: ~1B at 384 rows 26.8 -> 24.7 us, ~3B / ~8B at 320 rows 35.2 -> 32.3 / 43.0 -> 39.1 us)
-        int ks = big ? (tiles128 < 128 ? 2 : 1) : (tiles64 * 2 <= 256 ? 2 : 1);
-        // three slices where they fill the chip better than two and K divides (~3B at 193-256 rows: 80 tiles,
-        // 240 blocks instead of 160: 30.6 -> 28.8 us; four slices, 320 blocks in two rounds: 37.5 us)
-        if (big && ks == 2 && tiles128 * 3 <= 256 && K % (3 * 64) == 0 && K / (3 * 64) >= 8 &&
-            (size_t)3 * M * N * sizeof(float) <= g.split_ws_bytes)
-            ks = 3;
-        if (kQkvKs > 0) ks = kQkvKs;
-        while (ks > 1 && (K % (ks * 64) != 0 || (size_t)ks * M * N * sizeof(float) > g.split_ws_bytes)) ks >>= 1;
+        const TilePlan t = plan_tile<EPI>(M, N, K, g.split_ws ? g.split_ws_bytes : 0);
         if (!g.split_ws || (size_t)M * N * sizeof(float) > g.split_ws_bytes) return -1;
         GemmArgs gs = g;
-        gs.ksplit = ks;
+        gs.ksplit = t.ks;
         GemmArgs gp = gs;                                 // the products: no scaling, no epilogue work
         gp.ssq = nullptr;
         gp.Cf = g.split_ws;
-        if (big) {
-            dim3 grid((N + 127) / 128, (M + 127) / 128, ks);
+        if (t.big) {
+            dim3 grid((N + 127) / 128, (M + 127) / 128, t.ks);
             AX_SPLIT_LAUNCH(gp.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_STORE_F32, 2, 1, 2, 4), grid, 512, gp);
         } else {
-            dim3 grid((N + 127) / 128, (M + 63) / 64, ks);
+            dim3 grid((N + 127) / 128, (M + 63) / 64, t.ks);
             AX_SPLIT_LAUNCH(gp.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_STORE_F32, 1, 1, 2, 4), grid, 512, gp);
         }
         launch_qkv_reduce(gs, s);
@@ -1115,40 +1148,17 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             else gemm_bf16_stream_kernel<EPI_RESIDUAL, 6, 3, 1, true, false><<<mid_cb * mid_ks, 256, 0, s>>>(gs, mid_cb, 1);
             return launch_residual_reduce(gs, s);
         }
-        // Few output tiles (M = 256 against N = 2048 is 64 tiles of 64 x 128 for 256 CUs): cut K
-        // until there are ~256 blocks, each still with 8 or more k-steps; fp32 partial slabs go to
-        // the workspace and residual_reduce_kernel finishes.
-        auto slices = [&](long long tiles) {
-            int ks = 1;
-            if (!g.split_ws || N % 64 != 0) return ks;
-            // (a cut that would overshoot one round of 256 blocks is not taken once 144 or more CUs have a block:
-            // ~3B at 193-256 rows, 96 tiles: 192 blocks instead of 384, O projection 20.6 -> 18.7 us, down projection -
-            // then on 128-row blocks, 4 slices, 192 blocks - 39.1 -> 30.7 us; ~1B at 384 rows 37.5 -> 30.2 us,
-            // ~8B O projection at 384 rows 39.3 -> 31.0 us, ~3B at 144 rows 18.5 -> 16.8 us)
-            static const int fill = env_int("AX_SLICE_FILL", 144);   // measurement switch: 256 = always cut up to a full round
-            while (ks < SPLITK_MAX && tiles * ks < 256 && !(tiles * ks >= fill && tiles * ks * 2 > 256) &&
-                   K % (ks * 2 * 64) == 0 && K / (ks * 2 * 64) >= 8 && (size_t)ks * 2 * M * N * sizeof(float) <= g.split_ws_bytes)
-                ks *= 2;
-            return ks;
-        };
-        // 128-row blocks: when there are plenty of tiles without any cut (or more 64-row tiles than one
-        // round of two per CU: ~3B O projection at 704-768 rows 52 -> 45-48 us), or when K is long (down
-        // projection) and at most 4 slices give ~200 blocks or more.  Measured against 64-row
-        // blocks: ~8B down projection 57 -> 49 us at M = 256, 98 -> 81 at 512, 907 -> 564 at 3584;
-        // ~1B at M = 256 would need 8 slices and is no faster, so it keeps 64-row blocks.
-        const int ks128 = slices(tiles128);
-        const bool big = kResTile >= 0 ? kResTile > 0 : (M > 128 && pad_ok && (tiles128 >= kResBig || tiles64 > 256 || (K >= 4096 && ks128 <= 4 && tiles128 * ks128 >= 192)));
-        const int ks = big ? ks128 : slices(tiles64);
+        const TilePlan t = plan_tile<EPI>(M, N, K, g.split_ws ? g.split_ws_bytes : 0);
         GemmArgs gs = g;
-        gs.ksplit = ks;
-        if (big) {
-            dim3 grid((N + 127) / 128, (M + 127) / 128, ks);
+        gs.ksplit = t.ks;
+        if (t.big) {
+            dim3 grid((N + 127) / 128, (M + 127) / 128, t.ks);
             AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_RESIDUAL, 2, 1, 2, 4), grid, 512, gs);
         } else {
-            dim3 grid((N + 127) / 128, (M + 63) / 64, ks);
+            dim3 grid((N + 127) / 128, (M + 63) / 64, t.ks);
             AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_RESIDUAL, 1, 1, 2, 4), grid, 512, gs);
         }
-        return ks > 1 ? launch_residual_reduce(gs, s) : N / 32;
+        return t.ks > 1 ? launch_residual_reduce(gs, s) : N / 32;
     } else if constexpr (EPI == EPI_SWIGLU) {
         // 17-192 rows: one streaming block of all the rows (32 to 192) per 128 columns, over K slices
         // (raw gate | up products in slabs, swiglu_reduce_kernel finishes): every weight is read
@@ -1254,14 +1264,73 @@ static bool use_skinny(int epi, int M, int N, int K) {
     return !(epi == EPI_QKV || epi == EPI_SWIGLU || (epi == EPI_RESIDUAL && K >= 2 * N));
 }
 
-static const int kBlockMinM = env_int("AX_BLOCK_MIN_M", 257);
+// ------------------------------------------------------------------------------ more than 256 rows
+// The block kernel has the largest tiles and wins wherever they fill the chip; two kernels made for fewer rows are ahead of it where
+// its plan leaves CUs idle or pads rows, and stay candidates (times as in plan_gemm_block, fitted to the same calls):
+//   * the tile kernel, QKV and residual GEMMs of up to 512 rows whose blocks fit one round (~1B QKV at 288 rows 17.7 -> 14.6 us, ~1B down
+//     at 512 rows 43.9 -> 31.7, ~3B down at 257 rows 34.8 -> 30.6; no call of more than 512 rows gains over 3 %);
+//   * streaming blocks of 96 to 192 rows (plain activations; 96 or 128 in hi + lo parts), SwiGLU of up to 640 rows (~8B width at 320 rows:
+//     block kernel, 512 padded rows, 108 us, 2 x 160 rows 86; at 576 rows 189 and 163; in hi + lo parts at 576 rows 310 and 285;
+//     above, where it needs two rounds, it falls behind: ~1B at 1536 rows 112 and 138, at 704 53 and 59).
+enum ManyRows { MANY_BLOCK, MANY_TILE, MANY_STREAM };
+struct ManyPlan { ManyRows kernel; BlockPlan block; int stream_tm; };
+
+template <int EPI>
+static float tile_us(int M, int N, int K, bool split, size_t ws_bytes) {
+    static constexpr struct { float lo, full, fixed; } kTile[2][2] = {{{0.357f, 0.372f, 2.3f}, {0.429f, 0.60f, 1.75f}},      // step of 64 k: 64-row blocks,
+                                                                      {{0.465f, 0.579f, 3.7f}, {0.756f, 1.066f, 2.4f}}};     // 128-row blocks; plain, split
+    const TilePlan p = plan_tile<EPI>(M, N, K, ws_bytes);
+    const int rows = p.big ? 128 : 64;
+    const long long blocks = (long long)((N + 127) / 128) * ((M + rows - 1) / rows) * p.ks;
+    if (blocks > 256) return 1e30f;
+    const auto& t = kTile[p.big][split];
+    const float us = t.fixed + K / p.ks / 64 * (t.lo + (t.full - t.lo) * blocks / 256);
+    return us + (EPI == EPI_QKV || p.ks > 1 ? gemm_reduce_us((Epilogue)EPI, M, N, p.ks) : 6.4f);
+}
+
+// SwiGLU streaming blocks of 32 tm rows x 128 columns of gate and of up, one on a CU at a time
+static float stream_us(int M, int N, int K, bool split, int tm) {
+    const long long blocks = (long long)((N + 127) / 128) * ((M + 32 * tm - 1) / (32 * tm)), rest = blocks % 256;
+    const float step = split ? 0.324f + 0.361f * tm : 0.148f + 0.218f * tm, fixed = split ? 11.0f : 11.4f, lo = split ? 0.63f : 0.71f;
+    return blocks / 256 * (step * (K / 64) + fixed) + (rest ? step * (lo + (1.f - lo) * rest / 256) * (K / 64) + fixed : 0.f);
+}
+
+template <int EPI>
+static ManyPlan plan_many(int M, int N, int K, bool split, size_t ws_bytes) {
+    ManyPlan p{MANY_BLOCK, plan_gemm_block((Epilogue)EPI, M, N, K, split, ws_bytes), 0};
+    if constexpr (EPI == EPI_QKV || EPI == EPI_RESIDUAL) {
+        if (M <= 512 && (EPI == EPI_RESIDUAL || (size_t)M * N * sizeof(float) <= ws_bytes) && tile_us<EPI>(M, N, K, split, ws_bytes) < p.block.us)
+            p.kernel = MANY_TILE;
+    } else if constexpr (EPI == EPI_SWIGLU) {
+        float best = p.block.us;
+        for (int tm = 3; M <= 640 && tm <= (split ? 4 : 6); ++tm) {      // (a second ring of activations does not fit the registers of larger blocks)
+            const float us = stream_us(M, N, K, split, tm);
+            if (us < best) { best = us; p.kernel = MANY_STREAM; p.stream_tm = tm; }
+        }
+    }
+    return p;
+}
+static bool many_rows(int M, int N, bool gathered) { return M > 256 && !gathered && N % 64 == 0; }
+
+static void launch_swiglu_stream(const GemmArgs& g, int tm, hipStream_t s) {
+    const int gx = (g.N + 127) / 128, gy = (g.M + 32 * tm - 1) / (32 * tm);
+    switch (tm) {
+        case 3: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3, 2, false), gx * gy, 256, g, gx, gy); break;
+        case 5: gemm_bf16_stream_kernel<EPI_SWIGLU, 5, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
+        case 6: gemm_bf16_stream_kernel<EPI_SWIGLU, 6, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
+        default: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3, 2, false), gx * gy, 256, g, gx, gy); break;
+    }
+}
 
 template <int EPI>
 static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
-    if (M >= kBlockMinM && !g.a_rows && N % 64 == 0) {
-        const BlockPlan p = plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
-        return launch_gemm_block((Epilogue)EPI, g, p, s);
+    if (many_rows(M, N, g.a_rows != nullptr)) {
+        const ManyPlan p = plan_many<EPI>(M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
+        if (p.kernel == MANY_BLOCK) return launch_gemm_block((Epilogue)EPI, g, p.block, s);
+        if (p.kernel == MANY_TILE) return launch_lds_tile<EPI>(g, s);
+        launch_swiglu_stream(g, p.stream_tm, s);
+        return 0;
     }
     if (use_skinny(EPI, M, N, K)) {
         // wavefronts per block (= K slices): enough to keep ~2k wavefronts in flight (~4k for the SwiGLU
@@ -1284,22 +1353,29 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         // Two blocks of 128 rows or three of 96.  One block runs per CU at a time, so a launch takes (rounds of 256 blocks) x (time of
         // a block), and a block's time grows with the operand rows it pulls (its activation rows + 2 x 128 weight rows).
         const int gx = (N + 127) / 128;
-        if ((3 * gx + 255) / 256 * (96 + 256) < (2 * gx + 255) / 256 * (128 + 256))
-            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3, 2, false), gx * 3, 256, g, gx, 3);
-        else
-            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3, 2, false), gx * 2, 256, g, gx, 2);
+        launch_swiglu_stream(g, (3 * gx + 255) / 256 * (96 + 256) < (2 * gx + 255) / 256 * (128 + 256) ? 3 : 4, s);
         return 0;
     }
     return launch_lds_tile<EPI>(g, s);
 }
 
-bool gemm_block_shape(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes, int* rows, int* cols, int* slices) {
-    if (M < kBlockMinM || N % 64 != 0) return false;
-    const BlockPlan p = plan_gemm_block(epi, M, N, K, split, ws_bytes);
-    *rows = p.shape == 0 ? 256 : 128;
-    *cols = p.shape == 2 ? 128 : 256;
-    *slices = p.ks;
-    return true;
+template <int EPI>
+static GemmPlan many_rows_plan(int M, int N, int K, bool split, size_t ws_bytes) {
+    const ManyPlan p = plan_many<EPI>(M, N, K, split, ws_bytes);
+    if (p.kernel == MANY_STREAM) return {"stream", 32 * p.stream_tm, 256, 1};
+    if constexpr (EPI == EPI_QKV || EPI == EPI_RESIDUAL)
+        if (p.kernel == MANY_TILE) {
+            const TilePlan t = plan_tile<EPI>(M, N, K, ws_bytes);
+            return {"tile", t.big ? 128 : 64, 128, t.ks};
+        }
+    return {"block", p.block.shape == 0 ? 256 : 128, p.block.shape == 2 ? 128 : 256, p.block.ks};
+}
+GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
+    if (!many_rows(M, N, false)) return {"", 0, 0, 0};
+    if (epi == EPI_STORE_F32) return many_rows_plan<EPI_STORE_F32>(M, N, K, split, ws_bytes);
+    if (epi == EPI_RESIDUAL) return many_rows_plan<EPI_RESIDUAL>(M, N, K, split, ws_bytes);
+    if (epi == EPI_SWIGLU) return many_rows_plan<EPI_SWIGLU>(M, N, K, split, ws_bytes);
+    return many_rows_plan<EPI_QKV>(M, N, K, split, ws_bytes);
 }
 
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s) {

@@ -10,9 +10,11 @@
 //   * 8 wavefronts, two per SIMD.  4 wavefronts of 128 x 128 outputs need a third fewer LDS reads but were 5-15 % slower: one
 //     wavefront per SIMD leaves the matrix cores idle at every barrier.
 //   * Smaller tiles (128 x 256, 128 x 128) move 1.5x / 2x the operands per product; they are for launches that would leave CUs without a
-//     block (the planner at the end weighs tile and K-slice choices by measured step times).
+//     block (the planner at the end weighs tile and K-slice choices by measured times).
 #include "gemm_device.h"
 #include "lds_copy.h"
+
+#include <algorithm>
 
 namespace ax {
 
@@ -340,33 +342,56 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
 }
 
 // ------------------------------------------------------------------------------ planning
-// Tile shapes.  Step times: microseconds per stage of 32 k of one block, `lo` with few CUs at work and `full` with a block on every CU
-// (two on every CU for 128 x 128), measured on calls of 700-4700 rows; split activations take twice the products and
-// 1.3-1.5x the operands.
-struct BlockShape { int bm, bn, capacity; float lo, full, lo_split, full_split; };
-static constexpr BlockShape kShapes[] = {
-    {256, 256, 256, 0.64f, 0.92f, 1.15f, 1.62f},
-    {128, 256, 256, 0.36f, 0.51f, 0.62f, 0.86f},
-    {128, 128, 512, 0.28f, 0.62f, 0.50f, 1.05f},
+// Tile shapes and their times in microseconds, fitted (to 4 %) to the four GEMMs of seven decoder layers (d_model 2048-5120, plain and split
+// activations) at 27 row counts from 257 to 4096, every shape and slice count: over these the plan's choice is 0.2-0.7 % off the
+// fastest.  A block's step is 32 k.
+struct BlockShape {
+    int bm, bn, capacity;             // capacity: blocks that run at once
+    float epilogue;                   // a fused epilogue, as a share of the 256 x 256 block's
+    struct Times {
+        float lo, half, full;         // a step with few blocks at work, with one on every CU (128 x 128: two run on a CU), at capacity
+        float fixed;                  // a block's prologue and end
+        float padding;                // share of the time that rows past M cost (they re-read the last row: L2 hits)
+        float tail;                   // what a partial round behind whole ones takes of its time alone
+    } plain, split;
 };
+static constexpr BlockShape kShapes[] = {
+    {256, 256, 256, 1.00f, {0.54f, 0.f, 0.836f, 3.0f, 0.79f, 1.f}, {0.97f, 0.f, 1.62f, 3.7f, 0.87f, 1.f}},
+    {128, 256, 256, 0.49f, {0.41f, 0.f, 0.505f, 2.4f, 0.44f, 1.f}, {0.49f, 0.f, 0.836f, 2.9f, 0.74f, 1.f}},
+    {128, 128, 512, 0.38f, {0.257f, 0.321f, 0.58f, 2.75f, 0.42f, 0.85f}, {0.416f, 0.576f, 0.984f, 2.3f, 0.53f, 0.95f}},
+};
+
+// QKV slabs much beyond the L2s are slow to add up (the K and V of the sum are scattered into pages): 5120 x 7168 at 3072 rows, two slices
+// of 88 MB, 311 us, whole 251.  (Residual slabs pay up to 280 MB: 13824 x 5120 at 3520 rows, four slices 542 us, whole 641.)
+static constexpr size_t kMaxQkvSlabs = 96u << 20;
+
+float gemm_reduce_us(Epilogue epi, int M, int N, int ks) {
+    const float mb = M * (float)N * 4e-6f;
+    return epi == EPI_QKV ? 4.7f + (0.287f * ks + 0.306f) * mb : 3.f + (0.371f * ks + 0.226f) * mb;
+}
 
 BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
     BlockPlan best{-1, 1, 0.f};
     for (int c = 0; c < 3; ++c) {
-        const BlockShape& t = kShapes[c];
-        const int on = epi == EPI_SWIGLU ? t.bn / 2 : t.bn;
+        const BlockShape& s = kShapes[c];
+        const BlockShape::Times& t = split ? s.split : s.plain;
+        const int on = epi == EPI_SWIGLU ? s.bn / 2 : s.bn, gy = (M + s.bm - 1) / s.bm;
         if (epi == EPI_SWIGLU && c == 2) continue;           // gate and up of 64 columns: not built
-        const long long tiles = (long long)((N + on - 1) / on) * ((M + t.bm - 1) / t.bm);
-        const float lo = split ? t.lo_split : t.lo, full = split ? t.full_split : t.full;
         for (int ks = 1; ks <= 4; ++ks) {
             if (ks > 1 && (epi == EPI_STORE_F32 || epi == EPI_SWIGLU || K % (32 * ks) != 0 || K / ks < 512 ||
-                           (size_t)ks * M * N * sizeof(float) > ws_bytes))
+                           (size_t)ks * M * N * sizeof(float) > (epi == EPI_QKV ? std::min(ws_bytes, kMaxQkvSlabs) : ws_bytes)))
                 continue;
-            const long long blocks = tiles * ks, rounds = blocks / t.capacity, rest = blocks % t.capacity;
-            float us = rounds * full + (rest ? lo + (full - lo) * rest / t.capacity : 0.f);
-            us = us * (K / ks / 32) + 6.f * (rounds + (rest ? 1 : 0));
-            // slabs: written once, read once by the kernel that finishes the product
-            if (ks > 1) us += 5.f + 2.f * ks * M * (float)N * 4 / 5e6f;
+            const long long blocks = (long long)((N + on - 1) / on) * gy * ks, rounds = blocks / s.capacity, rest = blocks % s.capacity;
+            // (QKV: 2 us less than fitted - in a model the residual GEMM before it is mostly sliced, which leaves fewer partial sums of x^2 to read)
+            const float steps = K / ks / 32, end = t.fixed + (ks > 1 ? 0.f : s.epilogue * (epi == EPI_SWIGLU ? 11.f : 27.f) - (epi == EPI_QKV ? 2.f : 0.f));
+            float us = rounds * (t.full * steps + end);
+            if (rest) {
+                const float step = s.capacity == 256 ? t.lo + (t.full - t.lo) * rest / 256
+                                   : rest <= 256     ? t.lo + (t.half - t.lo) * rest / 256 : t.full;
+                us += (step * steps + end) * (rounds ? t.tail : 1.f);
+            }
+            us *= t.padding + (1.f - t.padding) * M / (gy * s.bm);
+            if (ks > 1) us += gemm_reduce_us(epi, M, N, ks);
             if (best.shape < 0 || us < best.us) best = {c, ks, us};
         }
     }

@@ -93,9 +93,10 @@ constexpr int SPLITK_MAX = 8;
 // EPI_QKV above 64 rows writes its raw products to split_ws first: -1, and nothing launched, if one [M, N] fp32
 // slab does not fit there.
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s);
-// Whether a GEMM whose rows are not gathered runs on the block kernel, and on which shape (columns of operands: half of them gate, half
-// up for EPI_SWIGLU) and K slices.
-bool gemm_block_shape(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes, int* rows, int* cols, int* slices);
+// The plan of a GEMM of more than 256 rows that are not gathered ("" = fewer rows, or N not a multiple of 64): kernel ("block", "tile" or
+// "stream"), rows of A and of W per block (EPI_SWIGLU: half of the latter gate, half up) and K slices.
+struct GemmPlan { const char* kernel; int rows, cols, slices; };
+GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
 // Repacks a row-major bf16 [N, K] matrix (N % 16 == 0, K % 32 == 0) into what every bf16-model GEMM
 // kernel reads: fp16 values in 16-row panels, 32-k chunks in MFMA operand order; src and dst must not overlap.
 // `bad` (device int, may be NULL) is set to 1 if some weight does not survive the narrowing (not finite in fp16).

@@ -90,23 +90,40 @@ def test_split_attention_plan():
 
 
 def test_many_row_gemm_plans_are_launchable():
-    """Every plan names a block that is built (SwiGLU has no 128 x 128 one) and K slices that are whole, long enough, and fit the
-    scratch and the kernels that add them up."""
+    """Every plan names a block that is built (block kernel: SwiGLU has no 128 x 128 one; tile kernel: QKV and residual GEMMs of up to 512
+    rows; streaming blocks: SwiGLU, up to 192 rows, 128 in hi + lo parts) and K slices that are whole, long enough, and fit
+    the scratch and the kernels that add them up."""
     rng = np.random.default_rng(4)
     seen = set()
-    for _ in range(4000):
+    for _ in range(6000):
         epi, split = int(rng.integers(0, 4)), bool(rng.integers(0, 2))
         M, N, K = int(np.exp(rng.uniform(np.log(257), np.log(6000)))), 64 * int(rng.integers(1, 260)), 64 * int(rng.integers(1, 260))
         ws = int(rng.choice([0, M * N * 4, 3 * M * N * 4 - 1, 32 * M * N]))
-        rows, cols, slices = B.ax_dbg_gemm_plan(epi, M, N, K, split, ws)
-        if (rows, cols, slices) == (0, 0, 0):
-            continue
-        seen.add((epi, rows, cols, slices > 1))
-        assert (rows, cols) in ((256, 256), (128, 256)) + (((128, 128),) if epi != 2 else ())
-        assert 1 <= slices <= 4 and K % (32 * slices) == 0
-        assert slices == 1 or (epi in (1, 3) and K // slices >= 512 and slices * M * N * 4 <= ws)
-    assert len(seen) >= 12, seen
-    assert B.ax_dbg_gemm_plan(1, 256, 2048, 2048) == (0, 0, 0) == B.ax_dbg_gemm_plan(1, 512, 2064, 2048)
+        kernel, rows, cols, slices = B.ax_dbg_gemm_plan(epi, M, N, K, split, ws)
+        seen.add((epi, kernel, rows, cols, slices > 1))
+        assert slices >= 1 and (slices == 1 or (epi in (1, 3) and slices * M * N * 4 <= ws))
+        if kernel == "block":
+            assert (rows, cols) in ((256, 256), (128, 256)) + (((128, 128),) if epi != 2 else ())
+            assert slices <= 4 and K % (32 * slices) == 0 and (slices == 1 or K // slices >= 512)
+        elif kernel == "tile":
+            assert epi in (1, 3) and M <= 512 and rows in (64, 128) and cols == 128 and slices <= 8 and K % (64 * slices) == 0
+            assert epi == 1 or M * N * 4 <= ws                       # QKV products go through a slab whatever the slices
+        else:
+            assert kernel == "stream" and epi == 2 and (cols, slices) == (256, 1) and rows in ((96, 128) if split else (96, 128, 160, 192))
+    assert len(seen) >= 20, seen
+    assert B.ax_dbg_gemm_plan(1, 256, 2048, 2048)[0] == "" == B.ax_dbg_gemm_plan(1, 512, 2064, 2048)[0]
+
+
+# (epilogue, rows, N, K, hi + lo parts) of decoder layers 2048, 3072 and 4096 wide: choices whose alternatives took 8-50 % longer
+@pytest.mark.parametrize("epi,M,N,K,split,want", [
+    (3, 288, 3072, 2048, False, ("tile", 64, 128, 2)), (3, 768, 5120, 3072, False, ("block", 128, 128, 1)), (3, 3072, 7168, 5120, False, ("block", 128, 256, 1)),
+    (3, 1280, 3072, 2048, False, ("block", 128, 128, 1)), (1, 512, 2048, 8192, False, ("tile", 128, 128, 4)),
+    (1, 257, 3072, 8192, False, ("tile", 64, 128, 2)), (1, 768, 3072, 8192, False, ("block", 256, 256, 4)),
+    (1, 1280, 3072, 3072, False, ("block", 128, 128, 1)), (1, 640, 4096, 14336, False, ("block", 256, 256, 4)),
+    (2, 320, 14336, 4096, False, ("stream", 160, 256, 1)), (2, 576, 14336, 4096, True, ("stream", 96, 256, 1)),
+    (2, 4096, 8192, 2048, False, ("block", 256, 256, 1)), (2, 288, 8192, 2048, False, ("block", 128, 256, 1))])
+def test_many_row_gemm_plan_of_measured_calls(epi, M, N, K, split, want):
+    assert B.ax_dbg_gemm_plan(epi, M, N, K, split, 8 * M * 4096 * 4) == want
 
 
 def test_extend_rejects_bad_arguments_before_any_launch():
