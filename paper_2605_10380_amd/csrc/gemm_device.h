@@ -17,6 +17,16 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
+// The same for epilogues with 64 results a lane: the division without the scaling a divisor of 1 or more does not need (7 instructions
+// instead of 11).  One Newton step makes the reciprocal good to half a unit, one residual the quotient; the quotient misses
+// correct rounding only within 2^-45 of a tie.  fixup: infinities and NaNs as a division has them.
+__device__ __forceinline__ float silu_lean(float g) {
+    const float d = 1.0f + __expf(-g);
+    float r = __builtin_amdgcn_rcpf(d);
+    r = fmaf(fmaf(-d, r, 1.0f), r, r);
+    const float q = g * r;
+    return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, g), r, q), d, g);
+}
 
 // 8 bf16 (one 16-byte fragment) -> 8 fp16.  A bf16 is the top half of an fp32, so each half of
 // a dword becomes an fp32 by a shift or a mask; bf16 has fewer significant bits than fp16, so

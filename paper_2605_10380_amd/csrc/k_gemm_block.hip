@@ -243,7 +243,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     const float inv = g.ssq ? s_inv[row_of(i, r + q)] : 1.0f, ga = acc[i][0][r + q] * inv;
-                    h[q] = silu_f(ga) * (acc[i][1][r + q] * inv);
+                    h[q] = silu_lean(ga) * (acc[i][1][r + q] * inv);
                 }
                 const int m = m0 + row_of(i, r + odd);
                 const f32x2 v = pair_of_columns(h[0], h[1], odd);
