@@ -30,6 +30,32 @@ ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps
 ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char **kernel, int *rows, int *cols,
                            int *slices);
 
+/* One GEMM of a bf16-weight layer on a block shape of the many-row kernel that the caller names, with everything a layer uses: hi + lo
+ * activations, a pending RMSNorm of A's rows, K slices and each epilogue.  All pointers are device memory; weights row-major bf16.
+ * rows x cols: 256 x 256, 128 x 256 or 128 x 128 (not for SwiGLU).  N % 64 == 0, K % 64 == 0, head_dim 64 or 128. */
+typedef struct {
+    int epilogue;                       /* 0 C = product; 1 C += product, C16 = C * gain; 2 C16 = silu(A W^T) (A W2^T); 3 QKV */
+    int rows, cols, slices;             /* slices > 1 (epilogues 1 and 3): K % (32 slices) == 0, split_ws of slices x M x N floats */
+    int M, N, K;
+    const void *A; long long a_lo;      /* fp16 [M, K]; lo parts this many elements behind (0 = none) */
+    const void *W, *W2;                 /* [N, K] */
+    const float *ssq; int n_parts;      /* partial sums of x^2 of the rows of A, [M][n_parts]; NULL = A as it is */
+    float eps;
+    float *C;                           /* [M, N] (epilogues 0, 1) */
+    void *C16; long long c_lo;          /* fp16 [M, N]; epilogue 3: q after rotary [M, n_q_heads * head_dim]; lo parts as for A */
+    const void *gain; float *ssq_out;   /* epilogue 1: bf16 [N]; [M][*n_parts_out], room for M * N / 8 */
+    int n_parts_out;                    /* written */
+    int n_q_heads, n_kv_heads, head_dim;                        /* epilogue 3: N = (n_q_heads + 2 n_kv_heads) * head_dim ... */
+    void *pool; long long pool_blocks;                          /* ... a one-layer KV pool of 16-token blocks ... */
+    const int *row_pos, *row_slot; const float *cos, *sin;      /* ... position and slot of the rows, rotary tables [pos][head_dim / 2] */
+    void *split_ws; size_t split_ws_bytes;
+} ax_dbg_block_gemm;
+ax_status ax_dbg_gemm_block(ax_dbg_block_gemm *args, void *hip_stream);
+
+/* Work of the attention of one call of long extends (n sequences of P cached and T new tokens): items (128 stacked rows x a range of keys),
+ * groups of rows whose keys several items share, and the partial-record slots those use per KV head.  Host only. */
+ax_status ax_dbg_attention_items(const ax_model_config *cfg, int n, const int *P, const int *T, int *items, int *merges, int *slots);
+
 /* The residual GEMM as a bf16-weight decoder layer runs it (O and down projections): x[M,N] (float,
  * updated in place) += A[M,K] W[N,K]^T, then a16[M,N] = fp16(x * gain[n]) and per-row partial sums
  * of x^2: ssq[m * (*n_parts) + p], p < *n_parts (written by the call; at most N / 8), whose sum
@@ -87,6 +113,7 @@ ax_status ax_dbg_phase_order(void *buf, size_t bytes, int blocks, int rounds, fl
  * and fp16 for AX_BF16 models.  AX_F32: buffer 5 is rmsnorm(x) * gain of the n_out output rows.
  * AX_BF16: buffer 1 is unused and buffer 5 is fp16(x * final gain) of all rows (the division by
  * the rms happens inside the LM-head GEMM).
+ * 12 - 15: the lo parts of buffers 2 - 5 of a model with split activations (2 - 5 are the hi parts).
  * Copies min(bytes, buffer size) bytes. */
 ax_status ax_dbg_read(ax_model *model, int which, void *host_dst, size_t bytes);
 

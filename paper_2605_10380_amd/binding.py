@@ -25,6 +25,15 @@ class ax_model_config(C.Structure):
         ("max_tokens", C.c_int), ("max_seqs", C.c_int), ("act_split", C.c_int)]
 
 
+class ax_dbg_block_gemm(C.Structure):
+    _fields_ = ([(n, C.c_int) for n in ("epilogue", "rows", "cols", "slices", "M", "N", "K")] +
+                [("A", C.c_void_p), ("a_lo", C.c_longlong), ("W", C.c_void_p), ("W2", C.c_void_p), ("ssq", C.c_void_p), ("n_parts", C.c_int),
+                 ("eps", C.c_float), ("C", C.c_void_p), ("C16", C.c_void_p), ("c_lo", C.c_longlong), ("gain", C.c_void_p),
+                 ("ssq_out", C.c_void_p), ("n_parts_out", C.c_int), ("n_q_heads", C.c_int), ("n_kv_heads", C.c_int), ("head_dim", C.c_int),
+                 ("pool", C.c_void_p), ("pool_blocks", C.c_longlong), ("row_pos", C.c_void_p), ("row_slot", C.c_void_p), ("cos", C.c_void_p),
+                 ("sin", C.c_void_p), ("split_ws", C.c_void_p), ("split_ws_bytes", C.c_size_t)])
+
+
 class ax_exspec_stats(C.Structure):
     _fields_ = [(n, C.c_int64) for n in ("rounds", "fallbacks", "drafted", "accepted")]
 
@@ -83,6 +92,9 @@ def _load():
         "ax_dbg_split_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
                                        C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+        "ax_dbg_gemm_block": (C.c_int, [C.POINTER(ax_dbg_block_gemm), vp]),
+        "ax_dbg_attention_items": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int),
+                                             C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_gemm": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, vp]),
         "ax_dbg_gemm_time": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t,
                                        C.c_int, C.POINTER(C.c_float), vp]),
@@ -389,6 +401,21 @@ def ax_dbg_gemm_plan(epilogue: int, M: int, N: int, K: int, split: bool = False,
     n, r, c, k = C.c_char_p(), C.c_int(), C.c_int(), C.c_int()
     _check(lib.ax_dbg_gemm_plan(epilogue, M, N, K, int(split), split_ws_bytes, C.byref(n), C.byref(r), C.byref(c), C.byref(k)))
     return n.value.decode(), r.value, c.value, k.value
+
+
+def ax_dbg_gemm_block(stream: int = 0, **args) -> int:
+    """Fields of ax_dbg_block_gemm by name; returns the partial sums per row that epilogue 1 left."""
+    a = ax_dbg_block_gemm(**args)
+    _check(lib.ax_dbg_gemm_block(C.byref(a), C.c_void_p(stream)))
+    return a.n_parts_out
+
+
+def ax_dbg_attention_items(cfg, P, T):
+    """(items, groups shared by several items, record slots) of a call of long extends."""
+    n = len(P)
+    i, m, s = C.c_int(), C.c_int(), C.c_int()
+    _check(lib.ax_dbg_attention_items(C.byref(cfg), n, (C.c_int * n)(*P), (C.c_int * n)(*T), C.byref(i), C.byref(m), C.byref(s)))
+    return i.value, m.value, s.value
 
 
 def ax_dbg_gemm(dtype: int, epilogue: int, A: int, W: int, W2: int, Cptr: int, M: int, N: int, K: int, stream: int = 0):

@@ -210,6 +210,14 @@ int choose_splits(size_t max_records, int items, int nq, int max_steps) {
 // Merge records: first slot and number of slices.
 struct AttnItem { int s, r0, lo, hi, slot, n; };
 
+// The groups (4 tiles of 32 stacked rows) of sequence s, each with all the key steps its last row sees.
+void item_groups(int s, int P, int T, int G, std::vector<AttnItem>& groups) {
+    for (int r0 = 0; r0 < T * G; r0 += 128) {
+        const int r_last = std::min(r0 + 128, T * G) - 1;
+        groups.push_back({s, r0, 0, (P + r_last / G + 1 + 31) / 32, -1, 0});
+    }
+}
+
 // Cuts the q-tile groups of a call (AttnItem: lo = 0, hi = all key steps) into items of about equal length and orders them.
 // A block is one item of 4 tiles; b of them share a CU (up to 4 at head_dim 64, 3 at 128, 2 with split activations: registers), so
 // 256 b / heads items per head run at the same time.  Every cut costs partial records (8 or 16 KB a tile, written and read back by a
@@ -388,11 +396,8 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         std::vector<AttnItem> groups;
         int longest = 1;
         for (int s = 0; s < n; ++s)
-            for (int r0 = 0; r0 < T_each[s] * G; r0 += 32 * cp.tile_nq) {
-                const int r_last = std::min(r0 + 32 * cp.tile_nq, T_each[s] * G) - 1;
-                groups.push_back({s, r0, 0, (int)((kvs[s]->seq.len + r_last / G + 1 + 31) / 32), -1, 0});
-                longest = std::max(longest, groups.back().hi);
-            }
+            item_groups(s, (int)kvs[s]->seq.len, T_each[s], G, groups);
+        for (const AttnItem& g : groups) longest = std::max(longest, g.hi);
         if ((size_t)cp.n_tiles * cp.tile_nq * c.n_kv_heads > m->lay.max_records)
             return fail(AX_ERR_UNSUPPORTED, "%d attention tile groups of %d tiles exceed the workspace's %zu partial records",
                         cp.n_tiles, cp.tile_nq, m->lay.max_records);
@@ -1251,6 +1256,66 @@ ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t 
     return AX_OK;
 }
 
+ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
+    if (!a || !a->A || !a->W || a->M <= 0 || a->N <= 0 || a->K <= 0 || a->epilogue < 0 || a->epilogue > 3 || (a->ssq && a->n_parts <= 0))
+        return fail(AX_ERR_INVALID, "bad argument");
+    if (a->N % 64 != 0 || a->K % 64 != 0) return fail(AX_ERR_UNSUPPORTED, "N %% 64 == 0 and K %% 64 == 0 needed");
+    const bool shape_ok = (a->rows == 256 && a->cols == 256) || (a->rows == 128 && (a->cols == 256 || (a->cols == 128 && a->epilogue != 2)));
+    if (!shape_ok) return fail(AX_ERR_INVALID, "no %d x %d block for epilogue %d", a->rows, a->cols, a->epilogue);
+    const size_t slab = (size_t)a->M * a->N * sizeof(float);
+    if (a->slices < 1 || a->slices > ax::SPLITK_MAX || a->K % (32 * a->slices) != 0 ||
+        (a->slices > 1 && ((a->epilogue != 1 && a->epilogue != 3) || !a->split_ws || a->split_ws_bytes < a->slices * slab)))
+        return fail(AX_ERR_INVALID, "%d K slices", a->slices);
+    if ((a->epilogue <= 1 && !a->C) || (a->epilogue >= 1 && !a->C16) || (a->epilogue == 1 && (!a->gain || !a->ssq_out)) ||
+        (a->epilogue == 2 && !a->W2) ||
+        (a->epilogue == 3 && (a->n_q_heads <= 0 || a->n_kv_heads <= 0 || (a->head_dim != 64 && a->head_dim != 128) ||
+                              a->N != (a->n_q_heads + 2 * a->n_kv_heads) * a->head_dim || !a->pool || a->pool_blocks <= 0 || !a->row_pos ||
+                              !a->row_slot || !a->cos || !a->sin)))
+        return fail(AX_ERR_INVALID, "bad argument");
+    hipStream_t s = (hipStream_t)hip_stream;
+    void *pw = nullptr, *pw2 = nullptr;
+    HIP_TRY(hipMalloc(&pw, (size_t)a->N * a->K * 2));
+    ax::launch_pack_weights(a->W, pw, a->N, a->K, s);
+    if (a->epilogue == 2) {
+        hipError_t e2 = hipMalloc(&pw2, (size_t)a->N * a->K * 2);
+        if (e2 != hipSuccess) { (void)hipFree(pw); return fail(AX_ERR_DEVICE, "hipMalloc: %s", hipGetErrorString(e2)); }
+        ax::launch_pack_weights(a->W2, pw2, a->N, a->K, s);
+    }
+    ax::GemmArgs g{};
+    g.A = a->A; g.a_lo_off = a->a_lo; g.W = pw; g.W2 = pw2; g.M = a->M; g.N = a->N; g.K = a->K;
+    g.ssq = a->ssq; g.nparts = a->n_parts; g.d_norm = a->K; g.eps = a->eps;
+    g.Cf = a->C; g.C16 = a->C16; g.c_lo_off = a->c_lo; g.gain_next = a->gain; g.ssq_out = a->ssq_out;
+    g.split_ws = (float*)a->split_ws; g.split_ws_bytes = a->split_ws_bytes;
+    g.rope.kv = {a->pool, a->pool_blocks, a->n_kv_heads, a->head_dim, 16};
+    g.rope.n_q_heads = a->n_q_heads; g.rope.q_out = a->C16; g.rope.row_pos = a->row_pos; g.rope.row_slot = a->row_slot;
+    g.rope.cos = a->cos; g.rope.sin = a->sin;
+    a->n_parts_out = ax::launch_gemm_block_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    (void)hipFree(pw);
+    if (pw2) (void)hipFree(pw2);
+    if (e != hipSuccess) return fail(AX_ERR_DEVICE, "debug GEMM: %s", hipGetErrorString(e));
+    return AX_OK;
+}
+
+ax_status ax_dbg_attention_items(const ax_model_config* cfg, int n, const int* P, const int* T, int* items, int* merges, int* slots) {
+    ax_status why;
+    if (!config_ok(cfg, &why)) return fail(why, "model config rejected");
+    if (n <= 0 || !P || !T || !items || !merges || !slots) return fail(AX_ERR_INVALID, "bad argument");
+    std::vector<AttnItem> groups, it, mg;
+    for (int s = 0; s < n; ++s) {
+        if (P[s] < 0 || T[s] <= 0) return fail(AX_ERR_INVALID, "sequence %d", s);
+        item_groups(s, P[s], T[s], cfg->n_q_heads / cfg->n_kv_heads, groups);
+    }
+    const Layout lay = make_layout(*cfg);
+    plan_items(groups, cfg->n_kv_heads, cfg->head_dim == 64, lay.q_lo != 0, 0, 2 * lay.max_records, it, mg);
+    *items = (int)it.size();
+    *merges = (int)mg.size();
+    *slots = 0;
+    for (const AttnItem& m : mg) *slots += m.n;
+    return AX_OK;
+}
+
 ax_status ax_dbg_gemm(int dtype, int epilogue, const void* A, const void* W, const void* W2, void* C, int M,
                       int N, int K, void* hip_stream) {
     if (!A || !W || !C || M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > 2 ||
@@ -1469,9 +1534,11 @@ ax_status ax_dbg_read(ax_model* m, int which, void* host_dst, size_t bytes) {
     const Layout& L = m->lay;
     const size_t off[6] = {L.x, L.qkv, L.q, L.attn, L.ffn, L.h};
     const size_t len[6] = {L.h - L.x, L.q - L.qkv, L.q_bytes, L.attn_bytes, L.ffn_bytes, L.h_bytes};   // hi parts only
-    if (which < 0 || which > 5) return fail(AX_ERR_INVALID, "bad buffer id");
+    const bool lo = which >= 12;
+    if (lo) which -= 10;
+    if (which < 0 || which > 5 || (lo && !L.h_lo)) return fail(AX_ERR_INVALID, "bad buffer id");
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(host_dst, m->ws + off[which], std::min(bytes, len[which]), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(host_dst, m->ws + off[which] + (lo ? len[which] : 0), std::min(bytes, len[which]), hipMemcpyDeviceToHost));
     return AX_OK;
 }
 

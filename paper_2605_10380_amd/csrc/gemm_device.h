@@ -46,6 +46,7 @@ __device__ __forceinline__ f16x8 load_w(const bf16* p) { return *(const f16x8*)p
 
 // Split activations (see GemmArgs): v goes out as hi = fp16(v) and, lo_off elements further on, lo = fp16(v - hi).
 __device__ __forceinline__ void store_split(f16* p, long long lo_off, float v) {
+    v = split_value(v);
     const f16 hi = (f16)v;
     *p = hi;
     if (lo_off) p[lo_off] = (f16)(v - (float)hi);
@@ -54,8 +55,9 @@ __device__ __forceinline__ void store_split4(f16* p, long long lo_off, const flo
     f16x4 hi, lo;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        hi[r] = (f16)v[r];
-        lo[r] = (f16)(v[r] - (float)hi[r]);
+        const float x = split_value(v[r]);
+        hi[r] = (f16)x;
+        lo[r] = (f16)(x - (float)hi[r]);
     }
     *(f16x4*)p = hi;
     if (lo_off) *(f16x4*)(p + lo_off) = lo;

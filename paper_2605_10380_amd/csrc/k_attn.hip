@@ -632,7 +632,7 @@ void attn_block_kernel(AttnArgs a) {
                 f16x4 hi, lo;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float v = o[d][r + q] * inv;
+                    const float v = split_value(o[d][r + q] * inv);
                     hi[q] = (f16)v;
                     lo[q] = (f16)(v - (float)hi[q]);
                 }
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) { L += red[i][1][ql]; o += red[i][2 + sg][ql]; }
     f16* dst = a.out + ((long long)(row0 + r / G) * a.Hq + hk * G + r % G) * HD + ch0 + sg;
-    const float res = o / L;
+    const float res = split_value(o / L);
     const f16 hi = (f16)res;
     *dst = hi;
     if (a.out_lo_off) dst[a.out_lo_off] = (f16)(res - (float)hi);
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
         f16x8 v, lo;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const float ov = acc[c0 + c] * inv;
+            const float ov = split_value(acc[c0 + c] * inv);
             v[c] = (f16)ov;
             lo[c] = (f16)(ov - (float)v[c]);
         }

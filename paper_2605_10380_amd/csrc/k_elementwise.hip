@@ -26,7 +26,7 @@ __global__ void embed_norm_kernel(const bf16* __restrict__ emb, const int* __res
     for (int c = threadIdx.x; c < d; c += 256) {
         const float v = (float)src[c];
         x[(long long)r * d + c] = v;
-        const float av = v * (float)gain[c];
+        const float av = split_value(v * (float)gain[c]);
         const f16 hi = (f16)av;
         a[(long long)r * d + c] = hi;
         if (a_lo_off) a[(long long)r * d + c + a_lo_off] = (f16)(av - (float)hi);     // split activations: the rounding remainder

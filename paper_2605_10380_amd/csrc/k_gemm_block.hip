@@ -43,6 +43,7 @@ __device__ __forceinline__ f32x2 pair_of_columns(float r0, float r1, bool odd) {
     return odd ? (f32x2){got, r1} : (f32x2){r0, got};
 }
 __device__ __forceinline__ void store_split2(f16* p, long long lo_off, f32x2 v) {
+    v = (f32x2){split_value(v[0]), split_value(v[1])};
     const f16x2 hi = {(f16)v[0], (f16)v[1]};
     *(f16x2*)p = hi;
     if (lo_off) *(f16x2*)(p + lo_off) = (f16x2){(f16)(v[0] - (float)hi[0]), (f16)(v[1] - (float)hi[1])};
@@ -439,6 +440,10 @@ int launch_gemm_block(Epilogue epi, const GemmArgs& g, const BlockPlan& p, hipSt
         case EPI_SWIGLU: return launch_block<EPI_SWIGLU>(g, p, s);
         default: return launch_block<EPI_QKV>(g, p, s);
     }
+}
+
+int launch_gemm_block_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s) {
+    return launch_gemm_block(epi, g, {rows == 256 ? 0 : cols == 256 ? 1 : 2, slices, 0.f}, s);
 }
 
 }  // namespace ax

@@ -60,6 +60,14 @@ struct RopeArgs {
 // consumer multiplies both parts against the SAME weight fragment (two MFMAs per fragment: no extra weight
 // traffic, twice the matrix-core work and activation traffic).  An offset of 0 means "not split".
 //
+// Both parts have to come from the same fp32 v.  Left alone the compiler folds a product in front into the conversion (v_fma_mixlo: one
+// rounding from the exact product) for one of them and rounds to fp32 first for the other; where the two disagree - near a tie, one value
+// in 30 000 - hi + lo was a whole fp16 step off.  So v is made a value of its own before it is split.
+__device__ __forceinline__ float split_value(float v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
 // One GEMM of a bf16-weight model: C = A[M,K] * W[N,K]^T, A fp16, W bf16.
 struct GemmArgs {
     const void* A;                    // fp16 [rows, K]
@@ -97,6 +105,8 @@ int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s);
 // "stream"), rows of A and of W per block (EPI_SWIGLU: half of the latter gate, half up) and K slices.
 struct GemmPlan { const char* kernel; int rows, cols, slices; };
 GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
+// A GEMM on the block kernel with the shape and slices of `rows`, `cols`, `slices` whatever the plan would say (tests); returns as launch_gemm_bf16.
+int launch_gemm_block_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s);
 // Repacks a row-major bf16 [N, K] matrix (N % 16 == 0, K % 32 == 0) into what every bf16-model GEMM
 // kernel reads: fp16 values in 16-row panels, 32-k chunks in MFMA operand order; src and dst must not overlap.
 // `bad` (device int, may be NULL) is set to 1 if some weight does not survive the narrowing (not finite in fp16).

@@ -1,0 +1,242 @@
+"""GPU: the kernels behind calls of more than 256 rows, every tile shape x epilogue x slicing x activation layout against float64, and
+the calls whose plan picks them."""
+import numpy as np
+import pytest
+
+from oracle import decoder as O
+from paper_2605_10380_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+BLOCKS = [(256, 256), (128, 256), (128, 128)]
+STORE, RESIDUAL, SWIGLU, QKV = range(4)
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def hi_lo(x):
+    """[2, ...]: fp16 hi and lo parts."""
+    hi = x.astype(np.float16)
+    return np.stack([hi, (x - hi.astype(np.float64)).astype(np.float16)])
+
+
+def operands(rng, M, N, K, split):
+    a = rng.standard_normal((M, K)) * 0.5
+    parts = hi_lo(a) if split else a.astype(np.float16)[None]
+    w = I.f32_to_bf16_bits(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
+    return parts, parts.astype(np.float64).sum(0), w
+
+
+def value(t, split):
+    """Value of a result that came as hi + lo parts, or as fp16."""
+    x = t.cpu().numpy().astype(np.float64)
+    return x[0] + x[1] if split else x[0]
+
+
+def fp16_bound(want, split):
+    """fp16: 2^-11 of the value; hi + lo parts: 2^-22, and what is below fp16's smallest subnormal.  Plus fp32 sums as in the other GEMM
+    tests: 2e-5 of the largest value."""
+    scale = np.abs(want).max()
+    return (2.0 ** -22 if split else 2.0 ** -11) * np.abs(want) + 2e-5 * scale + 2.0 ** -24
+
+
+CASES = [(b, epi, split, slices, hd, K)
+         for b in BLOCKS for epi in (STORE, RESIDUAL, SWIGLU, QKV) for split in (0, 1)
+         for slices, K in ((1, 64), (1, 576), (3, 576)) for hd in ((64, 128) if epi == QKV else (0,))
+         if not (epi == SWIGLU and b == (128, 128)) and not (slices > 1 and epi in (STORE, SWIGLU))]
+
+
+@pytest.mark.parametrize("block,epi,split,slices,hd,K", CASES)
+def test_block_gemm(torch, block, epi, split, slices, hd, K):
+    """300 rows (a whole tile and a part of one), columns that end inside a tile, fewer and more steps than stages, whole and in slices, A as
+    it is or with a pending norm."""
+    from paper_2605_10380_amd import binding as B
+    M = 300
+    Hq, Hkv = 3, 1
+    N = {64: 320, 128: 640}.get(hd, 320)
+    rng = np.random.default_rng(hash((block, epi, split, slices, hd, K)) % (1 << 31))
+    parts, a, w = operands(rng, M, N, K, split)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    bf = lambda x: torch.from_numpy(x).view(torch.bfloat16).cuda()
+    keep = dict(A=dev(parts), W=bf(w))
+    args = dict(epilogue=epi, rows=block[0], cols=block[1], slices=slices, M=M, N=N, K=K, a_lo=M * K if split else 0)
+    ref = a @ O.widen(w).T
+    if epi != RESIDUAL:                                        # the pending norm of A: five partial sums a row
+        ssq = rng.uniform(0.1, 2.0, (M, 5)).astype(np.float32)
+        keep["ssq"] = dev(ssq)
+        args.update(n_parts=5, eps=1e-5)
+        ref /= np.sqrt(ssq.astype(np.float64).sum(1, keepdims=True) / K + 1e-5)
+    if slices > 1:
+        keep["split_ws"] = torch.full((slices * M * N,), float("nan"), dtype=torch.float32, device="cuda")
+        args["split_ws_bytes"] = slices * M * N * 4
+    n16 = 3 * hd if epi == QKV else N
+    c16 = torch.full((1 + split, M, n16), float("nan"), dtype=torch.float16, device="cuda")
+    if epi != STORE:
+        keep["C16"] = c16
+        args["c_lo"] = M * n16 if split else 0
+    if epi in (STORE, RESIDUAL):
+        c0 = rng.standard_normal((M, N), dtype=np.float32)
+        keep["C"] = dev(c0.copy())
+    if epi == RESIDUAL:
+        gain = I.f32_to_bf16_bits(1.0 + 0.1 * rng.standard_normal(N, dtype=np.float32))
+        keep.update(gain=bf(gain), ssq_out=torch.full((M * N // 8,), float("nan"), dtype=torch.float32, device="cuda"))
+    if epi == SWIGLU:
+        w2 = I.f32_to_bf16_bits(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
+        keep["W2"] = bf(w2)
+    if epi == QKV:
+        Hkv = (N // hd - 3) // 2
+        n_blocks = 40
+        pos = rng.integers(0, 500, M).astype(np.int32)
+        slot = rng.permutation(n_blocks * 16)[:M].astype(np.int32)
+        ang = np.arange(500)[:, None] * 10000.0 ** (-2.0 * np.arange(hd // 2) / hd)
+        pool = torch.full((2, Hkv, n_blocks, 16 * hd), float("nan"), dtype=torch.float16, device="cuda")
+        keep.update(pool=pool, row_pos=dev(pos), row_slot=dev(slot), cos=dev(np.cos(ang).astype(np.float32)), sin=dev(np.sin(ang).astype(np.float32)))
+        args.update(n_q_heads=3, n_kv_heads=Hkv, head_dim=hd, pool_blocks=n_blocks)
+    torch.cuda.synchronize()
+    n_out = B.ax_dbg_gemm_block(**args, **{k: t.data_ptr() for k, t in keep.items()})
+
+    if epi == STORE:
+        assert (np.abs(keep["C"].cpu().numpy() - ref) <= 2e-5 * np.abs(ref).max()).all()
+    elif epi == RESIDUAL:
+        want = c0 + ref
+        got = keep["C"].cpu().numpy().astype(np.float64)
+        assert np.abs(got - want).max() <= 2e-5 * np.abs(want).max()
+        want16 = got * O.widen(gain)[None, :]
+        assert (np.abs(value(c16, split) - want16) <= fp16_bound(want16, split)).all()
+        assert n_out == (1 if slices > 1 else N // 64)
+        sums = keep["ssq_out"].cpu().numpy()[:M * n_out].reshape(M, n_out).astype(np.float64).sum(1)
+        assert np.allclose(sums, (want ** 2).sum(1), rtol=4e-5)
+    elif epi == SWIGLU:
+        up = a @ O.widen(w2).T / np.sqrt(ssq.astype(np.float64).sum(1, keepdims=True) / K + 1e-5)
+        want = O.silu(ref) * up
+        # gate and up: 2e-5 of their largest values each, and __expf's few units in the last place of fp32
+        bound = fp16_bound(want, split) + 4e-5 * np.abs(ref).max() * np.abs(up).max()
+        assert (np.abs(value(c16, split) - want) <= bound).all()
+    else:
+        qkv = ref.reshape(M, -1, hd)
+        half, cs, sn = hd // 2, np.cos(ang[pos])[:, None], np.sin(ang[pos])[:, None]
+        rot = lambda t: np.concatenate([t[..., :half] * cs - t[..., half:] * sn, t[..., half:] * cs + t[..., :half] * sn], -1)
+        wq, wk, wv = rot(qkv[:, :3]), rot(qkv[:, 3:3 + Hkv]), qkv[:, 3 + Hkv:]
+        assert (np.abs(value(c16, split).reshape(M, 3, hd) - wq) <= fp16_bound(wq, split)).all()
+        mem = pool.cpu().numpy().astype(np.float64)
+        k = mem[0].reshape(Hkv, n_blocks * 16, hd)
+        v = mem[1].reshape(Hkv, n_blocks, hd, 16).transpose(0, 1, 3, 2).reshape(Hkv, n_blocks * 16, hd)
+        assert (np.abs(k[:, slot] - wk.transpose(1, 0, 2)) <= fp16_bound(wk, 0).transpose(1, 0, 2)).all()
+        assert (np.abs(v[:, slot] - wv.transpose(1, 0, 2)) <= fp16_bound(wv, 0).transpose(1, 0, 2)).all()
+        rest = np.setdiff1d(np.arange(n_blocks * 16), slot)    # no slot but the rows' own was written
+        assert np.isnan(k[:, rest]).all() and np.isnan(v[:, rest]).all()
+    assert torch.isfinite(c16).all() or epi == STORE
+
+
+# what the plan picks, and a call that reaches it: (epilogue, M, N, K, plan); few-column cases of every tile, slice count and kernel
+PLANNED = [
+    (RESIDUAL, 257, 320, 64, ("tile", 64, 128, 1)), (RESIDUAL, 257, 320, 1024, ("tile", 64, 128, 2)),
+    (RESIDUAL, 449, 4160, 64, ("tile", 128, 128, 1)), (RESIDUAL, 500, 1600, 8192, ("tile", 128, 128, 4)),
+    (RESIDUAL, 513, 320, 64, ("block", 128, 128, 1)), (RESIDUAL, 513, 320, 2048, ("block", 128, 128, 4)),
+    (RESIDUAL, 449, 4160, 1024, ("block", 128, 256, 2)), (RESIDUAL, 500, 4160, 4096, ("block", 256, 256, 4)),
+    (SWIGLU, 257, 320, 64, ("block", 128, 256, 1)), (SWIGLU, 385, 14400, 64, ("block", 256, 256, 1)),
+    (SWIGLU, 500, 320, 1024, ("stream", 96, 256, 1)), (SWIGLU, 257, 14400, 64, ("stream", 160, 256, 1)),
+    (SWIGLU, 321, 14400, 64, ("stream", 192, 256, 1))]
+
+
+@pytest.mark.parametrize("epi,M,N,K,plan", PLANNED)
+def test_planned_gemm(torch, epi, M, N, K, plan):
+    """A GEMM of more than 256 rows on each kernel the plan knows, against float64."""
+    import test_gpu_kernels as T
+    from paper_2605_10380_amd import binding as B
+    assert B.ax_dbg_gemm_plan(epi, M, N, K, False, 8 * M * N * 4) == plan
+    if epi == RESIDUAL:
+        T.test_bf16_residual_gemm_with_norm_preparation(torch, M, N, K, True)
+    else:
+        T.test_bf16_gemm(torch, M, N, K, epi)
+
+
+@pytest.mark.parametrize("M,N,K,split", [(1600, 7744, 192, True), (1030, 5056, 8192, True), (1664, 7680, 448, True)])
+def test_residual_gemm_of_many_rows(torch, M, N, K, split):
+    """The residual epilogue with norm preparation over a thousand rows, columns that are no multiple of a tile."""
+    import test_gpu_kernels as T
+    T.test_bf16_residual_gemm_with_norm_preparation(torch, M, N, K, split)
+
+
+def _random_many_row_cases(n=18, seed=20260519):
+    """Seeded shapes above 256 rows with N a multiple of 64, as every model's are: all epilogues of the debug entry."""
+    rng = np.random.default_rng(seed)
+    return [(int(np.exp(rng.uniform(np.log(257), np.log(1700)))), 64 * int(rng.integers(1, 100)), 64 * int(rng.integers(1, 40)), i % 3) for i in range(n)]
+
+
+@pytest.mark.parametrize("M,N,K,epi", _random_many_row_cases())
+def test_many_row_gemm_seeded_random_shapes(torch, M, N, K, epi):
+    import test_gpu_kernels as T
+    T.test_bf16_gemm(torch, M, N, K, epi)
+
+
+# one layer, hi + lo activations or not: shapes whose four GEMMs (QKV, O, gate / up, down) take these kernels
+LAYERS = [
+    ((256, 4, 2, 64, 320, 300, 0), ("tile", "tile", "block", "tile")), ((2048, 4, 2, 64, 320, 640, 1), ("block", "block", "stream", "block")),
+    ((1024, 8, 4, 64, 320, 500, 0), ("tile", "tile", "stream", "tile"))]
+
+
+@pytest.mark.parametrize("dims,kernels", LAYERS)
+def test_layer_of_planned_gemms(torch, dims, kernels):
+    import test_gpu_kernels as T
+    from paper_2605_10380_amd import binding as B
+    d, hq, hkv, hd, F, rows, split = dims
+    qkv = (hq + 2 * hkv) * hd
+    ws = rows * max(8 * d, qkv) * 4
+    got = tuple(B.ax_dbg_gemm_plan(e, rows, n, k, bool(split), ws)[0]
+                for e, n, k in ((QKV, qkv, d), (RESIDUAL, d, hq * hd), (SWIGLU, F, d), (RESIDUAL, d, F)))
+    assert got == kernels
+    sh = I.DecoderShape("planned", 1, d, hq, hkv, hd, F, 512, "bf16")
+    attn, attn_ref, x, x_ref = T._one_layer(torch, sh, 0, rows, 24, rows, split)
+    assert np.abs(attn - attn_ref).max() <= 4e-3 * np.abs(attn_ref).max()
+    assert np.abs(x - x_ref).max() <= 4e-3 * np.abs(x_ref).max()
+
+
+@pytest.mark.parametrize("hd,hkv,G,P,T,split,least", [
+    (64, 32, 4, 1100, 1056, 0, 1),                             # 33 groups for 32 places a head: the last one is cut
+    (64, 2, 4, 4000, 96, 0, 1), (128, 8, 3, 1500, 200, 1, 1)])
+def test_block_attention_cut_groups(torch, hd, hkv, G, P, T, split, least):
+    """Attention items of groups that are cut beside (first case) groups that write their output themselves."""
+    import test_gpu_kernels as K
+    from paper_2605_10380_amd import binding as B
+    sh = I.DecoderShape("attn-cut", 1, 128, hkv * G, hkv, hd, 192, 512, "bf16")
+    items, merges, slots = B.ax_dbg_attention_items(B.make_config(sh, P + T + 16, max(T, 64), 1, split), [P], [T])
+    groups = -(-T * G // 128)
+    assert merges >= least and items == groups - merges + slots
+    if groups > 32:
+        assert merges < groups
+    got, ref, x, xr = K._one_layer(torch, sh, P, T, 25, max(T, 64), split)
+    assert np.abs(got - ref).max() <= 4e-3 * np.abs(ref).max()
+    assert np.abs(x - xr).max() <= 4e-3 * np.abs(xr).max()
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,F", [(2048, 8, 2, 64, 2048), (1024, 8, 4, 128, 9216)])
+@pytest.mark.parametrize("T,calls", [(9, 8), (17, 5), (48, 3), (144, 2), (200, 1), (300, 1), (700, 1)])
+def test_hi_and_lo_parts_add_up(torch, d, hq, hkv, hd, F, T, calls):
+    """Split activations: hi + lo of the LM head's input is x * gain to 2^-22 whichever kernel finished the residual stream - also where
+    x * gain lies so close to a tie that rounding it once or through fp32 makes a difference."""
+    from paper_2605_10380_amd import binding as B
+    sh = I.DecoderShape("parts", 1, d, hq, hkv, hd, F, 512, "bf16")
+    w = I.make_weights(sh, 31)
+    gain = O.widen(w["final_norm"])
+    dm = B.DeviceModel(sh, w, max_pos=1024, max_tokens=max(T, 64), pool_tokens=1024, act_split=1)
+    kv = dm.new_kv()
+    rng = np.random.default_rng(T + d)
+    for _ in range(calls):
+        B.ax_kv_truncate(kv, 0)
+        dm.extend(kv, rng.integers(0, sh.vocab, T).astype(np.int32), B.AX_OUT_LAST_ARGMAX)
+        x, hi, lo = np.zeros((T, d), np.float32), np.zeros((T, d), np.float16), np.zeros((T, d), np.float16)
+        B.ax_dbg_read(dm.model, 0, x)
+        B.ax_dbg_read(dm.model, 5, hi)
+        B.ax_dbg_read(dm.model, 15, lo)
+        want = x.astype(np.float64) * gain
+        # fp32 product 2^-24, lo part 2^-11 of half an fp16 step, and lo parts below the smallest subnormal
+        err = np.abs(hi.astype(np.float64) + lo.astype(np.float64) - want)
+        assert (err <= 2.0 ** -22 * np.abs(want) + 2.0 ** -24).all(), (int((err > 2.0 ** -22 * np.abs(want) + 2.0 ** -24).sum()), err.max())
+    B.ax_kv_free(kv)
+    dm.close()
