@@ -164,9 +164,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
 }
 
 // ------------------------------------------------------------------------------ MFMA split kernel
-// One wavefront = one (group of NQ q tiles of 32 stacked rows, KV head, key slice).  With NQ > 1
-// the K and V operands of a 32-key step are loaded once and used for every q tile of the group:
-// a verify step (T = 1 + k rows, (1 + k) * G stacked rows) is then a single group per KV head.
+// One block = one (q tile of 32 stacked rows, KV head, key slice).
 //
 // S^T = K * Q^T is computed so that the score tile comes out with lane <-> query row
 // (column l % 32) and registers <-> keys: register r of lane l is key (r/4)*8 + (l/32)*4 + r%4
@@ -272,8 +270,8 @@ struct AttnArgs {
 // one wavefront-wide load (and handed out with shuffles), and the K/V operands of step s + 1
 // are in flight while step s is multiplied.
 // NW = 4: the wavefronts of a block meet in LDS, so a wavefront's serial chain of key steps is a quarter of the slice while only one
-// partial record per slice goes to memory and through the combine kernel.  Whole steps: ~1B verify over 4352 keys 843 -> 826 us,
-// ~8B over 8704 4108 -> 4021 us, 16 ~3B sessions verified together 5359 -> 5162 us.
+// partial record per slice goes to memory and through the combine kernel.  Whole steps: ~8B verify over 8704 keys 4108 -> 4021 us, 16 ~3B
+// sessions verified together 5359 -> 5162 us (~1B verify over 4352 keys 843 -> 826 us, no more than its runs differ).
 // NW = 1: caches too short to give every CU such a block (~1B decode over 1301 keys: 727 us a step, 755 with NW = 4).
 // QS: q comes as hi and lo parts (split activations): the score product takes both against the same K operand.
 template <int HD, int NW, bool QS>
@@ -655,30 +653,30 @@ void attn_block_kernel(AttnArgs a) {
     }
 }
 
-// Merges the key slices of one q tile.  grid (n_groups * Hkv * NQ, HD / 4), 256 threads =
+// Merges the key slices of one q tile.  grid (n_tiles * Hkv, HD / 4), 256 threads =
 // 32 query rows x 8 slice groups; a block produces 4 output channels.  A thread loads the
 // (m, l, 4 channels) of its slices s = sg, sg + 8, ... in one go (up to 16 slices in registers),
 // the row maximum and then the weighted sums meet in LDS.  With a shared-prefix pass the slices
 // of that pass follow the tile's own: they live in the records of the shared pass's tile group
 // that holds the row (rows of all sequences stacked: global row * G + g).
-template <int HD, int NQ>
+template <int HD>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     constexpr int PS = HD * 32 + 64;
     constexpr int MAXS = 16;                                   // slices per thread held in registers
     __shared__ float red[8][6][32];
     const int Hkv = a.kv.n_kv_heads, G = a.Hq / Hkv;
-    const int t = blockIdx.x % NQ, hk = (blockIdx.x / NQ) % Hkv, tile = blockIdx.x / (NQ * Hkv);
+    const int hk = blockIdx.x % Hkv, tile = blockIdx.x / Hkv;
     const int ch0 = blockIdx.y * 4;
     const int ql = threadIdx.x & 31, sg = threadIdx.x >> 5;
     const int4 ti0 = *(const int4*)(a.tile_info + tile * 8);
     const int row0 = a.tile_info[tile * 8 + 4];
-    const int r_first = ti0.y + t * 32, n_stacked = ti0.w * G;
+    const int r_first = ti0.y, n_stacked = ti0.w * G;
     if (r_first >= n_stacked) return;                          // whole q tile past the end (block-uniform)
     const int r = r_first + ql;
     const bool valid = r < n_stacked;
     const int own_splits = a.n_splits, n_splits = own_splits + a.shared_splits;
-    const float* base = a.partials + ((long long)(tile * Hkv + hk) * own_splits * NQ + t) * PS + ql;
-    const long long stride = (long long)NQ * PS;               // between slices
+    const float* base = a.partials + (long long)(tile * Hkv + hk) * own_splits * PS + ql;
+    const long long stride = PS;                               // between slices
     const float* sbase = nullptr;                              // the row's record in the shared pass, slice 0
     long long sstride = 0;
     if (a.shared_splits > 0) {
@@ -755,8 +753,9 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
 // LDS and every load of a pass is independent.  Pass 1: the row's reference exponents of all
 // slices -> maximum.  Pass 2: weights 2^(m_s - M), weighted sums, one 16-byte (HD = 64) or
 // 32-byte store of the normalised fp16 outputs.
-template <int HD, int NQ, bool ITEMS>
+template <int HD, bool ITEMS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
+    constexpr int NQ = ITEMS ? 4 : 1;                          // tiles per group
     constexpr int PS = HD * 32 + 64, CPT = HD / 8, SU = 4;
     const int Hkv = a.kv.n_kv_heads, G = a.Hq / Hkv;
     const int t = blockIdx.x % NQ, hk = (blockIdx.x / NQ) % Hkv, tile = blockIdx.x / (NQ * Hkv);
@@ -826,9 +825,9 @@ size_t attention_partial_floats(int n_tiles, int n_kv_heads, int head_dim, int n
     return (size_t)n_tiles * n_kv_heads * n_splits * ((size_t)head_dim * 32 + 64);
 }
 
-template <int HD, int NQ>
-static void launch_attn_mfma(const AttnArgs& a, int n_groups, int waves, hipStream_t s) {
-    dim3 grid(n_groups, a.kv.n_kv_heads, a.n_splits), cgrid(n_groups * a.kv.n_kv_heads * NQ, HD / 4);
+template <int HD>
+static void launch_tiles(const AttnArgs& a, int n_tiles, int waves, hipStream_t s) {
+    dim3 grid(n_tiles, a.kv.n_kv_heads, a.n_splits);
     if (waves == 4) {
         if (a.q_lo_off) attn_split_kernel<HD, 4, true><<<grid, 256, 0, s>>>(a);
         else attn_split_kernel<HD, 4, false><<<grid, 256, 0, s>>>(a);
@@ -838,10 +837,9 @@ static void launch_attn_mfma(const AttnArgs& a, int n_groups, int waves, hipStre
     }
     // few records with many slices (one session): blocks of 4 channels that spread the slices over
     // threads; many records with few slices (many sessions): one block per record
-    if (n_groups * a.kv.n_kv_heads >= 64 && a.n_splits + a.shared_splits <= 32)
-        attn_merge_kernel<HD, NQ, false><<<n_groups * a.kv.n_kv_heads * NQ, 256, 0, s>>>(a);
-    else
-        attn_combine_kernel<HD, NQ><<<cgrid, 256, 0, s>>>(a);
+    const int records = n_tiles * a.kv.n_kv_heads;
+    if (records >= 64 && a.n_splits + a.shared_splits <= 32) attn_merge_kernel<HD, false><<<records, 256, 0, s>>>(a);
+    else attn_combine_kernel<HD><<<dim3(records, HD / 4), 256, 0, s>>>(a);
 }
 
 template <int HD, int NQ>
@@ -850,19 +848,17 @@ static void launch_block(const AttnArgs& a, int n_items, hipStream_t s) {
     if (a.q_lo_off) attn_block_kernel<HD, NQ, 3, true><<<grid, 64 * NQ, 0, s>>>(a);
     else attn_block_kernel<HD, NQ, 3, false><<<grid, 64 * NQ, 0, s>>>(a);
 }
-// The items of a block-kernel pass, then the tiles whose keys they cut.
+// The items of a block-kernel pass, then the groups of 4 tiles whose keys they cut (n_merge; the shared-prefix pass has none).
 template <int NQ>
 static void launch_items(const AttnArgs& a, int n_items, int n_merge, hipStream_t s) {
+    if (a.kv.head_dim == 64) launch_block<64, NQ>(a, n_items, s);
+    else launch_block<128, NQ>(a, n_items, s);
+    if (n_merge == 0) return;
     AttnArgs mg = a;
     mg.tile_info = a.tile_info + (size_t)n_items * 8;
-    const unsigned mgrid = (unsigned)(n_merge * a.kv.n_kv_heads * NQ);
-    if (a.kv.head_dim == 64) {
-        launch_block<64, NQ>(a, n_items, s);
-        if (n_merge) attn_merge_kernel<64, NQ, true><<<mgrid, 256, 0, s>>>(mg);
-    } else {
-        launch_block<128, NQ>(a, n_items, s);
-        if (n_merge) attn_merge_kernel<128, NQ, true><<<mgrid, 256, 0, s>>>(mg);
-    }
+    const unsigned mgrid = (unsigned)(n_merge * a.kv.n_kv_heads * 4);
+    if (a.kv.head_dim == 64) attn_merge_kernel<64, true><<<mgrid, 256, 0, s>>>(mg);
+    else attn_merge_kernel<128, true><<<mgrid, 256, 0, s>>>(mg);
 }
 
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, const StepView& sv,
@@ -903,7 +899,7 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
             a.shared_nq = sv.shared_nq;
             a.shared_len = sv.shared_len;
         }
-        if (hd == 64) launch_attn_mfma<64, 1>(a, sv.n_tiles, split_waves, s); else launch_attn_mfma<128, 1>(a, sv.n_tiles, split_waves, s);
+        if (hd == 64) launch_tiles<64>(a, sv.n_tiles, split_waves, s); else launch_tiles<128>(a, sv.n_tiles, split_waves, s);
     }
 }
 
