@@ -120,7 +120,7 @@ Layout make_layout(const ax_model_config& c) {
     }
     L.partials = take(c.dtype == AX_BF16 ? 2 * L.max_records * ((size_t)c.head_dim * 32 + 64) * 4 : 0);
     // fp32 slabs of GEMMs that finish in a second kernel: K-slice partials of the residual GEMMs (SPLITK_MAX slabs of
-    // [T, d_model]; the SwiGLU GEMM's slices take what fits) and the raw products of the QKV GEMM above 64 rows, which
+    // [T, d_model]; the SwiGLU GEMM's slices take what fits) and the raw products of the QKV GEMM from 65 rows up, which
     // needs ONE whole [T, (Hq + 2 Hkv) hd] slab whatever the ratio of that width to d_model
     L.splitk_bytes = c.dtype == AX_BF16 ? std::max(T * c.d_model * 4 * ax::SPLITK_MAX,
                                                    T * (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * 4) : 0;
@@ -219,7 +219,7 @@ void item_groups(int s, int P, int T, int G, std::vector<AttnItem>& groups) {
 }
 
 // Cuts the q-tile groups of a call (AttnItem: lo = 0, hi = all key steps) into items of about equal length and orders them.
-// A block is one item of 4 tiles; b of them share a CU (up to 4 at head_dim 64, 3 at 128, 2 with split activations: registers), so
+// A block is one item of 4 tiles; b of them share a CU (up to 4 at head_dim 64, 3 at 128 - one fewer with split activations), so
 // 256 b / heads items per head run at the same time.  Every cut costs partial records (8 or 16 KB a tile, written and read back by a
 // merge kernel), so groups are cut only while that fills the chip: for each b, the shortest item length for which all items still run
 // at once; the b whose length x step time + cost of the records is smallest (step times measured with b blocks on every CU).

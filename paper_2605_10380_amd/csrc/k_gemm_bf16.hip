@@ -9,12 +9,12 @@
 //   * skinny kernel (M <= 16, the O projection and narrow stores to 32: verify steps, pure weight streaming): one block owns 16 output
 //     columns, its wavefronts split K, W goes HBM -> registers -> v_mfma_f32_16x16x32_f16
 //     with no LDS in the streaming loop; the per-wavefront partial sums meet in LDS.
-//   * tile kernel   (more rows, to 256): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
+//   * tile kernel   (more rows, to 256, and some launches of up to 512): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
 //     v_mfma_f32_32x32x16_f16, global loads several K slices ahead.
-//   * stream kernel (logits from 17 rows, SwiGLU at 193-256 rows of wide matrices, and - over K slices - the SwiGLU GEMM of
-//     17-192 rows and the down projection of 129-192): activations through LDS, weights straight into MFMA operands.
+//   * stream kernel (logits from 17 rows, SwiGLU at 193-256 rows of wide matrices and some launches of up to 640, and - over K slices -
+//     the SwiGLU GEMM of 17-192 rows and the down projection of 129-192): activations through LDS, weights straight into MFMA operands.
 //     The launcher states each crossover with the figures behind it.
-//   * block kernel  (more than 256 rows; k_gemm_block.hip).
+//   * block kernel  (more than 256 rows; k_gemm_block.hip; which of the three, plan_many below).
 //
 // RMSNorm is folded into the GEMMs around it.  The GEMM that produces the residual stream x
 // also writes a = fp16(x * gain_next) and, per row and per block of columns, a partial sum of
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs g) {
 // wavefronts side by side along N, all working on the same BM = TM*32 rows; a wavefront owns 32
 // output columns, i.e. one 32-row tile each of W (gate) and W2 (up).  The weight loads run D
 // k-steps ahead in a register ring, the activation tile is double buffered in LDS, one barrier
-// per k-step of 64.  Above 256 rows the block kernel is faster (~1B gate / up at 4096 rows: 382 -> 270 us).
+// per k-step of 64.  With thousands of rows the block kernel is faster (~1B gate / up at 4096 rows: 382 -> 262 us).
 //
 // Blocks are renumbered so that the gy row tiles that share a weight tile have consecutive ids
 // on one XCD (workgroups are dealt to the 8 XCDs round robin), i.e. share that XCD's L2.

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmF32Args g) {
         } else if (EPI == EPI_SWIGLU) {
             if (live) g.C[o] = v[0] / (1.0f + expf(-v[0])) * v[NB - 1];
         } else {
-            const float other = __shfl_xor(v[0], 8, 64);         // the pair's other channel (EPI_QKV: MT * 256 is a multiple of the block)
+            const float other = __shfl_xor(v[0], 8, 64);         // the pair's other channel (whole wavefronts get here: MT * 256 is a multiple of 64)
             if (live) {
                 g.C[o] = v[0];                                   // the product as it is, for inspection
                 const RopeArgs& ro = g.rope;

@@ -96,9 +96,10 @@ struct GemmArgs {
 constexpr int SPLITK_MAX = 8;
 // EPI_RESIDUAL with gain_next: returns the number of partial sums of x^2 per row the launch leaves in
 // ssq_out (rows are that many floats apart): the consumer of the pending norm passes it as nparts.
-// It depends on which kernel ran (a few per row after a K-split reduce kernel, N / 32 or N / 8-16
+// It depends on which kernel ran (a few per row after a K-split reduce kernel, N / 64, N / 32 or N / 8-16
 // from kernels that finish a column block on their own).  Other epilogues return 0.
-// EPI_QKV above 64 rows writes its raw products to split_ws first: -1, and nothing launched, if one [M, N] fp32
+// EPI_QKV writes its raw products to split_ws first on the tile kernel (65-256 rows, and where the plan takes it up to 512) and in K
+// slices; of up to 256 rows it has no other way there: -1, and nothing launched, if one [M, N] fp32
 // slab does not fit there.
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s);
 // The plan of a GEMM of more than 256 rows that are not gathered ("" = fewer rows, or N not a multiple of 64): kernel ("block", "tile" or

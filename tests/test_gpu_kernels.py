@@ -20,12 +20,13 @@ def torch_cuda():
 
 
 # M values: skinny path (<= 16, and to 32 rows for some epilogues) and tile path (ragged); K / N pick
-# different wavefront counts in the skinny kernel and both tile shapes; M >= 257 (and 193-256 for
-# wide matrices) takes the streaming SwiGLU kernel (steady-state loop and drain, ragged rows and columns)
+# different wavefront counts in the skinny kernel and both tile shapes; 193-256 rows of wide matrices take the streaming SwiGLU
+# kernel.  More than 256 rows: N a multiple of 64 (as every model's is) goes by the plan of many-row GEMMs (see test_gpu_many_rows.py,
+# which asserts it), any other N to the tile kernel, which only these debug calls do
 GEMM_CASES = [(1, 64, 64), (9, 3072, 2048), (9, 2048, 8192), (17, 512, 256), (33, 128, 1024), (64, 2064, 192),
               (65, 384, 128), (100, 200 * 16, 320), (256, 3072, 2048), (300, 1024, 512), (512, 33 * 128, 256),
               (400, 1040, 1024), (384, 2048, 576), (300, 2048, 256), (230, 14336, 128), (257, 8192, 128), (640, 8192, 192), (320, 14336, 128),
-              # thousands of rows: every epilogue through the streaming kernel (ragged rows and columns, drain path)
+              # thousands of rows: the tile kernel (N = 7712) and the block kernel
               (1600, 7712, 192), (1664, 7680, 448),
               (144, 65600, 128), (131, 65536, 192), (17, 65600, 128), (40, 65536, 192), (100, 65568, 128), (190, 65536, 128), (300, 65600, 128),   # streaming blocks for wide outputs (logits) from 17 rows
               (144, 8192, 3072), (190, 4096, 1536), (150, 4112, 1536),  # 17-192 rows: SwiGLU over K slices (32- to 192-row blocks)
@@ -111,12 +112,12 @@ def test_bf16_gemm_seeded_random_shapes(torch_cuda, M, N, K, epi):
 # the residual GEMM with the next norm's preparation, through every kernel that implements it:
 # skinny with 8 / 12 / 16 columns per block (to 16 rows, and to 32 rows when K is short), tile kernels
 # unsplit and with K slices (64- and 128-row
-# blocks), streaming kernel
+# blocks), block kernel; N = 7712 and 5088 (no multiple of 64, no model's width) stay on the tile kernel at any row count
 RESIDUAL_CASES = [(9, 2048, 512, False), (9, 3072, 256, False), (33, 4096, 192, False), (16, 1040, 128, False),
                   (24, 2048, 256, False), (24, 1024, 4096, True), (64, 1024, 128, False),
                   (100, 512, 256, False), (256, 2048, 2048, True), (256, 2048, 2048, False), (300, 1024, 4096, True),
                   (512, 4096, 4096, True), (520, 3072, 8192, True), (300, 4096, 14336, True), (1600, 7712, 192, True),
-                  (1030, 5088, 8192, True),        # long K and one even round of blocks: streaming kernel
+                  (1030, 5088, 8192, True),
                   (144, 3072, 8192, True), (131, 2048, 8192, True), (190, 2048, 8192, True), (161, 1024, 12288, True)]   # 160- / 192-row streaming blocks, K slices
 
 
@@ -287,7 +288,7 @@ def _one_layer(torch_cuda, sh, P, T, seed, max_tokens, act_split=0):
 @pytest.mark.parametrize("hd,hkv,G,P,T,split", [
     (64, 2, 4, 0, 65, 0), (64, 2, 4, 31, 100, 0), (64, 1, 1, 0, 300, 0), (64, 8, 4, 777, 96, 0), (64, 4, 3, 1000, 130, 1),
     (128, 2, 3, 0, 43, 0), (128, 1, 8, 500, 17, 0), (128, 8, 1, 640, 257, 0), (128, 2, 5, 33, 90, 1),
-    (64, 32, 4, 40, 1056, 0)])                                 # more groups of tiles than run at once: the rest is cut
+    (64, 32, 4, 40, 1056, 0)])                                 # more groups of tiles than run at once (cut ones: test_gpu_many_rows.py)
 def test_block_attention_items(torch_cuda, hd, hkv, G, P, T, split):
     """Attention of long extends at the edges of its tiles (32 rows), groups (128), key steps (32), pages (16) and key
     ranges, over pool memory full of NaN patterns."""
@@ -314,8 +315,8 @@ def test_split_attention_wavefronts(torch_cuda, hd, hkv, G, P, T, split):
     (64, 2, 1, 64, 64, 257, 0), (192, 3, 1, 128, 320, 300, 0), (512, 8, 2, 64, 1088, 511, 0), (2048, 8, 2, 128, 2112, 385, 0),
     (1088, 5, 5, 64, 4096, 640, 0), (320, 4, 2, 128, 448, 270, 1), (1024, 8, 4, 64, 2560, 513, 1)])
 def test_many_row_gemms(torch_cuda, d, hq, hkv, hd, F, T, split):
-    """The block GEMMs of calls with more than 256 rows: row, column and K remainders of all tile shapes, K slices (the long K of the
-    down projection against few columns), both activation layouts."""
+    """Layers of more than 256 rows with few columns: the tile kernel, 128 x 128 and 128 x 256 blocks, K slices (the long K of the down
+    projection), both activation layouts.  (Every tile shape and epilogue: test_gpu_many_rows.py.)"""
     sh = I.DecoderShape("gemm-edge", 1, d, hq, hkv, hd, F, 512, "bf16")
     got, ref, x, xr = _one_layer(torch_cuda, sh, 0, T, 22, T, split)
     assert np.abs(got - ref).max() <= 4e-3 * np.abs(ref).max()
