@@ -190,6 +190,9 @@ __device__ __forceinline__ void block_inv_rms_few(const GemmArgs& g, int first_r
 struct BlockPlan { int shape, ks; float us; };
 BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
 float gemm_reduce_us(Epilogue epi, int M, int N, int ks);      // time of the kernel that adds up ks slabs (EPI_QKV, EPI_RESIDUAL)
+// What a whole residual GEMM costs the GEMM behind it: N / 64 or N / 32 partial sums of x^2 a row to read in every block's prologue, where
+// slabs added up leave a few (~3B at 1200 rows: O whole 40.9 us + gate / up 149.7, O in slices 39.1 + 143.6).
+float gemm_partials_us(int M);
 // a_rows must be NULL and N % 64 == 0; returns the partial sums per row it leaves, as launch_gemm_bf16.
 int launch_gemm_block(Epilogue epi, const GemmArgs& g, const BlockPlan& p, hipStream_t s);
 // Second halves of K-sliced GEMMs (k_gemm_bf16.hip): add the g.ksplit slabs of g.split_ws and run the epilogue.

@@ -1285,7 +1285,7 @@ static float tile_us(int M, int N, int K, bool split, size_t ws_bytes) {
     if (blocks > 256) return 1e30f;
     const auto& t = kTile[p.big][split];
     const float us = t.fixed + K / p.ks / 64 * (t.lo + (t.full - t.lo) * blocks / 256);
-    return us + (EPI == EPI_QKV || p.ks > 1 ? gemm_reduce_us((Epilogue)EPI, M, N, p.ks) : 6.4f);
+    return us + (EPI == EPI_QKV || p.ks > 1 ? gemm_reduce_us((Epilogue)EPI, M, N, p.ks) : 6.4f + gemm_partials_us(M));
 }
 
 // SwiGLU streaming blocks of 32 tm rows x 128 columns of gate and of up, one on a CU at a time

@@ -1,10 +1,11 @@
 // GEMMs of many rows (bf16-weight models): C = A[M,K] * W[N,K]^T on the fp16 matrix cores, both operands staged through LDS by
 // the memory pipeline itself (global_load_lds: no registers, no ds_write in between), blocks of up to 256 x 256 outputs.
 //
-// What bounds it: a CU takes ~20.6 bytes per clock out of L2 (64 lines of 128 B in flight over ~400 clocks), and 256 x 256 outputs
+// What bounds it: a CU takes ~20 bytes per clock out of L2 (64 lines of 128 B in flight over ~400 clocks), and 256 x 256 outputs
 // need 32 KB of operands per 32 k, 1024 clocks of its matrix cores - so ~64 % of the matrix rate is what the largest tile that fits the
-// registers can reach, and that is what the counters show (gate / up of the ~3B shape with K = 8192: matrix cores busy 64 %
-// of the cycles, 20.6 B per clock and CU, no LDS bank conflicts, LDS a quarter busy, clock held at 1.7 GHz by power).
+// registers can reach.  Counters (gate / up of the ~3B shape at 4096 rows; profiles/config5_block_kernel_counters.txt): matrix cores busy
+// 60 % of the cycles, 19.1 B per clock and CU, pending-request queue full half of the time, LDS instructions in a quarter of the cycles and
+// under 1 % of them in conflict, clock held at 1.79 GHz by power.
 //   * Stages of 32 k, up to four in LDS, so that the copies of three steps are in flight: with two stages of 64 k the queue of outstanding
 //     lines ran dry between a stage's arrival and the issue of the next one (~1B gate / up, 4096 rows: 283 -> 264 us).
 //   * 8 wavefronts, two per SIMD.  4 wavefronts of 128 x 128 outputs need a third fewer LDS reads but were 5-15 % slower: one
@@ -371,6 +372,8 @@ float gemm_reduce_us(Epilogue epi, int M, int N, int ks) {
     return epi == EPI_QKV ? 4.7f + (0.287f * ks + 0.306f) * mb : 3.f + (0.371f * ks + 0.226f) * mb;
 }
 
+float gemm_partials_us(int M) { return std::min(4e-3f * M, 7.f); }
+
 BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
     BlockPlan best{-1, 1, 0.f};
     for (int c = 0; c < 3; ++c) {
@@ -392,7 +395,7 @@ BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t 
                 us += (step * steps + end) * (rounds ? t.tail : 1.f);
             }
             us *= t.padding + (1.f - t.padding) * M / (gy * s.bm);
-            if (ks > 1) us += gemm_reduce_us(epi, M, N, ks);
+            us += ks > 1 ? gemm_reduce_us(epi, M, N, ks) : epi == EPI_RESIDUAL ? gemm_partials_us(M) : 0.f;
             if (best.shape < 0 || us < best.us) best = {c, ks, us};
         }
     }

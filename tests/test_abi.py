@@ -119,7 +119,7 @@ def test_many_row_gemm_plans_are_launchable():
     (3, 288, 3072, 2048, False, ("tile", 64, 128, 2)), (3, 768, 5120, 3072, False, ("block", 128, 128, 1)), (3, 3072, 7168, 5120, False, ("block", 128, 256, 1)),
     (3, 1280, 3072, 2048, False, ("block", 128, 128, 1)), (1, 512, 2048, 8192, False, ("tile", 128, 128, 4)),
     (1, 257, 3072, 8192, False, ("tile", 64, 128, 2)), (1, 768, 3072, 8192, False, ("block", 256, 256, 4)),
-    (1, 1280, 3072, 3072, False, ("block", 128, 128, 1)), (1, 640, 4096, 14336, False, ("block", 256, 256, 4)),
+    (1, 1280, 3072, 3072, False, ("block", 128, 256, 2)), (1, 640, 4096, 14336, False, ("block", 256, 256, 4)),
     (2, 320, 14336, 4096, False, ("stream", 160, 256, 1)), (2, 576, 14336, 4096, True, ("stream", 96, 256, 1)),
     (2, 4096, 8192, 2048, False, ("block", 256, 256, 1)), (2, 288, 8192, 2048, False, ("block", 128, 256, 1))])
 def test_many_row_gemm_plan_of_measured_calls(epi, M, N, K, split, want):
