@@ -30,6 +30,11 @@ ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps
 ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char **kernel, int *rows, int *cols,
                            int *slices);
 
+/* The same for activations in panels (only the block kernel reads those; M > 256, N % 64 == 0), and whether a call of that many rows of a
+ * model keeps its layers' activations so: 1 or 0.  Host only. */
+ax_status ax_dbg_panel_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int *rows, int *cols, int *slices);
+ax_status ax_dbg_layer_panels(const ax_model_config *cfg, int rows, int *panels);
+
 /* One GEMM of a bf16-weight layer on a block shape of the many-row kernel that the caller names, with everything a layer uses: hi + lo
  * activations, a pending RMSNorm of A's rows, K slices and each epilogue.  All pointers are device memory; weights row-major bf16.
  * rows x cols: 256 x 256, 128 x 256 or 128 x 128 (not for SwiGLU).  N % 64 == 0, K % 64 == 0, head_dim 64 or 128. */
@@ -49,6 +54,8 @@ typedef struct {
     void *pool; long long pool_blocks;                          /* ... a one-layer KV pool of 16-token blocks ... */
     const int *row_pos, *row_slot; const float *cos, *sin;      /* ... position and slot of the rows, rotary tables [pos][head_dim / 2] */
     void *split_ws; size_t split_ws_bytes;
+    int a_panels, c_panels;             /* A (and ssq, as [n_parts][M]), C16 (and ssq_out; epilogues 1 and 2) in panels of 16 rows, as calls of many
+                                           rows hold them: 8 columns of a panel's rows at a time, each row's 8 side by side */
 } ax_dbg_block_gemm;
 ax_status ax_dbg_gemm_block(ax_dbg_block_gemm *args, void *hip_stream);
 

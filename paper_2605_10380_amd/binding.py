@@ -31,7 +31,8 @@ class ax_dbg_block_gemm(C.Structure):
                  ("eps", C.c_float), ("C", C.c_void_p), ("C16", C.c_void_p), ("c_lo", C.c_longlong), ("gain", C.c_void_p),
                  ("ssq_out", C.c_void_p), ("n_parts_out", C.c_int), ("n_q_heads", C.c_int), ("n_kv_heads", C.c_int), ("head_dim", C.c_int),
                  ("pool", C.c_void_p), ("pool_blocks", C.c_longlong), ("row_pos", C.c_void_p), ("row_slot", C.c_void_p), ("cos", C.c_void_p),
-                 ("sin", C.c_void_p), ("split_ws", C.c_void_p), ("split_ws_bytes", C.c_size_t)])
+                 ("sin", C.c_void_p), ("split_ws", C.c_void_p), ("split_ws_bytes", C.c_size_t),
+                 ("a_panels", C.c_int), ("c_panels", C.c_int)])
 
 
 class ax_exspec_stats(C.Structure):
@@ -92,6 +93,8 @@ def _load():
         "ax_dbg_split_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
                                        C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+        "ax_dbg_panel_plan": (C.c_int, [C.c_int] * 5 + [C.c_size_t] + [C.POINTER(C.c_int)] * 3),
+        "ax_dbg_layer_panels": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.POINTER(C.c_int)]),
         "ax_dbg_gemm_block": (C.c_int, [C.POINTER(ax_dbg_block_gemm), vp]),
         "ax_dbg_attention_items": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int),
                                              C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
@@ -401,6 +404,20 @@ def ax_dbg_gemm_plan(epilogue: int, M: int, N: int, K: int, split: bool = False,
     n, r, c, k = C.c_char_p(), C.c_int(), C.c_int(), C.c_int()
     _check(lib.ax_dbg_gemm_plan(epilogue, M, N, K, int(split), split_ws_bytes, C.byref(n), C.byref(r), C.byref(c), C.byref(k)))
     return n.value.decode(), r.value, c.value, k.value
+
+
+def ax_dbg_panel_plan(epilogue: int, M: int, N: int, K: int, split: bool = False, split_ws_bytes: int = 1 << 40):
+    """(rows, cols, slices): the block and K slices of a GEMM of more than 256 rows with its activations in panels."""
+    out = [C.c_int() for _ in range(3)]
+    _check(lib.ax_dbg_panel_plan(epilogue, M, N, K, int(split), split_ws_bytes, *[C.byref(x) for x in out]))
+    return tuple(x.value for x in out)
+
+
+def ax_dbg_layer_panels(cfg, rows: int) -> bool:
+    """Whether a call of that many rows keeps the activations of its layers in panels."""
+    out = C.c_int()
+    _check(lib.ax_dbg_layer_panels(C.byref(cfg), rows, C.byref(out)))
+    return bool(out.value)
 
 
 def ax_dbg_gemm_block(stream: int = 0, **args) -> int:

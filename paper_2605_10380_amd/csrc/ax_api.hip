@@ -152,6 +152,8 @@ struct ax_model {
     std::vector<Graph> graphs;
     hipStream_t capture_stream = nullptr;
     bool use_graphs = true;
+    // how the last call left its activations (ax_dbg_read hands out rows)
+    struct { int rows = 0; bool layers = false, out = false; } panels;
     // optional per-kernel timing (test / benchmark instrumentation, off by default)
     bool prof_on = false;
     struct ProfSpan { int cls; hipEvent_t a, b; };
@@ -493,6 +495,12 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
     return AX_OK;
 }
 
+// Whether a call of that many rows keeps the activations of its layers in panels.
+bool layer_panels(const ax_model_config& c, const Layout& L, int rows) {
+    return c.dtype == AX_BF16 && (ax::gemm_layer_panels(rows, c.d_model, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim,
+                                                                      c.n_q_heads * c.head_dim, c.d_ff, L.h_lo != 0, L.splitk_bytes));
+}
+
 // Device half: descriptor upload and the kernel sequence of one forward.  `verify_k` >= 0
 // appends the greedy acceptance and the copy of (accepted, next token) to host_result.  With
 // `capturing` the launches go into a stream capture: no event is recorded and the kernel
@@ -604,8 +612,13 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
         base.M = R;
         base.split_ws = (float*)(ws + L.splitk);
         base.split_ws_bytes = L.splitk_bytes;
-        auto normed = [&](ax::GemmArgs& g) { g.A = h; g.a_lo_off = L.h_lo; g.ssq = ssq; g.nparts = nparts; g.d_norm = d_model; g.eps = c.rms_eps; g.K = d_model; };
-        ax::launch_embed_norm(m->tok_emb, sv.row_tok, m->norm_attn[0], x, h, L.h_lo, ssq, nparts, R, d_model, stream);
+        // activations go in panels from kernel to kernel (calls of many rows); a last norm whose reader picks some stays in rows
+        const bool panels = layer_panels(c, L, R),
+                   out_panels = panels && ((n_out == R && (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_ALL_LOGITS)));
+        bool h_panels = panels;
+        m->panels = {R, panels, out_panels};
+        auto normed = [&](ax::GemmArgs& g) { g.a_panels = h_panels; g.a_total_rows = R; g.A = h; g.a_lo_off = L.h_lo; g.ssq = ssq; g.nparts = nparts; g.d_norm = d_model; g.eps = c.rms_eps; g.K = d_model; };
+        ax::launch_embed_norm(m->tok_emb, sv.row_tok, m->norm_attn[0], x, h, L.h_lo, h_panels, ssq, nparts, R, d_model, stream);
         for (int l = 0; l < c.n_layers; ++l) {
             {
                 ax::GemmArgs g = base;
@@ -619,19 +632,20 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
             }
             { ProfScope ps(m, 1, stream);
               ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, (float*)(ws + L.partials), n_splits,
-                                 split_waves(cp.n_tiles * c.n_kv_heads, cp.max_steps), stream, L.q_lo, L.attn_lo); }
+                                 split_waves(cp.n_tiles * c.n_kv_heads, cp.max_steps), stream, L.q_lo, L.attn_lo, panels); }
             { ProfScope empty(m, 6, stream); }         // bracket around nothing: the cost of the two events
             {
                 ax::GemmArgs g = base;
                 g.A = attn; g.a_lo_off = L.attn_lo; g.K = qdim; g.W = m->wo[(size_t)l]; g.N = d_model;
                 g.Cf = x; g.C16 = h; g.c_lo_off = L.h_lo; g.gain_next = m->norm_mlp[(size_t)l]; g.ssq_out = ssq;
+                g.a_panels = g.c_panels = panels; g.a_total_rows = R;
                 ProfScope ps(m, 2, stream);
                 nparts = ax::launch_gemm_bf16(ax::EPI_RESIDUAL, g, stream);
             }
             {
                 ax::GemmArgs g = base;
                 normed(g);
-                g.W = m->w_gate[(size_t)l]; g.W2 = m->w_up[(size_t)l]; g.N = c.d_ff; g.C16 = ffn; g.c_lo_off = L.ffn_lo;
+                g.W = m->w_gate[(size_t)l]; g.W2 = m->w_up[(size_t)l]; g.N = c.d_ff; g.C16 = ffn; g.c_lo_off = L.ffn_lo; g.c_panels = panels;
                 ProfScope ps(m, 3, stream);
                 ax::launch_gemm_bf16(ax::EPI_SWIGLU, g, stream);
             }
@@ -640,6 +654,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
                 g.A = ffn; g.a_lo_off = L.ffn_lo; g.K = c.d_ff; g.W = m->w_down[(size_t)l]; g.N = d_model;
                 g.Cf = x; g.C16 = h; g.c_lo_off = L.h_lo; g.ssq_out = ssq;
                 g.gain_next = l + 1 < c.n_layers ? m->norm_attn[(size_t)l + 1] : m->final_norm;
+                g.a_panels = panels; g.a_total_rows = R; g.c_panels = h_panels = l + 1 < c.n_layers ? panels : out_panels;
                 ProfScope ps(m, 4, stream);
                 nparts = ax::launch_gemm_bf16(ax::EPI_RESIDUAL, g, stream);
             }
@@ -730,6 +745,7 @@ ax_status run_verify_graph(ax_model* m, ax_kv* kv, const int32_t* toks, int T, v
         if (e != hipSuccess) return fail(AX_ERR_DEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
         m->graphs.push_back({key, cp.pool->uid, exec});
     }
+    m->panels = {T, layer_panels(m->cfg, m->lay, T), false};
     HIP_TRY(hipGraphLaunch(exec, stream));
     return AX_OK;
 }
@@ -1256,6 +1272,24 @@ ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t 
     return AX_OK;
 }
 
+ax_status ax_dbg_panel_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int* rows, int* cols, int* slices) {
+    if (epilogue < 0 || epilogue > 3 || M <= 0 || N <= 0 || K <= 0 || !rows || !cols || !slices) return fail(AX_ERR_INVALID, "bad argument");
+    if (M <= 256 || K % 64 != 0 || N % 64 != 0) return fail(AX_ERR_UNSUPPORTED, "panels need M > 256, K %% 64 == 0, N %% 64 == 0");
+    const ax::GemmPlan p = ax::gemm_panel_plan((ax::Epilogue)epilogue, M, N, K, split != 0, split_ws_bytes);
+    *rows = p.rows;
+    *cols = p.cols;
+    *slices = p.slices;
+    return AX_OK;
+}
+
+ax_status ax_dbg_layer_panels(const ax_model_config* cfg, int rows, int* panels) {
+    ax_status why;
+    if (!config_ok(cfg, &why)) return fail(why, "model config rejected");
+    if (rows <= 0 || !panels) return fail(AX_ERR_INVALID, "bad argument");
+    *panels = layer_panels(*cfg, make_layout(*cfg), rows);
+    return AX_OK;
+}
+
 ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
     if (!a || !a->A || !a->W || a->M <= 0 || a->N <= 0 || a->K <= 0 || a->epilogue < 0 || a->epilogue > 3 || (a->ssq && a->n_parts <= 0))
         return fail(AX_ERR_INVALID, "bad argument");
@@ -1289,6 +1323,7 @@ ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
     g.rope.kv = {a->pool, a->pool_blocks, a->n_kv_heads, a->head_dim, 16};
     g.rope.n_q_heads = a->n_q_heads; g.rope.q_out = a->C16; g.rope.row_pos = a->row_pos; g.rope.row_slot = a->row_slot;
     g.rope.cos = a->cos; g.rope.sin = a->sin;
+    g.a_panels = a->a_panels != 0; g.c_panels = a->c_panels != 0;
     a->n_parts_out = ax::launch_gemm_block_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1538,7 +1573,17 @@ ax_status ax_dbg_read(ax_model* m, int which, void* host_dst, size_t bytes) {
     if (lo) which -= 10;
     if (which < 0 || which > 5 || (lo && !L.h_lo)) return fail(AX_ERR_INVALID, "bad buffer id");
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(host_dst, m->ws + off[which] + (lo ? len[which] : 0), std::min(bytes, len[which]), hipMemcpyDeviceToHost));
+    const char* src = m->ws + off[which] + (lo ? len[which] : 0);
+    HIP_TRY(hipMemcpy(host_dst, src, std::min(bytes, len[which]), hipMemcpyDeviceToHost));
+    const bool in_panels[6] = {false, false, false, m->panels.layers, m->panels.layers, m->panels.out};
+    if (in_panels[which]) {                                    // the last call's rows, as rows
+        const ax_model_config& c = m->cfg;
+        const int rows = m->panels.rows, K = which == 3 ? c.n_q_heads * c.head_dim : which == 4 ? c.d_ff : c.d_model;
+        std::vector<uint16_t> got((size_t)rows * K);
+        HIP_TRY(hipMemcpy(got.data(), src, got.size() * 2, hipMemcpyDeviceToHost));
+        const size_t n = std::min(bytes / 2, got.size());
+        for (size_t i = 0; i < n; ++i) ((uint16_t*)host_dst)[i] = got[(size_t)ax::act_index(true, (int)(i / K), (int)(i % K), rows, K)];
+    }
     return AX_OK;
 }
 

@@ -185,14 +185,34 @@ __device__ __forceinline__ void block_inv_rms_few(const GemmArgs& g, int first_r
     }
 }
 
+// The same with activations in panels, partial sums as [parts][rows]: a thread adds up a row (or, with twice as many threads as rows, half of one),
+// 16 loads in flight.  `rows` is the number of threads or half of it.
+__device__ __forceinline__ void block_inv_rms_panels(const GemmArgs& g, int first_row, int rows, float* s_inv) {
+    const int r = threadIdx.x & (rows - 1), gm = min(first_row + r, g.M - 1), groups = blockDim.x / rows;
+    float v = 0.f;
+    for (int p0 = threadIdx.x / rows; p0 < g.nparts; p0 += 16 * groups) {
+        float t[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) t[u] = g.ssq[(long long)min(p0 + u * groups, g.nparts - 1) * g.M + gm];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v += p0 + u * groups < g.nparts ? t[u] : 0.f;
+    }
+    if (groups > 1) {
+        if (threadIdx.x >= rows) s_inv[r] = v;
+        __syncthreads();
+        if (threadIdx.x < rows) v += s_inv[r];
+    }
+    if (threadIdx.x < rows) s_inv[r] = 1.0f / sqrtf(v / (float)g.d_norm + g.eps);
+}
+
 // ------------------------------------------------------------------------------ host interface between the GEMM files
 // Many-row GEMMs (k_gemm_block.hip): which tile shape and how many K slices, and the time the plan expects.
 struct BlockPlan { int shape, ks; float us; };
-BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
-float gemm_reduce_us(Epilogue epi, int M, int N, int ks);      // time of the kernel that adds up ks slabs (EPI_QKV, EPI_RESIDUAL)
+BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, bool panels, size_t ws_bytes);      // panels: A (and C16) in panels
+float gemm_reduce_us(Epilogue epi, int M, int N, int ks, bool panels);      // time of the kernel that adds up ks slabs (EPI_QKV, EPI_RESIDUAL)
 // What a whole residual GEMM costs the GEMM behind it: N / 64 or N / 32 partial sums of x^2 a row to read in every block's prologue, where
 // slabs added up leave a few (~3B at 1200 rows: O whole 40.9 us + gate / up 149.7, O in slices 39.1 + 143.6).
-float gemm_partials_us(int M);
+float gemm_partials_us(int M, bool panels);
 // a_rows must be NULL and N % 64 == 0; returns the partial sums per row it leaves, as launch_gemm_bf16.
 int launch_gemm_block(Epilogue epi, const GemmArgs& g, const BlockPlan& p, hipStream_t s);
 // Second halves of K-sliced GEMMs (k_gemm_bf16.hip): add the g.ksplit slabs of g.split_ws and run the epilogue.

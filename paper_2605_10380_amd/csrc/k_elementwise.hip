@@ -16,21 +16,46 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Embedding gather that also prepares the first RMSNorm of bf16-weight models: the fp16 copy
 // scaled by the norm gain and the row's sum of squares (in partial 0; the other partials are
 // zeroed so that the row looks like the output of a GEMM with `nparts` column blocks).
+// A thread takes eight columns at a time: one 16-byte load (the caller's tensors allowing), and 16-byte stores that are whole pieces of a
+// panel row.
 __global__ void embed_norm_kernel(const bf16* __restrict__ emb, const int* __restrict__ row_tok,
                                   const bf16* __restrict__ gain, float* __restrict__ x,
-                                  f16* __restrict__ a, long long a_lo_off, float* __restrict__ ssq, int nparts, int d) {
+                                  f16* __restrict__ a, long long a_lo_off, bool panels, float* __restrict__ ssq, int nparts, int d) {
+    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    typedef f16 f16x8 __attribute__((ext_vector_type(8)));
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
     __shared__ float part[4];
     const int r = blockIdx.x;
     const bf16* src = emb + (long long)row_tok[r] * d;
     float ss = 0.f;
-    for (int c = threadIdx.x; c < d; c += 256) {
-        const float v = (float)src[c];
-        x[(long long)r * d + c] = v;
-        const float av = split_value(v * (float)gain[c]);
-        const f16 hi = (f16)av;
-        a[(long long)r * d + c] = hi;
-        if (a_lo_off) a[(long long)r * d + c + a_lo_off] = (f16)(av - (float)hi);     // split activations: the rounding remainder
-        ss += v * v;
+    const bool aligned = (((size_t)emb | (size_t)gain) & 15) == 0;
+    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
+        bf16x8 e, gn;
+        if (aligned) {
+            e = *(const bf16x8*)(src + c);
+            gn = *(const bf16x8*)(gain + c);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                e[i] = src[c + i];
+                gn[i] = gain[c + i];
+            }
+        }
+        f32x4 xv[2];
+        f16x8 hi, lo;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float v = (float)e[i], av = split_value(v * (float)gn[i]);
+            xv[i >> 2][i & 3] = v;
+            hi[i] = (f16)av;
+            lo[i] = (f16)(av - (float)hi[i]);                // split activations: the rounding remainder
+            ss += v * v;
+        }
+        *(f32x4*)(x + (long long)r * d + c) = xv[0];
+        *(f32x4*)(x + (long long)r * d + c + 4) = xv[1];
+        f16* at = a + act_index(panels, r, c, gridDim.x, d);
+        *(f16x8*)at = hi;
+        if (a_lo_off) *(f16x8*)(at + a_lo_off) = lo;
     }
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
@@ -39,9 +64,9 @@ __global__ void embed_norm_kernel(const bf16* __restrict__ emb, const int* __res
         ssq[(long long)r * nparts + p] = p == 0 ? part[0] + part[1] + part[2] + part[3] : 0.f;
 }
 
-void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off,
+void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off, bool panels,
                        float* ssq, int nparts, int n_rows, int d, hipStream_t s) {
-    embed_norm_kernel<<<n_rows, 256, 0, s>>>((const bf16*)emb, row_tok, (const bf16*)gain, x, (f16*)a, a_lo_off, ssq,
+    embed_norm_kernel<<<n_rows, 256, 0, s>>>((const bf16*)emb, row_tok, (const bf16*)gain, x, (f16*)a, a_lo_off, panels, ssq,
                                              nparts, d);
 }
 

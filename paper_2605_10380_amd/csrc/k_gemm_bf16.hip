@@ -339,8 +339,57 @@ __global__ __launch_bounds__(256) void residual_reduce_kernel(GemmArgs g) {
         if (threadIdx.x == 0) g.ssq_out[(long long)m * gridDim.x + blockIdx.x] = (s_ss[0] + s_ss[1]) + (s_ss[2] + s_ss[3]);
     }
 }
+// The same with a in panels.  A block is a panel of 16 rows x COLS columns, 16 lanes to a row: a wavefront reads 256 bytes of four rows at a
+// time, all loads of a slab in flight together, and writes 64-byte pieces of the panel's runs.  Leaves ceil(N / COLS) sums a row.
+template <int COLS>
+__global__ __launch_bounds__(256) void residual_reduce_panels_kernel(GemmArgs g) {
+    constexpr int IT = COLS / 64;
+    const int m = blockIdx.y * 16 + (threadIdx.x >> 4), mc = min(m, g.M - 1);
+    const long long slab = (long long)g.M * g.N;
+    f32x4 xn[IT];
+    int n[IT];
+    long long o[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        n[it] = blockIdx.x * COLS + it * 64 + (threadIdx.x & 15) * 4;
+        o[it] = (long long)mc * g.N + min(n[it], g.N - 4);
+        xn[it] = *(const f32x4*)(g.Cf + o[it]);
+    }
+    for (int ks = 0; ks < g.ksplit; ++ks) {
+        f32x4 part[IT];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) part[it] = *(const f32x4*)(g.split_ws + ks * slab + o[it]);
+#pragma unroll
+        for (int it = 0; it < IT; ++it) xn[it] += part[it];
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        if (n[it] >= g.N) continue;
+        float h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            h[r] = xn[it][r] * (float)((const bf16*)g.gain_next)[n[it] + r];
+            ss += xn[it][r] * xn[it][r];
+        }
+        if (m < g.M) {
+            *(f32x4*)(g.Cf + o[it]) = xn[it];
+            store_split4((f16*)g.C16 + act_index(true, m, n[it], g.M, g.N), g.c_lo_off, h);
+        }
+    }
+#pragma unroll
+    for (int w = 8; w > 0; w >>= 1) ss += __shfl_xor(ss, w, 64);
+    if ((threadIdx.x & 15) == 0 && m < g.M) g.ssq_out[ssq_index(true, m, blockIdx.x, g.M, gridDim.x)] = ss;
+}
 // launches it; returns the partial sums per row it leaves
 int launch_residual_reduce(const GemmArgs& g, hipStream_t s) {
+    if (g.c_panels) {
+        const unsigned panels = (unsigned)(g.M + 15) / 16;
+        const int cols = (long long)panels * g.N >= 512 * 512 ? 512 : 256, parts = (g.N + cols - 1) / cols;
+        if (cols == 512) residual_reduce_panels_kernel<512><<<dim3((unsigned)parts, panels), 256, 0, s>>>(g);
+        else residual_reduce_panels_kernel<256><<<dim3((unsigned)parts, panels), 256, 0, s>>>(g);
+        return parts;
+    }
     const int parts = (g.N + REDUCE_COLS - 1) / REDUCE_COLS;
     residual_reduce_kernel<<<dim3((unsigned)parts, (unsigned)g.M), 256, 0, s>>>(g);
     return parts;
@@ -348,55 +397,74 @@ int launch_residual_reduce(const GemmArgs& g, hipStream_t s) {
 
 // Second half of a K-split QKV GEMM: sums the K-slice partials, applies 1 / rms of the row,
 // rotates q and k heads by the row's position and writes q to the activation buffer, k and v
-// into the row's KV slot.  grid (rows, ceil(items / 256)): a thread owns one (head, channel pair)
-// item of its row, so all its operands are requested in one go while wavefront 0 works out the
-// row's 1 / rms.
+// into the row's KV slot.  A thread owns four channel pairs of one head of one row, a block 1024 / (head_dim / 2) rows of
+// the head: for q and k neighbours are channels (whole runs of 128 or 256 bytes in, 64 or 128 out), for v rows, whose tokens lie side by
+// side in a page.  grid (blocks of rows, heads).
+template <int HD>
 __global__ __launch_bounds__(256) void qkv_reduce_rope_kernel(GemmArgs g) {
-    __shared__ float s_inv;
-    const int m = blockIdx.x, N = g.N;
+    constexpr int half = HD / 2, QUADS = half / 4, ROWS = 256 / QUADS, TPR = 256 / ROWS;      // TPR threads add up a row's sum of squares
+    __shared__ float s_inv[ROWS];
     const RopeArgs& ro = g.rope;
-    const int Hq = ro.n_q_heads, Hkv = ro.kv.n_kv_heads, hd = ro.kv.head_dim, half = hd >> 1;
-    const int n_items = (Hq + 2 * Hkv) * half;
-    const int it = min((int)(blockIdx.y * 256 + threadIdx.x), n_items - 1);
-    const bool live = blockIdx.y * 256 + threadIdx.x < n_items;
-    const int head = it / half, j = it - head * half;
-    const int pos = ro.row_pos[m], slot = ro.row_slot[m];
-    const long long slab = (long long)g.M * N;
-    const float* p = g.split_ws + (long long)m * N + head * hd + j;
-    float pa[SPLITK_MAX], pb[SPLITK_MAX];
-#pragma unroll
-    for (int ks = 0; ks < SPLITK_MAX; ++ks) {
-        pa[ks] = ks < g.ksplit ? p[ks * slab] : 0.f;
-        pb[ks] = ks < g.ksplit ? p[ks * slab + half] : 0.f;
+    const int N = g.N, M = g.M, Hq = ro.n_q_heads, Hkv = ro.kv.n_kv_heads, head = blockIdx.y;
+    const bool is_v = head >= Hq + Hkv;
+    const int row = is_v ? threadIdx.x % ROWS : threadIdx.x / QUADS, j = (is_v ? threadIdx.x / ROWS : threadIdx.x % QUADS) * 4;
+    const int m = blockIdx.x * ROWS + row, mc = min(m, M - 1);
+    const int pos = ro.row_pos[mc], slot = ro.row_slot[mc];
+    const long long slab = (long long)M * N;
+    const float* p = g.split_ws + (long long)mc * N + head * HD + j;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll 4
+    for (int ks = 0; ks < g.ksplit; ++ks) {
+        a += *(const f32x4*)(p + ks * slab);
+        b += *(const f32x4*)(p + ks * slab + half);
     }
-    const float c = ro.cos[(long long)pos * half + j], sg = ro.sin[(long long)pos * half + j];
-    if (threadIdx.x < 64) {
-        const float inv = g.ssq ? wave_inv_rms(g.ssq, m, g.nparts, g.d_norm, g.eps, threadIdx.x) : 1.0f;
-        if (threadIdx.x == 0) s_inv = inv;
+    f32x4 c = a, sn = a;
+    if (!is_v) {
+        c = *(const f32x4*)(ro.cos + (long long)pos * half + j);
+        sn = *(const f32x4*)(ro.sin + (long long)pos * half + j);
+    }
+    if (g.ssq) {
+        const int r = threadIdx.x / TPR, rm = min((int)blockIdx.x * ROWS + r, M - 1);
+        float v = 0.f;
+        for (int q = threadIdx.x % TPR; q < g.nparts; q += TPR) v += g.ssq[ssq_index(g.a_panels, rm, q, M, g.nparts)];
+#pragma unroll
+        for (int o = TPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (threadIdx.x % TPR == 0) s_inv[r] = 1.0f / sqrtf(v / (float)g.d_norm + g.eps);
+    } else if (threadIdx.x < ROWS) {
+        s_inv[threadIdx.x] = 1.0f;
     }
     __syncthreads();
-    if (!live) return;
-    float a = 0.f, b = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < SPLITK_MAX; ++ks) { a += pa[ks]; b += pb[ks]; }
-    a *= s_inv;
-    b *= s_inv;
+    if (m >= M) return;
+    const float inv = s_inv[row];
     f16* pool = (f16*)ro.kv.base;
-    if (head < Hq + Hkv) {
-        f16* dst = head < Hq ? (f16*)ro.q_out + ((long long)m * Hq + head) * hd
-                             : pool + ro.kv.plane(ro.layer, 0, head - Hq) + (long long)slot * hd;
+    a *= inv;
+    b *= inv;
+    if (!is_v) {
+        f16* dst = head < Hq ? (f16*)ro.q_out + ((long long)m * Hq + head) * HD
+                             : pool + ro.kv.plane(ro.layer, 0, head - Hq) + (long long)slot * HD;
         const long long lo_off = head < Hq ? g.c_lo_off : 0;      // q may be split; the cache holds one fp16 per entry
-        store_split(dst + j, lo_off, a * c - b * sg);
-        store_split(dst + j + half, lo_off, b * c + a * sg);
+        float va[4], vb[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            va[r] = a[r] * c[r] - b[r] * sn[r];
+            vb[r] = b[r] * c[r] + a[r] * sn[r];
+        }
+        store_split4(dst + j, lo_off, va);
+        store_split4(dst + j + half, lo_off, vb);
     } else {
-        f16* dst = pool + ro.kv.plane(ro.layer, 1, head - Hq - Hkv) + (long long)(slot >> 4) * 16 * hd + (slot & 15);
-        dst[(long long)j * 16] = (f16)a;
-        dst[(long long)(j + half) * 16] = (f16)b;
+        f16* dst = pool + ro.kv.plane(ro.layer, 1, head - Hq - Hkv) + (long long)(slot >> 4) * 16 * HD + (slot & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            dst[(long long)(j + r) * 16] = (f16)a[r];
+            dst[(long long)(j + r + half) * 16] = (f16)b[r];
+        }
     }
 }
 
 void launch_qkv_reduce(const GemmArgs& g, hipStream_t s) {
-    qkv_reduce_rope_kernel<<<dim3((unsigned)g.M, (unsigned)((g.N / 2 + 255) / 256)), 256, 0, s>>>(g);
+    const unsigned heads = (unsigned)(g.rope.n_q_heads + 2 * g.rope.kv.n_kv_heads);
+    if (g.rope.kv.head_dim == 64) qkv_reduce_rope_kernel<64><<<dim3((unsigned)(g.M + 31) / 32, heads), 256, 0, s>>>(g);
+    else qkv_reduce_rope_kernel<128><<<dim3((unsigned)(g.M + 15) / 16, heads), 256, 0, s>>>(g);
 }
 
 // Second half of a K-sliced SwiGLU GEMM: out[m, n] = fp16(silu(gate * inv) * (up * inv)) with gate
@@ -1273,7 +1341,7 @@ static bool use_skinny(int epi, int M, int N, int K) {
 //     block kernel, 512 padded rows, 108 us, 2 x 160 rows 86; at 576 rows 189 and 163; in hi + lo parts at 576 rows 310 and 285;
 //     above, where it needs two rounds, it falls behind: ~1B at 1536 rows 112 and 138, at 704 53 and 59).
 enum ManyRows { MANY_BLOCK, MANY_TILE, MANY_STREAM };
-struct ManyPlan { ManyRows kernel; BlockPlan block; int stream_tm; };
+struct ManyPlan { ManyRows kernel; BlockPlan block; int stream_tm; float us; };
 
 template <int EPI>
 static float tile_us(int M, int N, int K, bool split, size_t ws_bytes) {
@@ -1285,7 +1353,7 @@ static float tile_us(int M, int N, int K, bool split, size_t ws_bytes) {
     if (blocks > 256) return 1e30f;
     const auto& t = kTile[p.big][split];
     const float us = t.fixed + K / p.ks / 64 * (t.lo + (t.full - t.lo) * blocks / 256);
-    return us + (EPI == EPI_QKV || p.ks > 1 ? gemm_reduce_us((Epilogue)EPI, M, N, p.ks) : 6.4f + gemm_partials_us(M));
+    return us + (EPI == EPI_QKV || p.ks > 1 ? gemm_reduce_us((Epilogue)EPI, M, N, p.ks, false) : 6.4f + gemm_partials_us(M, false));
 }
 
 // SwiGLU streaming blocks of 32 tm rows x 128 columns of gate and of up, one on a CU at a time
@@ -1297,15 +1365,17 @@ static float stream_us(int M, int N, int K, bool split, int tm) {
 
 template <int EPI>
 static ManyPlan plan_many(int M, int N, int K, bool split, size_t ws_bytes) {
-    ManyPlan p{MANY_BLOCK, plan_gemm_block((Epilogue)EPI, M, N, K, split, ws_bytes), 0};
+    ManyPlan p{MANY_BLOCK, plan_gemm_block((Epilogue)EPI, M, N, K, split, false, ws_bytes), 0, 0.f};
+    p.us = p.block.us;
     if constexpr (EPI == EPI_QKV || EPI == EPI_RESIDUAL) {
-        if (M <= 512 && (EPI == EPI_RESIDUAL || (size_t)M * N * sizeof(float) <= ws_bytes) && tile_us<EPI>(M, N, K, split, ws_bytes) < p.block.us)
-            p.kernel = MANY_TILE;
+        if (M <= 512 && (EPI == EPI_RESIDUAL || (size_t)M * N * sizeof(float) <= ws_bytes)) {
+            const float us = tile_us<EPI>(M, N, K, split, ws_bytes);
+            if (us < p.us) { p.us = us; p.kernel = MANY_TILE; }
+        }
     } else if constexpr (EPI == EPI_SWIGLU) {
-        float best = p.block.us;
         for (int tm = 3; M <= 640 && tm <= (split ? 4 : 6); ++tm) {      // (a second ring of activations does not fit the registers of larger blocks)
             const float us = stream_us(M, N, K, split, tm);
-            if (us < best) { best = us; p.kernel = MANY_STREAM; p.stream_tm = tm; }
+            if (us < p.us) { p.us = us; p.kernel = MANY_STREAM; p.stream_tm = tm; }
         }
     }
     return p;
@@ -1325,6 +1395,7 @@ static void launch_swiglu_stream(const GemmArgs& g, int tm, hipStream_t s) {
 template <int EPI>
 static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
+    if (g.a_panels) return launch_gemm_block((Epilogue)EPI, g, plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, true, g.split_ws ? g.split_ws_bytes : 0), s);
     if (many_rows(M, N, g.a_rows != nullptr)) {
         const ManyPlan p = plan_many<EPI>(M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
         if (p.kernel == MANY_BLOCK) return launch_gemm_block((Epilogue)EPI, g, p.block, s);
@@ -1359,6 +1430,7 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     return launch_lds_tile<EPI>(g, s);
 }
 
+static GemmPlan block_plan(const BlockPlan& p) { return {"block", p.shape == 0 ? 256 : 128, p.shape == 2 ? 128 : 256, p.ks}; }
 template <int EPI>
 static GemmPlan many_rows_plan(int M, int N, int K, bool split, size_t ws_bytes) {
     const ManyPlan p = plan_many<EPI>(M, N, K, split, ws_bytes);
@@ -1368,7 +1440,7 @@ static GemmPlan many_rows_plan(int M, int N, int K, bool split, size_t ws_bytes)
             const TilePlan t = plan_tile<EPI>(M, N, K, ws_bytes);
             return {"tile", t.big ? 128 : 64, 128, t.ks};
         }
-    return {"block", p.block.shape == 0 ? 256 : 128, p.block.shape == 2 ? 128 : 256, p.block.ks};
+    return block_plan(p.block);
 }
 GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
     if (!many_rows(M, N, false)) return {"", 0, 0, 0};
@@ -1376,6 +1448,20 @@ GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_byte
     if (epi == EPI_RESIDUAL) return many_rows_plan<EPI_RESIDUAL>(M, N, K, split, ws_bytes);
     if (epi == EPI_SWIGLU) return many_rows_plan<EPI_SWIGLU>(M, N, K, split, ws_bytes);
     return many_rows_plan<EPI_QKV>(M, N, K, split, ws_bytes);
+}
+
+GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
+    return block_plan(plan_gemm_block(epi, M, N, K, split, true, ws_bytes));
+}
+
+// By the times that the plans expect: panels make the block kernel faster at every size, but only that kernel reads them, and to 640
+// rows the ones made for fewer rows are ahead of it on some GEMMs.
+bool gemm_layer_panels(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes) {
+    if (M <= 256) return false;
+    auto panels = [&](Epilogue epi, int N, int K) { return plan_gemm_block(epi, M, N, K, split, true, ws_bytes).us; };
+    const float rows = plan_many<EPI_QKV>(M, qkv, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, qdim, split, ws_bytes).us +
+                       plan_many<EPI_SWIGLU>(M, d_ff, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, d_ff, split, ws_bytes).us;
+    return panels(EPI_QKV, qkv, d_model) + panels(EPI_RESIDUAL, d_model, qdim) + panels(EPI_SWIGLU, d_ff, d_model) + panels(EPI_RESIDUAL, d_model, d_ff) < rows;
 }
 
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s) {

@@ -1,21 +1,26 @@
 // GEMMs of many rows (bf16-weight models): C = A[M,K] * W[N,K]^T on the fp16 matrix cores, both operands staged through LDS by
 // the memory pipeline itself (global_load_lds: no registers, no ds_write in between), blocks of up to 256 x 256 outputs.
 //
-// What bounds it: a CU takes ~20 bytes per clock out of L2 (64 lines of 128 B in flight over ~400 clocks), and 256 x 256 outputs
-// need 32 KB of operands per 32 k, 1024 clocks of its matrix cores - so ~64 % of the matrix rate is what the largest tile that fits the
-// registers can reach.  Counters (gate / up of the ~3B shape at 4096 rows; profiles/config5_block_kernel_counters.txt): matrix cores busy
-// 60 % of the cycles, 19.1 B per clock and CU, pending-request queue full half of the time, LDS instructions in a quarter of the cycles and
-// under 1 % of them in conflict, clock held at 1.79 GHz by power.
+// What bounds it: power.  With all compute units at work the clock sinks until the matrix cores' energy fits (8192 x 8192 x 8192: 1373 TFLOP/s
+// on random values, 1997 on zeros, the same instructions), so what counts is energy and idle clocks around the products.
+//   * 4 wavefronts of 128 x 128 outputs: a third fewer LDS reads per product than 8 of 128 x 64, whose reads and copies together also
+//     took every clock that LDS has.  One wavefront per SIMD has nobody to fill its gaps, so the order of its instructions is written
+//     out: one LDS read or copy at most between two products, 32 clocks each.  (4096 x 16384 x 2048, store of fp16: 264 us on 8
+//     wavefronts, 228 on 4; the same loop in the compiler's order was no faster than 8 wavefronts.)
+//   * A in panels: 16 rows x 32 k are 1 KB in one piece, in rows 16 half lines of 128 bytes.
 //   * Stages of 32 k, up to four in LDS, so that the copies of three steps are in flight: with two stages of 64 k the queue of outstanding
-//     lines ran dry between a stage's arrival and the issue of the next one (~1B gate / up, 4096 rows: 283 -> 264 us).
-//   * 8 wavefronts, two per SIMD.  4 wavefronts of 128 x 128 outputs need a third fewer LDS reads but were 5-15 % slower: one
-//     wavefront per SIMD leaves the matrix cores idle at every barrier.
+//     lines ran dry between a stage's arrival and the issue of the next one.
+//   * SwiGLU and QKV multiply transposed (C^T: a lane is a row, its registers neighbouring columns): 1 / rms is one value a lane, and eight
+//     columns leave as 16 bytes, which in panels are whole lines.
+//   * 1 / rms of the rows: a thread sums a row's partial sums, which panels keep [part][row].  (In rows, half a wavefront a row and a butterfly:
+//     SwiGLU of ~1B at 4096 rows 285 us a launch, so 239.)
 //   * Smaller tiles (128 x 256, 128 x 128) move 1.5x / 2x the operands per product; they are for launches that would leave CUs without a
-//     block (the planner at the end weighs tile and K-slice choices by measured times).
+//     block, and where two on a CU hide the epilogue (the planner at the end weighs tile and K-slice choices by measured times).
 #include "gemm_device.h"
 #include "lds_copy.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ax {
 
@@ -50,19 +55,61 @@ __device__ __forceinline__ void store_split2(f16* p, long long lo_off, f32x2 v) 
     if (lo_off) *(f16x2*)(p + lo_off) = (f16x2){(f16)(v[0] - (float)hi[0]), (f16)(v[1] - (float)hi[1])};
 }
 
+// f(0), f(1), .. f(N - 1) with the numbers as types (a loop this long is not unrolled, and accumulators indexed by its counter would go to memory).
+template <int N, class F>
+__device__ __forceinline__ void for_each(F f) {
+    if constexpr (N > 0) {
+        for_each<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
+// Two quads of columns (registers 8 p .. 8 p + 3 and + 4 .. + 7 of a transposed accumulator, packed to fp16) of one row, of which lanes l and
+// l + 32 hold four columns each: afterwards the lane holds all eight of quad 2 p + lane / 32, 16 bytes that lie together in memory.
+__device__ __forceinline__ u32x4 eight_columns(const f16x4 (&q)[2]) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 a = __builtin_bit_cast(u32x2, q[0]), b = __builtin_bit_cast(u32x2, q[1]);
+    u32x4 out;
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const auto t = __builtin_amdgcn_permlane32_swap(a[d], b[d], false, false);
+        out[d] = t[0];
+        out[2 + d] = t[1];
+    }
+    return out;
+}
+// Eight fp32 values of a lane (columns as above) -> fp16 at p, and their lo parts lo_off elements behind.
+__device__ __forceinline__ void store_eight(f16* p, long long lo_off, const float (&v)[8]) {
+    f16x4 hi[2], lo[2];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const float x = split_value(v[r]);
+        hi[r >> 2][r & 3] = (f16)x;
+        lo[r >> 2][r & 3] = (f16)(x - (float)hi[r >> 2][r & 3]);
+    }
+    const u32x4 h = eight_columns(hi);
+    if (p) *(u32x4*)p = h;
+    if (lo_off) {
+        const u32x4 l = eight_columns(lo);
+        if (p) *(u32x4*)(p + lo_off) = l;
+    }
+}
+
 // EPI: the epilogue (GemmArgs).  TM x TN tiles of 32 x 32 outputs per wavefront, WM x WN wavefronts, S stages in LDS.
 // SPLIT: split activations - hi and lo parts of A are staged and multiplied against the same B fragments.
 // SLICED: K is cut into g.ksplit slices over extra blocks; raw products go to slabs of g.split_ws.
 // Blocks are renumbered: XCD c (workgroups are dealt out round robin) takes the c-th eighth of the tiles, in groups of `group` row tiles
 // walked column by column, so that the ~32 tiles an XCD works on at a time share operands in its L2.
-template <int EPI, int TM, int TN, int WM, int WN, int S, bool SPLIT, bool SLICED>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
+template <int EPI, int TM, int TN, int WM, int WN, int S, int OCC, bool SPLIT, bool SLICED>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
+void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
     constexpr int NW = WM * WN, BM = WM * TM * 32, BN = WN * TN * 32, BK = 32, NA = SPLIT ? 2 : 1;
     constexpr int A_BYTES = NA * BM * 64, B_BYTES = BN * 64, STAGE = A_BYTES + B_BYTES;
     constexpr int LA = NA * BM / 16 / NW, LB = BN / 16 / NW, L = LA + LB;      // copies per wavefront and stage
     static_assert(NA * BM % (16 * NW) == 0 && BN % (16 * NW) == 0, "whole copies per wavefront");
-    static_assert(EPI != EPI_SWIGLU || TN == 2, "SwiGLU: one gate and one up tile per wavefront");
+    static_assert(TN % 2 == 0, "column tiles come in pairs: gate and up, the halves of a head, 64 columns of x");
     constexpr int OUT_N = EPI == EPI_SWIGLU ? BN / 2 : BN;
+    constexpr bool TRANSPOSED = !SLICED && (EPI == EPI_SWIGLU || EPI == EPI_QKV);      // accumulators hold C^T: a lane is a row of C
     __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
     __shared__ float s_inv[BM];
 
@@ -83,20 +130,31 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
     const int kspan = SLICED ? K / g.ksplit : K, kbase = kz * kspan;
 
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-    // copies of this wavefront: A units of 16 rows x 32 k (lane: row lane / 4, 16-byte slot lane % 4), B units of one chunk of a panel
-    // (1 KB as packed).  Slot s of row r holds k-group s ^ swz(r): see the operand reads.
+    // copies of this wavefront: A units of 16 rows x 32 k, B units of one chunk of a panel (1 KB as packed).
+    // A as rows: lane l copies slot l % 4 of row l / 4; slot s of row r holds k-group s ^ swz(r): see the operand reads.
+    // A in panels (act_at): the unit is a chunk, copied as it lies; rows a short last panel does not have are its last one again.
     auto swz = [](int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); };
-    const char* a_base = (const char*)g.A + ((long long)m0 * K + kbase) * 2;
     unsigned a_off[LA];
     const char* a_ptr[LA];
+    int a_step[LA];                                          // bytes from one stage to the next
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-        const int unit = wave * LA + i, part = unit / (BM / 16), row = (unit % (BM / 16)) * 16 + (lane >> 2);
-        a_off[i] = (unsigned)min(row, M - 1 - m0) * (unsigned)K * 2u + (unsigned)(((lane & 3) ^ swz(row)) * 16);
-        a_ptr[i] = a_base + (SPLIT && part ? g.a_lo_off * 2 : 0);
+        const int unit = wave * LA + i, part = unit / (BM / 16), u = unit % (BM / 16);
+        const char* base = (const char*)g.A + (SPLIT && part ? g.a_lo_off * 2 : 0);
+        if (g.a_panels) {
+            const int panel = min((m0 >> 4) + u, (M - 1) >> 4), rows = min(16, M - panel * 16);
+            a_step[i] = rows * 64;
+            a_ptr[i] = base + (long long)panel * 32 * K + (long long)(kbase >> 5) * a_step[i];
+            a_off[i] = (unsigned)((lane >> 4) * rows + min(lane & 15, rows - 1)) * 16u;
+        } else {
+            const int row = u * 16 + (lane >> 2);
+            a_step[i] = 64;
+            a_ptr[i] = base + ((long long)m0 * K + kbase) * 2;
+            a_off[i] = (unsigned)min(row, M - 1 - m0) * (unsigned)K * 2u + (unsigned)(((lane & 3) ^ swz(row)) * 16);
+        }
     }
     const char* b_ptr[LB];
-    const unsigned b_off = (unsigned)lane * 16;
+    unsigned b_off = (unsigned)lane * 16;
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
         const int pl = wave * LB + i;                                  // panel of the stage
@@ -104,13 +162,32 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
         const int panel = min((n0 >> 4) + (second ? pl - BN / 32 : pl), (N >> 4) - 1);
         b_ptr[i] = (const char*)(second ? g.W2 : g.W) + ((long long)panel * 16 * K + (long long)kbase * 16) * 2;
     }
-    auto load_stage = [&](int s, int buf) {
+    // copy i of this wavefront for the next stage not copied yet, into buffer `buf`.  The offsets move on in vector registers, one addition
+    // beside each copy of A and one for B: scalar pointers, advanced together, were 20 instructions in a row behind the last product.
+    auto copy = [&](int buf, int i) {
         const unsigned at = lds0 + buf * STAGE;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) copy_to_lds(a_ptr[i] + (long long)s * 64, a_off[i], at + (wave * LA + i) * 1024);
-#pragma unroll
-        for (int i = 0; i < LB; ++i) copy_to_lds(b_ptr[i] + (long long)s * 1024, b_off, at + A_BYTES + (wave * LB + i) * 1024);
+        if (i < LA) {
+            copy_to_lds(a_ptr[i], a_off[i], at + (wave * LA + i) * 1024);
+            a_off[i] += a_step[i];
+            asm volatile("" : "+v"(a_off[i]));               // (here, not with the others at the loop's end)
+        } else {
+            copy_to_lds(b_ptr[i - LA], b_off, at + A_BYTES + (wave * LB + i - LA) * 1024);
+            if (i == L - 1) b_off += 1024;
+        }
     };
+
+    const int nsteps = kspan / BK;
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nsteps)
+#pragma unroll
+            for (int i = 0; i < L; ++i) copy(s, i);
+    const bool inv_here = g.ssq && !SLICED;
+    if (inv_here) {
+        if (g.a_panels) block_inv_rms_panels(g, m0, BM, s_inv);
+        else if (g.nparts <= 4) block_inv_rms_few(g, m0, BM, s_inv);
+        else block_inv_rms<16>(g, m0, BM, s_inv);
+    }
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -119,99 +196,103 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int nsteps = kspan / BK;
-#pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-        if (s < nsteps) load_stage(s, s);
-    const bool inv_here = g.ssq && !SLICED;
-    if (inv_here) {
-        if (g.nparts <= 4) block_inv_rms_few(g, m0, BM, s_inv);
-        else block_inv_rms<4>(g, m0, BM, s_inv);
-    }
-
-    // operand reads.  A: row r, k-group kg at r * 64 + (kg ^ swz(r)) * 16 - at one k-group, eight rows in a row fall into all eight 16-byte
-    // columns of 128 bytes and sixteen into all sixteen of 256.  B: as packed, contiguous.
-    unsigned a_at[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) a_at[c] = (wm * TM * 32 + lrow) * 64 + ((2 * c + lg) ^ swz(lrow)) * 16;
-    // first panel of column tile j
-    const int half_tiles = EPI == EPI_QKV ? g.rope.kv.head_dim >> 6 : 1;      // QKV: 32-column tiles in half a head (1 or 2)
-    auto tile_panel = [&](int j) {
-        if (EPI == EPI_SWIGLU) return wn * 2 + j * (BN / 32);
-        if (EPI == EPI_QKV) return ((wn / half_tiles) * 2 * half_tiles + wn % half_tiles + j * half_tiles) * 2;   // j = 0, 1: the halves of a head
-        return (wn * TN + j) * 2;
-    };
-    unsigned b_at[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) b_at[j] = A_BYTES + (tile_panel(j) + (lrow >> 4)) * 1024 + lg * 256 + (lrow & 15) * 16;
-
-    // Fragments of the stage's two MFMA steps (16 k each) live in two register sets: the reads of the next step are issued ahead of the
-    // products of the current one.  A stage's second step reads ahead into the next stage, so that is where the stages change: by
-    // then every read of the current buffer has been issued, and (lgkmcnt) come back.
-    f16x8 fa[2][NA][TM], fb[2][TN];
-    auto read = [&](int set, const char* st, int c) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[set][j] = *(const f16x8*)(st + b_at[j] + c * 512);
-#pragma unroll
-        for (int p = 0; p < NA; ++p)
-#pragma unroll
-            for (int i = 0; i < TM; ++i) fa[set][p][i] = *(const f16x8*)(st + a_at[c] + p * BM * 64 + i * 2048);
-    };
-    auto multiply = [&](int set) {
-#pragma unroll
-        for (int p = 0; p < NA; ++p)
+    // the large tiles' accumulators stay in accumulation registers from here to the epilogue (left alone, the compiler moves all of them
+    // to ordinary ones and back between the loops)
+    auto pin = [&]() {
+        if constexpr (OCC == 1) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][p][i], fb[set][j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+        }
     };
-    constexpr int READS = NA * TM + TN, PRODUCTS = NA * TM * TN;
-    auto interleave = [&]() {                                // one product between two reads
+
+    // operand reads.  A as rows: row r, k-group kg at r * 64 + (kg ^ swz(r)) * 16 - at one k-group, eight rows in a row fall into all eight
+    // 16-byte columns of 128 bytes and sixteen into all sixteen of 256.  B, and A in panels: as packed, contiguous.
+    unsigned a_at[2];
 #pragma unroll
-        for (int k = 0; k < READS; ++k) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        }
-        if (PRODUCTS > READS) __builtin_amdgcn_sched_group_barrier(0x008, PRODUCTS - READS, 0);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int c = 0; c < 2; ++c)
+        a_at[c] = wm * TM * 2048 + (g.a_panels ? (lrow >> 4) * 1024 + (2 * c + lg) * 256 + (lrow & 15) * 16 : lrow * 64 + ((2 * c + lg) ^ swz(lrow)) * 16);
+    // column tile j of the wavefront, as a tile of the stage: j and j + 1 are gate and up, or the halves of a head
+    const int half_tiles = EPI == EPI_QKV ? g.rope.kv.head_dim >> 6 : 1;      // QKV: 32-column tiles in half a head (1 or 2)
+    auto tile_of = [&](int j) {
+        if (EPI == EPI_SWIGLU) return (j & 1) * (BN / 64) + wn * (TN / 2) + (j >> 1);
+        if (EPI == EPI_QKV && half_tiles == 2) return TN == 4 ? wn * 4 + (j >> 1) + (j & 1) * 2 : (wn >> 1) * 4 + (wn & 1) + j * 2;
+        return wn * TN + j;
     };
-    auto stage = [&](int s) { return smem + (s % S) * STAGE; };
+    unsigned b_at[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b_at[j] = A_BYTES + (tile_of(j) * 2 + (lrow >> 4)) * 1024 + lg * 256 + (lrow & 15) * 16;
 
-    auto first_step = [&](int s) {
-        __builtin_amdgcn_sched_barrier(0);
-        read(1, stage(s), 1);
-        multiply(0);
-        interleave();
+    // A stage is two MFMA steps of 16 k; the fragments of the step being multiplied and of the one after it live in two register sets.
+    // One wavefront per SIMD: what it issues is in this order and nothing fills a gap, so reads (and, in a stage's first step, the
+    // copies of the stage S - 1 ahead) go one by one between products, 32 clocks apart.  A stage's second step reads from the
+    // next stage, so that is where the stages change: by then the reads of the current one have come back (lgkmcnt).
+    f16x8 fb[2][TN], fa[2][NA * TM];
+    constexpr int READS = NA * TM + TN, PRODUCTS = NA * TM * TN;
+    auto read = [&](int set, const char* st, int c, int i) {
+        if (i < TN) fb[set][i] = *(const f16x8*)(st + b_at[i] + c * 512);
+        else fa[set][i - TN] = *(const f16x8*)(st + a_at[c] + (i - TN) / TM * BM * 64 + (i - TN) % TM * 2048);
     };
-    if (nsteps >= S) wait_copies_and_sync<(S - 2) * L>(); else wait_copies_and_sync<0>();
-    read(0, stage(0), 0);
-    if (S - 1 < nsteps) load_stage(S - 1, S - 1);
-    int s = 0;
-    for (; s + S < nsteps; ++s) {
-        first_step(s);
-        wait_copies_and_sync<(S - 2) * L>();                 // stage s + 1 has landed for everybody, nobody reads stage s any more
-        load_stage(s + S, s % S);
-        read(0, stage(s + 1), 0);
-        multiply(1);
-        interleave();
+    auto product = [&](int set, int q) {                     // columns back and forth: every product keeps one operand of the one before
+        const int p = q / (TM * TN), i = q / TN % TM, j = i & 1 ? TN - 1 - q % TN : q % TN;
+        if constexpr (TRANSPOSED) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[set][j], fa[set][p * TM + i], acc[i][j], 0, 0, 0);
+        else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][p * TM + i], fb[set][j], acc[i][j], 0, 0, 0);
+    };
+    auto step = [&](auto with_copies, int set, const char* next, int c, int copy_buf) {     // products of `set`, reads of the other one, copies
+        constexpr bool COPIES = decltype(with_copies)::value;
+#pragma unroll
+        for (int q = 0; q < PRODUCTS; ++q) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (q < READS) read(set ^ 1, next, c, q);
+            if constexpr (COPIES) {
+#pragma unroll
+                for (int i = 0; i < L; ++i)
+                    if ((2 * i + 1) * PRODUCTS / (2 * L) == q) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        copy(copy_buf, i);
+                    }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            product(set, q);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    static_assert(READS <= PRODUCTS, "a read per product");
+    constexpr std::true_type copies{};
+    constexpr std::false_type no_copies{};
+    auto after = [](int buf) { return buf + 1 == S ? 0 : buf + 1; };
+
+    pin();
+    if (nsteps >= S - 1) wait_copies_and_sync<(S - 2) * L>(); else wait_copies_and_sync<0>();
+#pragma unroll
+    for (int i = 0; i < READS; ++i) read(0, smem, 0, i);
+    __builtin_amdgcn_s_waitcnt(0xc07f);                      // (with a scalar load still out, the loop's first product would wait for every read)
+    __builtin_amdgcn_sched_barrier(0);
+    int s = 0, buf = 0, done = S - 1;                        // done: the buffer of step s - 1, which nobody reads any more
+    for (; s + S - 1 < nsteps; ++s) {
+        step(copies, 0, smem + buf * STAGE, 1, done);
+        done = buf;
+        buf = after(buf);
+        wait_copies_and_sync<(S - 2) * L>();                 // step s + 1 has landed for everybody, step s has been read
+        step(no_copies, 1, smem + buf * STAGE, 0, 0);
     }
+    pin();
     for (; s < nsteps; ++s) {
-        first_step(s);
-        if (s + 1 < nsteps) {
-            wait_copies_and_sync<0>();
-            read(0, stage(s + 1), 0);
-        }
-        multiply(1);
+        step(no_copies, 0, smem + buf * STAGE, 1, 0);
+        buf = after(buf);
+        wait_copies_and_sync<0>();
+        step(no_copies, 1, smem + buf * STAGE, 0, 0);        // (the last one reads a buffer nobody needs, and its values go unused)
     }
+    pin();
 
+    // products as they are (C): register r of a lane is row row_of(i, r), column col_of(j)
     auto row_of = [&](int i, int r) { return (wm * TM + i) * 32 + (r >> 2) * 8 + lg * 4 + (r & 3); };
     const bool odd = lane & 1;
-    auto col_of = [&](int j) { return n0 + (EPI == EPI_SWIGLU ? wn * 32 : tile_panel(j) * 16) + lrow; };
+    auto col_of = [&](int j) { return n0 + tile_of(j) * 32 + lrow; };
 
     if constexpr (SLICED) {                                  // raw products of this K slice: its own slab
-        const long long ld = EPI == EPI_SWIGLU ? 2 * N : N;
-        float* __restrict__ C = g.split_ws + (long long)kz * M * ld;
+        float* __restrict__ C = g.split_ws + (long long)kz * M * N;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -219,7 +300,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     const int m = m0 + row_of(i, r), n = col_of(j);
-                    if (m < M && n < N) C[m * ld + (EPI == EPI_SWIGLU ? j * N : 0) + n] = acc[i][j][r];
+                    if (m < M && n < N) C[(long long)m * N + n] = acc[i][j][r];
                 }
     } else if constexpr (EPI == EPI_STORE_F32) {
 #pragma unroll
@@ -234,108 +315,110 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
                     if (m < M && n < N) g.Cf[(long long)m * N + n] = acc[i][j][r] * inv;
                 }
             }
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        f16* __restrict__ out = (f16*)g.C16;
-        const int n = col_of(0) & ~1;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                float h[2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float inv = g.ssq ? s_inv[row_of(i, r + q)] : 1.0f, ga = acc[i][0][r + q] * inv;
-                    h[q] = silu_lean(ga) * (acc[i][1][r + q] * inv);
-                }
-                const int m = m0 + row_of(i, r + odd);
-                const f32x2 v = pair_of_columns(h[0], h[1], odd);
-                if (m < M && n < N) store_split2(out + (long long)m * N + n, g.c_lo_off, v);
-            }
-    } else if constexpr (EPI == EPI_RESIDUAL) {              // N % 64 == 0: a wavefront's columns are all there or none of them
+    } else if constexpr (EPI == EPI_RESIDUAL) {              // N % 64 == 0: a pair of column tiles is there or it is not
         f16* __restrict__ a16 = (f16*)g.C16;
         float gain[TN];
-        const bool live_n = col_of(0) < N;
 #pragma unroll
         for (int j = 0; j < TN; ++j) gain[j] = g.gain_next ? (float)((const bf16*)g.gain_next)[min(col_of(j), N - 1)] : 0.f;
+        for_each<TM>([&](auto i_) {
+            for_each<TN / 2>([&](auto jp_) {
+                constexpr int i = decltype(i_)::value, jp = 2 * decltype(jp_)::value;
+                const bool live_n = col_of(jp) < N;
+                float xv[2][16], ss[16];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            float xv[TN][16], ss[16];
+                for (int r = 0; r < 16; ++r)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
+                    for (int j = 0; j < 2; ++j) xv[j][r] = g.Cf[(long long)min(m0 + row_of(i, r), M - 1) * N + min(col_of(jp + j), N - 1)];
 #pragma unroll
-                for (int j = 0; j < TN; ++j) xv[j][r] = g.Cf[(long long)min(m0 + row_of(i, r), M - 1) * N + min(col_of(j), N - 1)];
+                for (int r = 0; r < 16; ++r) {
+                    const int m = m0 + row_of(i, r);
+                    ss[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = m0 + row_of(i, r);
-                ss[r] = 0.f;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    xv[j][r] += acc[i][j][r];
-                    ss[r] += xv[j][r] * xv[j][r];
-                    if (m < M && live_n) g.Cf[(long long)m * N + col_of(j)] = xv[j][r];
-                }
-            }
-            if (g.gain_next) {
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    const int m = m0 + row_of(i, r + odd);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const f32x2 v = pair_of_columns(xv[j][r] * gain[j], xv[j][r + 1] * gain[j], odd);
-                        if (m < M && live_n) store_split2(a16 + (long long)m * N + (col_of(j) & ~1), g.c_lo_off, v);
+                    for (int j = 0; j < 2; ++j) {
+                        xv[j][r] += acc[i][jp + j][r];
+                        ss[r] += xv[j][r] * xv[j][r];
+                        if (m < M && live_n) g.Cf[(long long)m * N + col_of(jp + j)] = xv[j][r];
                     }
                 }
-            }
-            if (g.gain_next) {                               // partial sums of squares over the wavefront's TN * 32 columns
-                const float t = rows16_sum(ss, lane);
-                const int m = m0 + row_of(i, lrow >> 1);
-                if ((lrow & 1) == 0 && m < M && live_n) g.ssq_out[(long long)m * (N / (TN * 32)) + n0 / (TN * 32) + wn] = t;
+                if (g.gain_next) {
+#pragma unroll
+                    for (int r = 0; r < 16; r += 2) {
+                        const int m = m0 + row_of(i, r + odd);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const f32x2 v = pair_of_columns(xv[j][r] * gain[jp + j], xv[j][r + 1] * gain[jp + j], odd);
+                            if (m < M && live_n) store_split2(a16 + act_index(g.c_panels, m, col_of(jp + j) & ~1, M, N), g.c_lo_off, v);
+                        }
+                    }
+                    const float t = rows16_sum(ss, lane);    // partial sums of squares over the 64 columns
+                    const int m = m0 + row_of(i, lrow >> 1);
+                    const int part = (n0 + tile_of(jp) * 32) / 64;
+                    if ((lrow & 1) == 0 && m < M && live_n) g.ssq_out[ssq_index(g.c_panels, m, part, M, N / 64)] = t;
+                }
+            });
+        });
+    } else if constexpr (EPI == EPI_SWIGLU) {                // C^T: a lane is row lrow of tile i, registers are columns (r / 4) * 8 + lg * 4 + r % 4
+        f16* __restrict__ out = (f16*)g.C16;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = (wm * TM + i) * 32 + lrow, m = m0 + row;
+            const float inv = g.ssq ? s_inv[row] : 1.0f;
+#pragma unroll
+            for (int j = 0; j < TN; j += 2) {
+                const int nt = n0 + tile_of(j) * 32;
+                if (nt >= N) continue;
+#pragma unroll
+                for (int r = 0; r < 16; r += 8) {
+                    float h[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) h[q] = silu_lean(acc[i][j][r + q] * inv) * (acc[i][j + 1][r + q] * inv);
+                    store_eight(m < M ? out + act_index(g.c_panels, m, nt + r * 2 + lg * 8, M, N) : nullptr, g.c_lo_off, h);
+                }
             }
         }
-    } else {                                                 // EPI_QKV: tiles j = 0, 1 are the two halves of 32 rotary pairs
+    } else {                                                 // EPI_QKV, C^T: tiles j and j + 1 are the two halves of 32 rotary pairs
         const RopeArgs& ro = g.rope;
         const int hd = ro.kv.head_dim, half = hd >> 1, Hq = ro.n_q_heads, Hkv = ro.kv.n_kv_heads;
-        const int n = col_of(0), head = n / hd, ch = n - head * hd;          // head: wavefront-uniform
         f16* pool = (f16*)ro.kv.base;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            float cs[16], sn[16];
-            int slot[16];
+            const int row = (wm * TM + i) * 32 + lrow, m = m0 + row, mc = min(m, M - 1);
+            const float inv = g.ssq ? s_inv[row] : 1.0f;
+            const int slot = ro.row_slot[mc];
+            const long long angle = (long long)ro.row_pos[mc] * half;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = min(m0 + row_of(i, r), M - 1);
-                slot[r] = ro.row_slot[m];
-                const long long ao = (long long)ro.row_pos[m] * half + ch;
-                cs[r] = ro.cos[ao];
-                sn[r] = ro.sin[ao];
-            }
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                float a[2], b[2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float inv = g.ssq ? s_inv[row_of(i, r + q)] : 1.0f;
-                    a[q] = acc[i][0][r + q] * inv;
-                    b[q] = acc[i][1][r + q] * inv;
-                }
+            for (int j = 0; j < TN; j += 2) {
+                const int nt = n0 + tile_of(j) * 32, head = nt / hd, ch0 = nt - head * hd;      // wavefront-uniform
+                if (nt >= N) continue;
                 if (head < Hq + Hkv) {
-                    const f32x2 v0 = pair_of_columns(a[0] * cs[r] - b[0] * sn[r], a[1] * cs[r + 1] - b[1] * sn[r + 1], odd);
-                    const f32x2 v1 = pair_of_columns(b[0] * cs[r] + a[0] * sn[r], b[1] * cs[r + 1] + a[1] * sn[r + 1], odd);
-                    const int m = m0 + row_of(i, r + odd);
-                    if (m >= M || n >= N) continue;
                     f16* dst = head < Hq ? (f16*)ro.q_out + ((long long)m * Hq + head) * hd
-                                         : pool + ro.kv.plane(ro.layer, 0, head - Hq) + (long long)(odd ? slot[r + 1] : slot[r]) * hd;
+                                         : pool + ro.kv.plane(ro.layer, 0, head - Hq) + (long long)slot * hd;
                     const long long lo_off = head < Hq ? g.c_lo_off : 0;     // q may be split; the cache holds one fp16 per entry
-                    store_split2(dst + (ch & ~1), lo_off, v0);
-                    store_split2(dst + (ch & ~1) + half, lo_off, v1);
-                } else {
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        if (m0 + row_of(i, r + q) >= M || n >= N) continue;
-                        const int sl = slot[r + q];
-                        f16* dst = pool + ro.kv.plane(ro.layer, 1, head - Hq - Hkv) + (long long)(sl >> 4) * 16 * hd + (sl & 15);
-                        dst[(long long)ch * 16] = (f16)a[q];
-                        dst[(long long)(ch + half) * 16] = (f16)b[q];
+                    for (int r = 0; r < 16; r += 8) {
+                        float va[8], vb[8];
+#pragma unroll
+                        for (int q4 = 0; q4 < 8; q4 += 4) {
+                            const int ch = ch0 + (r + q4) * 2 + lg * 4;
+                            const f32x4 cs = *(const f32x4*)(ro.cos + angle + ch), sn = *(const f32x4*)(ro.sin + angle + ch);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const float a = acc[i][j][r + q4 + q] * inv, b = acc[i][j + 1][r + q4 + q] * inv;
+                                va[q4 + q] = a * cs[q] - b * sn[q];
+                                vb[q4 + q] = b * cs[q] + a * sn[q];
+                            }
+                        }
+                        f16* at = m < M ? dst + ch0 + r * 2 + lg * 8 : nullptr;
+                        store_eight(at, lo_off, va);
+                        store_eight(at ? at + half : nullptr, lo_off, vb);
+                    }
+                } else if (m < M) {
+                    f16* dst = pool + ro.kv.plane(ro.layer, 1, head - Hq - Hkv) + (long long)(slot >> 4) * 16 * hd + (slot & 15);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int ch = ch0 + (r >> 2) * 8 + lg * 4 + (r & 3);
+                        dst[(long long)ch * 16] = (f16)(acc[i][j][r] * inv);
+                        dst[(long long)(ch + half) * 16] = (f16)(acc[i][j + 1][r] * inv);
                     }
                 }
             }
@@ -344,40 +427,50 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_block_kernel(GemmArgs g, in
 }
 
 // ------------------------------------------------------------------------------ planning
-// Tile shapes and their times in microseconds, fitted (to 4 %) to the four GEMMs of seven decoder layers (d_model 2048-5120, plain and split
-// activations) at 27 row counts from 257 to 4096, every shape and slice count: over these the plan's choice is 0.2-0.7 % off the
-// fastest.  A block's step is 32 k.
+// 128 x 256 blocks of plain activations, more of them than CUs: two on a CU (three stages of LDS each), so that one's epilogue runs under the
+// other's products (SwiGLU, ~1B at 4096 rows: 256 x 256 blocks 285 us, these 260; QKV, ~3B at 4666 rows, one on a CU 171, these 150).
+// With no more than a CU each the fourth stage is worth more (2048 x 8192 at 4096 rows: 118 us, with three stages 127).
+static bool two_on_a_cu(long long blocks, bool split) { return blocks > 256 && !split; }
+
+// Tile shapes and their times in microseconds, with A in rows and in panels, fitted to the four GEMMs of decoder layers (d_model 2048-5120 and
+// 2048-4096) at 27 and 21 row counts from 257 to 4666, every shape and slice count.  A block's step is 32 k.
 struct BlockShape {
     int bm, bn, capacity;             // capacity: blocks that run at once
-    float epilogue;                   // a fused epilogue, as a share of the 256 x 256 block's
+    float end_swiglu, end_other, end_sliced;      // fused epilogues; raw products to a slab
     struct Times {
-        float lo, half, full;         // a step with few blocks at work, with one on every CU (128 x 128: two run on a CU), at capacity
+        float lo, half, full;         // a step with few blocks at work, with one on every CU (two run on a CU), at capacity
         float fixed;                  // a block's prologue and end
         float padding;                // share of the time that rows past M cost (they re-read the last row: L2 hits)
         float tail;                   // what a partial round behind whole ones takes of its time alone
     } plain, split;
 };
-static constexpr BlockShape kShapes[] = {
-    {256, 256, 256, 1.00f, {0.54f, 0.f, 0.836f, 3.0f, 0.79f, 1.f}, {0.97f, 0.f, 1.62f, 3.7f, 0.87f, 1.f}},
-    {128, 256, 256, 0.49f, {0.41f, 0.f, 0.505f, 2.4f, 0.44f, 1.f}, {0.49f, 0.f, 0.836f, 2.9f, 0.74f, 1.f}},
-    {128, 128, 512, 0.38f, {0.257f, 0.321f, 0.58f, 2.75f, 0.42f, 0.85f}, {0.416f, 0.576f, 0.984f, 2.3f, 0.53f, 0.95f}},
-};
+static constexpr int kBlockShapes = 4;                       // 3: 128 x 256, two on a CU with three stages each (plain activations)
+static constexpr BlockShape kShapes[2][kBlockShapes] = {
+    {{256, 256, 256, 11.f, 27.f, 0.f, {0.54f, 0.f, 0.836f, 3.0f, 0.79f, 1.f}, {0.97f, 0.f, 1.62f, 3.7f, 0.87f, 1.f}},
+     {128, 256, 256, 5.4f, 13.2f, 0.f, {0.41f, 0.f, 0.505f, 2.4f, 0.44f, 1.f}, {0.49f, 0.f, 0.836f, 2.9f, 0.74f, 1.f}},
+     {128, 128, 512, 0.f, 10.3f, 0.f, {0.257f, 0.321f, 0.58f, 2.75f, 0.42f, 0.85f}, {0.416f, 0.576f, 0.984f, 2.3f, 0.53f, 0.95f}},
+     {128, 256, 512, 0.f, 0.f, 0.f, {}, {}}},
+    {{256, 256, 256, 1.6f, 14.f, 4.3f, {0.419f, 0.f, 0.755f, 6.2f, 0.97f, 0.98f}, {0.809f, 0.f, 1.538f, 4.8f, 0.94f, 0.90f}},
+     {128, 256, 256, 3.0f, 7.5f, 1.8f, {0.278f, 0.f, 0.411f, 5.6f, 0.95f, 0.77f}, {0.42f, 0.f, 0.738f, 6.5f, 0.91f, 0.95f}},
+     {128, 128, 512, 0.f, 1.5f, 1.1f, {0.222f, 0.27f, 0.485f, 3.9f, 0.71f, 0.87f}, {0.361f, 0.479f, 0.932f, 1.f, 0.77f, 0.99f}},
+     {128, 256, 512, 0.f, 0.2f, 3.5f, {0.268f, 0.468f, 0.877f, 2.8f, 0.57f, 0.98f}, {}}}};
 
 // QKV slabs much beyond the L2s are slow to add up (the K and V of the sum are scattered into pages): 5120 x 7168 at 3072 rows, two slices
 // of 88 MB, 311 us, whole 251.  (Residual slabs pay up to 280 MB: 13824 x 5120 at 3520 rows, four slices 542 us, whole 641.)
 static constexpr size_t kMaxQkvSlabs = 96u << 20;
 
-float gemm_reduce_us(Epilogue epi, int M, int N, int ks) {
+float gemm_reduce_us(Epilogue epi, int M, int N, int ks, bool panels) {
     const float mb = M * (float)N * 4e-6f;
-    return epi == EPI_QKV ? 4.7f + (0.287f * ks + 0.306f) * mb : 3.f + (0.371f * ks + 0.226f) * mb;
+    if (epi == EPI_QKV) return panels ? 1.9f + (0.141f * ks + 0.15f) * mb : 4.7f + (0.287f * ks + 0.306f) * mb;
+    return panels ? 2.4f + (0.145f * ks + 0.344f) * mb : 3.f + (0.371f * ks + 0.226f) * mb;
 }
 
-float gemm_partials_us(int M) { return std::min(4e-3f * M, 7.f); }
+float gemm_partials_us(int M, bool panels) { return panels ? std::min(1e-3f * M, 2.f) : std::min(4e-3f * M, 7.f); }
 
-BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
+BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, bool panels, size_t ws_bytes) {
     BlockPlan best{-1, 1, 0.f};
-    for (int c = 0; c < 3; ++c) {
-        const BlockShape& s = kShapes[c];
+    for (int c = 0; c < (panels && !split ? 4 : 3); ++c) {
+        const BlockShape& s = kShapes[panels][c];
         const BlockShape::Times& t = split ? s.split : s.plain;
         const int on = epi == EPI_SWIGLU ? s.bn / 2 : s.bn, gy = (M + s.bm - 1) / s.bm;
         if (epi == EPI_SWIGLU && c == 2) continue;           // gate and up of 64 columns: not built
@@ -386,8 +479,9 @@ BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t 
                            (size_t)ks * M * N * sizeof(float) > (epi == EPI_QKV ? std::min(ws_bytes, kMaxQkvSlabs) : ws_bytes)))
                 continue;
             const long long blocks = (long long)((N + on - 1) / on) * gy * ks, rounds = blocks / s.capacity, rest = blocks % s.capacity;
-            // (QKV: 2 us less than fitted - in a model the residual GEMM before it is mostly sliced, which leaves fewer partial sums of x^2 to read)
-            const float steps = K / ks / 32, end = t.fixed + (ks > 1 ? 0.f : s.epilogue * (epi == EPI_SWIGLU ? 11.f : 27.f) - (epi == EPI_QKV ? 2.f : 0.f));
+            if (panels && !split && (c == 1 || c == 3) && two_on_a_cu(blocks, split) != (c == 3)) continue;
+            // (QKV with A in rows: 2 us less than fitted - in a model the residual GEMM before it is mostly sliced, which leaves fewer partial sums)
+            const float steps = K / ks / 32, end = t.fixed + (ks > 1 ? s.end_sliced : (epi == EPI_SWIGLU ? s.end_swiglu : s.end_other) - (epi == EPI_QKV && !panels ? 2.f : 0.f));
             float us = rounds * (t.full * steps + end);
             if (rest) {
                 const float step = s.capacity == 256 ? t.lo + (t.full - t.lo) * rest / 256
@@ -395,24 +489,27 @@ BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, size_t 
                 us += (step * steps + end) * (rounds ? t.tail : 1.f);
             }
             us *= t.padding + (1.f - t.padding) * M / (gy * s.bm);
-            us += ks > 1 ? gemm_reduce_us(epi, M, N, ks) : epi == EPI_RESIDUAL ? gemm_partials_us(M) : 0.f;
+            us += ks > 1 ? gemm_reduce_us(epi, M, N, ks, panels) : epi == EPI_RESIDUAL ? gemm_partials_us(M, panels) : 0.f;
             if (best.shape < 0 || us < best.us) best = {c, ks, us};
         }
     }
     return best;
 }
 
-template <int EPI, int TM, int TN, int WM, int WN, int S, bool SPLIT, bool SLICED>
+template <int EPI, int TM, int TN, int WM, int WN, int S, int OCC, bool SPLIT, bool SLICED>
 static void launch_tiles(const GemmArgs& g, hipStream_t s) {
     constexpr int BM = WM * TM * 32, ON = EPI == EPI_SWIGLU ? WN * TN * 16 : WN * TN * 32;
     const int gx = (g.N + ON - 1) / ON, gy = (g.M + BM - 1) / BM;
-    gemm_block_kernel<EPI, TM, TN, WM, WN, S, SPLIT, SLICED><<<gx * gy * (SLICED ? g.ksplit : 1), 64 * WM * WN, 0, s>>>(g, gx, gy, gy < 8 ? gy : 8);
+    gemm_block_kernel<EPI, TM, TN, WM, WN, S, OCC, SPLIT, SLICED><<<gx * gy * (SLICED ? g.ksplit : 1), 64 * WM * WN, 0, s>>>(g, gx, gy, gy < 8 ? gy : 8);
 }
 template <int EPI, bool SPLIT, bool SLICED>
 static void launch_shape(const GemmArgs& g, int shape, hipStream_t s) {
-    if (shape == 0) launch_tiles<EPI, 4, 2, 2, 4, SPLIT ? 3 : 4, SPLIT, SLICED>(g, s);
-    else if (shape == 1) launch_tiles<EPI, 2, 2, 2, 4, 4, SPLIT, SLICED>(g, s);
-    else if constexpr (EPI != EPI_SWIGLU) launch_tiles<EPI, 2, 2, 2, 2, SPLIT ? 3 : 4, SPLIT, SLICED>(g, s);
+    if (shape == 0) launch_tiles<EPI, 4, 4, 2, 2, SPLIT ? 3 : 4, 1, SPLIT, SLICED>(g, s);
+    else if (shape == 1) launch_tiles<EPI, 2, 4, 2, 2, 4, 1, SPLIT, SLICED>(g, s);
+    else if (shape == 3) {
+        if constexpr (!SPLIT) launch_tiles<EPI, 2, 4, 2, 2, 3, 2, false, SLICED>(g, s);
+    }
+    else if constexpr (EPI != EPI_SWIGLU) launch_tiles<EPI, 2, 2, 2, 2, SPLIT ? 3 : 4, 2, SPLIT, SLICED>(g, s);
 }
 
 template <int EPI>
@@ -446,7 +543,8 @@ int launch_gemm_block(Epilogue epi, const GemmArgs& g, const BlockPlan& p, hipSt
 }
 
 int launch_gemm_block_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s) {
-    return launch_gemm_block(epi, g, {rows == 256 ? 0 : cols == 256 ? 1 : 2, slices, 0.f}, s);
+    const int out = epi == EPI_SWIGLU ? cols / 2 : cols, blocks = (g.N + out - 1) / out * ((g.M + rows - 1) / rows) * slices;
+    return launch_gemm_block(epi, g, {rows == 256 ? 0 : cols == 128 ? 2 : two_on_a_cu(blocks, g.a_lo_off != 0) ? 3 : 1, slices, 0.f}, s);
 }
 
 }  // namespace ax

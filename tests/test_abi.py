@@ -139,3 +139,26 @@ def test_extend_rejects_bad_arguments_before_any_launch():
     assert B.ax_kv_len(kv) == 0
     B.ax_kv_free(kv)
     B.ax_pool_destroy(pool)
+
+
+def test_panel_plans_are_launchable():
+    """Plans of GEMMs whose activations lie in panels: a block that is built and K slices that are whole, long enough and fit the scratch.
+    Calls of up to 256 rows never keep panels."""
+    rng = np.random.default_rng(7)
+    seen = set()
+    for _ in range(6000):
+        epi, split = int(rng.integers(0, 4)), bool(rng.integers(0, 2))
+        M, N, K = int(np.exp(rng.uniform(np.log(257), np.log(6000)))), 64 * int(rng.integers(1, 260)), 64 * int(rng.integers(1, 260))
+        ws = int(rng.choice([0, M * N * 4, 3 * M * N * 4 - 1, 32 * M * N]))
+        rows, cols, slices = B.ax_dbg_panel_plan(epi, M, N, K, split, ws)
+        seen.add((epi, rows, cols, slices > 1))
+        assert (rows, cols) in ((256, 256), (128, 256)) + (((128, 128),) if epi != 2 else ())
+        assert 1 <= slices <= 4 and (slices == 1 or (epi in (1, 3) and slices * M * N * 4 <= ws and K % (32 * slices) == 0 and K // slices >= 512))
+    assert len(seen) >= 14, seen
+    for M, N in ((256, 2048), (512, 2064)):
+        with pytest.raises(B.AxError):
+            B.ax_dbg_panel_plan(1, M, N, 2048)
+    for name in ("1b", "3b", "8b"):
+        cfg = B.make_config(I.SHAPES[name], 8192, 4096)
+        assert [B.ax_dbg_layer_panels(cfg, r) for r in (1, 16, 17, 64, 256, 1024, 4096)] == [False] * 5 + [True, True]
+    assert not B.ax_dbg_layer_panels(B.make_config(I.SHAPES["tiny"], 1024, 64), 9)

@@ -240,3 +240,108 @@ def test_hi_and_lo_parts_add_up(torch, d, hq, hkv, hd, F, T, calls):
         assert (err <= 2.0 ** -22 * np.abs(want) + 2.0 ** -24).all(), (int((err > 2.0 ** -22 * np.abs(want) + 2.0 ** -24).sum()), err.max())
     B.ax_kv_free(kv)
     dm.close()
+
+
+def panels(x):
+    """[.., M, K] -> [.., M * K], 16-row panels: a panel's rows of 8 columns at a time, a short last panel in shorter runs."""
+    *lead, M, K = x.shape
+    return np.concatenate([x[..., r:r + 16, :].reshape(*lead, -1, K // 8, 8).swapaxes(-3, -2).reshape(*lead, -1) for r in range(0, M, 16)], -1)
+
+
+def rows_of(x, M, K):
+    """The inverse of panels."""
+    out = np.empty((*x.shape[:-1], M, K), x.dtype)
+    for r in range(0, M, 16):
+        n = min(16, M - r)
+        out[..., r:r + n, :] = x[..., r * K:(r + n) * K].reshape(*x.shape[:-1], K // 8, n, 8).swapaxes(-3, -2).reshape(*x.shape[:-1], n, K)
+    return out
+
+
+PANEL_CASES = [(b, epi, split, slices, M, N, K)
+               for b in BLOCKS for epi in (STORE, RESIDUAL, SWIGLU, QKV) for split in (0, 1)
+               for slices, M, N, K in ((1, 300, 320, 576), (1, 257, 640, 64), (3, 385, 320, 576))
+               if not (epi == SWIGLU and b == (128, 128)) and not (slices > 1 and epi in (STORE, SWIGLU))]
+# more than 256 blocks of 128 x 256: two on a compute unit
+PANEL_CASES += [((128, 256), epi, 0, 1, 300, 22080 if epi != SWIGLU else 11072, K) for epi in (STORE, RESIDUAL, SWIGLU, QKV) for K in (64, 160 * 2)]
+PANEL_CASES += [((128, 256), RESIDUAL, 0, 3, 300, 7424, 576)]
+
+
+@pytest.mark.parametrize("block,epi,split,slices,M,N,K", PANEL_CASES)
+def test_block_gemm_in_panels(torch, block, epi, split, slices, M, N, K):
+    """Activations in panels, a short last one among them: the same bits as in rows on 256 x 256 blocks (every output is the same sum in the
+    same order whatever the block), which the test above holds against float64."""
+    from paper_2605_10380_amd import binding as B
+    rng = np.random.default_rng(M + N + K + split)
+    parts, _, w = operands(rng, M, N, K, split)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    bf = lambda x: torch.from_numpy(x).view(torch.bfloat16).cuda()
+    hd, n16 = 64, (N - 128 if epi == QKV else N)
+    pos, slot = rng.integers(0, 500, M).astype(np.int32), rng.permutation(40 * 16)[:M].astype(np.int32)
+    ang = np.arange(500)[:, None] * 10000.0 ** (-2.0 * np.arange(hd // 2) / hd)
+    c0, gain = rng.standard_normal((M, N), dtype=np.float32), I.f32_to_bf16_bits(1.0 + 0.1 * rng.standard_normal(N, dtype=np.float32))
+    ssq, w2 = rng.uniform(0.1, 2.0, (M, 1)).astype(np.float32), rng.permutation(w)
+
+    def run(block, in_panels):
+        keep = dict(A=dev(panels(parts) if in_panels else parts), W=bf(w))
+        args = dict(epilogue=epi, rows=block[0], cols=block[1], slices=slices, M=M, N=N, K=K, a_lo=M * K if split else 0, a_panels=in_panels)
+        if epi != RESIDUAL:
+            keep["ssq"] = dev(ssq)
+            args.update(n_parts=1, eps=1e-5)
+        if slices > 1:
+            keep["split_ws"] = torch.full((slices * M * N,), float("nan"), dtype=torch.float32, device="cuda")
+            args["split_ws_bytes"] = slices * M * N * 4
+        if epi != STORE:
+            keep["C16"] = torch.full((1 + split, M * n16), float("nan"), dtype=torch.float16, device="cuda")
+            args["c_lo"] = M * n16 if split else 0
+        if epi in (STORE, RESIDUAL):
+            keep["C"] = dev(c0.copy())
+        if epi in (RESIDUAL, SWIGLU):
+            args["c_panels"] = in_panels
+        if epi == RESIDUAL:
+            keep.update(gain=bf(gain), ssq_out=torch.full((M * N // 8,), float("nan"), dtype=torch.float32, device="cuda"))
+        if epi == SWIGLU:
+            keep["W2"] = bf(w2)
+        if epi == QKV:
+            keep.update(pool=torch.full((2, 1, 40, 16 * hd), -7.0, dtype=torch.float16, device="cuda"), row_pos=dev(pos), row_slot=dev(slot),
+                        cos=dev(np.cos(ang).astype(np.float32)), sin=dev(np.sin(ang).astype(np.float32)))
+            args.update(n_q_heads=N // hd - 2, n_kv_heads=1, head_dim=hd, pool_blocks=40)
+        torch.cuda.synchronize()
+        n_out = B.ax_dbg_gemm_block(**args, **{k: t.data_ptr() for k, t in keep.items()})
+        out = {k: keep[k].cpu().numpy() for k in ("C", "C16", "pool") if k in keep}
+        if epi in (RESIDUAL, SWIGLU) and in_panels:
+            out["C16"] = rows_of(out["C16"], M, N).reshape(1 + split, -1)
+        sums = None
+        if epi == RESIDUAL:
+            sums = keep["ssq_out"].cpu().numpy()[:M * n_out]
+            sums = (sums.reshape(n_out, M).T if in_panels else sums.reshape(M, n_out)).astype(np.float64).sum(1)
+        return out, sums
+
+    want, want_sums = run((256, 256), 0)
+    got, sums = run(block, 1)
+    assert want.keys() == got.keys()
+    for k in want:
+        assert np.array_equal(want[k], got[k]), (k, np.abs(want[k].astype(np.float64) - got[k]).max())
+    if epi == RESIDUAL:
+        assert np.allclose(sums, want_sums, rtol=1e-5)         # fp32 sums of x^2 in another order
+
+
+@pytest.mark.parametrize("T", [5, 300])
+def test_embedding_that_is_not_16_byte_aligned(torch, T):
+    """The embedding and the gains are read where the caller has them, at any address a bf16 can have."""
+    from paper_2605_10380_amd import binding as B
+    sh = I.DecoderShape("odd", 1, 128, 2, 1, 64, 192, 512, "bf16")
+    w = I.make_weights(sh, 5)
+    toks = np.random.default_rng(T).integers(0, sh.vocab, T).astype(np.int32)
+
+    def logits(shift):
+        t = {k: [torch.from_numpy(a).view(torch.bfloat16).cuda() for a in v] if isinstance(v, list) else torch.from_numpy(v).view(torch.bfloat16).cuda() for k, v in w.items()}
+
+        def moved(x):
+            flat = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")[shift:shift + x.numel()]
+            return flat.copy_(x.flatten()).view(x.shape)
+        t["tok_emb"], t["norm_attn"] = moved(t["tok_emb"]), [moved(x) for x in t["norm_attn"]]
+        dm = B.DeviceModel(sh, t, max_pos=512, max_tokens=T, pool_tokens=512)
+        out = dm.extend(dm.new_kv(), toks, B.AX_OUT_ALL_LOGITS).cpu().numpy()
+        return out
+
+    assert np.array_equal(logits(0), logits(1)) and np.array_equal(logits(0), logits(3))
