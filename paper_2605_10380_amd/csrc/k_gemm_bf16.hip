@@ -740,11 +740,20 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     __shared__ __attribute__((aligned(16))) f32x4 red[NW][NB][MT][64];
     __shared__ float s_inv[MT * 16];
 
+    // The kernel is a chain of memory round trips, and the scalar loads of its arguments are the first: everything the loads below need is
+    // asked for here, in one trip (left alone, the compiler fetches arguments where they are used, five trips one after the other).
     const f16* __restrict__ X = (const f16*)g.A;
     const bf16* __restrict__ W = (const bf16*)g.W;
     const bf16* __restrict__ W2 = (const bf16*)g.W2;
     const int M = g.M, N = g.N, K = g.K;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#define AX_ARGS "s"(X), "s"(W), "s"(M), "s"(N), "s"(K), "s"(g.a_lo_off), "s"((int)g.a_panels), "s"(g.a_total_rows), "s"(g.ssq), "s"(g.nparts)
+    if constexpr (EPI == EPI_QKV) asm volatile("" :: AX_ARGS, "s"(g.rope.kv.head_dim), "s"(g.rope.row_pos), "s"(g.rope.row_slot), "s"(g.rope.cos), "s"(g.rope.sin));
+    else if constexpr (EPI == EPI_RESIDUAL) asm volatile("" :: AX_ARGS, "s"(g.Cf), "s"(g.gain_next));
+    else if constexpr (EPI == EPI_SWIGLU) asm volatile("" :: AX_ARGS, "s"(W2));
+    else asm volatile("" :: AX_ARGS, "s"(g.a_rows));
+#undef AX_ARGS
+    const int* const a_rows = EPI == EPI_STORE_F32 ? g.a_rows : nullptr;      // only logits pick their rows
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int lr = lane & 15, lg = lane >> 4;
     const int n0 = blockIdx.x * COLS;
     const int kslice = K / NW, kbeg = wave * kslice, kend = kbeg + kslice;
@@ -752,29 +761,39 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     int wrow;                            // weight row this lane streams
     int q_head = 0, q_j0 = 0;            // EPI_QKV: head and first channel of the block
     if (EPI == EPI_QKV) {
-        const int hd = g.rope.kv.head_dim, per = hd / 16;
-        q_head = blockIdx.x / per;
-        q_j0 = (blockIdx.x % per) * 8;
+        const int hd = g.rope.kv.head_dim, blocks = hd == 64 ? 2 : 3;        // log2 of the blocks of a head
+        q_head = blockIdx.x >> blocks;
+        q_j0 = (blockIdx.x & ((1 << blocks) - 1)) * 8;
         wrow = q_head * hd + (lr < 8 ? q_j0 + lr : hd / 2 + q_j0 + lr - 8);
     } else {
         wrow = min(n0 + min(lr, COLS - 1), N - 1);
     }
     const bool wlane = lr < COLS;      // COLS < 16: the other MFMA rows are zero, their lanes request nothing
-    const bf16* wp = W + packed_row(wrow, K) + lg * PK_KG;          // packed layout: k advances by 32 -> + 512 elements
-    const bf16* wp2 = NB == 2 ? W2 + packed_row(wrow, K) + lg * PK_KG : nullptr;
+    // Loads are a wavefront's own address (scalar registers, advanced by the scalar unit) and a lane's 32-bit offset to it: none of a load's
+    // address takes vector instructions, or more than one register.  Weights: from the block's first panel.
+    const long long first_panel = packed_row((EPI == EPI_QKV ? q_head * g.rope.kv.head_dim + q_j0 : n0) & ~15, K);
+    const char* wb = (const char*)(W + first_panel);
+    const char* wb2 = NB == 2 ? (const char*)(W2 + first_panel) : nullptr;
+    const unsigned wo = (unsigned)(packed_row(wrow, K) - first_panel + lg * PK_KG) * 2u;      // packed layout: k advances by 32 -> + 1 KB
     // 8-column blocks: a load instruction costs the memory pipeline the same with half of its lanes
     // idle (the 8 MFMA rows that are not there), and these launches are bound by exactly that - a CU
     // pulled 16 GB/s of weights against 26 GB/s from 16-column blocks.  So the upper half of each
     // 16-lane row fetches the block's 8 rows at the NEXT k-step (one chunk further), and for that
     // step the operand is shifted down 8 lanes; MFMA rows 8-15 then hold products nobody reads.
     constexpr bool DUAL = COLS == 8 && MT <= 2 && NB == 1;
-    const bf16* wpd = W + packed_row(min(n0 + (lr & 7), N - 1), K) + lg * PK_KG + (lr >> 3) * PK_CHUNK;
-    const f16* xp[MT];
+    const unsigned wod = (unsigned)(packed_row(min(n0 + (lr & 7), N - 1), K) - first_panel + lg * PK_KG + (lr >> 3) * PK_CHUNK) * 2u;
+    auto weights = [&](const char* base, unsigned off, int k) { return (const u32x4*)(base + (long long)k * 32 + off); };
+    unsigned xo[MT];
+    const unsigned row_step = g.a_panels ? 16u : (unsigned)K * 2u, group_step = g.a_panels ? g.a_total_rows * 16u : 16u;      // bytes
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int m = min(t * 16 + lr, M - 1);
-        xp[t] = X + (long long)(g.a_rows ? g.a_rows[m] : m) * K + lg * 8;
+        const int row = a_rows ? a_rows[m] : m;
+        xo[t] = (unsigned)row * row_step + lg * group_step;
     }
+    // A of up to 16 rows in one panel (act_index): 32 k of 9 rows are 576 bytes in a row, 4 or 5 lines instead of 9 halves
+    const int xs = g.a_panels ? g.a_total_rows * 2 : 2;             // bytes per k
+    auto acts = [&](int t, int part, int k) { return (const f16x8*)((const char*)(part ? X + g.a_lo_off : X) + (long long)k * xs + xo[t]); };
 
     f32x4 acc[NB][MT];
 #pragma unroll
@@ -787,7 +806,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     // that will run the epilogue: at these sizes a kernel is a chain of memory latencies, and
     // anything loaded after the K loop would add a full round trip to it.
     f32x4 pre_x[MT], pre_cs[MT], pre_sn[MT];
-    float pre_g[4] = {0.f, 0.f, 0.f, 0.f};
+    unsigned pre_g[4] = {0u, 0u, 0u, 0u};      // bf16 as it is: converted or packed here, they would be waited for ahead of the first weights
     int pre_pos[MT], pre_slot[MT];
     if (wave == 0) {
 #pragma unroll
@@ -796,17 +815,13 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
             if (EPI == EPI_RESIDUAL) {
                 pre_x[t] = *(const f32x4*)(g.Cf + (long long)m * N + min(n0 + lg * 4, N - 4));
             } else if (EPI == EPI_QKV) {
-                const int hd = g.rope.kv.head_dim;
                 pre_pos[t] = g.rope.row_pos[m];
                 pre_slot[t] = g.rope.row_slot[m];
-                const long long ao = (long long)pre_pos[t] * (hd / 2) + q_j0 + (lg & 1) * 4;
-                pre_cs[t] = *(const f32x4*)(g.rope.cos + ao);
-                pre_sn[t] = *(const f32x4*)(g.rope.sin + ao);
             }
         }
         if (EPI == EPI_RESIDUAL && g.gain_next) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) pre_g[r] = (float)((const bf16*)g.gain_next)[min(n0 + lg * 4 + r, N - 1)];
+            for (int r = 0; r < 4; ++r) pre_g[r] = ((const unsigned short*)g.gain_next)[min(n0 + lg * 4 + r, N - 1)];
         }
     }
 
@@ -814,16 +829,19 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     // rows w, w + NW, .. into 1 / rms after the K loop, from registers filled here (up to 16 rows, 256
     // partials per row and 4 rows per wavefront; anything larger is fetched after the loop).
     constexpr int RPW = (MT * 16 + NW - 1) / NW;
-    constexpr bool PRE_SSQ = MT == 1 && RPW <= 4;          // 17-32 rows: only small test shapes arrive here with a norm pending
+    constexpr bool NORMED = EPI != EPI_RESIDUAL;           // (what a residual GEMM reads awaits no norm)
+    constexpr bool PRE_SSQ = NORMED && MT == 1 && RPW <= 4;          // 17-32 rows: only small test shapes arrive here with a norm pending
     float pre_ss[PRE_SSQ ? RPW : 1][4];
     const bool pre_ssq = PRE_SSQ && g.ssq && g.nparts <= 256;
-    if (pre_ssq) {
+    if constexpr (PRE_SSQ) {                               // (no branch around the loads, see below: without a norm something else is read, and not used)
+        const float* sums = g.ssq ? g.ssq : (const float*)X;
+        const int nparts = g.ssq ? g.nparts : 1;
 #pragma unroll
-        for (int j = 0; j < (PRE_SSQ ? RPW : 1); ++j) {
+        for (int j = 0; j < RPW; ++j) {
             const int m = min(wave + j * NW, M - 1);
-            const float* src = g.ssq + (long long)(g.a_rows ? g.a_rows[m] : m) * g.nparts;
+            const float* src = sums + (long long)(a_rows ? a_rows[m] : m) * nparts;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) pre_ss[j][u] = src[min(u * 64 + lane, g.nparts - 1)];
+            for (int u = 0; u < 4; ++u) pre_ss[j][u] = src[min(u * 64 + lane, nparts - 1)];
         }
     }
 
@@ -843,6 +861,17 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
         }
     };
 
+    // the angles follow from the positions, a second round trip: asked for behind the first operands
+    auto request_angles = [&]() {
+        if (EPI != EPI_QKV || wave != 0) return;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const long long ao = (long long)pre_pos[t] * (g.rope.kv.head_dim / 2) + q_j0 + (lg & 1) * 4;
+            pre_cs[t] = *(const f32x4*)(g.rope.cos + ao);
+            pre_sn[t] = *(const f32x4*)(g.rope.sin + ao);
+        }
+    };
+
     // One trip = U MFMA k-steps (32 each).  All weight and activation loads of trip i + 1 are issued
     // before trip i is multiplied (two register sets), so a wavefront always has a trip's worth
     // of loads (U KB of weights) in flight while its matrix pipe is busy.
@@ -851,38 +880,26 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
         constexpr int U = 4, S = 32 * U;
         u32x4 rw[2][NB][DUAL ? U / 2 : U];
         f16x8 fx[2][NA][MT][U];
-#pragma unroll
-        for (int set = 0; set < 2; ++set)
-#pragma unroll
-            for (int p = 0; p < NA; ++p)
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) fx[set][p][t][u] = (f16x8){0, 0, 0, 0, 0, 0, 0, 0};   // rows past M stay zero
         auto loads = [&](int set, int kk) {
             if constexpr (DUAL) {
 #pragma unroll
-                for (int v = 0; v < U / 2; ++v) rw[set][0][v] = __builtin_nontemporal_load((const u32x4*)(wpd + (long long)(kk + 64 * v) * 16));
+                for (int v = 0; v < U / 2; ++v) rw[set][0][v] = __builtin_nontemporal_load(weights(wb, wod, kk + 64 * v));
             } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    rw[set][0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load((const u32x4*)(wp + (long long)(kk + 32 * u) * 16)) : (u32x4){0u, 0u, 0u, 0u};
-                    if (NB == 2) rw[set][NB - 1][u] = __builtin_nontemporal_load((const u32x4*)(wp2 + (long long)(kk + 32 * u) * 16));
+                    rw[set][0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load(weights(wb, wo, kk + 32 * u)) : (u32x4){0u, 0u, 0u, 0u};
+                    if (NB == 2) rw[set][NB - 1][u] = __builtin_nontemporal_load(weights(wb2, wo, kk + 32 * u));
                 }
             }
-            // activation rows past M: no load (a block re-reads its wavefronts' whole activation slice, and at
-            // 9 rows of 16 that is most of what the CU's load pipeline carries)
+            // activation rows past M: the last row's address again, which costs no line of its own (a block re-reads its wavefronts' whole
+            // activation slice, at 9 rows of 16 most of what the CU's load pipeline carries); their products go nowhere.  A branch around
+            // the loads instead, and the compiler no longer knows how many are out: it waited for all of them ahead of the second trip.
 #pragma unroll
-            for (int t = 0; t < MT; ++t) {
-                if (t * 16 + lr < M) {
+            for (int t = 0; t < MT; ++t)
 #pragma unroll
-                    for (int u = 0; u < U; ++u) fx[set][0][t][u] = *(const f16x8*)(xp[t] + kk + 32 * u);
-                    if (SPLIT) {
+                for (int p = 0; p < NA; ++p)
 #pragma unroll
-                        for (int u = 0; u < U; ++u) fx[set][NA - 1][t][u] = *(const f16x8*)(xp[t] + g.a_lo_off + kk + 32 * u);
-                    }
-                }
-            }
+                    for (int u = 0; u < U; ++u) fx[set][p][t][u] = *acts(t, p, kk + 32 * u);
         };
         auto compute = [&](int set) {
 #pragma unroll
@@ -903,37 +920,48 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                 }
         };
         const int ntr = kslice / S;
-        if (ntr > 0) loads(0, kbeg);
-        if (pre_ssq) finish_pre_ssq();
-        int t = 0;
-        for (; t + 2 < ntr; t += 2) {                                // both loads unconditional
-            loads(1, kbeg + (t + 1) * S);
-            compute(0);
-            loads(0, kbeg + (t + 2) * S);
-            compute(1);
-        }
-        if (t + 1 < ntr) {
-            loads(1, kbeg + (t + 1) * S);
-            compute(0);
-            compute(1);
-        } else if (t < ntr) {
-            compute(0);
+        auto issue = [&](int set, int trip) {                        // all of a trip's loads, before anything that follows
+            loads(set, kbeg + trip * S);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (ntr > 0) {
+            issue(0, 0);
+            request_angles();
+            if (pre_ssq) finish_pre_ssq();
+            int t = 0;
+            for (; t + 2 < ntr; t += 2) {                            // both loads unconditional
+                issue(1, t + 1);
+                compute(0);
+                issue(0, t + 2);
+                compute(1);
+            }
+            if (t + 1 < ntr) {
+                issue(1, t + 1);
+                compute(0);
+                compute(1);
+            } else {
+                compute(0);
+            }
+        } else {
+            request_angles();
+            if (pre_ssq) finish_pre_ssq();
         }
         k = kbeg + ntr * S;
     } else {
+        request_angles();
         for (; k + 128 <= kend; k += 128) {
             static_assert(!SPLIT, "more than two row tiles: not instantiated with split activations");
             u32x4 rw[NB][4];
             f16x8 fx[MT][4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                rw[0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load((const u32x4*)(wp + (long long)(k + 32 * u) * 16)) : (u32x4){0u, 0u, 0u, 0u};
-                if (NB == 2) rw[NB - 1][u] = __builtin_nontemporal_load((const u32x4*)(wp2 + (long long)(k + 32 * u) * 16));
+                rw[0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load(weights(wb, wo, k + 32 * u)) : (u32x4){0u, 0u, 0u, 0u};
+                if (NB == 2) rw[NB - 1][u] = __builtin_nontemporal_load(weights(wb2, wo, k + 32 * u));
             }
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) fx[t][u] = *(const f16x8*)(xp[t] + k + 32 * u);
+                for (int u = 0; u < 4; ++u) fx[t][u] = *acts(t, 0, k + 32 * u);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -948,13 +976,13 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     for (; k < kend; k += 32) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const f16x8 fw = load_w((b == 0 ? wp : wp2) + (long long)k * 16);
+            const f16x8 fw = __builtin_bit_cast(f16x8, *weights(b == 0 ? wb : wb2, wo, k));
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
-                const f16x8 fx = *(const f16x8*)(xp[t] + k);
+                const f16x8 fx = *acts(t, 0, k);
                 acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw, fx, acc[b][t], 0, 0, 0);
                 if (SPLIT) {
-                    const f16x8 fl = *(const f16x8*)(xp[t] + g.a_lo_off + k);
+                    const f16x8 fl = *acts(t, 1, k);
                     acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw, fl, acc[b][t], 0, 0, 0);
                 }
             }
@@ -967,9 +995,9 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
         for (int t = 0; t < MT; ++t) red[wave][b][t][lane] = acc[b][t];
     if (pre_ssq) {                       // deferred RMSNorm: the wavefronts share the rows
         if (MT > 2) finish_pre_ssq();    // (the MT <= 2 loop did it behind its first loads)
-    } else if (g.ssq) {
+    } else if (NORMED && g.ssq) {
         for (int r = wave; r < min(MT * 16, M); r += NW) {
-            const float inv = wave_inv_rms(g.ssq, g.a_rows ? g.a_rows[r] : r, g.nparts, g.d_norm, g.eps, lane);
+            const float inv = wave_inv_rms(g.ssq, a_rows ? a_rows[r] : r, g.nparts, g.d_norm, g.eps, lane);
             if (lane == 0) s_inv[r] = inv;
         }
     }
@@ -987,7 +1015,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
         }
         const int m = t * 16 + lr, n = n0 + lg * 4;
         const bool mok = m < M && lg * 4 < COLS;
-        const float inv = g.ssq ? s_inv[t * 16 + lr] : 1.0f;
+        const float inv = NORMED && g.ssq ? s_inv[t * 16 + lr] : 1.0f;
         const long long o = (long long)m * N + n;
         if (EPI == EPI_STORE_F32) {
             if (mok && n < N) *(f32x4*)(g.Cf + o) = sum[0] * inv;
@@ -996,7 +1024,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                 float h[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) h[r] = silu_f(sum[0][r] * inv) * (sum[NB - 1][r] * inv);
-                store_split4((f16*)g.C16 + o, g.c_lo_off, h);
+                store_split4((f16*)g.C16 + act_index(g.c_panels, m, n, M, N), g.c_lo_off, h);
             }
         } else if (EPI == EPI_RESIDUAL) {
             float ss = 0.f;
@@ -1007,10 +1035,10 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                     float h[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        h[r] = xn[r] * pre_g[r];
+                        h[r] = xn[r] * __uint_as_float(pre_g[r] << 16);
                         ss += xn[r] * xn[r];
                     }
-                    store_split4((f16*)g.C16 + o, g.c_lo_off, h);
+                    store_split4((f16*)g.C16 + act_index(g.c_panels, m, n, M, N), g.c_lo_off, h);
                 }
             }
             if (g.gain_next) {           // sum of squares over the block's COLS columns, per row
@@ -1395,7 +1423,7 @@ static void launch_swiglu_stream(const GemmArgs& g, int tm, hipStream_t s) {
 template <int EPI>
 static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
-    if (g.a_panels) return launch_gemm_block((Epilogue)EPI, g, plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, true, g.split_ws ? g.split_ws_bytes : 0), s);
+    if (g.a_panels && M > 256) return launch_gemm_block((Epilogue)EPI, g, plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, true, g.split_ws ? g.split_ws_bytes : 0), s);
     if (many_rows(M, N, g.a_rows != nullptr)) {
         const ManyPlan p = plan_many<EPI>(M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
         if (p.kernel == MANY_BLOCK) return launch_gemm_block((Epilogue)EPI, g, p.block, s);
@@ -1403,7 +1431,8 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         launch_swiglu_stream(g, p.stream_tm, s);
         return 0;
     }
-    if (use_skinny(EPI, M, N, K)) {
+    const bool far_rows = g.a_rows && (unsigned long long)g.a_total_rows * K * 2 > 0xffffffffull;      // gathered rows past what the offsets below hold
+    if (use_skinny(EPI, M, N, K) && !far_rows) {
         // wavefronts per block (= K slices): enough to keep ~2k wavefronts in flight (~4k for the SwiGLU
         // GEMM: 8 instead of 4 wavefronts per block took the ~1B verify kernel from 16.6 to 14.7 us), each with
         // at least 128 of K; K / nw must stay a multiple of the MFMA k (32)

@@ -89,7 +89,7 @@ struct GemmArgs {
     const void* A;                    // fp16 [rows, K]
     long long a_lo_off;               // split activations: the lo parts of A lie this many elements behind A (0 = none)
     long long c_lo_off;               // ... and the lo parts of C16 (and of rope.q_out) this many elements behind it
-    bool a_panels, c_panels;          // A, C16 lie in panels (act_index) instead of rows: M > 256 (see gemm_layer_panels)
+    bool a_panels, c_panels;          // A, C16 lie in panels (act_index) instead of rows: M > 256 (see gemm_layer_panels), or the call has up to 16 rows
     int a_total_rows;                 // rows A has (a gather picks M of them)
     const int* a_rows;                // optional gather: A row of output row m is a_rows[m]
     const void *W, *W2;               // [N, K] packed by launch_pack_weights (fp16, MFMA operand order); W2 only for EPI_SWIGLU
