@@ -244,10 +244,19 @@ __device__ __forceinline__ bool online_softmax_step(f32x16& s, int kv0, int g, i
 // head's q rows (with 8 KV heads: one head per XCD; K, V and q each cross HBM once).
 struct AttnWork { int tile, hk, split; };
 __device__ __forceinline__ AttnWork attn_work() {
-    const unsigned nx = gridDim.x, nz = gridDim.z, total = nx * gridDim.y * nz;
+    const unsigned nx = gridDim.x, nz = gridDim.z, total = nx * gridDim.y * nz;      // nz: a power of two (choose_splits)
     unsigned id = blockIdx.x + nx * (blockIdx.y + gridDim.y * blockIdx.z);
     if ((total & 7u) == 0) id = (id & 7u) * (total >> 3) + (id >> 3);
-    return {(int)(id % nx), (int)(id / (nx * nz)), (int)((id / nx) % nz)};
+    const unsigned rest = id / nx;
+    return {(int)(id - rest * nx), (int)(rest >> __builtin_ctz(nz)), (int)(rest & (nz - 1))};
+}
+// r / G for stacked rows of the split kernel (r < 2^20: a step away from the next integer is more than the rounding of two fp32 operations)
+__device__ __forceinline__ int row_of_stacked(int r, float inv_g) { return (int)((r + 0.5f) * inv_g); }
+
+// A tile record (StepView::tile_info): wavefront-uniform and not written while a kernel runs, so one scalar load.
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ i32x8 tile_record(const int* info, int tile) {
+    return *(const __attribute__((address_space(4))) i32x8*)(info + tile * 8);
 }
 
 struct AttnArgs {
@@ -257,7 +266,7 @@ struct AttnArgs {
     int n_rows;
     bool out_panels;                  // out [n_rows, Hq * hd] in panels (act_index) instead of rows
     KVGeom kv;
-    int layer, Hq, n_splits;
+    int layer, Hq, G, n_splits;       // G: query heads per KV head; n_splits: a power of two
     const int* tile_info;      // 8 ints per q tile, item or merge record (see StepView)
     const int* bt;
     float* partials;
@@ -284,32 +293,36 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
     constexpr int PS = HD * 32 + 64;     // floats of one partial: O^T [HD][32], m[32], l[32]
     __shared__ f32x4 s_o[NW][NW > 1 ? DT * 4 : 1][64];
     __shared__ float s_m[NW][32], s_l[NW][32];
+    // all arguments in one round trip (left alone, the compiler fetches them where they are used)
+    asm volatile("" :: "s"(a.q), "s"(a.q_lo_off), "s"(a.kv.base), "s"(a.kv.n_blocks), "s"(a.kv.n_kv_heads), "s"(a.layer), "s"(a.Hq), "s"(a.G), "s"(a.n_splits),
+                       "s"(a.tile_info), "s"(a.bt), "s"(a.partials));
     const AttnWork wk = attn_work();
     const int tile = wk.tile, hk = wk.hk, split = wk.split;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5;
-    const int Hq = a.Hq, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
-    const int4 ti0 = *(const int4*)(a.tile_info + tile * 8), ti1 = *(const int4*)(a.tile_info + tile * 8 + 4);
-    const int r0 = ti0.y, P = ti0.z, T = ti0.w, row0 = ti1.x;
+    const int Hq = a.Hq, Hkv = a.kv.n_kv_heads, G = a.G;
+    const float inv_g = 1.0f / (float)G;
+    const i32x8 ti = tile_record(a.tile_info, tile);
+    const int r0 = ti[1], P = ti[2], T = ti[3], row0 = ti[4];
     const int n_stacked = T * G;
-    const int* tab = a.bt + ti1.y;
+    const int* tab = a.bt + ti[5];
     const int kv_len = P + T, last_blk = (kv_len - 1) >> 4;
 
     // keys this group can see at all: up to the position of its last valid row.  (Keys past the end of the
     // sequence, reached only by its last step, re-read the last valid K row - see fetch - and their scores are
     // replaced by -inf, so K is never read from unwritten slots; V is, and process() zeroes those operands.)
     const int r_last = min(r0 + 31, n_stacked - 1);
-    const int kv_end = P + r_last / G + 1;
-    const int first = ti1.w >> 5;                        // first key step (keys before it belong to the shared pass)
+    const int kv_end = P + row_of_stacked(r_last, inv_g) + 1;
+    const int first = ti[7] >> 5;                        // first key step (keys before it belong to the shared pass)
     const int steps = (kv_end + 31) / 32;
-    const int per = (steps - first + a.n_splits - 1) / a.n_splits;
+    const int per = (steps - first + a.n_splits - 1) >> __builtin_ctz(a.n_splits);
     const int b_lo = first + split * per, b_hi = min(steps, b_lo + per);      // the block's key steps
     const int per_w = (max(b_hi - b_lo, 0) + NW - 1) / NW;
     const int s_lo = b_lo + wave * per_w, s_hi = min(b_hi, s_lo + per_w);     // this wavefront's (may be none)
 
     // this lane's query row (clamped rows compute garbage that is never written)
-    const int rq = min(r0 + ql, n_stacked - 1), tq = rq / G;
-    const int pos_q = P + tq, pos_min = P + min(r0, n_stacked - 1) / G;       // pos_min: earliest position of the tile (uniform)
-    const f16* qrow = a.q + ((long long)(row0 + tq) * Hq + hk * G + rq % G) * HD;
+    const int rq = min(r0 + ql, n_stacked - 1), tq = row_of_stacked(rq, inv_g);
+    const int pos_q = P + tq, pos_min = P + row_of_stacked(min(r0, n_stacked - 1), inv_g);       // pos_min: earliest position of the tile (uniform)
+    const f16* qrow = a.q + ((long long)(row0 + tq) * Hq + hk * G + rq - tq * G) * HD;
     f16x8 qf[NP][KQ];
 #pragma unroll
     for (int p = 0; p < NP; ++p)
@@ -391,14 +404,26 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
     for (int chunk = s_lo; chunk < s_hi; chunk += 32) {          // 32 steps = 64 blocks = one table load
         tabv = tab[min(2 * chunk + lane, last_blk)];
         const int c_hi = min(s_hi, chunk + 32);
-        fetch(0, chunk, chunk);
-        for (int st = chunk; st < c_hi; st += 2) {
-            if (st + 1 < c_hi) fetch(1, st + 1, chunk);
+        // (no fetch sits behind a branch that the products ahead of it do not share: the compiler then knows how many loads are out and
+        // waits for one step's operands while the next one's stay in flight)
+        auto issue = [&](int buf, int st) {
+            fetch(buf, st, chunk);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        issue(0, chunk);
+        int st = chunk;
+        for (; st + 2 < c_hi; st += 2) {
+            issue(1, st + 1);
             process(0, st);
-            if (st + 1 < c_hi) {
-                if (st + 2 < c_hi) fetch(0, st + 2, chunk);
-                process(1, st + 1);
-            }
+            issue(0, st + 2);
+            process(1, st + 1);
+        }
+        if (st + 1 < c_hi) {
+            issue(1, st + 1);
+            process(0, st);
+            process(1, st + 1);
+        } else {
+            process(0, st);
         }
     }
 
@@ -666,13 +691,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     constexpr int PS = HD * 32 + 64;
     constexpr int MAXS = 16;                                   // slices per thread held in registers
     __shared__ float red[8][6][32];
-    const int Hkv = a.kv.n_kv_heads, G = a.Hq / Hkv;
+    // (all arguments in one round trip, as in attn_split_kernel)
+    asm volatile("" :: "s"(a.out), "s"(a.out_lo_off), "s"(a.n_rows), "s"((int)a.out_panels), "s"(a.kv.n_kv_heads), "s"(a.Hq), "s"(a.G), "s"(a.n_splits),
+                       "s"(a.tile_info), "s"(a.partials), "s"(a.shared_splits));
+    const int Hkv = a.kv.n_kv_heads, G = a.G;
     const int hk = blockIdx.x % Hkv, tile = blockIdx.x / Hkv;
     const int ch0 = blockIdx.y * 4;
     const int ql = threadIdx.x & 31, sg = threadIdx.x >> 5;
-    const int4 ti0 = *(const int4*)(a.tile_info + tile * 8);
-    const int row0 = a.tile_info[tile * 8 + 4];
-    const int r_first = ti0.y, n_stacked = ti0.w * G;
+    const i32x8 ti = tile_record(a.tile_info, tile);
+    const int row0 = ti[4], r_first = ti[1], n_stacked = ti[3] * G;
     if (r_first >= n_stacked) return;                          // whole q tile past the end (block-uniform)
     const int r = r_first + ql;
     const bool valid = r < n_stacked;
@@ -688,25 +715,28 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     }
     auto slice = [&](int s) { return s < own_splits ? base + s * stride : sbase + (s - own_splits) * sstride; };
 
+    // rows past the sequence's end read records like the others, and write nothing
     float mv[MAXS], lv[MAXS], ov[MAXS][4];
     float mloc = -INFINITY;
 #pragma unroll
     for (int i = 0; i < MAXS; ++i) {
-        const int s = sg + 8 * i;
         mv[i] = -INFINITY;
         lv[i] = 0.f;
 #pragma unroll
         for (int c = 0; c < 4; ++c) ov[i][c] = 0.f;
-        if (valid && s < n_splits) {
-            const float* p = slice(s);
-            mv[i] = p[HD * 32];
-            lv[i] = p[HD * 32 + 32];
+        if (8 * i >= n_splits) continue;                       // wavefront-uniform, and so are the loads behind it
+        const int s = sg + 8 * i;
+        const float* p = slice(min(s, n_splits - 1));
+        mv[i] = p[HD * 32];
+        lv[i] = p[HD * 32 + 32];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) ov[i][c] = p[(ch0 + c) * 32];
-        }
+        for (int c = 0; c < 4; ++c) ov[i][c] = p[(ch0 + c) * 32];
     }
 #pragma unroll
-    for (int i = 0; i < MAXS; ++i) mloc = fmaxf(mloc, mv[i]);
+    for (int i = 0; i < MAXS; ++i) {
+        if (sg + 8 * i >= n_splits) mv[i] = -INFINITY;
+        mloc = fmaxf(mloc, mv[i]);
+    }
     if (valid)                                                 // more than 128 slices: the rest from memory
         for (int s = sg + 8 * MAXS; s < n_splits; s += 8) mloc = fmaxf(mloc, slice(s)[HD * 32]);
     red[sg][0][ql] = mloc;
@@ -878,7 +908,7 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
         return;
     }
     AttnArgs a{};
-    a.q = (const f16*)q; a.out = (f16*)out; a.kv = kv; a.layer = layer; a.Hq = n_q_heads; a.n_splits = n_splits;
+    a.q = (const f16*)q; a.out = (f16*)out; a.kv = kv; a.layer = layer; a.Hq = n_q_heads; a.G = n_q_heads / kv.n_kv_heads; a.n_splits = n_splits;
     a.tile_info = sv.tile_info; a.bt = sv.bt; a.partials = partials;
     a.q_lo_off = q_lo_off; a.out_lo_off = out_lo_off; a.n_rows = sv.n_rows; a.out_panels = out_panels;
     const int hd = kv.head_dim;
