@@ -497,8 +497,8 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
 
 // Whether a call of that many rows keeps the activations of its layers in panels.
 bool layer_panels(const ax_model_config& c, const Layout& L, int rows) {
-    return c.dtype == AX_BF16 && (rows <= 16 || ax::gemm_layer_panels(rows, c.d_model, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim,
-                                                                      c.n_q_heads * c.head_dim, c.d_ff, L.h_lo != 0, L.splitk_bytes));
+    return c.dtype == AX_BF16 && ax::gemm_layer_panels(rows, c.d_model, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim,
+                                                       c.n_q_heads * c.head_dim, c.d_ff, L.h_lo != 0, L.splitk_bytes);
 }
 
 // Device half: descriptor upload and the kernel sequence of one forward.  `verify_k` >= 0
@@ -612,9 +612,10 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
         base.M = R;
         base.split_ws = (float*)(ws + L.splitk);
         base.split_ws_bytes = L.splitk_bytes;
-        // activations go in panels from kernel to kernel (calls of many rows, or of few); a last norm of many rows whose reader picks some stays in rows
+        // activations go in panels from kernel to kernel (calls of many rows, or of few); a last norm of more than 16 rows stays in rows where
+        // its reader picks some of them or streams (logits of 17-32 rows)
         const bool panels = layer_panels(c, L, R),
-                   out_panels = panels && (R <= 16 || (n_out == R && (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_ALL_LOGITS)));
+                   out_panels = panels && (R <= 16 || (R > 256 && n_out == R && (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_ALL_LOGITS)));
         bool h_panels = panels;
         m->panels = {R, panels, out_panels};
         auto normed = [&](ax::GemmArgs& g) { g.a_panels = h_panels; g.a_total_rows = R; g.A = h; g.a_lo_off = L.h_lo; g.ssq = ssq; g.nparts = nparts; g.d_norm = d_model; g.eps = c.rms_eps; g.K = d_model; };

@@ -783,17 +783,18 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     constexpr bool DUAL = COLS == 8 && MT <= 2 && NB == 1;
     const unsigned wod = (unsigned)(packed_row(min(n0 + (lr & 7), N - 1), K) - first_panel + lg * PK_KG + (lr >> 3) * PK_CHUNK) * 2u;
     auto weights = [&](const char* base, unsigned off, int k) { return (const u32x4*)(base + (long long)k * 32 + off); };
+    // A in panels (act_index): a row tile is one of them.  32 k of 9 rows are 576 bytes in a row, 4 or 5 lines instead of 9 halves.
     unsigned xo[MT];
-    const unsigned row_step = g.a_panels ? 16u : (unsigned)K * 2u, group_step = g.a_panels ? g.a_total_rows * 16u : 16u;      // bytes
+    int xs[MT];                                                     // bytes per k
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int m = min(t * 16 + lr, M - 1);
         const int row = a_rows ? a_rows[m] : m;
-        xo[t] = (unsigned)row * row_step + lg * group_step;
+        const int first = t * 16, panel_rows = min(16, g.a_total_rows - first);
+        xs[t] = g.a_panels ? panel_rows * 2 : 2;
+        xo[t] = g.a_panels ? (unsigned)first * (unsigned)K * 2u + (row - first) * 16u + lg * panel_rows * 16u : (unsigned)row * (unsigned)K * 2u + lg * 16u;
     }
-    // A of up to 16 rows in one panel (act_index): 32 k of 9 rows are 576 bytes in a row, 4 or 5 lines instead of 9 halves
-    const int xs = g.a_panels ? g.a_total_rows * 2 : 2;             // bytes per k
-    auto acts = [&](int t, int part, int k) { return (const f16x8*)((const char*)(part ? X + g.a_lo_off : X) + (long long)k * xs + xo[t]); };
+    auto acts = [&](int t, int part, int k) { return (const f16x8*)((const char*)(part ? X + g.a_lo_off : X) + (long long)k * xs[t] + xo[t]); };
 
     f32x4 acc[NB][MT];
 #pragma unroll
@@ -830,7 +831,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     // partials per row and 4 rows per wavefront; anything larger is fetched after the loop).
     constexpr int RPW = (MT * 16 + NW - 1) / NW;
     constexpr bool NORMED = EPI != EPI_RESIDUAL;           // (what a residual GEMM reads awaits no norm)
-    constexpr bool PRE_SSQ = NORMED && MT == 1 && RPW <= 4;          // 17-32 rows: only small test shapes arrive here with a norm pending
+    constexpr bool PRE_SSQ = NORMED && MT <= 2 && RPW <= 4;
     float pre_ss[PRE_SSQ ? RPW : 1][4];
     const bool pre_ssq = PRE_SSQ && g.ssq && g.nparts <= 256;
     if constexpr (PRE_SSQ) {                               // (no branch around the loads, see below: without a norm something else is read, and not used)
@@ -1123,6 +1124,8 @@ static void launch_skinny_nw(const GemmArgs& g, int nw, hipStream_t s) {
     launch_skinny_cols<EPI, MT, 16>(g, nw, s);
 }
 
+static constexpr int kPanelRows = 32;        // rows up to which the few-row kernel reads activations in panels
+
 // Dispatch thresholds.  Each is a measured crossover (figures at its use); the product build compiles them in
 // as constants.  Only a build with -DAX_TUNING_KNOBS (kernel tuning sessions) lets the environment override them.
 #ifdef AX_TUNING_KNOBS
@@ -1343,7 +1346,7 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
 // wavefronts (M x K / NW fp16) per 8-16 columns, so its time grows with M while one 64-row tile
 // costs the same for any M <= 64.  Measured crossovers (all three model shapes): every GEMM is
 // faster on the other kernels from 33 rows up (64 rows of the ~3B shape: 172 -> 114 us per layer);
-// from 17 rows up the QKV GEMM and the residual GEMM with the long K (down projection) are too
+// from 17 rows up, with activations in rows, the QKV GEMM and the residual GEMM with the long K (down projection) are too
 // (~3B at 17-32 rows: 18-22 -> 17-19 us and 18-23 -> 15-16 us) and so is the SwiGLU GEMM on its
 // K-sliced streaming blocks (see launch_lds_tile); the O projection is not.
 static bool use_skinny(int epi, int M, int N, int K) {
@@ -1355,8 +1358,7 @@ static bool use_skinny(int epi, int M, int N, int K) {
     if (M <= 16) return true;
     if (M > kSkinnyMaxM) return false;
     if (epi == EPI_STORE_F32 && N >= 256 * 256 && kLmStream) return false;    // logits: streaming blocks (see launch_lds_tile)
-    // (re-measured on whole verify steps of 17 rows, ~3B shape, 2.50 ms per step: keeping the QKV / SwiGLU / down
-    // GEMM on this kernel there - no reduce kernel behind them - gives 2.50 / 2.52 / 2.58 ms, all three 2.59 ms)
+    // (17-32 rows in rows, that is split activations; plain ones lie in panels there and stay on this kernel, see gemm_layer_panels)
     return !(epi == EPI_QKV || epi == EPI_SWIGLU || (epi == EPI_RESIDUAL && K >= 2 * N));
 }
 
@@ -1432,7 +1434,7 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         return 0;
     }
     const bool far_rows = g.a_rows && (unsigned long long)g.a_total_rows * K * 2 > 0xffffffffull;      // gathered rows past what the offsets below hold
-    if (use_skinny(EPI, M, N, K) && !far_rows) {
+    if ((use_skinny(EPI, M, N, K) || (g.a_panels && M <= kPanelRows)) && !far_rows) {
         // wavefronts per block (= K slices): enough to keep ~2k wavefronts in flight (~4k for the SwiGLU
         // GEMM: 8 instead of 4 wavefronts per block took the ~1B verify kernel from 16.6 to 14.7 us), each with
         // at least 128 of K; K / nw must stay a multiple of the MFMA k (32)
@@ -1483,9 +1485,14 @@ GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t w
     return block_plan(plan_gemm_block(epi, M, N, K, split, true, ws_bytes));
 }
 
-// By the times that the plans expect: panels make the block kernel faster at every size, but only that kernel reads them, and to 640
-// rows the ones made for fewer rows are ahead of it on some GEMMs.
+// Up to 16 rows: always (one panel; only the few-row kernel runs).  17-32 rows: plain activations, two panels, all four GEMMs on the few-row
+// kernel, without the reduce kernels that K-sliced tiles need behind them.  Whole calls of 17 / 24 / 32 rows in us, tiles and streaming blocks on
+// rows, then this: ~1B 1093 -> 948, 1116 -> 986, 1142 -> 1029; ~3B 2356 -> 2199, 2453 -> 2259, 2508 -> 2471.  Hi + lo parts double what a block
+// re-reads of the activations, and the tiles stay: ~8B 4177 and 4483, 4365 and 4794, 4551 and 5135.
+// More than 256 rows, by the times that the plans expect: panels make the block kernel faster at every size, but only that kernel reads them,
+// and to 640 rows the ones made for fewer rows are ahead of it on some GEMMs.
 bool gemm_layer_panels(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes) {
+    if (M <= kPanelRows) return M <= 16 || !split;
     if (M <= 256) return false;
     auto panels = [&](Epilogue epi, int N, int K) { return plan_gemm_block(epi, M, N, K, split, true, ws_bytes).us; };
     const float rows = plan_many<EPI_QKV>(M, qkv, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, qdim, split, ws_bytes).us +

@@ -89,7 +89,7 @@ struct GemmArgs {
     const void* A;                    // fp16 [rows, K]
     long long a_lo_off;               // split activations: the lo parts of A lie this many elements behind A (0 = none)
     long long c_lo_off;               // ... and the lo parts of C16 (and of rope.q_out) this many elements behind it
-    bool a_panels, c_panels;          // A, C16 lie in panels (act_index) instead of rows: M > 256 (see gemm_layer_panels), or the call has up to 16 rows
+    bool a_panels, c_panels;          // A, C16 lie in panels (act_index) instead of rows: see gemm_layer_panels
     int a_total_rows;                 // rows A has (a gather picks M of them)
     const int* a_rows;                // optional gather: A row of output row m is a_rows[m]
     const void *W, *W2;               // [N, K] packed by launch_pack_weights (fp16, MFMA operand order); W2 only for EPI_SWIGLU
@@ -125,8 +125,9 @@ int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s);
 struct GemmPlan { const char* kernel; int rows, cols, slices; };
 GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
 GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);      // with A in panels
-// Whether the layers of a call of M rows keep their activations in panels (act_index) from kernel to kernel: all four GEMMs then run on the
-// block kernel, with a_panels set, on its plan for panels.  N of a GEMM: the layer's sizes, all multiples of 64.
+// Whether the layers of a call of M rows keep their activations in panels (act_index) from kernel to kernel: all four GEMMs then run with
+// a_panels set, up to 32 rows on the few-row kernel and from 257 on the block kernel, on its plan for panels.  N of a GEMM: the layer's
+// sizes, all multiples of 64.
 bool gemm_layer_panels(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes);
 // A GEMM on the block kernel with the shape and slices of `rows`, `cols`, `slices` whatever the plan would say (tests); returns as launch_gemm_bf16.
 int launch_gemm_block_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s);

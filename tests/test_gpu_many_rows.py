@@ -326,10 +326,11 @@ def test_block_gemm_in_panels(torch, block, epi, split, slices, M, N, K):
 
 
 @pytest.mark.parametrize("split", [0, 1])
-@pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 15, 16, 17])
+@pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 15, 16, 17, 18, 24, 31, 32, 33])
 @pytest.mark.parametrize("hd,hkv,G,d,F", [(64, 2, 4, 256, 320), (128, 1, 8, 1024, 1600)])
-def test_layer_of_one_panel(torch, hd, hkv, G, d, F, T, split):
-    """Calls of up to 16 rows keep their activations in one panel of as many rows (17: in rows again), on blocks of 8, 12 and 16 columns."""
+def test_layer_of_one_or_two_panels(torch, hd, hkv, G, d, F, T, split):
+    """Calls of up to 16 rows keep their activations in one panel of as many rows, plain ones of up to 32 in two (33: in rows again), on blocks
+    of 8 and 16 columns."""
     import test_gpu_kernels as K
     sh = I.DecoderShape("one-panel", 1, d, hkv * G, hkv, hd, F, 512, "bf16")
     got, ref, x, xr = K._one_layer(torch, sh, 37, T, 30 + T, 64, split)
