@@ -541,6 +541,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
               qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, R = cp.n_rows;
 
     if (dt == ax::F32) {
+        m->panels = {R, false, false};
         // fp32 models: five launches per layer.  The norms are folded into the GEMMs that read them; the first layer reads
         // its rows straight from the embedding.
         ax::GemmF32Args base{};
@@ -746,7 +747,8 @@ ax_status run_verify_graph(ax_model* m, ax_kv* kv, const int32_t* toks, int T, v
         if (e != hipSuccess) return fail(AX_ERR_DEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
         m->graphs.push_back({key, cp.pool->uid, exec});
     }
-    m->panels = {T, layer_panels(m->cfg, m->lay, T), T <= 16};
+    const bool panels = layer_panels(m->cfg, m->lay, T);
+    m->panels = {T, panels, panels && T <= 16};
     HIP_TRY(hipGraphLaunch(exec, stream));
     return AX_OK;
 }

@@ -228,3 +228,27 @@ def test_workspace_guards_notice_a_write_past_a_region(B):
     dm.ws[-1] = 0xA5
     B.ax_kv_free(kv)
     dm.close()
+
+
+def test_fp32_lm_head_input_is_read_as_it_lies(B):
+    """ax_dbg_read of an fp32 model's LM-head input (rmsnorm(x) * gain, fp32) after a replayed verify round, whose rows a bf16 model would
+    keep in one panel, and after the extend behind it.  Bound: fp32 sums of d_model squares, 1e-5."""
+    sh = I.SHAPES["tiny"]
+    w = I.make_weights(sh, 4)
+    dm = B.DeviceModel(sh, w, max_pos=256, max_tokens=64, pool_tokens=512)
+    kv = dm.new_kv()
+    toks = I.templated_prompt(sh.vocab, 4, 60)
+    dm.extend(kv, toks[:30])
+    for call, rows in (("capture", 5), ("replay", 5), ("extend", 7)):
+        if call == "extend":
+            dm.extend(kv, toks[40:47], B.AX_OUT_ALL_ARGMAX)
+        else:
+            B.ax_kv_truncate(kv, 30)
+            dm.verify(kv, int(toks[30]), toks[31:35])
+        x, h = np.zeros((rows, sh.d_model), np.float32), np.zeros((rows, sh.d_model), np.float32)
+        B.ax_dbg_read(dm.model, 0, x)
+        B.ax_dbg_read(dm.model, 5, h)
+        x = x.astype(np.float64)
+        want = x / np.sqrt((x ** 2).mean(1, keepdims=True) + sh.rms_eps) * w["final_norm"].astype(np.float64)
+        assert np.abs(h - want).max() <= 1e-5 * np.abs(want).max(), call
+    dm.close()
