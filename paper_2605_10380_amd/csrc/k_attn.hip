@@ -749,10 +749,14 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     float l = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < MAXS; ++i) {
-        const float w = exp2f(mv[i] - M);                      // absent slices: 2^-inf = 0
-        l += w * lv[i];
+        if (8 * i >= n_splits) continue;
+        // absent slices: 2^-inf = 0, times 0 and not the values of the slice read instead, which may be infinite.  (Selects here, behind the
+        // barrier: zeroing the values above had the compiler wait for each group's loads in turn, ~1B k = 8 3.7 -> 4.6 us.)
+        const bool here = sg + 8 * i < n_splits;
+        const float w = exp2f(mv[i] - M);
+        l += w * (here ? lv[i] : 0.f);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] += w * ov[i][c];
+        for (int c = 0; c < 4; ++c) acc[c] += w * (here ? ov[i][c] : 0.f);
     }
     if (valid)
         for (int s = sg + 8 * MAXS; s < n_splits; s += 8) {

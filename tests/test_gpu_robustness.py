@@ -252,3 +252,37 @@ def test_fp32_lm_head_input_is_read_as_it_lies(B):
         want = x / np.sqrt((x ** 2).mean(1, keepdims=True) + sh.rms_eps) * w["final_norm"].astype(np.float64)
         assert np.abs(h - want).max() <= 1e-5 * np.abs(want).max(), call
     dm.close()
+
+
+@pytest.mark.parametrize("T,hkv", [(1, 8), (9, 2)])
+def test_an_infinite_value_reaches_only_its_own_channel(B, T, hkv):
+    """V of one cached key is infinite in one channel, in the last of four key slices: attention is infinite there, as the float64 sum is, not
+    NaN, and unchanged everywhere else.  (The merge adds slices in groups of eight: the absent ones count nothing at all.)"""
+    sh = I.DecoderShape("inf", 1, 128, hkv * 4, hkv, 64, 192, 512, "bf16")
+    P = 300
+    cfg = B.make_config(sh, P + 64, 512)
+    assert B.ax_dbg_split_plan(cfg, -(-T * 4 // 32) * hkv, -(-(P + T) // 32))[1] == 4
+    w = I.make_weights(sh, 6)
+    toks = I.templated_prompt(sh.vocab, 6, P + T)
+    dm = B.DeviceModel(sh, w, max_pos=P + 64, max_tokens=512, pool_tokens=512)
+    kv = dm.new_kv()
+    dm.extend(kv, toks[:P])
+
+    def attention():
+        B.ax_kv_truncate(kv, P)
+        dm.extend(kv, toks[P:], B.AX_OUT_LAST_ARGMAX)
+        out = np.zeros((T, sh.n_q_heads, 64), np.float16)
+        B.ax_dbg_read(dm.model, 3, out)
+        return out
+    plain = attention()
+    key, head, channel = 295, 1, 5
+    v = dm.pool_mem.view(dm.torch.float16).view(2, hkv, -1, 64, 16)[1]
+    v[head, int(B.ax_kv_blocks(kv)[key // 16]), channel, key % 16] = float("inf")
+    dm.torch.cuda.synchronize()
+    got = attention()
+    touched = np.zeros(got.shape, bool)
+    touched[:, head * 4:head * 4 + 4, channel] = True
+    assert (got[touched] == np.inf).all(), got[touched]
+    assert np.array_equal(got[~touched], plain[~touched])
+    B.ax_kv_free(kv)
+    dm.close()
