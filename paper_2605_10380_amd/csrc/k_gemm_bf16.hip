@@ -1363,33 +1363,33 @@ static bool use_skinny(int epi, int M, int N, int K) {
 }
 
 // ------------------------------------------------------------------------------ more than 256 rows
-// The block kernel has the largest tiles and wins wherever they fill the chip; two kernels made for fewer rows are ahead of it where
-// its plan leaves CUs idle or pads rows, and stay candidates (times as in plan_gemm_block, fitted to the same calls):
-//   * the tile kernel, QKV and residual GEMMs of up to 512 rows whose blocks fit one round (~1B QKV at 288 rows 17.7 -> 14.6 us, ~1B down
-//     at 512 rows 43.9 -> 31.7, ~3B down at 257 rows 34.8 -> 30.6; no call of more than 512 rows gains over 3 %);
+// Activations in rows: the block kernel has the largest tiles and wins wherever they fill the chip; two kernels made for fewer rows are ahead of
+// it where its plan leaves CUs idle or pads rows, and stay candidates (times fitted to the same calls as the block kernel's):
+//   * the tile kernel, QKV and residual GEMMs of up to 512 rows whose blocks fit one round (with the reduce kernels behind both: ~1B QKV at
+//     288 rows 18.6 -> 16.6 us, ~3B down at 257 rows 36.2 -> 33.5, ~8B QKV in hi + lo parts at 272 rows 53.1 -> 49.2);
 //   * streaming blocks of 96 to 192 rows (plain activations; 96 or 128 in hi + lo parts), SwiGLU of up to 640 rows (~8B width at 320 rows:
-//     block kernel, 512 padded rows, 108 us, 2 x 160 rows 86; at 576 rows 189 and 163; in hi + lo parts at 576 rows 310 and 285;
-//     above, where it needs two rounds, it falls behind: ~1B at 1536 rows 112 and 138, at 704 53 and 59).
+//     block kernel, 512 padded rows, 100 us, 2 x 160 rows 89; at 576 rows 185 and 180; in hi + lo parts at 576 rows 307 and 285).
 enum ManyRows { MANY_BLOCK, MANY_TILE, MANY_STREAM };
 struct ManyPlan { ManyRows kernel; BlockPlan block; int stream_tm; float us; };
 
 template <int EPI>
 static float tile_us(int M, int N, int K, bool split, size_t ws_bytes) {
-    static constexpr struct { float lo, full, fixed; } kTile[2][2] = {{{0.357f, 0.372f, 2.3f}, {0.429f, 0.60f, 1.75f}},      // step of 64 k: 64-row blocks,
-                                                                      {{0.465f, 0.579f, 3.7f}, {0.756f, 1.066f, 2.4f}}};     // 128-row blocks; plain, split
+    static constexpr struct { float lo, full, fixed, whole, qkv; } kTile[2][2] = {      // [128-row blocks][split]; a step is 64 k
+        {{0.328f, 0.372f, 5.6f, 5.1f, 0.4f}, {0.492f, 0.567f, 6.1f, 5.0f, 0.4f}}, {{0.346f, 0.620f, 7.0f, 12.2f, 1.5f}, {0.590f, 1.071f, 7.3f, 6.6f, 1.3f}}};
     const TilePlan p = plan_tile<EPI>(M, N, K, ws_bytes);
     const int rows = p.big ? 128 : 64;
     const long long blocks = (long long)((N + 127) / 128) * ((M + rows - 1) / rows) * p.ks;
     if (blocks > 256) return 1e30f;
     const auto& t = kTile[p.big][split];
     const float us = t.fixed + K / p.ks / 64 * (t.lo + (t.full - t.lo) * blocks / 256);
-    return us + (EPI == EPI_QKV || p.ks > 1 ? gemm_reduce_us((Epilogue)EPI, M, N, p.ks, false) : 6.4f + gemm_partials_us(M, false));
+    if (EPI == EPI_QKV) return us + t.qkv + gemm_reduce_us(EPI_QKV, M, N, p.ks, false);
+    return us + (p.ks > 1 ? gemm_reduce_us(EPI_RESIDUAL, M, N, p.ks, false) : t.whole + gemm_partials_us(M, false));
 }
 
 // SwiGLU streaming blocks of 32 tm rows x 128 columns of gate and of up, one on a CU at a time
 static float stream_us(int M, int N, int K, bool split, int tm) {
     const long long blocks = (long long)((N + 127) / 128) * ((M + 32 * tm - 1) / (32 * tm)), rest = blocks % 256;
-    const float step = split ? 0.324f + 0.361f * tm : 0.148f + 0.218f * tm, fixed = split ? 11.0f : 11.4f, lo = split ? 0.63f : 0.71f;
+    const float step = split ? 0.44f * tm : 0.076f + 0.239f * tm, fixed = split ? 13.6f : 12.6f, lo = split ? 0.65f : 0.71f;
     return blocks / 256 * (step * (K / 64) + fixed) + (rest ? step * (lo + (1.f - lo) * rest / 256) * (K / 64) + fixed : 0.f);
 }
 
@@ -1490,14 +1490,16 @@ GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t w
 // rows, then this: ~1B 1093 -> 948, 1116 -> 986, 1142 -> 1029; ~3B 2356 -> 2199, 2453 -> 2259, 2508 -> 2471.  Hi + lo parts double what a block
 // re-reads of the activations, and the tiles stay: ~8B 4177 and 4483, 4365 and 4794, 4551 and 5135.
 // More than 256 rows, by the times that the plans expect: panels make the block kernel faster at every size, but only that kernel reads them,
-// and to 640 rows the ones made for fewer rows are ahead of it on some GEMMs.
+// and the ones made for fewer rows are ahead of it where its third row tile is mostly padding (~8B at 257 rows: rows 11.4 ms, panels 11.8) and
+// in layers much wider than d_model.  Rows where they are expected 4 % ahead, 8 % with more than 3/8 of that tile filled: over 19 layers at 17
+// row counts from 257 to 512 the calls chosen so take 0.4 % (d_model 2048 and more) and 2 % (less) longer than with the faster layout and forms.
 bool gemm_layer_panels(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes) {
     if (M <= kPanelRows) return M <= 16 || !split;
     if (M <= 256) return false;
     auto panels = [&](Epilogue epi, int N, int K) { return plan_gemm_block(epi, M, N, K, split, true, ws_bytes).us; };
     const float rows = plan_many<EPI_QKV>(M, qkv, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, qdim, split, ws_bytes).us +
                        plan_many<EPI_SWIGLU>(M, d_ff, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, d_ff, split, ws_bytes).us;
-    return panels(EPI_QKV, qkv, d_model) + panels(EPI_RESIDUAL, d_model, qdim) + panels(EPI_SWIGLU, d_ff, d_model) + panels(EPI_RESIDUAL, d_model, d_ff) < rows;
+    return panels(EPI_QKV, qkv, d_model) + panels(EPI_RESIDUAL, d_model, qdim) + panels(EPI_SWIGLU, d_ff, d_model) + panels(EPI_RESIDUAL, d_model, d_ff) < (M <= 304 ? 1.04f : 1.08f) * rows;
 }
 
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s) {

@@ -428,32 +428,56 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
 
 // ------------------------------------------------------------------------------ planning
 // 128 x 256 blocks of plain activations, more of them than CUs: two on a CU (three stages of LDS each), so that one's epilogue runs under the
-// other's products (SwiGLU, ~1B at 4096 rows: 256 x 256 blocks 285 us, these 260; QKV, ~3B at 4666 rows, one on a CU 171, these 150).
+// other's products (~1B at 4096 rows, SwiGLU 285 us one on a CU, 247 two; ~3B QKV at 4666 rows 156 and 145, in 256 x 256 blocks 166).
 // With no more than a CU each the fourth stage is worth more (2048 x 8192 at 4096 rows: 118 us, with three stages 127).
 static bool two_on_a_cu(long long blocks, bool split) { return blocks > 256 && !split; }
 
-// Tile shapes and their times in microseconds, with A in rows and in panels, fitted to the four GEMMs of decoder layers (d_model 2048-5120 and
-// 2048-4096) at 27 and 21 row counts from 257 to 4666, every shape and slice count.  A block's step is 32 k.
+// Tile shapes and their times in microseconds, a block's step being 32 k.  Up to 512 rows, where launches are one round or a part of one: kernel
+// times inside models of 4-12 layers, fitted to the four GEMMs of 19 decoder layers (d_model 192-5120, plain and split activations), every
+// shape and slice count at 27 row counts from 257 to 1024, and the logits of 5 matrices; forms near the fastest and layers of 2048
+// and wider weigh most (half of the forms within 25 % of the fastest are within 3 % of it).  More rows, all in panels, whole rounds at the
+// clock that power leaves: the three GEMM classes of layers of 2048-4096 at 21 row counts from 257 to 4666.
 struct BlockShape {
     int bm, bn, capacity;             // capacity: blocks that run at once
-    float end_swiglu, end_other, end_sliced;      // fused epilogues; raw products to a slab
     struct Times {
+        struct { float swiglu, store, qkv, residual, slab; } end;      // a block's prologue and end: fused epilogues, raw products to a slab
         float lo, half, full;         // a step with few blocks at work, with one on every CU (two run on a CU), at capacity
-        float fixed;                  // a block's prologue and end
         float padding;                // share of the time that rows past M cost (they re-read the last row: L2 hits)
         float tail;                   // what a partial round behind whole ones takes of its time alone
-    } plain, split;
+        float crowd;                  // raw products of two blocks on a CU, as a multiple of one's alone
+    } times[3][2];                    // [A in rows; in panels, up to 512 rows; more][split]
 };
 static constexpr int kBlockShapes = 4;                       // 3: 128 x 256, two on a CU with three stages each (plain activations)
-static constexpr BlockShape kShapes[2][kBlockShapes] = {
-    {{256, 256, 256, 11.f, 27.f, 0.f, {0.54f, 0.f, 0.836f, 3.0f, 0.79f, 1.f}, {0.97f, 0.f, 1.62f, 3.7f, 0.87f, 1.f}},
-     {128, 256, 256, 5.4f, 13.2f, 0.f, {0.41f, 0.f, 0.505f, 2.4f, 0.44f, 1.f}, {0.49f, 0.f, 0.836f, 2.9f, 0.74f, 1.f}},
-     {128, 128, 512, 0.f, 10.3f, 0.f, {0.257f, 0.321f, 0.58f, 2.75f, 0.42f, 0.85f}, {0.416f, 0.576f, 0.984f, 2.3f, 0.53f, 0.95f}},
-     {128, 256, 512, 0.f, 0.f, 0.f, {}, {}}},
-    {{256, 256, 256, 1.6f, 14.f, 4.3f, {0.419f, 0.f, 0.755f, 6.2f, 0.97f, 0.98f}, {0.809f, 0.f, 1.538f, 4.8f, 0.94f, 0.90f}},
-     {128, 256, 256, 3.0f, 7.5f, 1.8f, {0.278f, 0.f, 0.411f, 5.6f, 0.95f, 0.77f}, {0.42f, 0.f, 0.738f, 6.5f, 0.91f, 0.95f}},
-     {128, 128, 512, 0.f, 1.5f, 1.1f, {0.222f, 0.27f, 0.485f, 3.9f, 0.71f, 0.87f}, {0.361f, 0.479f, 0.932f, 1.f, 0.77f, 0.99f}},
-     {128, 256, 512, 0.f, 0.2f, 3.5f, {0.268f, 0.468f, 0.877f, 2.8f, 0.57f, 0.98f}, {}}}};
+static constexpr int kFewRounds = 512;
+static constexpr BlockShape kShapes[kBlockShapes] = {
+    {256, 256, 256,
+     {{{{11.3f, 17.f, 20.f, 45.f, 14.3f}, 0.381f, 0.f, 0.883f, 0.73f, 1.f, 1.f},
+       {{13.5f, 20.f, 21.f, 50.f, 14.4f}, 0.667f, 0.f, 1.558f, 0.85f, 1.03f, 1.f}},
+      {{{11.3f, 17.f, 20.f, 45.f, 14.3f}, 0.297f, 0.f, 0.79f, 0.9f, 1.05f, 1.f},
+       {{13.5f, 20.f, 21.f, 50.f, 14.4f}, 0.525f, 0.f, 1.505f, 0.9f, 1.01f, 1.f}},
+      {{{7.8f, 20.2f, 20.2f, 20.2f, 10.5f}, 0.419f, 0.f, 0.755f, 0.97f, 0.98f, 1.f},
+       {{6.4f, 18.8f, 18.8f, 18.8f, 9.1f}, 0.809f, 0.f, 1.538f, 0.94f, 0.9f, 1.f}}}},
+    {128, 256, 256,
+     {{{{7.5f, 8.f, 11.f, 23.f, 8.6f}, 0.341f, 0.f, 0.55f, 0.5f, 0.96f, 1.f},
+       {{8.8f, 9.5f, 13.6f, 24.2f, 9.f}, 0.391f, 0.f, 0.852f, 0.68f, 1.05f, 1.f}},
+      {{{7.8f, 8.3f, 11.4f, 23.9f, 8.9f}, 0.263f, 0.f, 0.483f, 0.9f, 0.97f, 1.f},
+       {{9.2f, 9.9f, 14.1f, 25.2f, 9.4f}, 0.338f, 0.f, 0.817f, 0.9f, 1.02f, 1.f}},
+      {{{8.6f, 13.1f, 13.1f, 13.1f, 7.4f}, 0.278f, 0.f, 0.411f, 0.95f, 0.77f, 1.f},
+       {{9.5f, 14.f, 14.f, 14.f, 8.3f}, 0.42f, 0.f, 0.738f, 0.91f, 0.95f, 1.f}}}},
+    {128, 128, 512,
+     {{{{0.f, 5.6f, 7.5f, 11.9f, 5.4f}, 0.222f, 0.353f, 0.582f, 0.56f, 0.95f, 1.59f},
+       {{0.f, 6.f, 9.f, 12.1f, 5.5f}, 0.366f, 0.583f, 0.94f, 0.56f, 0.96f, 1.49f}},
+      {{{0.f, 5.7f, 7.7f, 12.1f, 5.5f}, 0.169f, 0.319f, 0.473f, 0.9f, 1.01f, 1.55f},
+       {{0.f, 6.1f, 9.2f, 12.3f, 5.6f}, 0.271f, 0.527f, 0.794f, 0.9f, 1.05f, 1.43f}},
+      {{{3.9f, 5.4f, 5.4f, 5.4f, 5.f}, 0.222f, 0.27f, 0.485f, 0.71f, 0.87f, 1.f},
+       {{1.f, 2.5f, 2.5f, 2.5f, 2.1f}, 0.361f, 0.479f, 0.932f, 0.77f, 0.99f, 1.f}}}},
+    {128, 256, 512,
+     {{{{6.2f, 6.f, 9.6f, 22.f, 7.8f}, 0.418f, 0.586f, 0.974f, 0.68f, 0.91f, 1.37f},
+       {}},
+      {{{6.4f, 6.2f, 9.9f, 22.7f, 8.f}, 0.332f, 0.553f, 0.844f, 0.9f, 1.05f, 1.28f},
+       {}},
+      {{{2.8f, 3.f, 3.f, 3.f, 6.3f}, 0.268f, 0.468f, 0.877f, 0.57f, 0.98f, 1.f},
+       {}}}}};
 
 // QKV slabs much beyond the L2s are slow to add up (the K and V of the sum are scattered into pages): 5120 x 7168 at 3072 rows, two slices
 // of 88 MB, 311 us, whole 251.  (Residual slabs pay up to 280 MB: 13824 x 5120 at 3520 rows, four slices 542 us, whole 641.)
@@ -461,17 +485,20 @@ static constexpr size_t kMaxQkvSlabs = 96u << 20;
 
 float gemm_reduce_us(Epilogue epi, int M, int N, int ks, bool panels) {
     const float mb = M * (float)N * 4e-6f;
-    if (epi == EPI_QKV) return panels ? 1.9f + (0.141f * ks + 0.15f) * mb : 4.7f + (0.287f * ks + 0.306f) * mb;
-    return panels ? 2.4f + (0.145f * ks + 0.344f) * mb : 3.f + (0.371f * ks + 0.226f) * mb;
+    if (panels && M > kFewRounds) return epi == EPI_QKV ? 1.9f + (0.141f * ks + 0.15f) * mb : 2.4f + (0.145f * ks + 0.344f) * mb;
+    if (epi == EPI_QKV) return 3.2f + (0.13f * ks + 0.15f) * mb;
+    return panels ? 4.f + (0.122f * ks + 0.3f) * mb : 4.1f + (0.088f * ks + 0.215f) * mb;
 }
 
-float gemm_partials_us(int M, bool panels) { return panels ? std::min(1e-3f * M, 2.f) : std::min(4e-3f * M, 7.f); }
+float gemm_partials_us(int M, bool panels) { return !panels ? std::min(3e-3f * M, 4.f) : M > kFewRounds ? std::min(1e-3f * M, 2.f) : 0.5f; }
 
 BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, bool panels, size_t ws_bytes) {
     BlockPlan best{-1, 1, 0.f};
-    for (int c = 0; c < (panels && !split ? 4 : 3); ++c) {
-        const BlockShape& s = kShapes[panels][c];
-        const BlockShape::Times& t = split ? s.split : s.plain;
+    const bool few = panels && M <= kFewRounds;
+    for (int c = 0; c < (split ? 3 : 4); ++c) {
+        const BlockShape& s = kShapes[c];
+        const BlockShape::Times& t = s.times[!panels ? 0 : few ? 1 : 2][split];
+        const float fused = epi == EPI_SWIGLU ? t.end.swiglu : epi == EPI_STORE_F32 ? t.end.store : epi == EPI_QKV ? t.end.qkv : t.end.residual;
         const int on = epi == EPI_SWIGLU ? s.bn / 2 : s.bn, gy = (M + s.bm - 1) / s.bm;
         if (epi == EPI_SWIGLU && c == 2) continue;           // gate and up of 64 columns: not built
         for (int ks = 1; ks <= 4; ++ks) {
@@ -479,17 +506,21 @@ BlockPlan plan_gemm_block(Epilogue epi, int M, int N, int K, bool split, bool pa
                            (size_t)ks * M * N * sizeof(float) > (epi == EPI_QKV ? std::min(ws_bytes, kMaxQkvSlabs) : ws_bytes)))
                 continue;
             const long long blocks = (long long)((N + on - 1) / on) * gy * ks, rounds = blocks / s.capacity, rest = blocks % s.capacity;
-            if (panels && !split && (c == 1 || c == 3) && two_on_a_cu(blocks, split) != (c == 3)) continue;
-            // (QKV with A in rows: 2 us less than fitted - in a model the residual GEMM before it is mostly sliced, which leaves fewer partial sums)
-            const float steps = K / ks / 32, end = t.fixed + (ks > 1 ? s.end_sliced : (epi == EPI_SWIGLU ? s.end_swiglu : s.end_other) - (epi == EPI_QKV && !panels ? 2.f : 0.f));
-            float us = rounds * (t.full * steps + end);
+            // two on a CU: in rows only whole (raw products gained nothing anywhere: ~3B QKV, O and down at 640-1024 rows 0-20 % behind)
+            if (c == 3 && !panels && ks > 1) continue;
+            if ((c == 1 || c == 3) && (panels || ks == 1) && two_on_a_cu(blocks, split) != (c == 3)) continue;
+            // (slices are for CUs without a block: ~3B QKV in hi + lo parts, 320 rows, four slices on 480 blocks 40.2 us, two on 240 33.6)
+            if (few && c == 2 && ks > 1 && blocks > 256) continue;
+            const float steps = K / ks / 32, end = ks > 1 ? t.end.slab : fused, crowd = ks > 1 ? t.crowd : 1.f;
+            float us = rounds * (t.full * steps + crowd * end);
             if (rest) {
                 const float step = s.capacity == 256 ? t.lo + (t.full - t.lo) * rest / 256
                                    : rest <= 256     ? t.lo + (t.half - t.lo) * rest / 256 : t.full;
-                us += (step * steps + end) * (rounds ? t.tail : 1.f);
+                us += (step * steps + (rest > 256 ? crowd : 1.f) * end) * (rounds ? t.tail : 1.f);
             }
             us *= t.padding + (1.f - t.padding) * M / (gy * s.bm);
             us += ks > 1 ? gemm_reduce_us(epi, M, N, ks, panels) : epi == EPI_RESIDUAL ? gemm_partials_us(M, panels) : 0.f;
+            if (few) us *= 1.f + 0.015f * (ks - 1);          // of forms that come out alike, more slices were mostly the slower ones
             if (best.shape < 0 || us < best.us) best = {c, ks, us};
         }
     }

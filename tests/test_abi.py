@@ -163,3 +163,10 @@ def test_panel_plans_are_launchable():
         few = name != "8b"                      # (the ~8B shape splits its activations)
         assert [B.ax_dbg_layer_panels(cfg, r) for r in (1, 16, 17, 32, 33, 256, 1024, 4096)] == [True, True, few, few, False, False, True, True]
     assert not B.ax_dbg_layer_panels(B.make_config(I.SHAPES["tiny"], 1024, 64), 9)
+
+
+@pytest.mark.parametrize("name,rows", [("1b", 288), ("3b", 304), ("8b", 288)])
+def test_rows_or_panels_as_measured(name, rows):
+    """Whole calls of 257 rows: in rows 1665 / 3834 / 11390 us, in panels 1759 / 3925 / 11780; of 384 rows panels are 1-4 % ahead."""
+    cfg = B.make_config(I.SHAPES[name], 8192, 4096)
+    assert [B.ax_dbg_layer_panels(cfg, r) for r in (257, rows, 336, 384, 512, 1024)] == [False, False, True, True, True, True]

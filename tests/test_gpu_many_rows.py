@@ -135,13 +135,14 @@ def test_block_gemm(torch, block, epi, split, slices, hd, K):
 
 # what the plan picks, and a call that reaches it: (epilogue, M, N, K, plan); few-column cases of every tile, slice count and kernel
 PLANNED = [
-    (RESIDUAL, 257, 320, 64, ("tile", 64, 128, 1)), (RESIDUAL, 257, 320, 1024, ("tile", 64, 128, 2)),
-    (RESIDUAL, 449, 4160, 64, ("tile", 128, 128, 1)), (RESIDUAL, 500, 1600, 8192, ("tile", 128, 128, 4)),
+    (RESIDUAL, 300, 320, 64, ("tile", 64, 128, 1)), (RESIDUAL, 321, 320, 1024, ("tile", 64, 128, 2)), (RESIDUAL, 257, 320, 4096, ("tile", 64, 128, 8)),
+    (RESIDUAL, 500, 3136, 4096, ("tile", 128, 128, 2)), (RESIDUAL, 500, 1600, 8192, ("tile", 128, 128, 4)),
     (RESIDUAL, 513, 320, 64, ("block", 128, 128, 1)), (RESIDUAL, 513, 320, 2048, ("block", 128, 128, 4)),
-    (RESIDUAL, 449, 4160, 1024, ("block", 128, 256, 2)), (RESIDUAL, 500, 4160, 4096, ("block", 256, 256, 4)),
-    (SWIGLU, 257, 320, 64, ("block", 128, 256, 1)), (SWIGLU, 385, 14400, 64, ("block", 256, 256, 1)),
-    (SWIGLU, 500, 320, 1024, ("stream", 96, 256, 1)), (SWIGLU, 257, 14400, 64, ("stream", 160, 256, 1)),
-    (SWIGLU, 321, 14400, 64, ("stream", 192, 256, 1))]
+    (RESIDUAL, 513, 3840, 2048, ("block", 128, 256, 2)), (RESIDUAL, 513, 14400, 64, ("block", 128, 256, 1)),      # (285 blocks: two on a compute unit)
+    (RESIDUAL, 500, 4160, 4096, ("block", 256, 256, 4)),
+    (SWIGLU, 257, 320, 64, ("block", 128, 256, 1)), (SWIGLU, 321, 11072, 512, ("block", 256, 256, 1)),
+    (SWIGLU, 500, 320, 3072, ("stream", 96, 256, 1)), (SWIGLU, 257, 14400, 1024, ("stream", 160, 256, 1)),
+    (SWIGLU, 513, 10240, 3072, ("stream", 192, 256, 1))]
 
 
 @pytest.mark.parametrize("epi,M,N,K,plan", PLANNED)
@@ -175,23 +176,28 @@ def test_many_row_gemm_seeded_random_shapes(torch, M, N, K, epi):
     T.test_bf16_gemm(torch, M, N, K, epi)
 
 
-# one layer, hi + lo activations or not: shapes whose four GEMMs (QKV, O, gate / up, down) take these kernels
+# one layer, hi + lo activations or not, and the kernels of its four GEMMs (QKV, O, gate / up, down): layers that keep rows, and layers in panels
 LAYERS = [
-    ((256, 4, 2, 64, 320, 300, 0), ("tile", "tile", "block", "tile")), ((2048, 4, 2, 64, 320, 640, 1), ("block", "block", "stream", "block")),
-    ((1024, 8, 4, 64, 320, 500, 0), ("tile", "tile", "stream", "tile"))]
+    ((384, 4, 2, 64, 2816, 257, 1), ("tile", "block", "block", "tile")), ((384, 8, 2, 64, 2816, 257, 1), ("tile", "tile", "block", "tile")),
+    ((704, 4, 2, 64, 14336, 320, 0), ("block", "tile", "stream", "tile")), ((2048, 16, 4, 128, 1088, 257, 1), ("tile", "block", "block", "block"))]
+PANEL_LAYERS = [
+    ((256, 4, 2, 64, 320, 310, 0), ((128, 128, 1), (128, 128, 1), (128, 256, 1), (128, 128, 1))),
+    ((2048, 4, 2, 64, 320, 640, 1), ((128, 128, 4), (128, 128, 1), (128, 256, 1), (128, 128, 1))),
+    ((1024, 8, 4, 64, 320, 500, 0), ((128, 128, 2), (128, 128, 1), (128, 256, 1), (128, 128, 1)))]
 
 
-@pytest.mark.parametrize("dims,kernels", LAYERS)
-def test_layer_of_planned_gemms(torch, dims, kernels):
+@pytest.mark.parametrize("dims,plans", LAYERS + PANEL_LAYERS)
+def test_layer_of_planned_gemms(torch, dims, plans):
     import test_gpu_kernels as T
     from paper_2605_10380_amd import binding as B
     d, hq, hkv, hd, F, rows, split = dims
-    qkv = (hq + 2 * hkv) * hd
+    qkv, in_panels = (hq + 2 * hkv) * hd, not isinstance(plans[0], str)
     ws = rows * max(8 * d, qkv) * 4
-    got = tuple(B.ax_dbg_gemm_plan(e, rows, n, k, bool(split), ws)[0]
-                for e, n, k in ((QKV, qkv, d), (RESIDUAL, d, hq * hd), (SWIGLU, F, d), (RESIDUAL, d, F)))
-    assert got == kernels
     sh = I.DecoderShape("planned", 1, d, hq, hkv, hd, F, 512, "bf16")
+    assert B.ax_dbg_layer_panels(B.make_config(sh, rows + 16, rows, 1, split), rows) == in_panels
+    gemms = ((QKV, qkv, d), (RESIDUAL, d, hq * hd), (SWIGLU, F, d), (RESIDUAL, d, F))
+    plan = B.ax_dbg_panel_plan if in_panels else lambda *a: B.ax_dbg_gemm_plan(*a)[0]
+    assert tuple(plan(e, rows, n, k, bool(split), ws) for e, n, k in gemms) == plans
     attn, attn_ref, x, x_ref = T._one_layer(torch, sh, 0, rows, 24, rows, split)
     assert np.abs(attn - attn_ref).max() <= 4e-3 * np.abs(attn_ref).max()
     assert np.abs(x - x_ref).max() <= 4e-3 * np.abs(x_ref).max()
