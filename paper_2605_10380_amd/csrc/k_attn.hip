@@ -794,7 +794,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     constexpr int NQ = ITEMS ? 4 : 1;                          // tiles per group
     constexpr int PS = HD * 32 + 64, CPT = HD / 8, SU = 4;
     const int Hkv = a.kv.n_kv_heads, G = a.Hq / Hkv;
-    const int t = blockIdx.x % NQ, hk = (blockIdx.x / NQ) % Hkv, tile = blockIdx.x / (NQ * Hkv);
+    // a head's tiles on one XCD (with 8 KV heads), the one whose attn_block_kernel left their records: tiles of a group end inside each other's
+    // lines of a panel, and spread over XCDs every such line was written in parts (~3B, T = 1024 over 6144 keys: 11.15 -> 10.6 us)
+    const int hk = blockIdx.x % Hkv, t = (blockIdx.x / Hkv) % NQ, tile = blockIdx.x / (NQ * Hkv);
     const int ql = threadIdx.x & 31, cg = threadIdx.x >> 5;
     const int4 ti0 = *(const int4*)(a.tile_info + tile * 8);
     const int row0 = a.tile_info[tile * 8 + 4];
