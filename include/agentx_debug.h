@@ -30,8 +30,8 @@ ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps
 ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char **kernel, int *rows, int *cols,
                            int *slices);
 
-/* The same for activations in panels (only the block kernel reads those; M > 256, N % 64 == 0), and whether a call of that many rows of a
- * model keeps its layers' activations so: 1 or 0.  Host only. */
+/* The same for activations in panels (M > 256, N % 64 == 0: only the block kernel reads those), and whether a call of that many rows of a
+ * model keeps its layers' activations in panels: 1 or 0 (up to 32 rows the few-row kernel reads them).  Host only. */
 ax_status ax_dbg_panel_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int *rows, int *cols, int *slices);
 ax_status ax_dbg_layer_panels(const ax_model_config *cfg, int rows, int *panels);
 

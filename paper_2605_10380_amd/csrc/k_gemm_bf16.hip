@@ -6,13 +6,14 @@
 // bf16 one.  Reason: bf16 activations (8 significant bits) put the logits of a 16-layer decoder
 // ~0.05 away from the exact result; fp16 activations (11 bits) keep them within 0.01.
 //
-//   * skinny kernel (M <= 16, the O projection and narrow stores to 32: verify steps, pure weight streaming): one block owns 16 output
-//     columns, its wavefronts split K, W goes HBM -> registers -> v_mfma_f32_16x16x32_f16
-//     with no LDS in the streaming loop; the per-wavefront partial sums meet in LDS.
-//   * tile kernel   (more rows, to 256, and some launches of up to 512): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
+//   * skinny kernel (up to 16 rows; to 32 the four GEMMs of a layer with plain activations, of one with hi + lo parts the O projection
+//     only, and narrow stores: verify steps, pure weight streaming): one block owns 16 output columns, its wavefronts split K,
+//     W goes HBM -> registers -> v_mfma_f32_16x16x32_f16 with no LDS in the streaming loop; the per-wavefront partial sums meet in LDS.
+//   * tile kernel   (33-256 rows, hi + lo parts from 17, and some launches of up to 512): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
 //     v_mfma_f32_32x32x16_f16, global loads several K slices ahead.
 //   * stream kernel (logits from 17 rows, SwiGLU at 193-256 rows of wide matrices and some launches of up to 640, and - over K slices -
-//     the SwiGLU GEMM of 17-192 rows and the down projection of 129-192): activations through LDS, weights straight into MFMA operands.
+//     the SwiGLU GEMM of 33-192 rows, hi + lo parts from 17, and the down projection of 129-192): activations through LDS, weights
+//     straight into MFMA operands.
 //     The launcher states each crossover with the figures behind it.
 //   * block kernel  (more than 256 rows; k_gemm_block.hip; which of the three, plan_many below).
 //
@@ -735,6 +736,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
 template <int EPI, int MT, int NW, int COLS = 16, bool SPLIT = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, NW >= 8 ? 4 : 8)))
 void gemm_bf16_skinny_kernel(GemmArgs g) {
+    static_assert(MT <= 2, "up to 32 rows");
     constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
     constexpr int NA = SPLIT ? 2 : 1;
     __shared__ __attribute__((aligned(16))) f32x4 red[NW][NB][MT][64];
@@ -780,7 +782,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     // pulled 16 GB/s of weights against 26 GB/s from 16-column blocks.  So the upper half of each
     // 16-lane row fetches the block's 8 rows at the NEXT k-step (one chunk further), and for that
     // step the operand is shifted down 8 lanes; MFMA rows 8-15 then hold products nobody reads.
-    constexpr bool DUAL = COLS == 8 && MT <= 2 && NB == 1;
+    constexpr bool DUAL = COLS == 8 && NB == 1;
     const unsigned wod = (unsigned)(packed_row(min(n0 + (lr & 7), N - 1), K) - first_panel + lg * PK_KG + (lr >> 3) * PK_CHUNK) * 2u;
     auto weights = [&](const char* base, unsigned off, int k) { return (const u32x4*)(base + (long long)k * 32 + off); };
     // A in panels (act_index): a row tile is one of them.  32 k of 9 rows are 576 bytes in a row, 4 or 5 lines instead of 9 halves.
@@ -827,11 +829,11 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     }
 
     // The same for the partial sums of x^2 behind the deferred RMSNorm: wavefront w turns those of
-    // rows w, w + NW, .. into 1 / rms after the K loop, from registers filled here (up to 16 rows, 256
-    // partials per row and 4 rows per wavefront; anything larger is fetched after the loop).
+    // rows w, w + NW, .. into 1 / rms behind its first operands, from registers filled here (up to 256 partials per
+    // row and 4 rows per wavefront; anything larger is fetched after the loop).
     constexpr int RPW = (MT * 16 + NW - 1) / NW;
     constexpr bool NORMED = EPI != EPI_RESIDUAL;           // (what a residual GEMM reads awaits no norm)
-    constexpr bool PRE_SSQ = NORMED && MT <= 2 && RPW <= 4;
+    constexpr bool PRE_SSQ = NORMED && RPW <= 4;
     float pre_ss[PRE_SSQ ? RPW : 1][4];
     const bool pre_ssq = PRE_SSQ && g.ssq && g.nparts <= 256;
     if constexpr (PRE_SSQ) {                               // (no branch around the loads, see below: without a norm something else is read, and not used)
@@ -877,103 +879,76 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     // before trip i is multiplied (two register sets), so a wavefront always has a trip's worth
     // of loads (U KB of weights) in flight while its matrix pipe is busy.
     int k = kbeg;
-    if constexpr (MT <= 2) {
-        constexpr int U = 4, S = 32 * U;
-        u32x4 rw[2][NB][DUAL ? U / 2 : U];
-        f16x8 fx[2][NA][MT][U];
-        auto loads = [&](int set, int kk) {
-            if constexpr (DUAL) {
+    constexpr int U = 4, S = 32 * U;
+    u32x4 rw[2][NB][DUAL ? U / 2 : U];
+    f16x8 fx[2][NA][MT][U];
+    auto loads = [&](int set, int kk) {
+        if constexpr (DUAL) {
 #pragma unroll
-                for (int v = 0; v < U / 2; ++v) rw[set][0][v] = __builtin_nontemporal_load(weights(wb, wod, kk + 64 * v));
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    rw[set][0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load(weights(wb, wo, kk + 32 * u)) : (u32x4){0u, 0u, 0u, 0u};
-                    if (NB == 2) rw[set][NB - 1][u] = __builtin_nontemporal_load(weights(wb2, wo, kk + 32 * u));
-                }
-            }
-            // activation rows past M: the last row's address again, which costs no line of its own (a block re-reads its wavefronts' whole
-            // activation slice, at 9 rows of 16 most of what the CU's load pipeline carries); their products go nowhere.  A branch around
-            // the loads instead, and the compiler no longer knows how many are out: it waited for all of them ahead of the second trip.
-#pragma unroll
-            for (int t = 0; t < MT; ++t)
-#pragma unroll
-                for (int p = 0; p < NA; ++p)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) fx[set][p][t][u] = *acts(t, p, kk + 32 * u);
-        };
-        auto compute = [&](int set) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    u32x4 raw = rw[set][b][DUAL ? u >> 1 : u];
-                    if (DUAL && (u & 1)) {                 // odd k-step: lanes 8-15 of each row hold it; row_shl:8 brings it to lanes 0-7
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) raw[i] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)raw[i], 0x108, 0xf, 0xf, true);
-                    }
-                    const f16x8 fw = __builtin_bit_cast(f16x8, raw);
-#pragma unroll
-                    for (int t = 0; t < MT; ++t)
-#pragma unroll
-                        for (int p = 0; p < NA; ++p)
-                            acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw, fx[set][p][t][u], acc[b][t], 0, 0, 0);
-                }
-        };
-        const int ntr = kslice / S;
-        auto issue = [&](int set, int trip) {                        // all of a trip's loads, before anything that follows
-            loads(set, kbeg + trip * S);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        if (ntr > 0) {
-            issue(0, 0);
-            request_angles();
-            if (pre_ssq) finish_pre_ssq();
-            int t = 0;
-            for (; t + 2 < ntr; t += 2) {                            // both loads unconditional
-                issue(1, t + 1);
-                compute(0);
-                issue(0, t + 2);
-                compute(1);
-            }
-            if (t + 1 < ntr) {
-                issue(1, t + 1);
-                compute(0);
-                compute(1);
-            } else {
-                compute(0);
-            }
+            for (int v = 0; v < U / 2; ++v) rw[set][0][v] = __builtin_nontemporal_load(weights(wb, wod, kk + 64 * v));
         } else {
-            request_angles();
-            if (pre_ssq) finish_pre_ssq();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                rw[set][0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load(weights(wb, wo, kk + 32 * u)) : (u32x4){0u, 0u, 0u, 0u};
+                if (NB == 2) rw[set][NB - 1][u] = __builtin_nontemporal_load(weights(wb2, wo, kk + 32 * u));
+            }
         }
-        k = kbeg + ntr * S;
+        // activation rows past M: the last row's address again, which costs no line of its own (a block re-reads its wavefronts' whole
+        // activation slice, at 9 rows of 16 most of what the CU's load pipeline carries); their products go nowhere.  A branch around
+        // the loads instead, and the compiler no longer knows how many are out: it waited for all of them ahead of the second trip.
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int p = 0; p < NA; ++p)
+#pragma unroll
+                for (int u = 0; u < U; ++u) fx[set][p][t][u] = *acts(t, p, kk + 32 * u);
+    };
+    auto compute = [&](int set) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                u32x4 raw = rw[set][b][DUAL ? u >> 1 : u];
+                if (DUAL && (u & 1)) {                 // odd k-step: lanes 8-15 of each row hold it; row_shl:8 brings it to lanes 0-7
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) raw[i] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)raw[i], 0x108, 0xf, 0xf, true);
+                }
+                const f16x8 fw = __builtin_bit_cast(f16x8, raw);
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int p = 0; p < NA; ++p)
+                        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw, fx[set][p][t][u], acc[b][t], 0, 0, 0);
+            }
+    };
+    const int ntr = kslice / S;
+    auto issue = [&](int set, int trip) {                        // all of a trip's loads, before anything that follows
+        loads(set, kbeg + trip * S);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (ntr > 0) {
+        issue(0, 0);
+        request_angles();
+        if (pre_ssq) finish_pre_ssq();
+        int t = 0;
+        for (; t + 2 < ntr; t += 2) {                            // both loads unconditional
+            issue(1, t + 1);
+            compute(0);
+            issue(0, t + 2);
+            compute(1);
+        }
+        if (t + 1 < ntr) {
+            issue(1, t + 1);
+            compute(0);
+            compute(1);
+        } else {
+            compute(0);
+        }
     } else {
         request_angles();
-        for (; k + 128 <= kend; k += 128) {
-            static_assert(!SPLIT, "more than two row tiles: not instantiated with split activations");
-            u32x4 rw[NB][4];
-            f16x8 fx[MT][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                rw[0][u] = (COLS == 16 || wlane) ? __builtin_nontemporal_load(weights(wb, wo, k + 32 * u)) : (u32x4){0u, 0u, 0u, 0u};
-                if (NB == 2) rw[NB - 1][u] = __builtin_nontemporal_load(weights(wb2, wo, k + 32 * u));
-            }
-#pragma unroll
-            for (int t = 0; t < MT; ++t)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) fx[t][u] = *acts(t, 0, k + 32 * u);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const f16x8 fw = __builtin_bit_cast(f16x8, rw[b][u]);
-#pragma unroll
-                    for (int t = 0; t < MT; ++t)
-                        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw, fx[t][u], acc[b][t], 0, 0, 0);
-                }
-        }
+        if (pre_ssq) finish_pre_ssq();
     }
+    k = kbeg + ntr * S;
     for (; k < kend; k += 32) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -994,9 +969,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int t = 0; t < MT; ++t) red[wave][b][t][lane] = acc[b][t];
-    if (pre_ssq) {                       // deferred RMSNorm: the wavefronts share the rows
-        if (MT > 2) finish_pre_ssq();    // (the MT <= 2 loop did it behind its first loads)
-    } else if (NORMED && g.ssq) {
+    if (!pre_ssq && NORMED && g.ssq) {   // deferred RMSNorm, not finished behind the first loads: the wavefronts share the rows
         for (int r = wave; r < min(MT * 16, M); r += NW) {
             const float inv = wave_inv_rms(g.ssq, a_rows ? a_rows[r] : r, g.nparts, g.d_norm, g.eps, lane);
             if (lane == 0) s_inv[r] = inv;

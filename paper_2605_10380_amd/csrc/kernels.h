@@ -78,8 +78,8 @@ __host__ __device__ __forceinline__ long long act_index(bool panels, int m, int 
     return (long long)first * K + (long long)(k >> 3) * (rows * 8) + (m & 15) * 8 + (k & 7);
 }
 
-// Partial sums of x^2 behind activations that await their norm: [rows][parts], with activations in panels [parts][rows], so that a thread
-// that adds up a row reads beside its neighbours.
+// Partial sums of x^2 behind activations that await their norm: [rows][parts]; in calls of more than 256 rows with activations in panels
+// [parts][rows], so that a thread that adds up a row reads beside its neighbours (`panels` here; panels of up to 32 rows keep [rows][parts]).
 __host__ __device__ __forceinline__ long long ssq_index(bool panels, int m, int part, int M, int nparts) {
     return panels ? (long long)part * M + m : (long long)m * nparts + part;
 }
