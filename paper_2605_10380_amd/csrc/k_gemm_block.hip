@@ -1,8 +1,9 @@
 // GEMMs of many rows (bf16-weight models): C = A[M,K] * W[N,K]^T on the fp16 matrix cores, both operands staged through LDS by
 // the memory pipeline itself (global_load_lds: no registers, no ds_write in between), blocks of up to 256 x 256 outputs.
 //
-// What bounds it: power.  With all compute units at work the clock sinks until the matrix cores' energy fits (8192 x 8192 x 8192: 1373 TFLOP/s
-// on random values, 1997 on zeros, the same instructions), so what counts is energy and idle clocks around the products.
+// What bounds it: power.  With all compute units at work the clock sinks until the matrix cores' energy fits (8192 x 8192 x 8192: 1324 TFLOP/s
+// on random values at 1.65 GHz, 1764 on zeros at 2.35, the same instructions; profiles/block_gemm_8192_power.txt), so what counts is energy
+// and idle clocks around the products.
 //   * 4 wavefronts of 128 x 128 outputs: a third fewer LDS reads per product than 8 of 128 x 64, whose reads and copies together also
 //     took every clock that LDS has.  One wavefront per SIMD has nobody to fill its gaps, so the order of its instructions is written
 //     out: one LDS read or copy at most between two products, 32 clocks each.  (4096 x 16384 x 2048, store of fp16: 264 us on 8
