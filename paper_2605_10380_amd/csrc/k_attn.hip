@@ -14,6 +14,8 @@
 #include "kernels.h"
 #include "lds_copy.h"
 
+#include <type_traits>
+
 namespace ax {
 
 typedef _Float16 f16;      // activation and KV-cache type of bf16-weight models
@@ -792,7 +794,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
 template <int HD, bool ITEMS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     constexpr int NQ = ITEMS ? 4 : 1;                          // tiles per group
-    constexpr int PS = HD * 32 + 64, CPT = HD / 8, SU = 4;
+    constexpr int PS = HD * 32 + 64, CPT = HD / 8;
     const int Hkv = a.kv.n_kv_heads, G = a.Hq / Hkv;
     // a head's tiles on one XCD (with 8 KV heads), the one whose attn_block_kernel left their records: tiles of a group end inside each other's
     // lines of a panel, and spread over XCDs every such line was written in parts (~3B, T = 1024 over 6144 keys: 11.15 -> 10.6 us)
@@ -825,24 +827,32 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     float L = 0.f, acc[CPT];
 #pragma unroll
     for (int c = 0; c < CPT; ++c) acc[c] = 0.f;
-    for (int s0 = 0; s0 < n_splits; s0 += SU) {
-        float mv[SU], lv[SU], ov[SU][CPT];
+    // N slices from s0 on, all their loads in flight together.  (The last ones as a group of their own size: a fourth slot that repeats a slice
+    // with weight 0 would turn an infinite value into NaN.)
+    auto add = [&](auto n_, int s0) {
+        constexpr int N = decltype(n_)::value;
+        float mv[N], lv[N], ov[N][CPT];
 #pragma unroll
-        for (int i = 0; i < SU; ++i) {
-            const float* p = slice(min(s0 + i, n_splits - 1));
-            mv[i] = s0 + i < n_splits ? p[HD * 32] : -INFINITY;            // absent slice: weight 0
+        for (int i = 0; i < N; ++i) {
+            const float* p = slice(s0 + i);
+            mv[i] = p[HD * 32];
             lv[i] = p[HD * 32 + 32];
 #pragma unroll
             for (int c = 0; c < CPT; ++c) ov[i][c] = p[(cg * CPT + c) * 32];
         }
 #pragma unroll
-        for (int i = 0; i < SU; ++i) {
+        for (int i = 0; i < N; ++i) {
             const float w = exp2f(mv[i] - M);
             L += w * lv[i];
 #pragma unroll
             for (int c = 0; c < CPT; ++c) acc[c] += w * ov[i][c];
         }
-    }
+    };
+    int s0 = 0;
+    for (; s0 + 4 <= n_splits; s0 += 4) add(std::integral_constant<int, 4>{}, s0);
+    if (n_splits - s0 == 3) add(std::integral_constant<int, 3>{}, s0);
+    else if (n_splits - s0 == 2) add(std::integral_constant<int, 2>{}, s0);
+    else if (n_splits - s0 == 1) add(std::integral_constant<int, 1>{}, s0);
     const float inv = 1.0f / L;
 #pragma unroll
     for (int c0 = 0; c0 < CPT; c0 += 8) {

@@ -254,19 +254,23 @@ def test_fp32_lm_head_input_is_read_as_it_lies(B):
     dm.close()
 
 
-@pytest.mark.parametrize("T,hkv", [(1, 8), (9, 2)])
-def test_an_infinite_value_reaches_only_its_own_channel(B, T, hkv):
-    """V of one cached key is infinite in one channel, in the last of four key slices: attention is infinite there, as the float64 sum is, not
-    NaN, and unchanged everywhere else.  (The merge adds slices in groups of eight: the absent ones count nothing at all.)"""
+@pytest.mark.parametrize("T,hkv,P,key", [(1, 8, 300, 295), (9, 2, 300, 295), (96, 8, 1500, 1490)])
+def test_an_infinite_value_reaches_only_its_own_channel(B, T, hkv, P, key):
+    """V of one cached key is infinite in one channel, in the last of four (96 rows: ten) key slices: attention is infinite there, as the float64
+    sum is, not NaN, and unchanged everywhere else.  (The merges add slices in groups of eight and four: the absent ones count nothing at all.)"""
     sh = I.DecoderShape("inf", 1, 128, hkv * 4, hkv, 64, 192, 512, "bf16")
-    P = 300
-    cfg = B.make_config(sh, P + 64, 512)
-    assert B.ax_dbg_split_plan(cfg, -(-T * 4 // 32) * hkv, -(-(P + T) // 32))[1] == 4
+    cfg = B.make_config(sh, P + T + 64, 512)
+    if T == 96:
+        items, merges, slots = B.ax_dbg_attention_items(cfg, [P], [T])
+        assert (items, merges, slots) == (30, 3, 30) and key // 32 >= -(-(P + T) // 32) * 9 // 10
+    else:
+        assert B.ax_dbg_split_plan(cfg, -(-T * 4 // 32) * hkv, -(-(P + T) // 32))[1] == 4
     w = I.make_weights(sh, 6)
     toks = I.templated_prompt(sh.vocab, 6, P + T)
-    dm = B.DeviceModel(sh, w, max_pos=P + 64, max_tokens=512, pool_tokens=512)
+    dm = B.DeviceModel(sh, w, max_pos=P + T + 64, max_tokens=512, pool_tokens=-(-(P + T) // 64) * 64 + 64)
     kv = dm.new_kv()
-    dm.extend(kv, toks[:P])
+    for at in range(0, P, 512):
+        dm.extend(kv, toks[at:min(at + 512, P)])
 
     def attention():
         B.ax_kv_truncate(kv, P)
@@ -275,7 +279,7 @@ def test_an_infinite_value_reaches_only_its_own_channel(B, T, hkv):
         B.ax_dbg_read(dm.model, 3, out)
         return out
     plain = attention()
-    key, head, channel = 295, 1, 5
+    head, channel = 1, 5
     v = dm.pool_mem.view(dm.torch.float16).view(2, hkv, -1, 64, 16)[1]
     v[head, int(B.ax_kv_blocks(kv)[key // 16]), channel, key % 16] = float("inf")
     dm.torch.cuda.synchronize()
