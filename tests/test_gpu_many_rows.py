@@ -142,7 +142,12 @@ PLANNED = [
     (RESIDUAL, 500, 4160, 4096, ("block", 256, 256, 4)),
     (SWIGLU, 257, 320, 64, ("block", 128, 256, 1)), (SWIGLU, 321, 11072, 512, ("block", 256, 256, 1)),
     (SWIGLU, 500, 320, 3072, ("stream", 96, 256, 1)), (SWIGLU, 257, 14400, 1024, ("stream", 160, 256, 1)),
-    (SWIGLU, 513, 10240, 3072, ("stream", 192, 256, 1))]
+    (SWIGLU, 513, 10240, 3072, ("stream", 192, 256, 1)),
+    # few columns, short K, ragged rows on the blocks
+    (RESIDUAL, 257, 320, 64, ("block", 128, 128, 1)), (RESIDUAL, 257, 320, 1024, ("block", 128, 128, 2)),
+    (RESIDUAL, 449, 4160, 64, ("block", 128, 128, 1)), (RESIDUAL, 449, 4160, 1024, ("block", 128, 128, 1)),
+    (SWIGLU, 385, 14400, 64, ("block", 128, 256, 1)), (SWIGLU, 500, 320, 1024, ("block", 128, 256, 1)),
+    (SWIGLU, 257, 14400, 64, ("block", 128, 256, 1)), (SWIGLU, 321, 14400, 64, ("block", 128, 256, 1))]
 
 
 @pytest.mark.parametrize("epi,M,N,K,plan", PLANNED)
@@ -178,6 +183,7 @@ def test_many_row_gemm_seeded_random_shapes(torch, M, N, K, epi):
 
 # one layer, hi + lo activations or not, and the kernels of its four GEMMs (QKV, O, gate / up, down): layers that keep rows, and layers in panels
 LAYERS = [
+    ((256, 4, 2, 64, 320, 300, 0), ("block", "tile", "block", "tile")),
     ((384, 4, 2, 64, 2816, 257, 1), ("tile", "block", "block", "tile")), ((384, 8, 2, 64, 2816, 257, 1), ("tile", "tile", "block", "tile")),
     ((704, 4, 2, 64, 14336, 320, 0), ("block", "tile", "stream", "tile")), ((2048, 16, 4, 128, 1088, 257, 1), ("tile", "block", "block", "block"))]
 PANEL_LAYERS = [
