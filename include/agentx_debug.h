@@ -31,7 +31,7 @@ ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t 
                            int *slices);
 
 /* The same for activations in panels (M > 256, N % 64 == 0: only the block kernel reads those), and whether a call of that many rows of a
- * model keeps its layers' activations in panels: 1 or 0 (up to 32 rows the few-row kernel reads them).  Host only. */
+ * model keeps its layers' activations in panels: 1 or 0 (rows, or strips: ax_dbg_gemm_regs).  Host only. */
 ax_status ax_dbg_panel_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int *rows, int *cols, int *slices);
 ax_status ax_dbg_layer_panels(const ax_model_config *cfg, int rows, int *panels);
 
@@ -58,6 +58,11 @@ typedef struct {
                                            rows hold them: 8 columns of a panel's rows at a time, each row's 8 side by side */
 } ax_dbg_block_gemm;
 ax_status ax_dbg_gemm_block(ax_dbg_block_gemm *args, void *hip_stream);
+/* The same on the kernel of 17 to 256 rows (any M <= 256 here): a tile of `rows` x `cols` (SwiGLU: half of them gate, half up), refused where there is
+ * no such tile; epilogues 1 to 3, slices for epilogue 1 only.  a_panels, c_panels also 2: strips, 32 columns of all rows at a time, panel after
+ * panel of 16 rows (the last one too: C16 has room for whole panels), inside them as panels; ssq and ssq_out are [n_parts][M] beside strips and
+ * beside panels of more than 32 rows. */
+ax_status ax_dbg_gemm_regs(ax_dbg_block_gemm *args, void *hip_stream);
 
 /* Work of the attention of one call of long extends (n sequences of P cached and T new tokens): items (128 stacked rows x a range of keys),
  * groups of rows whose keys several items share, and the partial-record slots those use per KV head.  Host only. */

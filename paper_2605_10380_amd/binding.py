@@ -96,6 +96,7 @@ def _load():
         "ax_dbg_panel_plan": (C.c_int, [C.c_int] * 5 + [C.c_size_t] + [C.POINTER(C.c_int)] * 3),
         "ax_dbg_layer_panels": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.POINTER(C.c_int)]),
         "ax_dbg_gemm_block": (C.c_int, [C.POINTER(ax_dbg_block_gemm), vp]),
+        "ax_dbg_gemm_regs": (C.c_int, [C.POINTER(ax_dbg_block_gemm), vp]),
         "ax_dbg_attention_items": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int),
                                              C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_gemm": (C.c_int, [C.c_int, C.c_int, vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, vp]),
@@ -424,6 +425,13 @@ def ax_dbg_gemm_block(stream: int = 0, **args) -> int:
     """Fields of ax_dbg_block_gemm by name; returns the partial sums per row that epilogue 1 left."""
     a = ax_dbg_block_gemm(**args)
     _check(lib.ax_dbg_gemm_block(C.byref(a), C.c_void_p(stream)))
+    return a.n_parts_out
+
+
+def ax_dbg_gemm_regs(stream=0, **args) -> int:
+    """The same on the kernel of 17 to 256 rows."""
+    a = ax_dbg_block_gemm(**args)
+    _check(lib.ax_dbg_gemm_regs(C.byref(a), C.c_void_p(stream)))
     return a.n_parts_out
 
 

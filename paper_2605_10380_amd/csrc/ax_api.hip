@@ -104,19 +104,22 @@ Layout make_layout(const ax_model_config& c) {
     const size_t parts = ax::act_split_on(c) ? 2 : 1;         // hi part, then (split activations) the lo part
     const size_t qdim = (size_t)c.n_q_heads * c.head_dim;
     L.x = take(T * c.d_model * 4);
-    L.h_bytes = T * c.d_model * a;
+    const size_t TP = (T + 15) / 16 * 16;                     // rows of activations: strips hold whole panels
+    L.h_bytes = TP * c.d_model * a;
     L.h = take(parts * L.h_bytes);
     L.ssq = take(T * (size_t)(c.d_model / 8 + 1) * 4);        // sum-of-squares partials per row
     L.qkv = take(c.dtype == AX_F32 ? T * (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * 4 : 0);   // fp32 models only
-    L.q_bytes = L.attn_bytes = T * qdim * a;
+    L.q_bytes = T * qdim * a;
+    L.attn_bytes = TP * qdim * a;
     L.q = take(parts * L.q_bytes);
     L.attn = take(parts * L.attn_bytes);
-    L.ffn_bytes = T * (size_t)c.d_ff * a;
+    L.ffn_bytes = TP * (size_t)c.d_ff * a;
     L.ffn = take(parts * L.ffn_bytes);
     if (parts == 2) {
-        L.h_lo = (long long)(T * c.d_model);
-        L.q_lo = L.attn_lo = (long long)(T * qdim);
-        L.ffn_lo = (long long)(T * c.d_ff);
+        L.h_lo = (long long)(TP * c.d_model);
+        L.q_lo = (long long)(T * qdim);
+        L.attn_lo = (long long)(TP * qdim);
+        L.ffn_lo = (long long)(TP * c.d_ff);
     }
     L.partials = take(c.dtype == AX_BF16 ? 2 * L.max_records * ((size_t)c.head_dim * 32 + 64) * 4 : 0);
     // fp32 slabs of GEMMs that finish in a second kernel: K-slice partials of the residual GEMMs (SPLITK_MAX slabs of
@@ -153,7 +156,7 @@ struct ax_model {
     hipStream_t capture_stream = nullptr;
     bool use_graphs = true;
     // how the last call left its activations (ax_dbg_read hands out rows)
-    struct { int rows = 0; bool layers = false, out = false; } panels;
+    struct { int rows = 0; ax::ActLayout layers = ax::ACT_ROWS, out = ax::ACT_ROWS; } acts;
     // optional per-kernel timing (test / benchmark instrumentation, off by default)
     bool prof_on = false;
     struct ProfSpan { int cls; hipEvent_t a, b; };
@@ -495,9 +498,9 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
     return AX_OK;
 }
 
-// Whether a call of that many rows keeps the activations of its layers in panels.
-bool layer_panels(const ax_model_config& c, const Layout& L, int rows) {
-    return c.dtype == AX_BF16 && ax::gemm_layer_panels(rows, c.d_model, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim,
+// How a call of that many rows keeps the activations of its layers.
+ax::ActLayout layer_layout(const ax_model_config& c, const Layout& L, int rows) {
+    return c.dtype != AX_BF16 ? ax::ACT_ROWS : ax::gemm_layer_layout(rows, c.d_model, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim,
                                                        c.n_q_heads * c.head_dim, c.d_ff, L.h_lo != 0, L.splitk_bytes);
 }
 
@@ -541,7 +544,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
               qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, R = cp.n_rows;
 
     if (dt == ax::F32) {
-        m->panels = {R, false, false};
+        m->acts = {R, ax::ACT_ROWS, ax::ACT_ROWS};
         // fp32 models: five launches per layer.  The norms are folded into the GEMMs that read them; the first layer reads
         // its rows straight from the embedding.
         ax::GemmF32Args base{};
@@ -615,12 +618,13 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
         base.split_ws_bytes = L.splitk_bytes;
         // activations go in panels from kernel to kernel (calls of many rows, or of few); a last norm of more than 16 rows stays in rows where
         // its reader picks some of them or streams (logits of 17-32 rows)
-        const bool panels = layer_panels(c, L, R),
-                   out_panels = panels && (R <= 16 || (R > 256 && n_out == R && (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_ALL_LOGITS)));
-        bool h_panels = panels;
-        m->panels = {R, panels, out_panels};
-        auto normed = [&](ax::GemmArgs& g) { g.a_panels = h_panels; g.a_total_rows = R; g.A = h; g.a_lo_off = L.h_lo; g.ssq = ssq; g.nparts = nparts; g.d_norm = d_model; g.eps = c.rms_eps; g.K = d_model; };
-        ax::launch_embed_norm(m->tok_emb, sv.row_tok, m->norm_attn[0], x, h, L.h_lo, h_panels, ssq, nparts, R, d_model, stream);
+        const ax::ActLayout layout = layer_layout(c, L, R);
+        const bool out_panels = layout == ax::ACT_PANELS && (R <= 16 || (R > 256 && n_out == R && (out_mode == AX_OUT_LAST_LOGITS || out_mode == AX_OUT_ALL_LOGITS)));
+        const ax::ActLayout out_layout = out_panels ? ax::ACT_PANELS : ax::ACT_ROWS;
+        ax::ActLayout h_layout = layout;
+        m->acts = {R, layout, out_layout};
+        auto normed = [&](ax::GemmArgs& g) { g.a_layout = h_layout; g.a_total_rows = R; g.A = h; g.a_lo_off = L.h_lo; g.ssq = ssq; g.nparts = nparts; g.d_norm = d_model; g.eps = c.rms_eps; g.K = d_model; };
+        ax::launch_embed_norm(m->tok_emb, sv.row_tok, m->norm_attn[0], x, h, L.h_lo, h_layout, ssq, nparts, R, d_model, stream);
         for (int l = 0; l < c.n_layers; ++l) {
             {
                 ax::GemmArgs g = base;
@@ -634,20 +638,20 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
             }
             { ProfScope ps(m, 1, stream);
               ax::launch_attention(dt, qb, attn, kg, l, sv, c.n_q_heads, (float*)(ws + L.partials), n_splits,
-                                 split_waves(cp.n_tiles * c.n_kv_heads, cp.max_steps), stream, L.q_lo, L.attn_lo, panels); }
+                                 split_waves(cp.n_tiles * c.n_kv_heads, cp.max_steps), stream, L.q_lo, L.attn_lo, layout); }
             { ProfScope empty(m, 6, stream); }         // bracket around nothing: the cost of the two events
             {
                 ax::GemmArgs g = base;
                 g.A = attn; g.a_lo_off = L.attn_lo; g.K = qdim; g.W = m->wo[(size_t)l]; g.N = d_model;
                 g.Cf = x; g.C16 = h; g.c_lo_off = L.h_lo; g.gain_next = m->norm_mlp[(size_t)l]; g.ssq_out = ssq;
-                g.a_panels = g.c_panels = panels; g.a_total_rows = R;
+                g.a_layout = g.c_layout = layout; g.a_total_rows = R;
                 ProfScope ps(m, 2, stream);
                 nparts = ax::launch_gemm_bf16(ax::EPI_RESIDUAL, g, stream);
             }
             {
                 ax::GemmArgs g = base;
                 normed(g);
-                g.W = m->w_gate[(size_t)l]; g.W2 = m->w_up[(size_t)l]; g.N = c.d_ff; g.C16 = ffn; g.c_lo_off = L.ffn_lo; g.c_panels = panels;
+                g.W = m->w_gate[(size_t)l]; g.W2 = m->w_up[(size_t)l]; g.N = c.d_ff; g.C16 = ffn; g.c_lo_off = L.ffn_lo; g.c_layout = layout;
                 ProfScope ps(m, 3, stream);
                 ax::launch_gemm_bf16(ax::EPI_SWIGLU, g, stream);
             }
@@ -656,7 +660,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
                 g.A = ffn; g.a_lo_off = L.ffn_lo; g.K = c.d_ff; g.W = m->w_down[(size_t)l]; g.N = d_model;
                 g.Cf = x; g.C16 = h; g.c_lo_off = L.h_lo; g.ssq_out = ssq;
                 g.gain_next = l + 1 < c.n_layers ? m->norm_attn[(size_t)l + 1] : m->final_norm;
-                g.a_panels = panels; g.a_total_rows = R; g.c_panels = h_panels = l + 1 < c.n_layers ? panels : out_panels;
+                g.a_layout = layout; g.a_total_rows = R; g.c_layout = h_layout = l + 1 < c.n_layers ? layout : out_layout;
                 ProfScope ps(m, 4, stream);
                 nparts = ax::launch_gemm_bf16(ax::EPI_RESIDUAL, g, stream);
             }
@@ -747,8 +751,8 @@ ax_status run_verify_graph(ax_model* m, ax_kv* kv, const int32_t* toks, int T, v
         if (e != hipSuccess) return fail(AX_ERR_DEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
         m->graphs.push_back({key, cp.pool->uid, exec});
     }
-    const bool panels = layer_panels(m->cfg, m->lay, T);
-    m->panels = {T, panels, panels && T <= 16};
+    const ax::ActLayout layout = layer_layout(m->cfg, m->lay, T);
+    m->acts = {T, layout, T <= 16 ? layout : ax::ACT_ROWS};
     HIP_TRY(hipGraphLaunch(exec, stream));
     return AX_OK;
 }
@@ -1289,16 +1293,18 @@ ax_status ax_dbg_layer_panels(const ax_model_config* cfg, int rows, int* panels)
     ax_status why;
     if (!config_ok(cfg, &why)) return fail(why, "model config rejected");
     if (rows <= 0 || !panels) return fail(AX_ERR_INVALID, "bad argument");
-    *panels = layer_panels(*cfg, make_layout(*cfg), rows);
+    *panels = layer_layout(*cfg, make_layout(*cfg), rows) == ax::ACT_PANELS;
     return AX_OK;
 }
 
-ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
-    if (!a || !a->A || !a->W || a->M <= 0 || a->N <= 0 || a->K <= 0 || a->epilogue < 0 || a->epilogue > 3 || (a->ssq && a->n_parts <= 0))
+extern "C++" {
+// The debug GEMMs of named tiles: `built` says whether there is such a tile, `launch` runs it.
+template <class Built, class Launch>
+static ax_status dbg_gemm_tiles(ax_dbg_block_gemm* a, void* hip_stream, Built built, Launch launch) {
+    if (!a || !a->A || !a->W || a->M <= 0 || a->N <= 0 || a->K <= 0 || a->epilogue < 0 || a->epilogue > 3 || (a->ssq && a->n_parts <= 0) || a->a_panels < 0 || a->a_panels > 2 || a->c_panels < 0 || a->c_panels > 2)
         return fail(AX_ERR_INVALID, "bad argument");
     if (a->N % 64 != 0 || a->K % 64 != 0) return fail(AX_ERR_UNSUPPORTED, "N %% 64 == 0 and K %% 64 == 0 needed");
-    const bool shape_ok = (a->rows == 256 && a->cols == 256) || (a->rows == 128 && (a->cols == 256 || (a->cols == 128 && a->epilogue != 2)));
-    if (!shape_ok) return fail(AX_ERR_INVALID, "no %d x %d block for epilogue %d", a->rows, a->cols, a->epilogue);
+    if (!built()) return fail(AX_ERR_INVALID, "no %d x %d block for epilogue %d", a->rows, a->cols, a->epilogue);
     const size_t slab = (size_t)a->M * a->N * sizeof(float);
     if (a->slices < 1 || a->slices > ax::SPLITK_MAX || a->K % (32 * a->slices) != 0 ||
         (a->slices > 1 && ((a->epilogue != 1 && a->epilogue != 3) || !a->split_ws || a->split_ws_bytes < a->slices * slab)))
@@ -1326,14 +1332,30 @@ ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
     g.rope.kv = {a->pool, a->pool_blocks, a->n_kv_heads, a->head_dim, 16};
     g.rope.n_q_heads = a->n_q_heads; g.rope.q_out = a->C16; g.rope.row_pos = a->row_pos; g.rope.row_slot = a->row_slot;
     g.rope.cos = a->cos; g.rope.sin = a->sin;
-    g.a_panels = a->a_panels != 0; g.c_panels = a->c_panels != 0;
-    a->n_parts_out = ax::launch_gemm_block_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);
+    g.a_layout = (ax::ActLayout)a->a_panels; g.c_layout = (ax::ActLayout)a->c_panels;
+    a->n_parts_out = launch(g, s);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(pw);
     if (pw2) (void)hipFree(pw2);
     if (e != hipSuccess) return fail(AX_ERR_DEVICE, "debug GEMM: %s", hipGetErrorString(e));
     return AX_OK;
+}
+
+}
+
+ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
+    auto built = [&] { return (a->rows == 256 && a->cols == 256) || (a->rows == 128 && (a->cols == 256 || (a->cols == 128 && a->epilogue != 2))); };
+    return dbg_gemm_tiles(a, hip_stream, built, [&](const ax::GemmArgs& g, hipStream_t s) {
+        return ax::launch_gemm_block_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);
+    });
+}
+
+ax_status ax_dbg_gemm_regs(ax_dbg_block_gemm* a, void* hip_stream) {
+    auto built = [&] { return ax::gemm_regs_built((ax::Epilogue)a->epilogue, a->a_lo != 0, a->rows, a->cols, a->slices) && a->M <= 256; };
+    return dbg_gemm_tiles(a, hip_stream, built, [&](const ax::GemmArgs& g, hipStream_t s) {
+        return ax::launch_gemm_regs_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);
+    });
 }
 
 ax_status ax_dbg_attention_items(const ax_model_config* cfg, int n, const int* P, const int* T, int* items, int* merges, int* slots) {
@@ -1578,14 +1600,14 @@ ax_status ax_dbg_read(ax_model* m, int which, void* host_dst, size_t bytes) {
     HIP_TRY(hipDeviceSynchronize());
     const char* src = m->ws + off[which] + (lo ? len[which] : 0);
     HIP_TRY(hipMemcpy(host_dst, src, std::min(bytes, len[which]), hipMemcpyDeviceToHost));
-    const bool in_panels[6] = {false, false, false, m->panels.layers, m->panels.layers, m->panels.out};
-    if (in_panels[which]) {                                    // the last call's rows, as rows
+    const ax::ActLayout layout[6] = {ax::ACT_ROWS, ax::ACT_ROWS, ax::ACT_ROWS, m->acts.layers, m->acts.layers, m->acts.out};
+    if (layout[which] != ax::ACT_ROWS) {                                    // the last call's rows, as rows
         const ax_model_config& c = m->cfg;
-        const int rows = m->panels.rows, K = which == 3 ? c.n_q_heads * c.head_dim : which == 4 ? c.d_ff : c.d_model;
-        std::vector<uint16_t> got((size_t)rows * K);
+        const int rows = m->acts.rows, K = which == 3 ? c.n_q_heads * c.head_dim : which == 4 ? c.d_ff : c.d_model;
+        std::vector<uint16_t> got((size_t)(rows + 15) / 16 * 16 * K);
         HIP_TRY(hipMemcpy(got.data(), src, got.size() * 2, hipMemcpyDeviceToHost));
-        const size_t n = std::min(bytes / 2, got.size());
-        for (size_t i = 0; i < n; ++i) ((uint16_t*)host_dst)[i] = got[(size_t)ax::act_index(true, (int)(i / K), (int)(i % K), rows, K)];
+        const size_t n = std::min(bytes / 2, (size_t)rows * K);
+        for (size_t i = 0; i < n; ++i) ((uint16_t*)host_dst)[i] = got[(size_t)ax::act_index(layout[which], (int)(i / K), (int)(i % K), rows, K)];
     }
     return AX_OK;
 }

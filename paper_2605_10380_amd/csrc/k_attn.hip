@@ -266,7 +266,7 @@ struct AttnArgs {
     f16* out;
     long long q_lo_off, out_lo_off;   // split activations: lo parts of q / out this many elements behind (0 = not split)
     int n_rows;
-    bool out_panels;                  // out [n_rows, Hq * hd] in panels (act_index) instead of rows
+    ActLayout out_layout;             // of out [n_rows, Hq * hd]
     KVGeom kv;
     int layer, Hq, G, n_splits;       // G: query heads per KV head; n_splits: a power of two
     const int* tile_info;      // 8 ints per q tile, item or merge record (see StepView)
@@ -655,7 +655,7 @@ void attn_block_kernel(AttnArgs a) {
         for (int d = 0; d < DT; ++d)
 #pragma unroll
             for (int r = 0; r < 16; r += 4) {
-                f16* dst = a.out + act_index(a.out_panels, row0 + tq, (hk * G + gq) * HD + d * 32 + r * 2 + g * 4, a.n_rows, Hq * HD);
+                f16* dst = a.out + act_index(a.out_layout, row0 + tq, (hk * G + gq) * HD + d * 32 + r * 2 + g * 4, a.n_rows, Hq * HD);
                 f16x4 hi, lo;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     constexpr int MAXS = 16;                                   // slices per thread held in registers
     __shared__ float red[8][6][32];
     // (all arguments in one round trip, as in attn_split_kernel)
-    asm volatile("" :: "s"(a.out), "s"(a.out_lo_off), "s"(a.n_rows), "s"((int)a.out_panels), "s"(a.kv.n_kv_heads), "s"(a.Hq), "s"(a.G), "s"(a.n_splits),
+    asm volatile("" :: "s"(a.out), "s"(a.out_lo_off), "s"(a.n_rows), "s"((int)a.out_layout), "s"(a.kv.n_kv_heads), "s"(a.Hq), "s"(a.G), "s"(a.n_splits),
                        "s"(a.tile_info), "s"(a.partials), "s"(a.shared_splits));
     const int Hkv = a.kv.n_kv_heads, G = a.G;
     const int hk = blockIdx.x % Hkv, tile = blockIdx.x / Hkv;
@@ -776,7 +776,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     float L = 0.f, o = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) { L += red[i][1][ql]; o += red[i][2 + sg][ql]; }
-    f16* dst = a.out + act_index(a.out_panels, row0 + r / G, (hk * G + r % G) * HD + ch0 + sg, a.n_rows, a.Hq * HD);
+    f16* dst = a.out + act_index(a.out_layout, row0 + r / G, (hk * G + r % G) * HD + ch0 + sg, a.n_rows, a.Hq * HD);
     const float res = split_value(o / L);
     const f16 hi = (f16)res;
     *dst = hi;
@@ -856,7 +856,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     const float inv = 1.0f / L;
 #pragma unroll
     for (int c0 = 0; c0 < CPT; c0 += 8) {
-        f16* dst = a.out + act_index(a.out_panels, row0 + r / G, (hk * G + r % G) * HD + cg * CPT + c0, a.n_rows, a.Hq * HD);
+        f16* dst = a.out + act_index(a.out_layout, row0 + r / G, (hk * G + r % G) * HD + cg * CPT + c0, a.n_rows, a.Hq * HD);
         f16x8 v, lo;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
@@ -911,7 +911,7 @@ static void launch_items(const AttnArgs& a, int n_items, int n_merge, hipStream_
 
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, const StepView& sv,
                       int n_q_heads, float* partials, int n_splits, int split_waves, hipStream_t s, long long q_lo_off,
-                      long long out_lo_off, bool out_panels) {
+                      long long out_lo_off, ActLayout out_layout) {
     if (dt == F32) {
         const int subs = 2 * sv.tile_nq, hd = kv.head_dim;      // 16-row tiles per record of 32 * tile_nq rows
         dim3 grid(sv.n_tiles * subs, kv.n_kv_heads);
@@ -926,7 +926,7 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
     AttnArgs a{};
     a.q = (const f16*)q; a.out = (f16*)out; a.kv = kv; a.layer = layer; a.Hq = n_q_heads; a.G = n_q_heads / kv.n_kv_heads; a.n_splits = n_splits;
     a.tile_info = sv.tile_info; a.bt = sv.bt; a.partials = partials;
-    a.q_lo_off = q_lo_off; a.out_lo_off = out_lo_off; a.n_rows = sv.n_rows; a.out_panels = out_panels;
+    a.q_lo_off = q_lo_off; a.out_lo_off = out_lo_off; a.n_rows = sv.n_rows; a.out_layout = out_layout;
     const int hd = kv.head_dim;
     if (sv.tile_nq == 4) {                                     // long extends: 4 tiles per block, K/V through LDS
         launch_items<4>(a, sv.n_items, sv.n_merge, s);

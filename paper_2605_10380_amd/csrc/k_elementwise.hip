@@ -20,7 +20,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 // panel row.
 __global__ void embed_norm_kernel(const bf16* __restrict__ emb, const int* __restrict__ row_tok,
                                   const bf16* __restrict__ gain, float* __restrict__ x,
-                                  f16* __restrict__ a, long long a_lo_off, bool panels, float* __restrict__ ssq, int nparts, int d) {
+                                  f16* __restrict__ a, long long a_lo_off, ActLayout layout, float* __restrict__ ssq, int nparts, int d) {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
     typedef f16 f16x8 __attribute__((ext_vector_type(8)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -53,7 +53,7 @@ __global__ void embed_norm_kernel(const bf16* __restrict__ emb, const int* __res
         }
         *(f32x4*)(x + (long long)r * d + c) = xv[0];
         *(f32x4*)(x + (long long)r * d + c + 4) = xv[1];
-        f16* at = a + act_index(panels, r, c, gridDim.x, d);
+        f16* at = a + act_index(layout, r, c, gridDim.x, d);
         *(f16x8*)at = hi;
         if (a_lo_off) *(f16x8*)(at + a_lo_off) = lo;
     }
@@ -64,9 +64,9 @@ __global__ void embed_norm_kernel(const bf16* __restrict__ emb, const int* __res
         ssq[(long long)r * nparts + p] = p == 0 ? part[0] + part[1] + part[2] + part[3] : 0.f;
 }
 
-void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off, bool panels,
+void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off, ActLayout layout,
                        float* ssq, int nparts, int n_rows, int d, hipStream_t s) {
-    embed_norm_kernel<<<n_rows, 256, 0, s>>>((const bf16*)emb, row_tok, (const bf16*)gain, x, (f16*)a, a_lo_off, panels, ssq,
+    embed_norm_kernel<<<n_rows, 256, 0, s>>>((const bf16*)emb, row_tok, (const bf16*)gain, x, (f16*)a, a_lo_off, layout, ssq,
                                              nparts, d);
 }
 

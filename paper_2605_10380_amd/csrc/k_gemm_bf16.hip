@@ -6,15 +6,13 @@
 // bf16 one.  Reason: bf16 activations (8 significant bits) put the logits of a 16-layer decoder
 // ~0.05 away from the exact result; fp16 activations (11 bits) keep them within 0.01.
 //
-//   * skinny kernel (up to 16 rows; to 32 the four GEMMs of a layer with plain activations, of one with hi + lo parts the O projection
-//     only, and narrow stores: verify steps, pure weight streaming): one block owns 16 output columns, its wavefronts split K,
-//     W goes HBM -> registers -> v_mfma_f32_16x16x32_f16 with no LDS in the streaming loop; the per-wavefront partial sums meet in LDS.
-//   * tile kernel   (33-256 rows, hi + lo parts from 17, and some launches of up to 512): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
+//   * skinny kernel (up to 16 rows, narrow logits to 32: decoding, verify steps, pure weight streaming): one block owns 16 output columns, its
+//     wavefronts split K, W goes HBM -> registers -> v_mfma_f32_16x16x32_f16 with no LDS in the streaming loop; the per-wavefront partial
+//     sums meet in LDS.
+//   * register kernel (17-256 rows; k_gemm_regs.h): the same idea with tiles of up to 128 x 128 outputs.
+//   * tile kernel   (some QKV and residual GEMMs of 257-512 rows, narrow logits): 8 wavefronts, LDS-staged 64 x 128 x 64 tiles,
 //     v_mfma_f32_32x32x16_f16, global loads several K slices ahead.
-//   * stream kernel (logits from 17 rows, SwiGLU at 193-256 rows of wide matrices and some launches of up to 640, and - over K slices -
-//     the SwiGLU GEMM of 33-192 rows, hi + lo parts from 17, and the down projection of 129-192): activations through LDS, weights
-//     straight into MFMA operands.
-//     The launcher states each crossover with the figures behind it.
+//   * stream kernel (logits from 17 rows, some SwiGLU GEMMs of 257-640): activations through LDS, weights straight into MFMA operands.
 //   * block kernel  (more than 256 rows; k_gemm_block.hip; which of the three, plan_many below).
 //
 // RMSNorm is folded into the GEMMs around it.  The GEMM that produces the residual stream x
@@ -30,6 +28,7 @@
 #include <type_traits>
 
 #include "gemm_device.h"
+#include "k_gemm_regs.h"
 
 namespace ax {
 
@@ -67,17 +66,15 @@ template <int EPI, int TM, int TN, int WM = 2, int WN = 2, bool SPLIT = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g) {
     constexpr int NT = 64 * WM * WN;                                         // threads per block
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32, BK = 64, LS = BK + 8;  // LS: padded row
-    constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
     constexpr int A_CH = BM * 8 / NT, B_CH = BN * 8 / NT;                  // 16-byte chunks per thread
-    constexpr int D = (NB == 2 && B_CH > 2) ? 2 : 4;                         // prefetch distance (even)
+    constexpr int D = 4;                                                     // prefetch distance (even)
     constexpr int NA = SPLIT ? 2 : 1;
     __shared__ __attribute__((aligned(16))) f16 sA[2][NA][BM * LS];
-    __shared__ __attribute__((aligned(16))) f16 sB[2][NB][BN * LS];
+    __shared__ __attribute__((aligned(16))) f16 sB[2][BN * LS];
     __shared__ float s_inv[BM];
 
     const f16* __restrict__ A = (const f16*)g.A;
     const bf16* __restrict__ W = (const bf16*)g.W;
-    const bf16* __restrict__ W2 = (const bf16*)g.W2;
     const int M = g.M, N = g.N, K = g.K;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave / WN, wn = wave % WN;
@@ -85,21 +82,19 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     const int kspan = g.ksplit > 1 ? K / g.ksplit : K, kbase = blockIdx.z * kspan;   // this block's K slice
 
-    f32x16 acc[NB][TM][TN];
+    f32x16 acc[TM][TN];
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[b][i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     // Software pipeline: global loads run D k-steps ahead in a register ring (slot = step % D),
     // LDS is double buffered, one barrier per k-step.  At step s: issue the loads of s + D,
     // multiply out of LDS buffer s % 2, move the registers of s + 1 into the other buffer.
     f16x8 ra[D][NA][A_CH];
-    u32x4 rb[D][NB][B_CH];          // weights as packed (fp16, MFMA operand order)
+    u32x4 rb[D][B_CH];          // weights as packed (fp16, MFMA operand order)
     long long a_off[A_CH], b_off[B_CH];
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
@@ -121,10 +116,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g
             if (SPLIT) ra[slot][NA - 1][i] = *(const f16x8*)(A + a_off[i] + k0 + g.a_lo_off);
         }
 #pragma unroll
-        for (int i = 0; i < B_CH; ++i) {
-            rb[slot][0][i] = __builtin_nontemporal_load((const u32x4*)(W + b_off[i] + (long long)k0 * 16));
-            if (NB == 2) rb[slot][NB - 1][i] = __builtin_nontemporal_load((const u32x4*)(W2 + b_off[i] + (long long)k0 * 16));
-        }
+        for (int i = 0; i < B_CH; ++i) rb[slot][i] = __builtin_nontemporal_load((const u32x4*)(W + b_off[i] + (long long)k0 * 16));
     };
     auto store_lds = [&](int slot, int buf) {
 #pragma unroll
@@ -137,33 +129,28 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g
         for (int i = 0; i < B_CH; ++i) {
             const int c = tid + NT * i, u = c & 127;
             const int row = (c >> 7) * 16 + (u & 15), col = (u >> 6) * 32 + ((u >> 4) & 3) * 8;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) *(f16x8*)(sB[buf][b] + row * LS + col) = __builtin_bit_cast(f16x8, rb[slot][b][i]);
+            *(f16x8*)(sB[buf] + row * LS + col) = __builtin_bit_cast(f16x8, rb[slot][i]);
         }
     };
     auto multiply = [&](int buf) {
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
-            f16x8 fa[NA][TM], fb[NB][TN];
+            f16x8 fa[NA][TM], fb[TN];
 #pragma unroll
             for (int p = 0; p < NA; ++p)
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
                     fa[p][i] = *(const f16x8*)(sA[buf][p] + ((wm * TM + i) * 32 + lrow) * LS + kk * 16 + lg * 8);
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int j = 0; j < TN; ++j)
+                fb[j] = *(const f16x8*)(sB[buf] + ((wn * TN + j) * 32 + lrow) * LS + kk * 16 + lg * 8);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    fb[b][j] = *(const f16x8*)(sB[buf][b] + ((wn * TN + j) * 32 + lrow) * LS + kk * 16 + lg * 8);
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int p = 0; p < NA; ++p)
-                            acc[b][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[p][i], fb[b][j], acc[b][i][j], 0, 0, 0);
+                    for (int p = 0; p < NA; ++p)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[p][i], fb[j], acc[i][j], 0, 0, 0);
         }
     };
 
@@ -225,20 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     const int m = m0 + row_of(i, r), n = col_of(j);
-                    if (m < M && n < N) C[(long long)m * N + n] = acc[0][i][j][r] * inv[i][r];
-                }
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        f16* __restrict__ out = (f16*)g.C16;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int m = m0 + row_of(i, r), n = col_of(j);
-                    if (m < M && n < N)
-                        store_split(out + (long long)m * N + n, g.c_lo_off,
-                                    silu_f(acc[0][i][j][r] * inv[i][r]) * (acc[NB - 1][i][j][r] * inv[i][r]));
+                    if (m < M && n < N) C[(long long)m * N + n] = acc[i][j][r] * inv[i][r];
                 }
     } else if constexpr (EPI == EPI_RESIDUAL) {
         if (g.ksplit > 1) {          // K slice: raw partial products, finished by residual_reduce_kernel
@@ -250,7 +224,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g
 #pragma unroll
                     for (int j = 0; j < TN; ++j) {
                         const int m = m0 + row_of(i, r), n = col_of(j);
-                        if (m < M && n < N) part[(long long)m * N + n] = acc[0][i][j][r];
+                        if (m < M && n < N) part[(long long)m * N + n] = acc[i][j][r];
                     }
             return;
         }
@@ -279,7 +253,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile_kernel(GemmArgs g
                     const int n = col_of(j);
                     if (m < M && n < N) {
                         const long long o = (long long)m * N + n;
-                        const float xn = xv[i][j][r] + acc[0][i][j][r];
+                        const float xn = xv[i][j][r] + acc[i][j][r];
                         g.Cf[o] = xn;
                         if (g.gain_next) {
                             store_split(a16 + o, g.c_lo_off, xn * gain[j]);
@@ -375,16 +349,16 @@ __global__ __launch_bounds__(256) void residual_reduce_panels_kernel(GemmArgs g)
         }
         if (m < g.M) {
             *(f32x4*)(g.Cf + o[it]) = xn[it];
-            store_split4((f16*)g.C16 + act_index(true, m, n[it], g.M, g.N), g.c_lo_off, h);
+            store_split4((f16*)g.C16 + act_index(g.c_layout, m, n[it], g.M, g.N), g.c_lo_off, h);
         }
     }
 #pragma unroll
     for (int w = 8; w > 0; w >>= 1) ss += __shfl_xor(ss, w, 64);
-    if ((threadIdx.x & 15) == 0 && m < g.M) g.ssq_out[ssq_index(true, m, blockIdx.x, g.M, gridDim.x)] = ss;
+    if ((threadIdx.x & 15) == 0 && m < g.M) g.ssq_out[ssq_index(ssq_by_part(g.c_layout, g.M), m, blockIdx.x, g.M, gridDim.x)] = ss;
 }
 // launches it; returns the partial sums per row it leaves
 int launch_residual_reduce(const GemmArgs& g, hipStream_t s) {
-    if (g.c_panels) {
+    if (g.c_layout != ACT_ROWS) {
         const unsigned panels = (unsigned)(g.M + 15) / 16;
         const int cols = (long long)panels * g.N >= 512 * 512 ? 512 : 256, parts = (g.N + cols - 1) / cols;
         if (cols == 512) residual_reduce_panels_kernel<512><<<dim3((unsigned)parts, panels), 256, 0, s>>>(g);
@@ -427,7 +401,7 @@ __global__ __launch_bounds__(256) void qkv_reduce_rope_kernel(GemmArgs g) {
     if (g.ssq) {
         const int r = threadIdx.x / TPR, rm = min((int)blockIdx.x * ROWS + r, M - 1);
         float v = 0.f;
-        for (int q = threadIdx.x % TPR; q < g.nparts; q += TPR) v += g.ssq[ssq_index(g.a_panels, rm, q, M, g.nparts)];
+        for (int q = threadIdx.x % TPR; q < g.nparts; q += TPR) v += g.ssq[ssq_index(ssq_by_part(g.a_layout, M), rm, q, M, g.nparts)];
 #pragma unroll
         for (int o = TPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
         if (threadIdx.x % TPR == 0) s_inv[r] = 1.0f / sqrtf(v / (float)g.d_norm + g.eps);
@@ -468,32 +442,6 @@ void launch_qkv_reduce(const GemmArgs& g, hipStream_t s) {
     else qkv_reduce_rope_kernel<128><<<dim3((unsigned)(g.M + 15) / 16, heads), 256, 0, s>>>(g);
 }
 
-// Second half of a K-sliced SwiGLU GEMM: out[m, n] = fp16(silu(gate * inv) * (up * inv)) with gate
-// and up the sums of the slices' raw products (slabs [ksplit][M][2 N]: gate | up) and inv the row's
-// 1 / rms.  grid (rows, ceil(N / 256)).
-__global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs g) {
-    __shared__ float s_inv;
-    const int m = blockIdx.x, N = g.N, n = blockIdx.y * 256 + threadIdx.x;
-    const long long slab = (long long)g.M * 2 * N;
-    const float* p = g.split_ws + (long long)m * 2 * N + min(n, N - 1);
-    float pa[SPLITK_MAX], pb[SPLITK_MAX];
-#pragma unroll
-    for (int ks = 0; ks < SPLITK_MAX; ++ks) {
-        pa[ks] = ks < g.ksplit ? p[ks * slab] : 0.f;
-        pb[ks] = ks < g.ksplit ? p[ks * slab + N] : 0.f;
-    }
-    if (threadIdx.x < 64) {
-        const float inv = g.ssq ? wave_inv_rms(g.ssq, g.a_rows ? g.a_rows[m] : m, g.nparts, g.d_norm, g.eps, threadIdx.x) : 1.0f;
-        if (threadIdx.x == 0) s_inv = inv;
-    }
-    __syncthreads();
-    if (n >= N) return;
-    float a = 0.f, b = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < SPLITK_MAX; ++ks) { a += pa[ks]; b += pb[ks]; }
-    store_split((f16*)g.C16 + (long long)m * N + n, g.c_lo_off, silu_f(a * s_inv) * (b * s_inv));
-}
-
 // ------------------------------------------------------------------------------ stream kernel
 // The LDS-staged kernel above moves both operands through LDS and spends more cycles there than on the matrix cores (a 32 x 64
 // wavefront tile reads 1.5 KB of LDS per MFMA).  Here only the activation tile goes through LDS; every wavefront
@@ -506,20 +454,15 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs g) {
 // Blocks are renumbered so that the gy row tiles that share a weight tile have consecutive ids
 // on one XCD (workgroups are dealt to the 8 XCDs round robin), i.e. share that XCD's L2.
 //
-// EPI_STORE_F32 (logits) and EPI_RESIDUAL with NS = 2: a wavefront's two weight streams are two 32-row tiles of the ONE
-// matrix, 32 columns apart, and a block covers 256 output columns.
-//
-// NS = 1: one weight stream per wavefront (block = 128 columns), and K may be cut into g.ksplit
-// slices over extra blocks whose raw fp32 partial products go to slabs that qkv_reduce_rope_kernel /
-// residual_reduce_kernel add up: calls of 129-192 rows (16 sessions verified together), where one
-// 160- or 192-row block reads each weight once and the slices give the chip its ~200 blocks.
+// EPI_STORE_F32 (logits): a wavefront's two weight streams are two 32-row tiles of the ONE matrix, 32 columns apart, and a block covers 256
+// output columns.
 //
 // SPLIT: split activations - the hi and lo parts of the A tile are both staged in LDS and multiplied against the
 // same weight registers.
-template <int EPI, int TM, int D, int NS = 2, bool SLICED = false, bool SPLIT = false>
+template <int EPI, int TM, int D, bool SPLIT = false>
 __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int gx, int gy) {
-    static_assert(EPI != EPI_SWIGLU || NS == 2, "SwiGLU streams gate and up");
-    constexpr int BM = TM * 32, BN = EPI == EPI_SWIGLU ? 128 : NS * 128, BK = 64, LS = BK + 8;
+    static_assert(EPI == EPI_SWIGLU || EPI == EPI_STORE_F32, "two epilogues");
+    constexpr int BM = TM * 32, BN = EPI == EPI_SWIGLU ? 128 : 256, BK = 64, LS = BK + 8, NS = 2;
     constexpr int A_CH = BM * 8 / 256;                       // 16-byte chunks of the A tile per thread
     constexpr int NA = SPLIT ? 2 : 1;
     __shared__ __attribute__((aligned(16))) f16 sA[2][NA][BM * LS];
@@ -530,12 +473,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lrow = lane & 31, lg = lane >> 5;
     const int nblk = gx * gy;
-    const int kz = blockIdx.x / nblk;                        // K slice (0 unless g.ksplit > 1)
-    int bid = blockIdx.x - kz * nblk;
+    int bid = blockIdx.x;
     if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
     const int bx = bid / gy, by = bid - bx * gy;
     const int m0 = by * BM, n0 = bx * BN;
-    const int kspan = SLICED ? K / g.ksplit : K, kbase = kz * kspan;      // SLICED: g.ksplit > 1 slices, a slab each
 
     // this lane's output columns = weight rows of its two streams: row n of W and of W2 (SwiGLU),
     // or rows n and n + 32 of W
@@ -545,15 +486,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
         ncol[t] = n0 + wave * (BN / 4) + lrow + (EPI == EPI_SWIGLU ? 0 : 32 * t);
-        wp[t] = (const bf16*)(EPI == EPI_SWIGLU && t == 1 ? g.W2 : g.W) + packed_row(min(ncol[t], N - 1), K) +
-                (long long)kbase * 16 + lg * PK_KG;
+        wp[t] = (const bf16*)(EPI == EPI_SWIGLU && t == 1 ? g.W2 : g.W) + packed_row(min(ncol[t], N - 1), K) + lg * PK_KG;
     }
     long long a_off[A_CH];
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
         const int c = tid + 256 * i, row = c >> 3, cc = c & 7;
         const int gm = min(m0 + row, M - 1);
-        a_off[i] = (long long)(g.a_rows ? g.a_rows[gm] : gm) * K + kbase + cc * 8;
+        a_off[i] = (long long)(g.a_rows ? g.a_rows[gm] : gm) * K + cc * 8;
     }
 
     f32x16 acc[NS][TM];
@@ -605,12 +545,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
         }
     };
 
-    const int nsteps = kspan / BK;
+    const int nsteps = K / BK;
     // deferred RMSNorm: 1/rms of this block's rows, before the operand rings take the registers (16
     // rows x 4 loads per thread in flight: one or two round trips; behind the ring loads the same
-    // table cost four to six, 10-15 % of the launch at 512-1024 rows).  Sliced SwiGLU: the reduce kernel scales.
+    // table cost four to six, 10-15 % of the launch at 512-1024 rows).
     // Few partials per row (K-split producer): behind the ring loads, their cold misses overlap.
-    const bool inv_here = g.ssq && !(EPI == EPI_SWIGLU && SLICED);
+    const bool inv_here = g.ssq != nullptr;
     if (inv_here && g.nparts > 4) block_inv_rms<16>(g, m0, BM, s_inv);
 #pragma unroll
     for (int s = 0; s < D; ++s)
@@ -646,18 +586,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
     }
 
     auto row_of = [&](int i, int r) { return i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3); };
-    if constexpr (EPI == EPI_SWIGLU && SLICED) {             // raw gate | up products of this K slice: slab [M][2 N]
-        float* __restrict__ C = g.split_ws + (long long)kz * M * 2 * N;
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int m = m0 + row_of(i, r);
-                    if (m < M && ncol[0] < N) C[(long long)m * 2 * N + t * N + ncol[0]] = acc[t][i][r];
-                }
-    } else if constexpr (EPI == EPI_SWIGLU) {
+    if constexpr (EPI == EPI_SWIGLU) {
         f16* __restrict__ out = (f16*)g.C16;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -668,8 +597,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
                 if (m < M && ncol[0] < N)
                     store_split(out + (long long)m * N + ncol[0], g.c_lo_off, silu_f(acc[0][i][r] * inv) * (acc[1][i][r] * inv));
             }
-    } else if constexpr (EPI == EPI_STORE_F32 || SLICED) {  // K slice: its own slab of raw products
-        float* __restrict__ C = SLICED ? (EPI == EPI_STORE_F32 ? g.Cf : g.split_ws) + (long long)kz * M * N : g.Cf;
+    } else {
+        float* __restrict__ C = g.Cf;
 #pragma unroll
         for (int t = 0; t < NS; ++t)
 #pragma unroll
@@ -680,41 +609,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream_kernel(GemmArgs g, int g
                     const float inv = g.ssq ? s_inv[row] : 1.0f;
                     if (m < M && ncol[t] < N) C[(long long)m * N + ncol[t]] = acc[t][i][r] * inv;
                 }
-    } else {                                                  // EPI_RESIDUAL; N % 32 == 0 (checked by the launcher)
-        static_assert(TM % 2 == 0, "the residual epilogue works on pairs of row tiles");
-        f16* __restrict__ a16 = (f16*)g.C16;
-#pragma unroll
-        for (int t = 0; t < NS; ++t) {
-            const int n = min(ncol[t], N - 1);
-            const float gain = g.gain_next ? (float)((const bf16*)g.gain_next)[n] : 0.f;
-#pragma unroll
-            for (int i0 = 0; i0 < TM; i0 += 2) {
-            float xv[2][16];                                  // the loads of two row tiles first, then their stores
-#pragma unroll
-            for (int i = i0; i < i0 + 2; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) xv[i - i0][r] = g.Cf[(long long)min(m0 + row_of(i, r), M - 1) * N + n];
-#pragma unroll
-            for (int i = i0; i < i0 + 2; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int m = m0 + row_of(i, r);
-                    const bool live = m < M && ncol[t] < N;
-                    const float xn = xv[i - i0][r] + acc[t][i][r];
-                    float ss = live ? xn * xn : 0.f;
-                    if (live) {
-                        const long long o = (long long)m * N + n;
-                        g.Cf[o] = xn;
-                        if (g.gain_next) store_split(a16 + o, g.c_lo_off, xn * gain);
-                    }
-                    if (g.gain_next) {                        // partial sum of squares over this tile's 32 columns
-#pragma unroll
-                        for (int o = 16; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-                        if (lrow == 0 && live) g.ssq_out[(long long)m * (N / 32) + (ncol[t] >> 5)] = ss;
-                    }
-                }
-            }
-        }
     }
 }
 
@@ -748,7 +642,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     const bf16* __restrict__ W = (const bf16*)g.W;
     const bf16* __restrict__ W2 = (const bf16*)g.W2;
     const int M = g.M, N = g.N, K = g.K;
-#define AX_ARGS "s"(X), "s"(W), "s"(M), "s"(N), "s"(K), "s"(g.a_lo_off), "s"((int)g.a_panels), "s"(g.a_total_rows), "s"(g.ssq), "s"(g.nparts)
+#define AX_ARGS "s"(X), "s"(W), "s"(M), "s"(N), "s"(K), "s"(g.a_lo_off), "s"((int)g.a_layout), "s"(g.a_total_rows), "s"(g.ssq), "s"(g.nparts)
     if constexpr (EPI == EPI_QKV) asm volatile("" :: AX_ARGS, "s"(g.rope.kv.head_dim), "s"(g.rope.row_pos), "s"(g.rope.row_slot), "s"(g.rope.cos), "s"(g.rope.sin));
     else if constexpr (EPI == EPI_RESIDUAL) asm volatile("" :: AX_ARGS, "s"(g.Cf), "s"(g.gain_next));
     else if constexpr (EPI == EPI_SWIGLU) asm volatile("" :: AX_ARGS, "s"(W2));
@@ -793,8 +687,8 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
         const int m = min(t * 16 + lr, M - 1);
         const int row = a_rows ? a_rows[m] : m;
         const int first = t * 16, panel_rows = min(16, g.a_total_rows - first);
-        xs[t] = g.a_panels ? panel_rows * 2 : 2;
-        xo[t] = g.a_panels ? (unsigned)first * (unsigned)K * 2u + (row - first) * 16u + lg * panel_rows * 16u : (unsigned)row * (unsigned)K * 2u + lg * 16u;
+        xs[t] = g.a_layout ? panel_rows * 2 : 2;
+        xo[t] = g.a_layout ? (unsigned)first * (unsigned)K * 2u + (row - first) * 16u + lg * panel_rows * 16u : (unsigned)row * (unsigned)K * 2u + lg * 16u;
     }
     auto acts = [&](int t, int part, int k) { return (const f16x8*)((const char*)(part ? X + g.a_lo_off : X) + (long long)k * xs[t] + xo[t]); };
 
@@ -998,7 +892,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                 float h[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) h[r] = silu_f(sum[0][r] * inv) * (sum[NB - 1][r] * inv);
-                store_split4((f16*)g.C16 + act_index(g.c_panels, m, n, M, N), g.c_lo_off, h);
+                store_split4((f16*)g.C16 + act_index(g.c_layout == ACT_PANELS ? ACT_PANELS : ACT_ROWS, m, n, M, N), g.c_lo_off, h);
             }
         } else if (EPI == EPI_RESIDUAL) {
             float ss = 0.f;
@@ -1012,7 +906,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                         h[r] = xn[r] * __uint_as_float(pre_g[r] << 16);
                         ss += xn[r] * xn[r];
                     }
-                    store_split4((f16*)g.C16 + act_index(g.c_panels, m, n, M, N), g.c_lo_off, h);
+                    store_split4((f16*)g.C16 + act_index(g.c_layout == ACT_PANELS ? ACT_PANELS : ACT_ROWS, m, n, M, N), g.c_lo_off, h);
                 }
             }
             if (g.gain_next) {           // sum of squares over the block's COLS columns, per row
@@ -1097,7 +991,7 @@ static void launch_skinny_nw(const GemmArgs& g, int nw, hipStream_t s) {
     launch_skinny_cols<EPI, MT, 16>(g, nw, s);
 }
 
-static constexpr int kPanelRows = 32;        // rows up to which the few-row kernel reads activations in panels
+static constexpr int kPanelRows = 32;        // rows up to which plain activations lie in panels of few rows
 
 // Dispatch thresholds.  Each is a measured crossover (figures at its use); the product build compiles them in
 // as constants.  Only a build with -DAX_TUNING_KNOBS (kernel tuning sessions) lets the environment override them.
@@ -1109,14 +1003,11 @@ static int env_int(const char* name, int dflt) {
 #else
 static constexpr int env_int(const char*, int dflt) { return dflt; }
 #endif
-static const int kSwigluStreamMinNK = env_int("AX_SWIGLU_STREAM_MIN_NK", 0);   // measurement switch: gate/up weights (2^20) per matrix from which verify-size calls stream (0 = never)
 static const int kSwigluWaves = env_int("AX_SWIGLU_WAVES", 4096);   // wavefronts in flight the SwiGLU launch aims for (two weight streams per wavefront)
 static const int kLmStream = env_int("AX_LM_STREAM", 1);   // experiment knob
-static const int kSkinnyMaxM = std::min(32, env_int("AX_SKINNY_MAX_M", 32));   // experiment knob: rows up to which the skinny kernel may run
 static const int kForceNW = env_int("AX_SKINNY_NW", 0);   // experiment knob: wavefronts per block, 0 = automatic
 
 // More rows: LDS-staged tiles.
-static const int kMidStream = env_int("AX_MID_STREAM", 1);   // experiment knob: 0 = tile kernels for 129-192 rows
 static const int kQkvTile = env_int("AX_QKV_TILE", -1);   // experiment knobs: force 64-row (0) or 128-row (1) blocks
 static const int kResTile = env_int("AX_RES_TILE", -1);
 static const int kResBig = env_int("AX_RES_BIG", 256);
@@ -1168,7 +1059,7 @@ static TilePlan plan_tile(int M, int N, int K, size_t ws_bytes) {
         // Measured against 64-row blocks: ~8B down projection 57 -> 49 us at M = 256, 98 -> 81 at 512;
         // ~1B at M = 256 would need 8 slices and is no faster, so it keeps 64-row blocks.
         const int ks128 = slices(tiles128);
-        const bool big = kResTile >= 0 ? kResTile > 0 : (M > 128 && pad_ok && (tiles128 >= kResBig || tiles64 > 256 || (K >= 4096 && ks128 <= 4 && tiles128 * ks128 >= 192)));
+        const bool big = kResTile >= 0 ? kResTile > 0 : (pad_ok && (tiles128 >= kResBig || tiles64 > 256 || (K >= 4096 && ks128 <= 4 && tiles128 * ks128 >= 192)));
         return {big, big ? ks128 : slices(tiles64)};
     }
 }
@@ -1176,19 +1067,6 @@ static TilePlan plan_tile(int M, int N, int K, size_t ws_bytes) {
 template <int EPI>
 static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
-    // 129-192 rows (16 sessions verified together), residual GEMM with a long K (down projection):
-    // one 160- or 192-row streaming block per 128 columns reads every weight once (64-row tiles
-    // pull it three times out of L2) and K slices give the chip its ~200 blocks: ~3B down
-    // projection at M = 144 36 -> 27 us.  With the shorter K of the QKV and O projections the
-    // slices are too short for a kernel with one wavefront per SIMD (QKV 24 -> 29 us): tile kernels.
-    const int mid_cb = (N + 127) / 128;
-    int mid_ks = 1;
-    const bool split = g.a_lo_off != 0;   // split activations: streaming blocks of at most 128 rows (a second A ring does not fit the registers of larger ones)
-    if (EPI == EPI_RESIDUAL && kMidStream && !split && M > 128 && M <= 192 && K >= 8192 && N % 64 == 0 && g.split_ws)
-        for (int ks : {8, 6, 4, 3, 2})
-            if (mid_ks == 1 && mid_cb * ks <= 288 && K % (ks * 64) == 0 && K / (ks * 64) >= 4 &&
-                (size_t)ks * 2 * M * N * sizeof(float) <= g.split_ws_bytes)
-                mid_ks = ks;
     if constexpr (EPI == EPI_QKV) {
         // A plain store GEMM writes fp32 products, a second kernel does the rms scaling, rotary
         // embedding and KV append: measured faster than a fused epilogue (one head per wavefront)
@@ -1213,13 +1091,6 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
         launch_qkv_reduce(gs, s);
         return 0;
     } else if constexpr (EPI == EPI_RESIDUAL) {
-        if (mid_ks > 1 && mid_cb * mid_ks >= 160) {            // (~1B width: 128 blocks, slower than the tile kernels)
-            GemmArgs gs = g;
-            gs.ksplit = mid_ks;
-            if (M <= 160) gemm_bf16_stream_kernel<EPI_RESIDUAL, 5, 3, 1, true, false><<<mid_cb * mid_ks, 256, 0, s>>>(gs, mid_cb, 1);
-            else gemm_bf16_stream_kernel<EPI_RESIDUAL, 6, 3, 1, true, false><<<mid_cb * mid_ks, 256, 0, s>>>(gs, mid_cb, 1);
-            return launch_residual_reduce(gs, s);
-        }
         const TilePlan t = plan_tile<EPI>(M, N, K, g.split_ws ? g.split_ws_bytes : 0);
         GemmArgs gs = g;
         gs.ksplit = t.ks;
@@ -1231,52 +1102,15 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_RESIDUAL, 1, 1, 2, 4), grid, 512, gs);
         }
         return t.ks > 1 ? launch_residual_reduce(gs, s) : N / 32;
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        // 17-192 rows: one streaming block of all the rows (32 to 192) per 128 columns, over K slices
-        // (raw gate | up products in slabs, swiglu_reduce_kernel finishes): every weight is read
-        // once and the slices give the chip ~256 blocks, where the tile kernels have 64 blocks (up
-        // to 64 rows: no K slices for two products) or pull every weight twice out of L2, and the
-        // skinny kernel re-reads its activations per 16 columns.  ~3B shape: 33 -> 26 us at 32 rows,
-        // 48 -> 28 us at 64 rows, 49 -> 42 us at 144 rows; ~8B: 72 -> 48 us at 32-48 rows.
-        // (above 128 rows only for matrices of the ~3B size or larger: at the ~1B size the 128 x 64 tiles are as fast or faster)
-        if (kMidStream && M <= (split ? 128 : 192) && (M <= 128 || (long long)N * K >= (20LL << 20)) && g.split_ws) {
-            const int cb = (N + 127) / 128;
-            int ks = 1;
-            for (int c : {8, 6, 4, 3, 2})
-                if (ks == 1 && cb * c <= 288 && K % (c * 64) == 0 && K / (c * 64) >= 6 &&
-                    (size_t)c * 2 * M * N * sizeof(float) <= g.split_ws_bytes)
-                    ks = c;
-            if (ks > 1 && cb * ks >= 128) {
-                GemmArgs gs = g;
-                gs.ksplit = ks;
-                const unsigned nb = (unsigned)(cb * ks);
-                switch ((M + 31) / 32) {
-                    case 1: AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 1, 3, 2, true), nb, 256, gs, cb, 1); break;
-                    case 2: AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 2, 3, 2, true), nb, 256, gs, cb, 1); break;
-                    case 3: AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3, 2, true), nb, 256, gs, cb, 1); break;
-                    case 4: AX_SPLIT_LAUNCH(gs.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3, 2, true), nb, 256, gs, cb, 1); break;
-                    case 5: gemm_bf16_stream_kernel<EPI_SWIGLU, 5, 3, 2, true, false><<<nb, 256, 0, s>>>(gs, cb, 1); break;
-                    default: gemm_bf16_stream_kernel<EPI_SWIGLU, 6, 3, 2, true, false><<<nb, 256, 0, s>>>(gs, cb, 1); break;
-                }
-                swiglu_reduce_kernel<<<dim3((unsigned)M, (unsigned)((N + 255) / 256)), 256, 0, s>>>(gs);
-                return 0;
-            }
-        }
-        // gate/up with two or more 128-row tiles: 128 x 64 tiles make a CU pull (128 + 2 * 64) rows of
-        // operands per k instead of (64 + 2 * 128) for the same number of blocks (2-3 % faster)
-        if (M > 128) {
-            dim3 tgrid((N + 63) / 64, (M + 127) / 128);
-            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI_SWIGLU, 1, 1, 4, 2), tgrid, 512, g);
-            return 0;
-        }
-    }
-    if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_SWIGLU) {
+    } else {
+        static_assert(EPI == EPI_STORE_F32, "SwiGLU runs on other kernels");
+        const bool split = g.a_lo_off != 0;     // (streaming blocks of at most 128 rows: a second A ring does not fit the registers of larger ones)
         // logits (N >= 64 K columns) of 17 rows or more: streaming blocks of up to 192 rows per 256 columns
         // read the LM head once per block row at 5-6 TB/s; the skinny kernel re-reads its activations
         // per 16 columns (17 rows of the ~3B shape: 182 -> 128 us) and 64-row tiles read the weights
         // once per tile (96-128 rows: 282-294 -> 149-157 us; 144 rows: 436 -> 202 us).  Rows per
         // block by the same rounds x block cost as the SwiGLU kernel.
-        if (EPI == EPI_STORE_F32 && M > 16 && N >= 256 * 256 && N % 32 == 0 && kLmStream) {
+        if (M > 16 && N >= 256 * 256 && N % 32 == 0 && kLmStream) {
             const int gx = (N + 255) / 256;
             int tm = (M + 31) / 32;
             if (M > 512) {
@@ -1292,47 +1126,27 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
             }
             const int gy = (M + 32 * tm - 1) / (32 * tm);
             switch (tm) {
-                case 1: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 1, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-                case 2: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 2, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-                case 3: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 3, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-                case 4: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-                case 5: gemm_bf16_stream_kernel<EPI_STORE_F32, 5, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
-                default: gemm_bf16_stream_kernel<EPI_STORE_F32, 6, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
+                case 1: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 1, 3), gx * gy, 256, g, gx, gy); break;
+                case 2: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 2, 3), gx * gy, 256, g, gx, gy); break;
+                case 3: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 3, 3), gx * gy, 256, g, gx, gy); break;
+                case 4: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3), gx * gy, 256, g, gx, gy); break;
+                case 5: gemm_bf16_stream_kernel<EPI_STORE_F32, 5, 3><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
+                default: gemm_bf16_stream_kernel<EPI_STORE_F32, 6, 3><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
             }
             return 0;
         }
         // last-row logits of more than 512 sequences (their rows gathered, which the block kernel does not do): 128 x 256 streaming
         // blocks where they fill the 256 CUs evenly - a single round of 128 or more, or rounds at least 3/4 full
         const long long sblocks = (long long)((N + 255) / 256) * ((M + 127) / 128), rounds = (sblocks + 255) / 256;
-        if (EPI == EPI_STORE_F32 && M >= 512 && N % 32 == 0 && sblocks >= 128 && (rounds == 1 || sblocks * 4 >= rounds * 256 * 3)) {
+        if (M >= 512 && N % 32 == 0 && sblocks >= 128 && (rounds == 1 || sblocks * 4 >= rounds * 256 * 3)) {
             const int gx = (N + 255) / 256, gy = (M + 127) / 128;
-            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3, 2, false), gx * gy, 256, g, gx, gy);
+            AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_STORE_F32, 4, 3), gx * gy, 256, g, gx, gy);
             return 0;
         }
         dim3 grid((N + 127) / 128, (M + 63) / 64);
-        AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_tile_kernel, (EPI, 1, 1, 2, 4), grid, 512, g);
+        AX_SPLIT_LAUNCH(split, gemm_bf16_tile_kernel, (EPI_STORE_F32, 1, 1, 2, 4), grid, 512, g);
     }
     return 0;
-}
-
-// Which rows go to the skinny kernel: a block of it re-reads the whole activation slice of its
-// wavefronts (M x K / NW fp16) per 8-16 columns, so its time grows with M while one 64-row tile
-// costs the same for any M <= 64.  Measured crossovers (all three model shapes): every GEMM is
-// faster on the other kernels from 33 rows up (64 rows of the ~3B shape: 172 -> 114 us per layer);
-// from 17 rows up, with activations in rows, the QKV GEMM and the residual GEMM with the long K (down projection) are too
-// (~3B at 17-32 rows: 18-22 -> 17-19 us and 18-23 -> 15-16 us) and so is the SwiGLU GEMM on its
-// K-sliced streaming blocks (see launch_lds_tile); the O projection is not.
-static bool use_skinny(int epi, int M, int N, int K) {
-    // (the largest gate/up matrices - ~8B shape, 2 x 59 M weights - once streamed faster through the K-sliced
-    // streaming blocks even at verify sizes, 51 -> 44 us at 9 rows; since this kernel skips activation rows
-    // past M and finishes 1 / rms behind its first loads it is ahead again: 37.8 / 38.3 / 41.0 us at 1 / 9 / 16
-    // rows against 41.9 / 42.1 / 42.2.  The switch stays for measurements: weights (2^20) per matrix from which to stream.)
-    if (epi == EPI_SWIGLU && kSwigluStreamMinNK > 0 && (long long)N * K >= (long long)kSwigluStreamMinNK << 20) return false;
-    if (M <= 16) return true;
-    if (M > kSkinnyMaxM) return false;
-    if (epi == EPI_STORE_F32 && N >= 256 * 256 && kLmStream) return false;    // logits: streaming blocks (see launch_lds_tile)
-    // (17-32 rows in rows, that is split activations; plain ones lie in panels there and stay on this kernel, see gemm_layer_panels)
-    return !(epi == EPI_QKV || epi == EPI_SWIGLU || (epi == EPI_RESIDUAL && K >= 2 * N));
 }
 
 // ------------------------------------------------------------------------------ more than 256 rows
@@ -1388,26 +1202,107 @@ static bool many_rows(int M, int N, bool gathered) { return M > 256 && !gathered
 static void launch_swiglu_stream(const GemmArgs& g, int tm, hipStream_t s) {
     const int gx = (g.N + 127) / 128, gy = (g.M + 32 * tm - 1) / (32 * tm);
     switch (tm) {
-        case 3: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3, 2, false), gx * gy, 256, g, gx, gy); break;
-        case 5: gemm_bf16_stream_kernel<EPI_SWIGLU, 5, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
-        case 6: gemm_bf16_stream_kernel<EPI_SWIGLU, 6, 3, 2, false, false><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
-        default: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3, 2, false), gx * gy, 256, g, gx, gy); break;
+        case 3: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 3, 3), gx * gy, 256, g, gx, gy); break;
+        case 5: gemm_bf16_stream_kernel<EPI_SWIGLU, 5, 3><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
+        case 6: gemm_bf16_stream_kernel<EPI_SWIGLU, 6, 3><<<gx * gy, 256, 0, s>>>(g, gx, gy); break;
+        default: AX_SPLIT_LAUNCH(g.a_lo_off != 0, gemm_bf16_stream_kernel, (EPI_SWIGLU, 4, 3), gx * gy, 256, g, gx, gy); break;
     }
+}
+
+// ------------------------------------------------------------------------------ 17-256 rows
+// The register kernel (k_gemm_regs.h): tile and K slices by the times of all tiles that are built, alone and on cold weights, for the four GEMMs
+// of the ~1B, ~3B and ~8B (hi + lo) layers at 2-16 panels of rows, 600 launches, most within 1.5 us.  A round of blocks is its first
+// round trips, sums and epilogue, and per 32 k the panels of W that no other row block has brought to the L2 and, cheaper, all others.
+// Slices cost slabs and the kernel that adds them up.  Inside models the forms chosen so are the fastest or within 2 us of it at 17-256 rows.
+struct RegsPlan { int shape, ks; float us; };
+static RegsPlan plan_regs(Epilogue epi, int M, int N, int K, bool split, bool slices, size_t ws_bytes) {
+    RegsPlan best{-1, 1, 0.f};
+    const int panels = (M + 15) / 16, chunks = K / 32, na = split ? 2 : 1;
+    const int force = env_int("AX_REGS", -1), force_epi = env_int("AX_REGS_EPI", -1), force_ks = env_int("AX_REGS_KS", 1);
+    for (int c = 0; c < kRegsShapes; ++c) {
+        const RegsShape& t = kRegs[split][c];
+        if (t.mt > panels + 1) continue;
+        const int cols = (epi == EPI_SWIGLU ? 8 : 16) * t.nt;
+        for (int ks = 1; ks <= 8; ks *= 2) {
+            if (ks > 1 && (epi != EPI_RESIDUAL || !slices || (size_t)ks * M * N * sizeof(float) > ws_bytes || chunks / ks < 16)) break;
+            if (!regs_built(epi, split, ks > 1, c)) continue;
+            const int gy = (panels + t.mt - 1) / t.mt, gx = (N + cols - 1) / cols;
+            const long long blocks = (long long)gx * gy * ks;
+            const float rounds = (blocks + 255) / 256, crowd = std::min(1.f, std::max(0.6f, blocks / 256.f));
+            const float miss = (float)t.nt / gy, hit = t.nt - miss + t.mt * na;
+            float us = rounds * (4.4f + 0.12f * std::max(0, t.mt * t.nt - 24) + (float)chunks / ks * (0.025f * crowd * miss + 0.0145f * hit));
+            if (ks > 1) us += 3.4f + 0.4f * ks + 0.4e-6f * ks * M * N;
+            if (force >= 0 && force_epi == (epi == EPI_RESIDUAL && K > 2 * N ? 4 : epi) && !(c == force && ks == force_ks)) us += 1e6f;
+            if (best.shape < 0 || us <= best.us) best = {c, ks, us};
+        }
+    }
+    return best;
+}
+static int launch_regs_plan(Epilogue epi, const GemmArgs& g, const RegsPlan& p, hipStream_t s) {
+    if (epi == EPI_QKV) { launch_regs_qkv(g, p.shape, s); return 0; }
+    if (epi == EPI_SWIGLU) { launch_regs_swiglu(g, p.shape, s); return 0; }
+    if (p.ks == 1) {
+        launch_regs_residual(g, p.shape, s);
+        const int cols = 16 * kRegs[g.a_lo_off != 0][p.shape].nt;
+        return (g.N + cols - 1) / cols;
+    }
+    GemmArgs gs = g;
+    gs.ksplit = p.ks;
+    launch_regs_slices(gs, p.shape, s);
+    return launch_residual_reduce(gs, s);
+}
+static int launch_regs(Epilogue epi, const GemmArgs& g, hipStream_t s) {
+    const bool split = g.a_lo_off != 0;
+    if (g.M > 256) {                                           // (SwiGLU of odd widths, which no layer has: 256 rows at a time)
+        for (int r0 = 0; r0 < g.M; r0 += 256) {
+            GemmArgs c = g;
+            c.M = std::min(256, g.M - r0);
+            c.A = (const f16*)g.A + (long long)r0 * g.K;
+            c.C16 = (f16*)g.C16 + (long long)r0 * g.N;
+            if (g.ssq) c.ssq = g.ssq + (long long)r0 * g.nparts;
+            launch_regs(epi, c, s);
+        }
+        return 0;
+    }
+    const size_t ws = g.split_ws ? g.split_ws_bytes : 0;
+    const RegsPlan p = plan_regs(epi, g.M, g.N, g.K, split, g.split_ws != nullptr, ws);
+    // hi + lo parts of many rows are bound by their products: 256 x 256 blocks through LDS multiply faster (~8B gate / up, 176-256 rows: 130-140 us, 100)
+    if (split && g.a_layout == ACT_STRIPS && g.N % 64 == 0) {
+        const BlockPlan b = plan_gemm_block(epi, g.M, g.N, g.K, split, true, ws);
+        const int fb = env_int("AX_BLOCK", -1);
+        if (fb < 0 ? b.us < p.us && env_int("AX_REGS", -1) < 0 : fb == (epi == EPI_RESIDUAL && g.K > 2 * g.N ? 4 : epi)) return launch_gemm_block(epi, g, b, s);
+    }
+    return launch_regs_plan(epi, g, p, s);
+}
+
+static int regs_shape(bool split, int rows, int cols) {
+    for (int c = 0; c < kRegsShapes; ++c)
+        if (kRegs[split][c].mt * 16 == rows && kRegs[split][c].nt * 16 == cols) return c;
+    return -1;
+}
+bool gemm_regs_built(Epilogue epi, bool split, int rows, int cols, int slices) {
+    const int c = regs_shape(split, rows, cols);
+    return c >= 0 && epi != EPI_STORE_F32 && (slices == 1 || epi == EPI_RESIDUAL) && regs_built(epi, split, slices > 1, c);
+}
+int launch_gemm_regs_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s) {
+    return launch_regs_plan(epi, g, {regs_shape(g.a_lo_off != 0, rows, cols), slices, 0.f}, s);
 }
 
 template <int EPI>
 static int launch_bf16(const GemmArgs& g, hipStream_t s) {
     const int M = g.M, N = g.N, K = g.K;
-    if (g.a_panels && M > 256) return launch_gemm_block((Epilogue)EPI, g, plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, true, g.split_ws ? g.split_ws_bytes : 0), s);
+    if (g.a_layout == ACT_PANELS && M > 256) return launch_gemm_block((Epilogue)EPI, g, plan_gemm_block((Epilogue)EPI, M, N, K, g.a_lo_off != 0, true, g.split_ws ? g.split_ws_bytes : 0), s);
     if (many_rows(M, N, g.a_rows != nullptr)) {
         const ManyPlan p = plan_many<EPI>(M, N, K, g.a_lo_off != 0, g.split_ws ? g.split_ws_bytes : 0);
         if (p.kernel == MANY_BLOCK) return launch_gemm_block((Epilogue)EPI, g, p.block, s);
-        if (p.kernel == MANY_TILE) return launch_lds_tile<EPI>(g, s);
+        if constexpr (EPI != EPI_SWIGLU) return launch_lds_tile<EPI>(g, s);
         launch_swiglu_stream(g, p.stream_tm, s);
         return 0;
     }
+    if (EPI != EPI_STORE_F32 && M > 16 && (M <= 256 || EPI == EPI_SWIGLU)) return launch_regs((Epilogue)EPI, g, s);
     const bool far_rows = g.a_rows && (unsigned long long)g.a_total_rows * K * 2 > 0xffffffffull;      // gathered rows past what the offsets below hold
-    if ((use_skinny(EPI, M, N, K) || (g.a_panels && M <= kPanelRows)) && !far_rows) {
+    // logits of 17-32 rows: narrow ones only (wide ones on streaming blocks, see launch_lds_tile)
+    if ((M <= 16 || (M <= 32 && EPI == EPI_STORE_F32 && !(N >= 256 * 256 && kLmStream))) && !far_rows) {
         // wavefronts per block (= K slices): enough to keep ~2k wavefronts in flight (~4k for the SwiGLU
         // GEMM: 8 instead of 4 wavefronts per block took the ~1B verify kernel from 16.6 to 14.7 us), each with
         // at least 128 of K; K / nw must stay a multiple of the MFMA k (32)
@@ -1419,19 +1314,11 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         if (kForceNW > 0 && K % (std::max(kForceNW, 1) * 32) == 0) nw = kForceNW;
         if (EPI == EPI_SWIGLU && nw == 16) nw = 8;        // LDS reduction buffer stays <= 64 KB
         if (M <= 16) launch_skinny_nw<EPI, 1>(g, nw, s);
-        else launch_skinny_nw<EPI, 2>(g, nw, s);
+        else if constexpr (EPI == EPI_STORE_F32) launch_skinny_nw<EPI, 2>(g, nw, s);
         return EPI == EPI_RESIDUAL ? N / cols : 0;
     }
-    // streaming SwiGLU kernel at 193-256 rows when the matrix is wide enough for ~200 blocks (~8B shape: 118 -> 97 us; ~1B / ~3B
-    // have 128 blocks there and lose: 32 -> 52, 45 -> 68 us)
-    if (EPI == EPI_SWIGLU && M > 192 && M <= 256 && (N + 127) / 128 * 2 >= 192) {
-        // Two blocks of 128 rows or three of 96.  One block runs per CU at a time, so a launch takes (rounds of 256 blocks) x (time of
-        // a block), and a block's time grows with the operand rows it pulls (its activation rows + 2 x 128 weight rows).
-        const int gx = (N + 127) / 128;
-        launch_swiglu_stream(g, (3 * gx + 255) / 256 * (96 + 256) < (2 * gx + 255) / 256 * (128 + 256) ? 3 : 4, s);
-        return 0;
-    }
-    return launch_lds_tile<EPI>(g, s);
+    if constexpr (EPI != EPI_SWIGLU) return launch_lds_tile<EPI>(g, s);
+    return 0;
 }
 
 static GemmPlan block_plan(const BlockPlan& p) { return {"block", p.shape == 0 ? 256 : 128, p.shape == 2 ? 128 : 256, p.ks}; }
@@ -1458,21 +1345,18 @@ GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t w
     return block_plan(plan_gemm_block(epi, M, N, K, split, true, ws_bytes));
 }
 
-// Up to 16 rows: always (one panel; only the few-row kernel runs).  17-32 rows: plain activations, two panels, all four GEMMs on the few-row
-// kernel, without the reduce kernels that K-sliced tiles need behind them.  Whole calls of 17 / 24 / 32 rows in us, tiles and streaming blocks on
-// rows, then this: ~1B 1093 -> 948, 1116 -> 986, 1142 -> 1029; ~3B 2356 -> 2199, 2453 -> 2259, 2508 -> 2471.  Hi + lo parts double what a block
-// re-reads of the activations, and the tiles stay: ~8B 4177 and 4483, 4365 and 4794, 4551 and 5135.
+// Up to 16 rows one panel, plain activations of up to 32 rows two; up to 256 rows strips.
 // More than 256 rows, by the times that the plans expect: panels make the block kernel faster at every size, but only that kernel reads them,
 // and the ones made for fewer rows are ahead of it where its third row tile is mostly padding (~8B at 257 rows: rows 11.4 ms, panels 11.8) and
 // in layers much wider than d_model.  Rows where they are expected 4 % ahead, 8 % with more than 3/8 of that tile filled: over 19 layers at 17
 // row counts from 257 to 512 the calls chosen so take 0.4 % (d_model 2048 and more) and 2 % (less) longer than with the faster layout and forms.
-bool gemm_layer_panels(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes) {
-    if (M <= kPanelRows) return M <= 16 || !split;
-    if (M <= 256) return false;
+ActLayout gemm_layer_layout(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes) {
+    if (M <= 16 || (M <= kPanelRows && !split)) return ACT_PANELS;
+    if (M <= 256) return ACT_STRIPS;
     auto panels = [&](Epilogue epi, int N, int K) { return plan_gemm_block(epi, M, N, K, split, true, ws_bytes).us; };
     const float rows = plan_many<EPI_QKV>(M, qkv, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, qdim, split, ws_bytes).us +
                        plan_many<EPI_SWIGLU>(M, d_ff, d_model, split, ws_bytes).us + plan_many<EPI_RESIDUAL>(M, d_model, d_ff, split, ws_bytes).us;
-    return panels(EPI_QKV, qkv, d_model) + panels(EPI_RESIDUAL, d_model, qdim) + panels(EPI_SWIGLU, d_ff, d_model) + panels(EPI_RESIDUAL, d_model, d_ff) < (M <= 304 ? 1.04f : 1.08f) * rows;
+    return panels(EPI_QKV, qkv, d_model) + panels(EPI_RESIDUAL, d_model, qdim) + panels(EPI_SWIGLU, d_ff, d_model) + panels(EPI_RESIDUAL, d_model, d_ff) < (M <= 304 ? 1.04f : 1.08f) * rows ? ACT_PANELS : ACT_ROWS;
 }
 
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s) {

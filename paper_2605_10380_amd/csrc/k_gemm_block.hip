@@ -115,6 +115,9 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
     __shared__ float s_inv[BM];
 
     const int M = g.M, N = g.N, K = g.K;
+    // (strips: calls of up to 256 rows, which only come here with hi + lo parts)
+    const bool in_panels = g.a_layout != ACT_ROWS, strips = SPLIT && g.a_layout == ACT_STRIPS;
+    const ActLayout c_layout = SPLIT || g.c_layout != ACT_STRIPS ? g.c_layout : ACT_ROWS;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wm = wave / WN, wn = wave % WN, lrow = lane & 31, lg = lane >> 5;
 
@@ -133,7 +136,7 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
     // copies of this wavefront: A units of 16 rows x 32 k, B units of one chunk of a panel (1 KB as packed).
     // A as rows: lane l copies slot l % 4 of row l / 4; slot s of row r holds k-group s ^ swz(r): see the operand reads.
-    // A in panels (act_at): the unit is a chunk, copied as it lies; rows a short last panel does not have are its last one again.
+    // A in panels or strips (act_index): the unit is a chunk, copied as it lies; rows a short last panel does not have are its last one again.
     auto swz = [](int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); };
     unsigned a_off[LA];
     const char* a_ptr[LA];
@@ -142,10 +145,10 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
     for (int i = 0; i < LA; ++i) {
         const int unit = wave * LA + i, part = unit / (BM / 16), u = unit % (BM / 16);
         const char* base = (const char*)g.A + (SPLIT && part ? g.a_lo_off * 2 : 0);
-        if (g.a_panels) {
-            const int panel = min((m0 >> 4) + u, (M - 1) >> 4), rows = min(16, M - panel * 16);
-            a_step[i] = rows * 64;
-            a_ptr[i] = base + (long long)panel * 32 * K + (long long)(kbase >> 5) * a_step[i];
+        if (in_panels) {
+            const int panel = min((m0 >> 4) + u, (M - 1) >> 4), rows = strips ? 16 : min(16, M - panel * 16);
+            a_step[i] = strips ? ((M + 15) >> 4) * 1024 : rows * 64;
+            a_ptr[i] = base + (strips ? (long long)panel * 1024 : (long long)panel * 32 * K) + (long long)(kbase >> 5) * a_step[i];
             a_off[i] = (unsigned)((lane >> 4) * rows + min(lane & 15, rows - 1)) * 16u;
         } else {
             const int row = u * 16 + (lane >> 2);
@@ -185,7 +188,7 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
             for (int i = 0; i < L; ++i) copy(s, i);
     const bool inv_here = g.ssq && !SLICED;
     if (inv_here) {
-        if (g.a_panels) block_inv_rms_panels(g, m0, BM, s_inv);
+        if (in_panels) block_inv_rms_panels(g, m0, BM, s_inv);
         else if (g.nparts <= 4) block_inv_rms_few(g, m0, BM, s_inv);
         else block_inv_rms<16>(g, m0, BM, s_inv);
     }
@@ -213,7 +216,7 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
     unsigned a_at[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c)
-        a_at[c] = wm * TM * 2048 + (g.a_panels ? (lrow >> 4) * 1024 + (2 * c + lg) * 256 + (lrow & 15) * 16 : lrow * 64 + ((2 * c + lg) ^ swz(lrow)) * 16);
+        a_at[c] = wm * TM * 2048 + (in_panels ? (lrow >> 4) * 1024 + (2 * c + lg) * 256 + (lrow & 15) * 16 : lrow * 64 + ((2 * c + lg) ^ swz(lrow)) * 16);
     // column tile j of the wavefront, as a tile of the stage: j and j + 1 are gate and up, or the halves of a head
     const int half_tiles = EPI == EPI_QKV ? g.rope.kv.head_dim >> 6 : 1;      // QKV: 32-column tiles in half a head (1 or 2)
     auto tile_of = [&](int j) {
@@ -348,13 +351,13 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
                             const f32x2 v = pair_of_columns(xv[j][r] * gain[jp + j], xv[j][r + 1] * gain[jp + j], odd);
-                            if (m < M && live_n) store_split2(a16 + act_index(g.c_panels, m, col_of(jp + j) & ~1, M, N), g.c_lo_off, v);
+                            if (m < M && live_n) store_split2(a16 + act_index(c_layout, m, col_of(jp + j) & ~1, M, N), g.c_lo_off, v);
                         }
                     }
                     const float t = rows16_sum(ss, lane);    // partial sums of squares over the 64 columns
                     const int m = m0 + row_of(i, lrow >> 1);
                     const int part = (n0 + tile_of(jp) * 32) / 64;
-                    if ((lrow & 1) == 0 && m < M && live_n) g.ssq_out[ssq_index(g.c_panels, m, part, M, N / 64)] = t;
+                    if ((lrow & 1) == 0 && m < M && live_n) g.ssq_out[ssq_index(ssq_by_part(c_layout, M), m, part, M, N / 64)] = t;
                 }
             });
         });
@@ -373,7 +376,7 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
                     float h[8];
 #pragma unroll
                     for (int q = 0; q < 8; ++q) h[q] = silu_lean(acc[i][j][r + q] * inv) * (acc[i][j + 1][r + q] * inv);
-                    store_eight(m < M ? out + act_index(g.c_panels, m, nt + r * 2 + lg * 8, M, N) : nullptr, g.c_lo_off, h);
+                    store_eight(m < M ? out + act_index(c_layout, m, nt + r * 2 + lg * 8, M, N) : nullptr, g.c_lo_off, h);
                 }
             }
         }

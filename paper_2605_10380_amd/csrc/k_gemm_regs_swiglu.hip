@@ -1,0 +1,10 @@
+#include "k_gemm_regs.h"
+
+namespace ax {
+
+void launch_regs_swiglu(const GemmArgs& g, int shape, hipStream_t s) {
+    if (g.a_lo_off) launch_regs_shape<EPI_SWIGLU, true, false>(g, shape, s);
+    else launch_regs_shape<EPI_SWIGLU, false, false>(g, shape, s);
+}
+
+}  // namespace ax

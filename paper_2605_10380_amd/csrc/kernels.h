@@ -68,20 +68,27 @@ __device__ __forceinline__ float split_value(float v) {
     return v;
 }
 
-// Activations of calls with many rows lie in panels where producer and consumer can (GemmArgs::a_panels): an [M, K] matrix as panels of 16
-// rows, like the packed weights, each k-group of 8 of a panel as one run of its rows.  A last panel of fewer rows has shorter runs, so the
-// matrix takes no more room than as rows.  A GEMM's copy of 16 rows x 32 k to LDS is then 1 KB of whole 128-byte lines, where rows make it
-// 16 half lines.
-__host__ __device__ __forceinline__ long long act_index(bool panels, int m, int k, int M, int K) {
-    if (!panels) return (long long)m * K + k;
-    const int first = m & ~15, rows = M - first < 16 ? M - first : 16;
-    return (long long)first * K + (long long)(k >> 3) * (rows * 8) + (m & 15) * 8 + (k & 7);
+// How the activations of a call lie between the kernels of a layer (gemm_layer_layout): an [M, K] matrix
+//   in rows;
+//   in panels of 16 rows, like the packed weights, each k-group of 8 of a panel as one run of its rows.  A last panel of fewer rows has shorter
+//     runs, so the matrix takes no more room than as rows.  A GEMM's copy of 16 rows x 32 k to LDS is then 1 KB of whole 128-byte lines,
+//     where rows make it 16 half lines;
+//   in strips: 32 k of all rows at a time, panel after panel, the last one of 16 rows like the others - what a kernel that takes many row tiles
+//     at once reads is one run, at one offset for all calls of as many panels.
+enum ActLayout : unsigned char { ACT_ROWS = 0, ACT_PANELS = 1, ACT_STRIPS = 2 };
+__host__ __device__ __forceinline__ long long act_index(ActLayout layout, int m, int k, int M, int K) {
+    // (one formula: rows are panels of one row, and a strip's panels lie 512 apart; three formulas to choose from cost every epilogue 0.1 us)
+    const int in_panel = layout == ACT_ROWS ? 0 : m & 15, first = m - in_panel;
+    const int run = layout == ACT_ROWS ? 1 : layout == ACT_STRIPS || M - first >= 16 ? 16 : M - first;        // rows side by side
+    const int strip = layout == ACT_STRIPS ? (M + 15) / 16 * 512 : run * 32;
+    return (long long)first * (layout == ACT_STRIPS ? 32 : K) + in_panel * 8 + (long long)(k >> 5) * strip + ((k >> 3) & 3) * (run * 8) + (k & 7);
 }
 
-// Partial sums of x^2 behind activations that await their norm: [rows][parts]; in calls of more than 256 rows with activations in panels
-// [parts][rows], so that a thread that adds up a row reads beside its neighbours (`panels` here; panels of up to 32 rows keep [rows][parts]).
-__host__ __device__ __forceinline__ long long ssq_index(bool panels, int m, int part, int M, int nparts) {
-    return panels ? (long long)part * M + m : (long long)m * nparts + part;
+// Partial sums of x^2 behind activations that await their norm: [rows][parts]; behind strips, and panels of more than 32 rows, [parts][rows], so
+// that a thread that adds up a row reads beside its neighbours.
+__host__ __device__ __forceinline__ bool ssq_by_part(ActLayout layout, int M) { return layout == ACT_STRIPS || (layout == ACT_PANELS && M > 32); }
+__host__ __device__ __forceinline__ long long ssq_index(bool by_part, int m, int part, int M, int nparts) {
+    return by_part ? (long long)part * M + m : (long long)m * nparts + part;
 }
 
 // One GEMM of a bf16-weight model: C = A[M,K] * W[N,K]^T, A fp16, W bf16.
@@ -89,7 +96,7 @@ struct GemmArgs {
     const void* A;                    // fp16 [rows, K]
     long long a_lo_off;               // split activations: the lo parts of A lie this many elements behind A (0 = none)
     long long c_lo_off;               // ... and the lo parts of C16 (and of rope.q_out) this many elements behind it
-    bool a_panels, c_panels;          // A, C16 lie in panels (act_index) instead of rows: see gemm_layer_panels
+    ActLayout a_layout, c_layout;     // of A and C16
     int a_total_rows;                 // rows A has (a gather picks M of them)
     const int* a_rows;                // optional gather: A row of output row m is a_rows[m]
     const void *W, *W2;               // [N, K] packed by launch_pack_weights (fp16, MFMA operand order); W2 only for EPI_SWIGLU
@@ -116,28 +123,30 @@ constexpr int SPLITK_MAX = 8;
 // ssq_out (rows are that many floats apart): the consumer of the pending norm passes it as nparts.
 // It depends on which kernel ran (a few per row after a K-split reduce kernel, N / 64, N / 32 or N / 8-16
 // from kernels that finish a column block on their own).  Other epilogues return 0.
-// EPI_QKV writes its raw products to split_ws first on the tile kernel (65-256 rows, and where the plan takes it up to 512) and in K
-// slices; of up to 256 rows it has no other way there: -1, and nothing launched, if one [M, N] fp32
-// slab does not fit there.
+// EPI_QKV writes its raw products to split_ws first on the tile kernel (where the plan takes it, up to 512 rows) and in K slices; of plans that do
+// not, -1 and nothing launched if one [M, N] fp32 slab does not fit there.
 int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s);
 // The plan of a GEMM of more than 256 rows that are not gathered ("" = fewer rows, or N not a multiple of 64): kernel ("block", "tile" or
 // "stream"), rows of A and of W per block (EPI_SWIGLU: half of the latter gate, half up) and K slices.
 struct GemmPlan { const char* kernel; int rows, cols, slices; };
 GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
 GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);      // with A in panels
-// Whether the layers of a call of M rows keep their activations in panels (act_index) from kernel to kernel: all four GEMMs then run with
-// a_panels set, up to 32 rows on the few-row kernel and from 257 on the block kernel, on its plan for panels.  N of a GEMM: the layer's
-// sizes, all multiples of 64.
-bool gemm_layer_panels(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes);
+// How the layers of a call of M rows keep their activations from kernel to kernel: all four GEMMs then run with this a_layout.  Panels up to 16 rows
+// on the few-row kernel, to 32 rows (plain activations) on the register kernel and from 257 on the block kernel, on its plan for panels; strips
+// only on the register kernel.  N of a GEMM: the layer's sizes, all multiples of 64.
+ActLayout gemm_layer_layout(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes);
 // A GEMM on the block kernel with the shape and slices of `rows`, `cols`, `slices` whatever the plan would say (tests); returns as launch_gemm_bf16.
 int launch_gemm_block_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s);
+// The same for the register kernel (up to 256 rows), and whether there is such a tile.
+int launch_gemm_regs_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s);
+bool gemm_regs_built(Epilogue epi, bool split, int rows, int cols, int slices);
 // Repacks a row-major bf16 [N, K] matrix (N % 16 == 0, K % 32 == 0) into what every bf16-model GEMM
 // kernel reads: fp16 values in 16-row panels, 32-k chunks in MFMA operand order; src and dst must not overlap.
 // `bad` (device int, may be NULL) is set to 1 if some weight does not survive the narrowing (not finite in fp16).
 void launch_pack_weights(const void* src, void* dst, int N, int K, hipStream_t s, int* bad = nullptr);
 // bf16-weight models: x[r,:] = emb[tok], a[r,:] = fp16(x * gain), ssq[r][0] = sum x^2, ssq[r][1..nparts) = 0
-// a_lo_off != 0: also the lo parts fp16(x * gain - a), that many elements behind a; panels: a in panels (act_index).  d % 8 == 0
-void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off, bool panels,
+// a_lo_off != 0: also the lo parts fp16(x * gain - a), that many elements behind a.  d % 8 == 0
+void launch_embed_norm(const void* emb, const int* row_tok, const void* gain, float* x, void* a, long long a_lo_off, ActLayout layout,
                        float* ssq, int nparts, int n_rows, int d, hipStream_t s);
 
 // fp32 models: h[i, :] = rmsnorm(x[rows[i], :]) * gain
@@ -166,11 +175,11 @@ void launch_gemm(DType dt, Epilogue epi, const void* A, const void* W, const voi
 // Causal attention of the new rows over the paged cache (which already holds the new rows).
 // out [n_rows, Hq, hd] in the activation type.  `partials` is fp32 scratch for the split-KV
 // path (bf16 only); n_splits >= 1, split_waves 1 or 4 wavefronts per block of it.
-// q_lo_off / out_lo_off: split activations (see GemmArgs): lo parts of q read, lo parts of out written (0 = none).  out_panels (bf16
-// only): out in panels (act_index) instead of rows.
+// q_lo_off / out_lo_off: split activations (see GemmArgs): lo parts of q read, lo parts of out written (0 = none).  out_layout (bf16
+// only): how out lies.
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer,
                       const StepView& sv, int n_q_heads, float* partials, int n_splits, int split_waves,
-                      hipStream_t s, long long q_lo_off = 0, long long out_lo_off = 0, bool out_panels = false);
+                      hipStream_t s, long long q_lo_off = 0, long long out_lo_off = 0, ActLayout out_layout = ACT_ROWS);
 // Floats of `partials` launch_attention needs for n_tiles q tiles (of 32 rows) and n_splits splits.
 size_t attention_partial_floats(int n_tiles, int n_kv_heads, int head_dim, int n_splits);
 // out[r] = argmax of logits[r, 0..V), lowest index on ties.  scratch: 2*rows*ARGMAX_PARTS ints.
