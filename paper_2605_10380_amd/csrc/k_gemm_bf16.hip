@@ -1230,8 +1230,10 @@ static RegsPlan plan_regs(Epilogue epi, int M, int N, int K, bool split, bool sl
             const long long blocks = (long long)gx * gy * ks;
             const float rounds = (blocks + 255) / 256, crowd = std::min(1.f, std::max(0.6f, blocks / 256.f));
             const float miss = (float)t.nt / gy, hit = t.nt - miss + t.mt * na;
-            float us = rounds * (4.4f + 0.12f * std::max(0, t.mt * t.nt - 24) + (float)chunks / ks * (0.025f * crowd * miss + 0.0145f * hit));
+            const int tiles = t.mt * t.nt;
+            float us = rounds * ((tiles <= 4 ? 3.4f : 4.4f) + 0.12f * std::max(0, tiles - 24) + (float)chunks / ks * (0.025f * crowd * miss + 0.0145f * hit));
             if (ks > 1) us += 3.4f + 0.4f * ks + 0.4e-6f * ks * M * N;
+            else if (epi == EPI_RESIDUAL) us += 0.01f * std::max(0, gx - 192);      // (partial sums of x^2 a row, for the next GEMM to read)
             if (force >= 0 && force_epi == (epi == EPI_RESIDUAL && K > 2 * N ? 4 : epi) && !(c == force && ks == force_ks)) us += 1e6f;
             if (best.shape < 0 || us <= best.us) best = {c, ks, us};
         }
