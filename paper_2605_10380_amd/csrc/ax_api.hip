@@ -300,7 +300,7 @@ void plan_items(std::vector<AttnItem>& groups, int n_heads, bool hd64, bool q_sp
 // into a pinned staging slot.  Nothing is launched here.
 struct CallPlan {
     int n = 0, n_rows = 0, n_out = 0, n_tiles = 0, tile_nq = 1, bt_total = 0, max_steps = 1, out_mode = 0, slot = 0;
-    int n_tiles_shared = 0, shared_nq = 4, shared_len = 0, shared_splits = 1;   // shared-prefix attention pass (0 groups = none)
+    int n_tiles_shared = 0, shared_len = 0, shared_splits = 1;   // shared-prefix attention pass (0 groups = none)
     std::vector<AttnItem> items, merges;                                        // block-kernel calls (tile_nq 4)
     size_t o_tok = 0, o_pos = 0, o_seq = 0, o_slot = 0, o_out = 0, o_P = 0, o_T = 0, o_row0 = 0, o_bt = 0, o_tinfo = 0,
            o_tab = 0, ints = 0;
@@ -387,11 +387,13 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         const int shared = (int)(common * 16) & ~31;
         if ((long long)(n - 1) * shared >= kSharedMinKeys) {
             cp.shared_len = shared;
-            cp.shared_nq = n_rows * G > 128 ? 8 : 4;
-            cp.n_tiles_shared = (int)((n_rows * G + 32 * cp.shared_nq - 1) / (32 * cp.shared_nq));
-            int want = std::max(1, 2048 / (cp.n_tiles_shared * c.n_kv_heads * cp.shared_nq));
+            const int tiles = ax::SHARED_TILES;
+            cp.n_tiles_shared = (int)((n_rows * G + 32 * tiles - 1) / (32 * tiles));
+            // a block on every CU (head_dim 64, whose blocks are half the size: two), beside those of the private keys (16 sessions of 9 rows over 6144 shared
+            // keys, half / these / twice as many slices: ~3B 4534 / 4214 / 4590 us a step, ~1B over 2048 keys 1781 / 1667 / 1629 from 1024 wavefronts on)
+            int want = std::max(1, (c.head_dim == 64 ? 2048 : 1024) / (cp.n_tiles_shared * c.n_kv_heads * tiles));
             want = std::min(want, std::max(1, shared / 64));
-            const size_t cap = m->lay.max_records / ((size_t)cp.n_tiles_shared * c.n_kv_heads * cp.shared_nq);
+            const size_t cap = m->lay.max_records / ((size_t)cp.n_tiles_shared * c.n_kv_heads * tiles);
             want = std::min(want, std::max(1, (int)cap));
             cp.shared_splits = 1;
             while (cp.shared_splits * 2 <= want) cp.shared_splits *= 2;
@@ -429,7 +431,7 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
     // checked all the same, before anything is committed, because a kernel would write past the region otherwise)
     if (c.dtype == AX_BF16 &&
         ((cp.tile_nq == 1 && (size_t)cp.n_tiles * c.n_kv_heads > m->lay.max_records) ||
-         (size_t)cp.n_tiles_shared * cp.shared_nq * c.n_kv_heads * cp.shared_splits > m->lay.max_records))
+         (size_t)cp.n_tiles_shared * ax::SHARED_TILES * c.n_kv_heads * cp.shared_splits > m->lay.max_records))
         return fail(AX_ERR_UNSUPPORTED, "%d attention tile groups of %d tiles exceed the workspace's %zu partial records",
                     cp.n_tiles, cp.tile_nq, m->lay.max_records);
 
@@ -481,7 +483,7 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         for (int i = 0; i < cp.shared_splits; ++i) {
             const int steps = cp.shared_len / 32, per = (steps + cp.shared_splits - 1) / cp.shared_splits, at = g * cp.shared_splits + i;
             int* ti = d + cp.o_tinfo + (size_t)(cp.n_tiles + at) * 8;
-            ti[0] = at; ti[1] = g * 32 * cp.shared_nq; ti[2] = cp.shared_len; ti[3] = (int)n_rows; ti[4] = 0; ti[5] = d[cp.o_bt + 0];
+            ti[0] = at; ti[1] = g * 32 * ax::SHARED_TILES; ti[2] = cp.shared_len; ti[3] = (int)n_rows; ti[4] = 0; ti[5] = d[cp.o_bt + 0];
             ti[6] = std::min((i + 1) * per, steps); ti[7] = std::min(i * per, steps);
         }
     for (size_t i = 0; i < cp.items.size(); ++i) {
@@ -523,7 +525,7 @@ ax_status enqueue_call(ax_model* m, const CallPlan& cp, void* out, hipStream_t s
     sv.bt = dev_d + cp.o_tab;
     sv.n_rows = cp.n_rows; sv.n_seq = cp.n; sv.n_out = cp.n_out; sv.n_tiles = cp.n_tiles; sv.tile_nq = cp.tile_nq;
     sv.n_items = (int)cp.items.size(); sv.n_merge = (int)cp.merges.size();
-    sv.n_tiles_shared = cp.n_tiles_shared; sv.shared_nq = cp.shared_nq; sv.shared_len = cp.shared_len; sv.shared_splits = cp.shared_splits;
+    sv.n_tiles_shared = cp.n_tiles_shared; sv.shared_len = cp.shared_len; sv.shared_splits = cp.shared_splits;
 
     const ax::DType dt = c.dtype == AX_F32 ? ax::F32 : ax::BF16;
     const ax::KVGeom& kg = cp.pool->geom;

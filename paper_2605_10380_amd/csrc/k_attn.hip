@@ -245,9 +245,8 @@ __device__ __forceinline__ bool online_softmax_step(f32x16& s, int kv0, int g, i
 // (head, slice) share one L2 and run at the same time, and so do the slices of one head, which all read that
 // head's q rows (with 8 KV heads: one head per XCD; K, V and q each cross HBM once).
 struct AttnWork { int tile, hk, split; };
-__device__ __forceinline__ AttnWork attn_work() {
-    const unsigned nx = gridDim.x, nz = gridDim.z, total = nx * gridDim.y * nz;      // nz: a power of two (choose_splits)
-    unsigned id = blockIdx.x + nx * (blockIdx.y + gridDim.y * blockIdx.z);
+__device__ __forceinline__ AttnWork attn_work(unsigned id, unsigned nx, unsigned ny, unsigned nz) {
+    const unsigned total = nx * ny * nz;                                             // nz: a power of two (choose_splits)
     if ((total & 7u) == 0) id = (id & 7u) * (total >> 3) + (id >> 3);
     const unsigned rest = id / nx;
     return {(int)(id - rest * nx), (int)(rest >> __builtin_ctz(nz)), (int)(rest & (nz - 1))};
@@ -274,7 +273,7 @@ struct AttnArgs {
     float* partials;
     // shared-prefix pass of a many-sequence call (see launch_attention); unused otherwise
     const float* shared_partials;
-    int shared_splits, shared_nq, shared_len;
+    int shared_splits, shared_len;
 };
 
 // Everything a step needs from memory is requested as early as possible, because at verify
@@ -287,18 +286,18 @@ struct AttnArgs {
 // sessions verified together 5359 -> 5162 us (~1B verify over 4352 keys 843 -> 826 us, no more than its runs differ).
 // NW = 1: caches too short to give every CU such a block (~1B decode over 1301 keys: 727 us a step, 755 with NW = 4).
 // QS: q comes as hi and lo parts (split activations): the score product takes both against the same K operand.
-template <int HD, int NW, bool QS>
-__global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
+// wk: the block's work; lds: split_lds(HD, NW) bytes of LDS.
+constexpr int split_lds(int hd, int nw) { return nw * ((nw > 1 ? hd / 8 : 1) * 1024 + 256); }
+// AHEAD: a key step's operands have registers of their own while the step before is multiplied (one block on a CU); else K of the next step is
+// asked for behind this one's scores and V behind its output, in the same registers (two blocks on a CU).
+template <int HD, int NW, bool QS, bool AHEAD>
+__device__ __forceinline__ void attn_split(const AttnArgs& a, AttnWork wk, char* lds) {
     constexpr int KQ = HD / 16;          // MFMA k-steps of the score product
     constexpr int NP = QS ? 2 : 1;
     constexpr int DT = HD / 32;          // 32-channel tiles of the output
     constexpr int PS = HD * 32 + 64;     // floats of one partial: O^T [HD][32], m[32], l[32]
-    __shared__ f32x4 s_o[NW][NW > 1 ? DT * 4 : 1][64];
-    __shared__ float s_m[NW][32], s_l[NW][32];
-    // all arguments in one round trip (left alone, the compiler fetches them where they are used)
-    asm volatile("" :: "s"(a.q), "s"(a.q_lo_off), "s"(a.kv.base), "s"(a.kv.n_blocks), "s"(a.kv.n_kv_heads), "s"(a.layer), "s"(a.Hq), "s"(a.G), "s"(a.n_splits),
-                       "s"(a.tile_info), "s"(a.bt), "s"(a.partials));
-    const AttnWork wk = attn_work();
+    auto s_o = (f32x4(*)[NW > 1 ? DT * 4 : 1][64])lds;
+    auto s_m = (float(*)[32])(lds + NW * (NW > 1 ? DT * 4 : 1) * 1024), s_l = s_m + NW;
     const int tile = wk.tile, hk = wk.hk, split = wk.split;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5;
     const int Hq = a.Hq, Hkv = a.kv.n_kv_heads, G = a.G;
@@ -342,16 +341,19 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
 
-    f16x8 kf[2][KQ];                     // K / V operands of the current and the next step
-    f16x4 vq[2][DT][4];
+    f16x8 kf[AHEAD ? 2 : 1][KQ];         // K / V operands of the current and the next step
+    f16x4 vq[AHEAD ? 2 : 1][DT][4];
     int tabv = 0;                        // block ids of steps [chunk, chunk + 32): lane i holds block 2*chunk + i
-    auto fetch = [&](int buf, int st, int chunk) {
+    auto fetch_k = [&](int buf, int st, int chunk) {
         const int kv0 = st * 32;
         const int key = min(kv0 + ql, kv_len - 1);
         const int kblk = __shfl(tabv, min(key >> 4, last_blk) - 2 * chunk, 64);
         const f16* krow = Kp + ((long long)kblk * 16 + (key & 15)) * HD + g * 8;
 #pragma unroll
         for (int kk = 0; kk < KQ; ++kk) kf[buf][kk] = *(const f16x8*)(krow + kk * 16);
+    };
+    auto fetch_v = [&](int buf, int st, int chunk) {
+        const int kv0 = st * 32;
         const int b0 = __shfl(tabv, min(kv0 >> 4, last_blk) - 2 * chunk, 64);
         const int b1 = __shfl(tabv, min((kv0 >> 4) + 1, last_blk) - 2 * chunk, 64);
 #pragma unroll
@@ -364,8 +366,24 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
             vq[buf][d][3] = *(const f16x4*)(v1 + 8);
         }
     };
-    auto process = [&](int buf, int st) {
+    auto process = [&](int buf, int st, auto behind_scores) {
         const int kv0 = st * 32;
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[buf][kk], qf[p][kk], s, 0, 0, 0);
+        behind_scores();
+        float alpha;
+        f16x8 pb[2];
+        if (online_softmax_step(s, kv0, g, pos_q, kv0 + 31 > pos_min, c, m, l, alpha, pb)) {
+#pragma unroll
+            for (int d = 0; d < DT; ++d)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+        }
         if (kv0 + 32 > kv_len) {
             // the sequence ends inside this step (its last one): slots of the last block past the end were never
             // written by this sequence and may hold anything - their V operands become exact zeros, so that a
@@ -377,21 +395,6 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         if (kv0 + qd * 8 + g * 4 + i >= kv_len) vq[buf][d][qd][i] = (f16)0.f;
-        }
-        f32x16 s;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KQ; ++kk)
-#pragma unroll
-            for (int p = 0; p < NP; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[buf][kk], qf[p][kk], s, 0, 0, 0);
-        float alpha;
-        f16x8 pb[2];
-        if (online_softmax_step(s, kv0, g, pos_q, kv0 + 31 > pos_min, c, m, l, alpha, pb)) {
-#pragma unroll
-            for (int d = 0; d < DT; ++d)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
         }
 #pragma unroll
         for (int d = 0; d < DT; ++d) {
@@ -409,23 +412,39 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
         // (no fetch sits behind a branch that the products ahead of it do not share: the compiler then knows how many loads are out and
         // waits for one step's operands while the next one's stay in flight)
         auto issue = [&](int buf, int st) {
-            fetch(buf, st, chunk);
+            fetch_k(buf, st, chunk);
+            fetch_v(buf, st, chunk);
             __builtin_amdgcn_sched_barrier(0);
         };
+        auto nothing = [] {};
         issue(0, chunk);
         int st = chunk;
+        if constexpr (!AHEAD) {
+            for (; st + 1 < c_hi; ++st) {
+                process(0, st, [&] {
+                    __builtin_amdgcn_sched_barrier(0);
+                    fetch_k(0, st + 1, chunk);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_v(0, st + 1, chunk);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            process(0, st, nothing);
+            continue;
+        }
         for (; st + 2 < c_hi; st += 2) {
             issue(1, st + 1);
-            process(0, st);
+            process(0, st, nothing);
             issue(0, st + 2);
-            process(1, st + 1);
+            process(1, st + 1, nothing);
         }
         if (st + 1 < c_hi) {
             issue(1, st + 1);
-            process(0, st);
-            process(1, st + 1);
+            process(0, st, nothing);
+            process(1, st + 1, nothing);
         } else {
-            process(0, st);
+            process(0, st, nothing);
         }
     }
 
@@ -478,8 +497,17 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
     }
 }
 
+template <int HD, int NW, bool QS>
+__global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[split_lds(HD, NW)];
+    // all arguments in one round trip (left alone, the compiler fetches them where they are used)
+    asm volatile("" :: "s"(a.q), "s"(a.q_lo_off), "s"(a.kv.base), "s"(a.kv.n_blocks), "s"(a.kv.n_kv_heads), "s"(a.layer), "s"(a.Hq), "s"(a.G), "s"(a.n_splits),
+                       "s"(a.tile_info), "s"(a.bt), "s"(a.partials));
+    attn_split<HD, NW, QS, true>(a, attn_work(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.z), lds);
+}
+
 // ------------------------------------------------------------------------------ MFMA block kernel
-// Long extends (many q tiles per KV head) and the shared-prefix pass: a block of NQ wavefronts owns NQ consecutive q tiles (32 * NQ
+// Long extends (many q tiles per KV head) and the shared-prefix pass: a block of NQ = 4 wavefronts owns 4 consecutive q tiles (128
 // stacked rows) of one KV head and a range of key steps - one ITEM of the list the host planned (StepView::items).  The K and V pages of
 // a 32-key step are copied to LDS by the memory pipeline (no registers in between), S stages deep, one barrier per step, and
 // shared by the NQ tiles; everything after that is the per-wavefront online softmax of attn_split_kernel.  An item that
@@ -492,18 +520,17 @@ __global__ __launch_bounds__(64 * NW) void attn_split_kernel(AttnArgs a) {
 //   V: [2 pages][HD channels][16 tokens]; the two halves of a channel's 32 bytes trade places in every other group of 8 channels.
 // The score product takes the keys in the order 0-3, 8-11, 4-7, 12-15 (of each page): then a lane ends up with the scores of
 // keys 8 g .. 8 g + 7 of both pages (g = lane / 32), and its V operand is ONE 16-byte read.
-template <int HD, int NQ, int S, bool QS = false>
-__global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(HD == 64 ? (QS ? 3 : 4) : (QS || NQ == 8 ? 2 : 3))))
-void attn_block_kernel(AttnArgs a) {
+constexpr int STAGES = 3;
+// id: the block's number of n_items * KV heads, items first; smem: STAGES * 128 * HD bytes of LDS.
+template <int HD, bool QS>
+__device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned id, unsigned nx, char* smem) {
+    constexpr int NQ = 4, S = STAGES;
     constexpr int KQ = HD / 16, DT = HD / 32, PS = HD * 32 + 64;
     constexpr int NP = QS ? 2 : 1;                    // q in hi and lo parts (split activations)
     constexpr int KB = 32 * HD * 2, STAGE = 2 * KB;   // bytes of K (and of V) per step
     constexpr int U = STAGE / 1024, L = (U + NQ - 1) / NQ, PU = U / 4;      // copy units per step, per wavefront, per page of K or V
     static_assert(U % NQ == 0, "whole units per wavefront");
-    __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
-
-    const unsigned nx = gridDim.x, total = nx * gridDim.y;
-    unsigned id = blockIdx.x + nx * blockIdx.y;       // (see attn_work: with 8 KV heads, one head per XCD)
+    const unsigned total = nx * (unsigned)a.kv.n_kv_heads;      // (see attn_work: with 8 KV heads, one head per XCD)
     if ((total & 7u) == 0) id = (id & 7u) * (total >> 3) + (id >> 3);
     const int item = (int)(id % nx), hk = (int)(id / nx);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ql = lane & 31, g = lane >> 5;
@@ -682,6 +709,27 @@ void attn_block_kernel(AttnArgs a) {
     }
 }
 
+template <int HD, bool QS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HD == 64 ? (QS ? 3 : 4) : (QS ? 2 : 3))))
+void attn_block_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(1024))) char smem[STAGES * 128 * HD];
+    attn_block<HD, QS>(a, blockIdx.x + gridDim.x * blockIdx.y, gridDim.x, smem);
+}
+
+// The shared-prefix pass of a many-sequence call and the private keys of its sequences in one launch: blocks of the former first, one on every CU, the
+// latter beside them.  The pass is bound by its products and the private keys by memory (16 sessions of the ~3B shape over 6144 shared and 1024-2048
+// private keys: 21.1 and 26.8 us one after the other, 39.2 together; with half as many records of the shared keys, on blocks of 4 tiles instead of 8, the
+// merge takes 8.3 instead of 12.6).
+template <int HD, bool QS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void attn_shared_kernel(AttnArgs sh, AttnArgs a, int items, int tiles) {
+    constexpr int PASS = STAGES * 128 * HD, OWN = split_lds(HD, 4);
+    __shared__ __attribute__((aligned(1024))) char lds[PASS > OWN ? PASS : OWN];
+    const unsigned heads = (unsigned)a.kv.n_kv_heads, n = (unsigned)items * heads;
+    if (blockIdx.x < n) attn_block<HD, QS>(sh, blockIdx.x, (unsigned)items, lds);
+    else attn_split<HD, 4, QS, false>(a, attn_work(blockIdx.x - n, (unsigned)tiles, heads, (unsigned)a.n_splits), lds);
+}
+
 // Merges the key slices of one q tile.  grid (n_tiles * Hkv, HD / 4), 256 threads =
 // 32 query rows x 8 slice groups; a block produces 4 output channels.  A thread loads the
 // (m, l, 4 channels) of its slices s = sg, sg + 8, ... in one go (up to 16 slices in registers),
@@ -711,9 +759,9 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     const float* sbase = nullptr;                              // the row's record in the shared pass, slice 0
     long long sstride = 0;
     if (a.shared_splits > 0) {
-        const int rc = min(r, n_stacked - 1), R = (row0 + rc / G) * G + rc % G, gsz = 32 * a.shared_nq;
-        sbase = a.shared_partials + ((long long)((R / gsz) * a.shared_splits * Hkv + hk) * a.shared_nq + (R % gsz) / 32) * PS + (R & 31);
-        sstride = (long long)Hkv * a.shared_nq * PS;
+        const int rc = min(r, n_stacked - 1), R = (row0 + rc / G) * G + rc % G, gsz = 32 * SHARED_TILES;
+        sbase = a.shared_partials + ((long long)((R / gsz) * a.shared_splits * Hkv + hk) * SHARED_TILES + (R % gsz) / 32) * PS + (R & 31);
+        sstride = (long long)Hkv * SHARED_TILES * PS;
     }
     auto slice = [&](int s) { return s < own_splits ? base + s * stride : sbase + (s - own_splits) * sstride; };
 
@@ -810,9 +858,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     const float* sbase = nullptr;                              // the row's record in a shared-prefix pass, slice 0
     long long sstride = 0;
     if (a.shared_splits > 0) {
-        const int R = (row0 + r / G) * G + r % G, gsz = 32 * a.shared_nq;
-        sbase = a.shared_partials + ((long long)((R / gsz) * a.shared_splits * Hkv + hk) * a.shared_nq + (R % gsz) / 32) * PS + (R & 31);
-        sstride = (long long)Hkv * a.shared_nq * PS;
+        const int R = (row0 + r / G) * G + r % G, gsz = 32 * SHARED_TILES;
+        sbase = a.shared_partials + ((long long)((R / gsz) * a.shared_splits * Hkv + hk) * SHARED_TILES + (R % gsz) / 32) * PS + (R & 31);
+        sstride = (long long)Hkv * SHARED_TILES * PS;
     }
     auto slice = [&](int s) { return s < own_splits ? base + s * stride : sbase + (s - own_splits) * sstride; };
 
@@ -876,7 +924,8 @@ size_t attention_partial_floats(int n_tiles, int n_kv_heads, int head_dim, int n
 template <int HD>
 static void launch_tiles(const AttnArgs& a, int n_tiles, int waves, hipStream_t s) {
     dim3 grid(n_tiles, a.kv.n_kv_heads, a.n_splits);
-    if (waves == 4) {
+    if (waves == 0) {                                          // done by attn_shared_kernel
+    } else if (waves == 4) {
         if (a.q_lo_off) attn_split_kernel<HD, 4, true><<<grid, 256, 0, s>>>(a);
         else attn_split_kernel<HD, 4, false><<<grid, 256, 0, s>>>(a);
     } else {
@@ -890,17 +939,16 @@ static void launch_tiles(const AttnArgs& a, int n_tiles, int waves, hipStream_t 
     else attn_combine_kernel<HD><<<dim3(records, HD / 4), 256, 0, s>>>(a);
 }
 
-template <int HD, int NQ>
+template <int HD>
 static void launch_block(const AttnArgs& a, int n_items, hipStream_t s) {
     dim3 grid((unsigned)n_items, (unsigned)a.kv.n_kv_heads);
-    if (a.q_lo_off) attn_block_kernel<HD, NQ, 3, true><<<grid, 64 * NQ, 0, s>>>(a);
-    else attn_block_kernel<HD, NQ, 3, false><<<grid, 64 * NQ, 0, s>>>(a);
+    if (a.q_lo_off) attn_block_kernel<HD, true><<<grid, 256, 0, s>>>(a);
+    else attn_block_kernel<HD, false><<<grid, 256, 0, s>>>(a);
 }
 // The items of a block-kernel pass, then the groups of 4 tiles whose keys they cut (n_merge; the shared-prefix pass has none).
-template <int NQ>
 static void launch_items(const AttnArgs& a, int n_items, int n_merge, hipStream_t s) {
-    if (a.kv.head_dim == 64) launch_block<64, NQ>(a, n_items, s);
-    else launch_block<128, NQ>(a, n_items, s);
+    if (a.kv.head_dim == 64) launch_block<64>(a, n_items, s);
+    else launch_block<128>(a, n_items, s);
     if (n_merge == 0) return;
     AttnArgs mg = a;
     mg.tile_info = a.tile_info + (size_t)n_items * 8;
@@ -929,7 +977,7 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
     a.q_lo_off = q_lo_off; a.out_lo_off = out_lo_off; a.n_rows = sv.n_rows; a.out_layout = out_layout;
     const int hd = kv.head_dim;
     if (sv.tile_nq == 4) {                                     // long extends: 4 tiles per block, K/V through LDS
-        launch_items<4>(a, sv.n_items, sv.n_merge, s);
+        launch_items(a, sv.n_items, sv.n_merge, s);
     } else {
         if (sv.n_tiles_shared > 0) {
             // Many sequences that share a cached prefix (the same leading blocks): the keys of the
@@ -940,11 +988,19 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
             AttnArgs sh = a;
             sh.tile_info = sv.tile_info + (size_t)sv.n_tiles * 8;
             sh.partials = partials + attention_partial_floats(sv.n_tiles, kv.n_kv_heads, hd, n_splits);
-            if (sv.shared_nq == 4) launch_items<4>(sh, sv.n_tiles_shared * sv.shared_splits, 0, s);
-            else launch_items<8>(sh, sv.n_tiles_shared * sv.shared_splits, 0, s);
+            const int items = sv.n_tiles_shared * sv.shared_splits;
+            if (split_waves == 4) {
+                const unsigned blocks = (unsigned)(items + sv.n_tiles * n_splits) * (unsigned)kv.n_kv_heads;
+                if (hd == 64 && q_lo_off) attn_shared_kernel<64, true><<<blocks, 256, 0, s>>>(sh, a, items, sv.n_tiles);
+                else if (hd == 64) attn_shared_kernel<64, false><<<blocks, 256, 0, s>>>(sh, a, items, sv.n_tiles);
+                else if (q_lo_off) attn_shared_kernel<128, true><<<blocks, 256, 0, s>>>(sh, a, items, sv.n_tiles);
+                else attn_shared_kernel<128, false><<<blocks, 256, 0, s>>>(sh, a, items, sv.n_tiles);
+                split_waves = 0;
+            } else {
+                launch_items(sh, items, 0, s);
+            }
             a.shared_partials = sh.partials;
             a.shared_splits = sv.shared_splits;
-            a.shared_nq = sv.shared_nq;
             a.shared_len = sv.shared_len;
         }
         if (hd == 64) launch_tiles<64>(a, sv.n_tiles, split_waves, s); else launch_tiles<128>(a, sv.n_tiles, split_waves, s);

@@ -13,6 +13,7 @@ namespace ax {
 // ("the activation type" below), products on the fp16 MFMA with fp32 accumulation.
 enum DType { F32 = 0, BF16 = 1 };
 
+constexpr int SHARED_TILES = 4;
 // Device views of the per-call descriptor (one packed int32 buffer uploaded per call).
 struct StepView {
     const int* row_tok;     // [n_rows] token id
@@ -28,7 +29,7 @@ struct StepView {
     // attention work, 8 ints (32 bytes, aligned) a record.  Stacked rows of a sequence: row t of query head g of a KV head is t * G + g.
     //   tile_nq == 1 (fp32 models; verify steps and short extends): n_tiles records of one 32-row tile each -
     //     sequence, first stacked row, P, T, first row of the sequence, block-table offset, 0, first key;
-    //     then (n_tiles_shared > 0: sequences whose block tables start alike) the items of a pass of groups of shared_nq tiles over
+    //     then (n_tiles_shared > 0: sequences whose block tables start alike) the items of a pass of groups of SHARED_TILES tiles over
     //     ALL rows of the call against keys [0, shared_len), shared_splits items per group
     //   tile_nq == 4 (long extends): n_items ITEMS of 4 tiles and a range of key steps of 32 each -
     //     slot of the partial records (-1: all the keys, writes the output itself), first stacked row, P, T, first row of the
@@ -37,7 +38,7 @@ struct StepView {
     //     first slot, first stacked row, number of slots, T, first row of the sequence, 0, 0, 0
     const int* tile_info;
     int n_rows, n_seq, n_out, n_tiles, tile_nq, n_items, n_merge;
-    int n_tiles_shared, shared_nq, shared_len, shared_splits;      // 0 groups = no shared-prefix pass
+    int n_tiles_shared, shared_len, shared_splits;                 // 0 groups = no shared-prefix pass
 };
 
 enum Epilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };

@@ -614,6 +614,40 @@ def test_batched_verify_over_a_long_shared_prefix(B, which):
     dm.close()
 
 
+@pytest.mark.parametrize("hd,G,split", [(64, 4, 0), (128, 3, 0), (64, 2, 1), (128, 4, 1)])
+def test_shared_and_private_keys_in_one_launch(B, hd, G, split):
+    """Sessions whose private keys are long enough for blocks of four wavefronts (7 sessions, 16 KV heads, 1 to 1100 private keys): the shared prefix, which
+    ends inside a block, and the private keys go in one launch.  Rows of a session that end inside a tile, sessions without private keys."""
+    sh = I.DecoderShape("shared", 1, 256, 16 * G, 16, hd, 192, 512, "bf16")
+    w = I.make_weights(sh, 41)
+    prefix = I.templated_prompt(sh.vocab, 41, 700)
+    dm = B.DeviceModel(sh, w, max_pos=2048, max_tokens=1200, pool_tokens=8192, max_seqs=7, act_split=split)
+    root, root_ref = dm.new_kv(), okv(sh)
+    dm.extend(root, prefix)
+    O.forward(sh, w, prefix, root_ref)
+    kvs, refs = [], []
+    for s, hl in enumerate([0, 1100, 37, 640, 1, 996, 300]):
+        kv, ref = B.ax_kv_fork(root, -1), root_ref.fork()
+        if hl:
+            h = I.zipf_tokens(sh.vocab, 41, f"h{s}", hl)
+            dm.extend(kv, h)
+            O.forward(sh, w, h, ref)
+        kvs.append(kv)
+        refs.append(ref)
+    cfg = B.make_config(sh, 2048, 1200, 7, split)
+    tiles = sum(-(-(3 + 2 * s) * G // 32) for s in range(7))
+    assert B.ax_dbg_split_plan(cfg, tiles * 16, (700 % 32 + 1100 + 15) // 32)[0] == 4
+    news = [I.zipf_tokens(sh.vocab, 41, f"n{s}", 3 + 2 * s) for s in range(7)]
+    got = dm.extend_batch(kvs, news, B.AX_OUT_ALL_LOGITS).cpu().numpy()
+    at = 0
+    for s in range(7):
+        check_logits(sh, got[at:at + len(news[s])], O.forward(sh, w, news[s], refs[s]), f"session {s}")
+        at += len(news[s])
+    for kv in kvs + [root]:
+        B.ax_kv_free(kv)
+    dm.close()
+
+
 def test_two_resident_models_forked_sessions(B):
     """The plan-out agent's shape at a size the oracle can follow: two decoders with their own
     weights and pools resident together; per model, sessions fork one shared prefix, build
