@@ -30,7 +30,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // fp32 models: everything on the fp32 matrix instruction (16x16x4), one block per tile of 16 stacked rows (t * G + g) and
 // KV head; its NW wavefronts take every NW-th page of 16 keys with their own online softmax and meet in LDS at the end,
 // so a call of a few rows still keeps NW chains of page loads in flight and needs no second kernel.  (A wavefront
-// per (row, query head) walking its keys 64 at a time took 137 us on a 5-row step over 512 keys; this takes 13 us.)
+// per (row, query head) walking its keys 64 at a time took 137 us on a 5-row step over 512 keys; this takes 12 us.)
 //
 // S^T = K * Q^T per page: lane l supplies slot l % 16 of the page (and stacked row l % 16 of q) at channels 16 c +
 // 4 * (l / 16) .. + 3 - one float4, element j for instruction j, the same order of channels on both sides - and receives
@@ -39,17 +39,22 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // is one float4 as well.
 //
 // HDT: 16-channel tiles the registers hold (head_dim <= 16 * HDT; channels past head_dim are zeros).
-template <int HDT, int NW>
+// FULL: head_dim is 16 * HDT.
+// OT: 16-channel tiles of the OUTPUT that the block computes (blockIdx.z: which).  A call of a few rows leaves most of the chip idle,
+// and on the one CU that its block runs on the products of 33 pages alone take 4.4 us.  With a block per 16 output channels each CU does the
+// scores again but only its part of the second product, of the V loads and of the merge.  5 rows over 517 keys: 13.3 -> 11.6 us,
+// with the loads ahead of the products (below) and the merge's weights worked out once instead of by every wavefront.
+template <int HDT, int OT, int NW, bool FULL>
 __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, KVGeom kv, int layer,
                                                            const int* __restrict__ tile_info, const int* __restrict__ bt, int Hq,
                                                            int subs) {
-    __shared__ __attribute__((aligned(16))) f32x4 s_o[NW][HDT][64];
-    __shared__ float s_m[NW][16], s_l[NW][16];
+    __shared__ __attribute__((aligned(16))) f32x4 s_o[NW][OT][64];
+    __shared__ float s_m[NW][16], s_l[NW][16], s_w[NW][16];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
     const int hd = kv.head_dim, Hkv = kv.n_kv_heads, G = Hq / Hkv, hk = blockIdx.y;
     const int* ti = tile_info + (blockIdx.x / subs) * 8;         // a record covers subs tiles of 16 rows
     const int4 ti0 = *(const int4*)ti, ti1 = *(const int4*)(ti + 4);
-    const int P = ti0.z, T = ti0.w, row0 = ti1.x, r0 = ti0.y + (int)(blockIdx.x % subs) * 16, n_stacked = T * G;
+    const int P = ti0.z, T = ti0.w, row0 = ti1.x, r0 = ti0.y + (int)(blockIdx.x % subs) * 16, n_stacked = T * G, c0 = blockIdx.z * OT;
     if (r0 >= n_stacked) return;                                 // the record's last tiles may lie past the sequence's rows
     const int* tab = bt + ti1.y;
     const int kv_len = P + T;
@@ -62,7 +67,9 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
     auto load_row = [&](const float* row, int c) {               // channels 16 c + 4 lg .. + 3 of a row of hd channels
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         const int ch = c * 16 + lg * 4;
-        if (vec) {
+        if (FULL) {
+            v = *(const f32x4*)(row + ch);
+        } else if (vec) {
             if (ch < hd) v = *(const f32x4*)(row + ch);
         } else {
 #pragma unroll
@@ -76,32 +83,44 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
 
     const float scale = 1.0f / sqrtf((float)hd);
     float m = -INFINITY, l = 0.f;                                // l: this lane's keys only, summed over the lanes at the end
-    f32x4 o[HDT];
+    f32x4 o[OT];
 #pragma unroll
-    for (int c = 0; c < HDT; ++c) o[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < OT; ++c) o[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
     const int r_last = min(r0 + 15, n_stacked - 1);
     const int pages = (P + r_last / G + 16) >> 4;                // up to the page of the tile's last visible key
-    // (fetching the next page's operands ahead was slower, 12.9 -> 15.6 us: a wavefront has two or three pages, and the
-    // second copy of the loop body costs more instruction fetches than the loads it hides)
-    for (int pg = wave; pg < pages; pg += NW) {
-        const int blk = tab[pg], kv0 = pg * 16;
+    // page ids of up to 64 of this wavefront's pages at a time; K of its next page is asked for behind this one's scores, V behind its output, in the
+    // same registers: one chain of loads less a page, and the loop stays one body (with a second one for a second set of operands the
+    // instruction fetches cost more than the loads it hid, 12.9 -> 15.6 us)
+    const int mine = wave < pages ? (pages - wave + NW - 1) / NW : 0;
+    int ids = 0;
+    auto page_id = [&](int i) {
+        if ((i & 63) == 0) ids = tab[min(wave + NW * (i + lane), pages - 1)];
+        return __builtin_amdgcn_readlane(ids, i & 63);
+    };
+    f32x4 kf[HDT], vf[OT];
+    auto load_k = [&](int blk) {
         const float* kp = Kp + ((long long)blk * 16 + lr) * hd;
-        const float* vp = Vp + (long long)blk * 16 * hd + lg * 4;
-        f32x4 kf[HDT], vf[HDT];
 #pragma unroll
         for (int c = 0; c < HDT; ++c) kf[c] = load_row(kp, c);
+    };
+    auto load_v = [&](int blk) {
+        const float* vp = Vp + (long long)blk * 16 * hd + lg * 4;
 #pragma unroll
-        for (int c = 0; c < HDT; ++c) {
-            vf[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            if (c * 16 + lr < hd) vf[c] = *(const f32x4*)(vp + (c * 16 + lr) * 16);
+        for (int c = 0; c < OT; ++c) {
+            if (!FULL) vf[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (FULL || c * 16 + lr < hd) vf[c] = *(const f32x4*)(vp + ((c0 + c) * 16 + lr) * 16);
         }
-        if (kv0 + 16 > kv_len) {                                 // slots past the sequence's end hold anything: exact zeros
-#pragma unroll
-            for (int c = 0; c < HDT; ++c)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) if (kv0 + lg * 4 + i >= kv_len) vf[c][i] = 0.f;
-        }
+    };
+    int blk = 0;
+    if (mine > 0) {
+        blk = page_id(0);
+        load_k(blk);
+        load_v(blk);
+    }
+    for (int i = 0; i < mine; ++i) {
+        const int kv0 = (wave + i * NW) * 16;
+        if (i + 1 < mine) blk = page_id(i + 1);                  // (the last page's again at the end: no branch around the loads)
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};     // two chains of dependent products
 #pragma unroll
         for (int c = 0; c < HDT; ++c) {
@@ -110,6 +129,9 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
             s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][2], qf[c][2], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][3], qf[c][3], s1, 0, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_k(blk);
+        __builtin_amdgcn_sched_barrier(0);
         float mx = -INFINITY;
         f32x4 p;
 #pragma unroll
@@ -128,39 +150,55 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
             l += p[i];
         }
         m = mn;
+        if (kv0 + 16 > kv_len) {                                 // slots past the sequence's end hold anything: exact zeros
 #pragma unroll
-        for (int c = 0; c < HDT; ++c) {
+            for (int c = 0; c < OT; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) if (kv0 + lg * 4 + i >= kv_len) vf[c][i] = 0.f;
+        }
+#pragma unroll
+        for (int c = 0; c < OT; ++c) {
             o[c] *= alpha;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][i], p[i], o[c], 0, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(blk);
+        __builtin_amdgcn_sched_barrier(0);
     }
 
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     if (lg == 0) { s_m[wave][lr] = m; s_l[wave][lr] = l; }
 #pragma unroll
-    for (int c = 0; c < HDT; ++c) s_o[wave][c][lane] = o[c];
+    for (int c = 0; c < OT; ++c) s_o[wave][c][lane] = o[c];
+    __syncthreads();
+    if (threadIdx.x < 16 * NW) {                                 // one (wavefront, row) per thread: its weight and its part of the row's sum
+        const int w = threadIdx.x >> 4;
+        float M = s_m[0][lr];
+#pragma unroll
+        for (int j = 1; j < NW; ++j) M = fmaxf(M, s_m[j][lr]);   // finite: every row sees key 0
+        const float e = expf(s_m[w][lr] - M);
+        s_w[w][lr] = e;
+        s_l[w][lr] *= e;
+    }
     __syncthreads();
     // wavefront w finishes channel tiles w, w + NW, ..: register i of lane l is channel 4 * (l / 16) + i of stacked row l % 16
-    float M = -INFINITY, L = 0.f, wt[NW];
+    if (wave >= OT || r0 + lr >= n_stacked) return;
+    float L = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][lr]);       // finite: every row sees key 0
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        wt[w] = expf(s_m[w][lr] - M);
-        L += wt[w] * s_l[w][lr];
-    }
-    if (r0 + lr >= n_stacked) return;
+    for (int w = 0; w < NW; ++w) L += s_l[w][lr];
     float* orow = out + ((long long)(row0 + tq) * Hq + hk * G + rq % G) * hd;
-    for (int c = wave; c < HDT; c += NW) {
+    for (int c = wave; c < OT; c += NW) {
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += wt[w] * s_o[w][c][lane];
+        for (int w = 0; w < NW; ++w) v += s_w[w][lr] * s_o[w][c][lane];
+        const int ch = (c0 + c) * 16 + lg * 4;
+        if (FULL) {
+            *(f32x4*)(orow + ch) = v / L;
+        } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int ch = c * 16 + lg * 4 + i;
-            if (ch < hd) orow[ch] = v[i] / L;
+            for (int i = 0; i < 4; ++i) if (ch + i < hd) orow[ch + i] = v[i] / L;
         }
     }
 }
@@ -965,10 +1003,22 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
         dim3 grid(sv.n_tiles * subs, kv.n_kv_heads);
         const float* qf = (const float*)q;
         float* of = (float*)out;
+        // Blocks of 16 output channels while there is a CU for each: 8 / 256 rows over 512 keys (head_dim 64, 2 KV heads) 13.1 -> 11.7 / 16.2 -> 14.6 us;
+        // at 512 rows, two rounds of blocks, the scores they repeat cost more than the idle CUs: 19.8 -> 30.6 us.
+        const long long blocks = (long long)grid.x * grid.y;
+        if (hd == 64 && blocks * 4 <= 256) {
+            grid.z = 4;
+            attn_f32_kernel<4, 1, 16, true><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        } else if (hd == 128 && blocks * 8 <= 256) {
+            grid.z = 8;
+            attn_f32_kernel<8, 1, 16, true><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        }
         // wavefronts per block: as many as the LDS record of their partial outputs (4 KB per 64 channels each) leaves room for
-        if (hd <= 64) attn_f32_kernel<4, 16><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
-        else if (hd <= 128) attn_f32_kernel<8, 8><<<grid, 512, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
-        else attn_f32_kernel<16, 4><<<grid, 256, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else if (hd == 64) attn_f32_kernel<4, 4, 16, true><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else if (hd < 64) attn_f32_kernel<4, 4, 16, false><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else if (hd == 128) attn_f32_kernel<8, 8, 8, true><<<grid, 512, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else if (hd < 128) attn_f32_kernel<8, 8, 8, false><<<grid, 512, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else attn_f32_kernel<16, 16, 4, false><<<grid, 256, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
         return;
     }
     AttnArgs a{};

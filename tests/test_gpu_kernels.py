@@ -263,6 +263,32 @@ def test_f32_model_head_dims_and_row_edges(torch_cuda, hd, d, F, P, T):
     dm.close()
 
 
+@pytest.mark.parametrize("hd,P,T", [(64, 0, 1), (64, 17, 5), (64, 530, 33), (64, 31, 170), (64, 31, 171), (128, 0, 2), (128, 500, 6),
+                                    (128, 33, 85), (128, 33, 86)])
+def test_f32_attention_channel_blocks(torch_cuda, hd, P, T):
+    """fp32 attention in blocks of 16 output channels and, one tile of rows further (3 query heads to a KV head: 170 rows of head_dim 64, 85 of
+    128), in whole ones: fewer pages than wavefronts and several each, a last page of one key, pool memory full of NaN patterns.  Bound: fp32
+    products and sums of head_dim and P + T terms, 2e-5 of the largest value as for the other fp32 stages."""
+    from paper_2605_10380_amd import binding as B
+    sh = I.DecoderShape("f32-attn", 1, 64, 6, 2, hd, 80, 301, "f32")
+    w = I.make_weights(sh, 12)
+    toks = I.templated_prompt(sh.vocab, 12, P + T)
+    dm = B.DeviceModel(sh, w, max_pos=P + T + 16, max_tokens=256, pool_tokens=P + T + 64, pool_fill=0xFF)
+    kv = dm.new_kv()
+    okv = O.KVCache(sh.n_layers, sh.n_kv_heads, sh.head_dim)
+    for at in range(0, P, 256):
+        dm.extend(kv, toks[at:min(P, at + 256)])
+        O.forward(sh, w, toks[at:min(P, at + 256)], okv)
+    dm.extend(kv, toks[P:], B.AX_OUT_LAST_ARGMAX)
+    got = np.zeros((T, sh.n_q_heads * hd), dtype=np.float32)
+    B.ax_dbg_read(dm.model, 3, got)
+    tr = {}
+    O.forward(sh, w, toks[P:], okv, trace=tr)
+    ref = tr["attn"].reshape(T, -1)
+    assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max()
+    dm.close()
+
+
 def _one_layer(torch_cuda, sh, P, T, seed, max_tokens, act_split=0):
     """Attention output and residual stream of the last T rows of a one-layer model, and the oracle's."""
     from paper_2605_10380_amd import binding as B
