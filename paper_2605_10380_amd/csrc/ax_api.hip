@@ -82,7 +82,7 @@ Layout make_layout(const ax_model_config& c) {
     const size_t T = (size_t)c.max_tokens, S = (size_t)c.max_seqs, a = (size_t)isz(c.dtype);
     const int G = c.n_q_heads / c.n_kv_heads;
     // Partial records of the attention: one per (q tile of 32 stacked rows, KV head, key slice).  The most a pass can need with
-    // one slice is (T G / 32 + 8 per sequence) tiles per KV head (groups of 4 or 8 tiles pad a sequence to whole groups); the slice
+    // one slice is (T G / 32 + 8 per sequence) tiles per KV head (groups of 4 tiles pad a sequence to whole groups); the slice
     // counts are then chosen to stay inside this capacity.  Room for two passes: single tiles and the shared-prefix pass.  Planned
     // items have the room of both: a call has either of the two, and items that run at once never need more than 4096 records.
     L.max_records = std::max((size_t)MIN_RECORDS, ((T * G + 31) / 32 + 8 * S + 2) * (size_t)c.n_kv_heads);

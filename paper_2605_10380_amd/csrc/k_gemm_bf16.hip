@@ -1016,6 +1016,8 @@ static const int kQkvKs = env_int("AX_QKV_KS", 0);   // experiment knob: K slice
 // Two block shapes, both of 8 wavefronts: 64 x 128 (2 x 4 wavefronts of 32 x 32) and 128 x 128
 // (wavefront tile 64 x 32).  The larger one pulls a third fewer operand bytes per output and
 // wins wherever it still gives the chip enough blocks (measured per GEMM class below).
+// (Figures at 256 rows and fewer below are from when these blocks served such calls, now the register kernel's; the rules, of tiles and CUs, are
+// reached at 257-512 rows and by odd widths.)
 struct TilePlan { bool big; int ks; };
 template <int EPI>
 static TilePlan plan_tile(int M, int N, int K, size_t ws_bytes) {
