@@ -862,7 +862,11 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     float L = 0.f, o = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) { L += red[i][1][ql]; o += red[i][2 + sg][ql]; }
-    f16* dst = a.out + act_index(a.out_layout, row0 + r / G, (hk * G + r % G) * HD + ch0 + sg, a.n_rows, a.Hq * HD);
+    const int m = row0 + r / G, k = (hk * G + r % G) * HD + ch0 + sg;
+    long long at;
+    if (a.out_layout == ACT_STRIPS) at = act_index(ACT_STRIPS, m, k, a.n_rows, a.Hq * HD);
+    else at = act_index_few(a.out_layout == ACT_PANELS, m, k, a.n_rows, a.Hq * HD);
+    f16* dst = a.out + at;
     const float res = split_value(o / L);
     const f16 hi = (f16)res;
     *dst = hi;

@@ -892,7 +892,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                 float h[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) h[r] = silu_f(sum[0][r] * inv) * (sum[NB - 1][r] * inv);
-                store_split4((f16*)g.C16 + act_index(g.c_layout == ACT_PANELS ? ACT_PANELS : ACT_ROWS, m, n, M, N), g.c_lo_off, h);
+                store_split4((f16*)g.C16 + act_index_few(g.c_layout == ACT_PANELS, m, n, M, N), g.c_lo_off, h);
             }
         } else if (EPI == EPI_RESIDUAL) {
             float ss = 0.f;
@@ -906,7 +906,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
                         h[r] = xn[r] * __uint_as_float(pre_g[r] << 16);
                         ss += xn[r] * xn[r];
                     }
-                    store_split4((f16*)g.C16 + act_index(g.c_layout == ACT_PANELS ? ACT_PANELS : ACT_ROWS, m, n, M, N), g.c_lo_off, h);
+                    store_split4((f16*)g.C16 + act_index_few(g.c_layout == ACT_PANELS, m, n, M, N), g.c_lo_off, h);
                 }
             }
             if (g.gain_next) {           // sum of squares over the block's COLS columns, per row
