@@ -313,6 +313,11 @@ struct AttnArgs {
     const float* shared_partials;
     int shared_splits, shared_len;
 };
+// Element (m, k) of the output: strips on a branch of their own, since the one formula for all layouts costs every store more.
+__device__ __forceinline__ long long out_index(const AttnArgs& a, int m, int k) {
+    if (a.out_layout == ACT_STRIPS) return act_index(ACT_STRIPS, m, k, a.n_rows, a.Hq * a.kv.head_dim);
+    return act_index_few(a.out_layout == ACT_PANELS, m, k, a.n_rows, a.Hq * a.kv.head_dim);
+}
 
 // Everything a step needs from memory is requested as early as possible, because at verify
 // sizes the kernel is a chain of dependent memory latencies, not a bandwidth problem: the tile
@@ -720,7 +725,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned id, unsig
         for (int d = 0; d < DT; ++d)
 #pragma unroll
             for (int r = 0; r < 16; r += 4) {
-                f16* dst = a.out + act_index(a.out_layout, row0 + tq, (hk * G + gq) * HD + d * 32 + r * 2 + g * 4, a.n_rows, Hq * HD);
+                f16* dst = a.out + out_index(a, row0 + tq, (hk * G + gq) * HD + d * 32 + r * 2 + g * 4);
                 f16x4 hi, lo;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -862,11 +867,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     float L = 0.f, o = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) { L += red[i][1][ql]; o += red[i][2 + sg][ql]; }
-    const int m = row0 + r / G, k = (hk * G + r % G) * HD + ch0 + sg;
-    long long at;
-    if (a.out_layout == ACT_STRIPS) at = act_index(ACT_STRIPS, m, k, a.n_rows, a.Hq * HD);
-    else at = act_index_few(a.out_layout == ACT_PANELS, m, k, a.n_rows, a.Hq * HD);
-    f16* dst = a.out + at;
+    f16* dst = a.out + out_index(a, row0 + r / G, (hk * G + r % G) * HD + ch0 + sg);
     const float res = split_value(o / L);
     const f16 hi = (f16)res;
     *dst = hi;
@@ -946,7 +947,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     const float inv = 1.0f / L;
 #pragma unroll
     for (int c0 = 0; c0 < CPT; c0 += 8) {
-        f16* dst = a.out + act_index(a.out_layout, row0 + r / G, (hk * G + r % G) * HD + cg * CPT + c0, a.n_rows, a.Hq * HD);
+        f16* dst = a.out + out_index(a, row0 + r / G, (hk * G + r % G) * HD + cg * CPT + c0);
         f16x8 v, lo;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {

@@ -118,6 +118,10 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
     // (strips: calls of up to 256 rows, which only come here with hi + lo parts)
     const bool in_panels = g.a_layout != ACT_ROWS, strips = SPLIT && g.a_layout == ACT_STRIPS;
     const ActLayout c_layout = SPLIT || g.c_layout != ACT_STRIPS ? g.c_layout : ACT_ROWS;
+    auto out_index = [&](int m, int n) {                         // (plain activations never leave here in strips)
+        if constexpr (SPLIT) return act_index(c_layout, m, n, g.M, g.N);
+        else return act_index_few(c_layout != ACT_ROWS, m, n, g.M, g.N);
+    };
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wm = wave / WN, wn = wave % WN, lrow = lane & 31, lg = lane >> 5;
 
@@ -351,7 +355,7 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
                             const f32x2 v = pair_of_columns(xv[j][r] * gain[jp + j], xv[j][r + 1] * gain[jp + j], odd);
-                            if (m < M && live_n) store_split2(a16 + act_index(c_layout, m, col_of(jp + j) & ~1, M, N), g.c_lo_off, v);
+                            if (m < M && live_n) store_split2(a16 + out_index(m, col_of(jp + j) & ~1), g.c_lo_off, v);
                         }
                     }
                     const float t = rows16_sum(ss, lane);    // partial sums of squares over the 64 columns
@@ -376,7 +380,7 @@ void gemm_block_kernel(GemmArgs g, int gx, int gy, int group) {
                     float h[8];
 #pragma unroll
                     for (int q = 0; q < 8; ++q) h[q] = silu_lean(acc[i][j][r + q] * inv) * (acc[i][j + 1][r + q] * inv);
-                    store_eight(m < M ? out + act_index(c_layout, m, nt + r * 2 + lg * 8, M, N) : nullptr, g.c_lo_off, h);
+                    store_eight(m < M ? out + out_index(m, nt + r * 2 + lg * 8) : nullptr, g.c_lo_off, h);
                 }
             }
         }
