@@ -24,6 +24,10 @@ ax_status ax_dbg_gemm(int dtype, int epilogue, const void *A, const void *W, con
  * key steps of 32 of the longest sequence.  Writes the wavefronts per block (1 or 4) and the key slices per item.  Host only. */
 ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps, int *waves, int *slices);
 
+/* Whether that many records (tiles of 32 stacked rows x KV heads) of so many key slices each (a shared prefix's among them) are added up by a block
+ * per record (1) or by blocks of 4 output channels (0).  Host only. */
+ax_status ax_dbg_merge_plan(int records, int slices, int *by_record);
+
 /* What a bf16-weight GEMM of more than 256 rows runs on: *kernel (static text) "block", "tile" or "stream", rows of A and of W per block
  * (SwiGLU: half of the latter gate, half up) and K slices; "" and zeros for fewer rows or N not a multiple of 64.  epilogue as
  * ax_dbg_gemm, 3 = QKV (rotary, KV append).  split: activations in hi + lo parts.  split_ws_bytes: scratch for K slices.  Host only. */

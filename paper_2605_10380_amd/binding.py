@@ -91,6 +91,7 @@ def _load():
         "ax_exspec_generate": (C.c_int, [vp, vp, vp, i32p, i64, C.c_int32, C.c_int, C.c_int, C.c_int, C.c_uint64, i32p,
                                          C.POINTER(ax_exspec_stats), vp]),
         "ax_dbg_split_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+        "ax_dbg_merge_plan": (C.c_int, [C.c_int, C.c_int, C.POINTER(C.c_int)]),
         "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
                                        C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_panel_plan": (C.c_int, [C.c_int] * 5 + [C.c_size_t] + [C.POINTER(C.c_int)] * 3),
@@ -398,6 +399,13 @@ def ax_dbg_split_plan(cfg, items: int, max_steps: int):
     waves, slices = C.c_int(), C.c_int()
     _check(lib.ax_dbg_split_plan(C.byref(cfg), items, max_steps, C.byref(waves), C.byref(slices)))
     return waves.value, slices.value
+
+
+def ax_dbg_merge_plan(records: int, slices: int) -> bool:
+    """Whether key slices are added up by a block per record."""
+    by_record = C.c_int()
+    _check(lib.ax_dbg_merge_plan(records, slices, C.byref(by_record)))
+    return bool(by_record.value)
 
 
 def ax_dbg_gemm_plan(epilogue: int, M: int, N: int, K: int, split: bool = False, split_ws_bytes: int = 1 << 40):

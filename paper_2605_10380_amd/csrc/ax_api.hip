@@ -1269,6 +1269,12 @@ ax_status ax_dbg_split_plan(const ax_model_config* cfg, int items, int max_steps
     return AX_OK;
 }
 
+ax_status ax_dbg_merge_plan(int records, int slices, int* by_record) {
+    if (records <= 0 || slices <= 0 || !by_record) return fail(AX_ERR_INVALID, "bad argument");
+    *by_record = ax::attention_merge_by_record(records, slices);
+    return AX_OK;
+}
+
 ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char** kernel, int* rows, int* cols,
                            int* slices) {
     if (epilogue < 0 || epilogue > 3 || M <= 0 || N <= 0 || K <= 0 || !kernel || !rows || !cols || !slices) return fail(AX_ERR_INVALID, "bad argument");

@@ -975,10 +975,8 @@ static void launch_tiles(const AttnArgs& a, int n_tiles, int waves, hipStream_t 
         if (a.q_lo_off) attn_split_kernel<HD, 1, true><<<grid, 64, 0, s>>>(a);
         else attn_split_kernel<HD, 1, false><<<grid, 64, 0, s>>>(a);
     }
-    // few records with many slices (one session): blocks of 4 channels that spread the slices over
-    // threads; many records with few slices (many sessions): one block per record
     const int records = n_tiles * a.kv.n_kv_heads;
-    if (records >= 64 && a.n_splits + a.shared_splits <= 32) attn_merge_kernel<HD, false><<<records, 256, 0, s>>>(a);
+    if (attention_merge_by_record(records, a.n_splits + a.shared_splits)) attn_merge_kernel<HD, false><<<records, 256, 0, s>>>(a);
     else attn_combine_kernel<HD><<<dim3(records, HD / 4), 256, 0, s>>>(a);
 }
 

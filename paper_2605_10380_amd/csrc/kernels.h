@@ -187,6 +187,12 @@ void launch_gemm(DType dt, Epilogue epi, const void* A, const void* W, const voi
 void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer,
                       const StepView& sv, int n_q_heads, float* partials, int n_splits, int split_waves,
                       hipStream_t s, long long q_lo_off = 0, long long out_lo_off = 0, ActLayout out_layout = ACT_ROWS);
+// Which kernel adds up the key slices of single tiles: a block per record (tile x KV head) that walks the record's slices (true), or blocks of 4
+// output channels that spread a record's slices over threads (false).  The first takes about 4 us + 0.4 a slice (head_dim 64: 0.2) while there is a
+// CU for every record, the second 2 us + 0.1 a record (0.05), so the line lies at records / 5 slices.  First / second in us, head_dim 128: 64 records
+// with 17 / 24 slices 10.9 and 7.9 / 12.7 and 8.0, 96 with 10 / 18 7.5 and 9.6 / 11.0 and 10.4, 128 with 18 11.1 and 13.2, 256 with 10 9.4 and 21.9;
+// head_dim 64: 64 with 17 7.4 and 5.0, 128 with 18 8.2 and 7.8, 256 with 10 6.7 and 12.3.  Over 32 slices the second, up to 128 records: 17.9 and 14.9.
+inline bool attention_merge_by_record(int records, int slices) { return records >= 64 && slices <= 32 && slices <= records / 5; }
 // Floats of `partials` launch_attention needs for n_tiles q tiles (of 32 rows) and n_splits splits.
 size_t attention_partial_floats(int n_tiles, int n_kv_heads, int head_dim, int n_splits);
 // out[r] = argmax of logits[r, 0..V), lowest index on ties.  scratch: 2*rows*ARGMAX_PARTS ints.
