@@ -24,6 +24,12 @@ ax_status ax_dbg_gemm(int dtype, int epilogue, const void *A, const void *W, con
  * key steps of 32 of the longest sequence.  Writes the wavefronts per block (1 or 4) and the key slices per item.  Host only. */
 ax_status ax_dbg_split_plan(const ax_model_config *cfg, int items, int max_steps, int *waves, int *slices);
 
+/* The pass over the keys of a prefix that the sequences of a call share: groups of 128 of the call's stacked rows, and key slices of each.  own_tiles:
+ * tiles of 32 stacked rows of the sequences, own_steps: key steps of 32 of them all behind the prefix; one_launch: these go in one launch with the pass
+ * (ax_dbg_split_plan: 4 wavefronts).  Host only. */
+ax_status ax_dbg_shared_plan(const ax_model_config *cfg, int rows, int keys, int own_tiles, long long own_steps, int one_launch, int *groups,
+                             int *slices);
+
 /* Whether that many records (tiles of 32 stacked rows x KV heads) of so many key slices each (a shared prefix's among them) are added up by a block
  * per record (1) or by blocks of 4 output channels (0).  Host only. */
 ax_status ax_dbg_merge_plan(int records, int slices, int *by_record);

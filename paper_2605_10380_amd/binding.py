@@ -91,6 +91,8 @@ def _load():
         "ax_exspec_generate": (C.c_int, [vp, vp, vp, i32p, i64, C.c_int32, C.c_int, C.c_int, C.c_int, C.c_uint64, i32p,
                                          C.POINTER(ax_exspec_stats), vp]),
         "ax_dbg_split_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+        "ax_dbg_shared_plan": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.c_int, C.c_int, C.c_longlong, C.c_int, C.POINTER(C.c_int),
+                                         C.POINTER(C.c_int)]),
         "ax_dbg_merge_plan": (C.c_int, [C.c_int, C.c_int, C.POINTER(C.c_int)]),
         "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
                                        C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
@@ -399,6 +401,13 @@ def ax_dbg_split_plan(cfg, items: int, max_steps: int):
     waves, slices = C.c_int(), C.c_int()
     _check(lib.ax_dbg_split_plan(C.byref(cfg), items, max_steps, C.byref(waves), C.byref(slices)))
     return waves.value, slices.value
+
+
+def ax_dbg_shared_plan(cfg, rows: int, keys: int, own_tiles: int, own_steps: int, one_launch: bool):
+    """(groups of 128 stacked rows, key slices) of the pass over a shared prefix."""
+    groups, slices = C.c_int(), C.c_int()
+    _check(lib.ax_dbg_shared_plan(C.byref(cfg), rows, keys, own_tiles, own_steps, int(one_launch), C.byref(groups), C.byref(slices)))
+    return groups.value, slices.value
 
 
 def ax_dbg_merge_plan(records: int, slices: int) -> bool:

@@ -211,6 +211,45 @@ int choose_splits(size_t max_records, int items, int nq, int max_steps) {
     return p2;
 }
 
+// Key slices of the shared-prefix pass: `groups` of SHARED_TILES tiles over `keys` shared keys; own_tiles single tiles of the sequences with own_steps key
+// steps of their own altogether; one_launch: these are blocks of four wavefronts and go in the same launch (launch_attention).
+//   * head_dim 64, whose blocks are half the size, and one launch with much private work: a power of two that gives every CU a block (head_dim 64: two) or
+//     fewer (16 sessions of 9 rows over 6144 shared keys, half / these / twice as many: ~3B 4534 / 4214 / 4590 us a step, ~1B over 2048 keys
+//     1781 / 1667 / 1629 from 1024 wavefronts on).
+//   * One launch with private work of less than half the shared keys': nobody fills the CUs that such a power leaves without a block, so as
+//     near to a block for each as it goes (~3B, 40 sessions of 9 rows, 9 groups over 6144 keys with 500 private ones, attention in us a layer: 88 in 2 slices,
+//     64 in 4; ~8B, 16 of 9, 5 groups, 1500: 66 in 4, 57 in 6 - but over 2500 keys, private work near the shared, 37 in 4, 44 in 6).
+//   * A launch of its own: as many blocks as run one, two or three (hi + lo parts: two) to a CU, by the time of a key step (times measured with that many on every
+//     CU) and what a slice more costs the merge.  One to a CU up to 5 groups, and up to 12 over 1000-2500 keys; two behind that (~3B over 6144 keys, one / two: 4
+//     groups 39.1 / 40.8, 7 56.5 / 49.8, 11 92.7 / 71.6, 20 170 / 106; over 2500: 4 28.9 / 32.4, 8 37.9 / 38.6, 20 85.6 / 63.6; ~8B over 6144: 5 50.7 / 50.6, 9 83.5 /
+//     70.9, 18 196 / 132).
+int shared_groups(int stacked_rows) { return (stacked_rows + 32 * ax::SHARED_TILES - 1) / (32 * ax::SHARED_TILES); }
+int shared_slices(size_t max_records, int groups, int n_heads, int head_dim, bool q_split, int keys, int own_tiles, long long own_steps, bool one_launch) {
+    const int blocks = groups * n_heads, steps = keys / 32;      // blocks of a slice
+    const int limit = std::min(std::max(1, keys / 64), std::max(1, (int)(max_records / ((size_t)blocks * ax::SHARED_TILES))));
+    auto some = [&](int n) { return std::min(limit, std::max(1, n)); };
+    if (head_dim == 64 || (one_launch && own_steps * 2 > (long long)groups * ax::SHARED_TILES * steps)) {
+        const int want = some((head_dim == 64 ? 512 : 256) / blocks);
+        int p2 = 1;
+        while (p2 * 2 <= want) p2 *= 2;
+        return p2;
+    }
+    int slices = some((256 + blocks / 2) / blocks);
+    if (!one_launch) {
+        static const struct { float fixed, step; } kTimes[2][3] = {{{5.f, 0.77f}, {9.f, 1.09f}, {10.f, 1.5f}}, {{5.5f, 0.94f}, {10.f, 1.42f}, {}}};
+        const float merge = 0.3f + 0.0017f * own_tiles * n_heads;
+        float best = 1e30f;
+        for (int b = 1; b <= (q_split ? 2 : 3); ++b) {
+            const int n = some(256 * b / blocks);
+            const auto& t = kTimes[q_split][b - 1];
+            const float us = t.fixed + t.step * ((steps + n - 1) / n) + merge * n;
+            if (us < best) { best = us; slices = n; }
+        }
+    }
+    const int per = (steps + slices - 1) / slices;
+    return (steps + per - 1) / per;                              // (none of them empty)
+}
+
 // Work of the block attention kernel: a group of q tiles of sequence s and its key steps [lo, hi); slot >= 0: partial records.
 // Merge records: first slot and number of slices.
 struct AttnItem { int s, r0, lo, hi, slot, n; };
@@ -387,16 +426,16 @@ ax_status prepare_call(ax_model* m, int n, ax_kv* const* kvs, const int32_t* tok
         const int shared = (int)(common * 16) & ~31;
         if ((long long)(n - 1) * shared >= kSharedMinKeys) {
             cp.shared_len = shared;
-            const int tiles = ax::SHARED_TILES;
-            cp.n_tiles_shared = (int)((n_rows * G + 32 * tiles - 1) / (32 * tiles));
-            // a block on every CU (head_dim 64, whose blocks are half the size: two), beside those of the private keys (16 sessions of 9 rows over 6144 shared
-            // keys, half / these / twice as many slices: ~3B 4534 / 4214 / 4590 us a step, ~1B over 2048 keys 1781 / 1667 / 1629 from 1024 wavefronts on)
-            int want = std::max(1, (c.head_dim == 64 ? 2048 : 1024) / (cp.n_tiles_shared * c.n_kv_heads * tiles));
-            want = std::min(want, std::max(1, shared / 64));
-            const size_t cap = m->lay.max_records / ((size_t)cp.n_tiles_shared * c.n_kv_heads * tiles);
-            want = std::min(want, std::max(1, (int)cap));
-            cp.shared_splits = 1;
-            while (cp.shared_splits * 2 <= want) cp.shared_splits *= 2;
+            cp.n_tiles_shared = shared_groups((int)n_rows * G);
+            int longest = 1;
+            long long own = 0;
+            for (int s = 0; s < n; ++s) {
+                const int steps = (int)(kvs[s]->seq.len + T_each[s] - shared + 31) / 32;
+                longest = std::max(longest, steps);
+                own += (long long)steps * ((T_each[s] * G + 31) / 32);
+            }
+            cp.shared_splits = shared_slices(m->lay.max_records, cp.n_tiles_shared, c.n_kv_heads, c.head_dim, m->lay.q_lo != 0, shared, cp.n_tiles, own,
+                                             split_waves(cp.n_tiles * c.n_kv_heads, longest) == 4);
         }
     }
     if (cp.tile_nq > 1) {
@@ -1266,6 +1305,16 @@ ax_status ax_dbg_split_plan(const ax_model_config* cfg, int items, int max_steps
     if ((size_t)items > records) return fail(AX_ERR_INVALID, "%d items exceed the %zu records of a pass", items, records);
     *waves = split_waves(items, max_steps);
     *slices = choose_splits(records, items, 1, max_steps);
+    return AX_OK;
+}
+
+ax_status ax_dbg_shared_plan(const ax_model_config* cfg, int rows, int keys, int own_tiles, long long own_steps, int one_launch, int* groups, int* slices) {
+    ax_status why;
+    if (!config_ok(cfg, &why)) return fail(why, "model config rejected");
+    if (rows <= 0 || rows > cfg->max_tokens || keys < 32 || own_tiles <= 0 || own_steps < 0 || !groups || !slices) return fail(AX_ERR_INVALID, "bad argument");
+    const Layout lay = make_layout(*cfg);
+    *groups = shared_groups(rows * (cfg->n_q_heads / cfg->n_kv_heads));
+    *slices = shared_slices(lay.max_records, *groups, cfg->n_kv_heads, cfg->head_dim, lay.q_lo != 0, keys, own_tiles, own_steps, one_launch != 0);
     return AX_OK;
 }
 

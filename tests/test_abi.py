@@ -89,6 +89,37 @@ def test_split_attention_plan():
             B.ax_dbg_split_plan(cfg, items, steps)
 
 
+def test_shared_prefix_plan():
+    """Slices of the pass over a shared prefix: none empty, none under two key steps but one, and their records fit a pass's; no more blocks than run
+    at once.  Where the pass has the chip to itself (a launch of its own, or little private work beside it) it leaves few compute units without a
+    block: 5 groups x 8 heads in 6 slices, not 4; two blocks on a unit for many groups over many keys."""
+    for name in ("1b", "3b", "8b"):
+        sh = I.SHAPES[name]
+        cfg, hd64 = B.make_config(sh, 8192, 1024, 64), sh.head_dim == 64
+        for rows in list(range(2, 150)) + [200, 288, 400, 600, 832, 1024]:
+            for keys in (32, 64, 96, 160, 1024, 2112, 2496, 6144, 8160):
+                tiles, steps = -(-rows // 9), keys // 32
+                for own, one in ((2 * tiles, False), (16 * tiles, True), (200 * tiles, True)):
+                    groups, slices = B.ax_dbg_shared_plan(cfg, rows, keys, tiles, own, one)
+                    blocks = groups * 8
+                    assert groups == -(-rows * (sh.n_q_heads // sh.n_kv_heads) // 128)
+                    assert slices == 1 or (blocks * slices <= (384 if one and not hd64 else 768) and slices * 2 <= steps), (name, rows, keys, own, one)
+                    assert blocks * slices * 4 <= (1024 * (sh.n_q_heads // 8) // 32 + 8 * 64 + 2) * 8
+                    assert slices & (slices - 1) == 0 or -(-steps // slices) * (slices - 1) < steps
+                    if not hd64 and steps * blocks >= 2 * 256 * 4 and not (one and own * 2 > groups * 4 * steps):
+                        assert blocks * slices >= 160, (name, rows, keys, own, one, slices)
+    plan = lambda name, *a: B.ax_dbg_shared_plan(B.make_config(I.SHAPES[name], 8192, 1024, 64), *a)
+    assert plan("8b", 144, 6144, 32, 96, False) == (5, 6)                     # 16 sessions of 9 rows, short histories
+    assert plan("8b", 144, 2496, 32, 1504, True) == (5, 4) and plan("8b", 144, 6144, 32, 1504, True) == (5, 6)
+    assert plan("3b", 144, 6144, 16, 48, False) == (4, 8) and plan("3b", 72, 6144, 8, 24, False) == (2, 16)
+    assert plan("3b", 288, 6144, 32, 96, False) == (7, 9) and plan("3b", 288, 2496, 32, 96, False) == (7, 4)
+    assert plan("8b", 576, 6144, 128, 384, False) == (18, 3) and plan("3b", 360, 6144, 40, 640, True)[1] == 4
+    assert plan("1b", 144, 2048, 32, 96, False) == (5, 8)
+    for args in ((0, 64, 1, 0), (1025, 64, 1, 0), (9, 31, 1, 0), (9, 64, 0, 0), (9, 64, 1, -1)):
+        with pytest.raises(B.AxError):
+            plan("3b", *args, False)
+
+
 def test_attention_merge_plan():
     """A block per record walks the record's slices one after the other, blocks of 4 channels cost their number: the first for many records of few
     slices.  8 sessions over a shared prefix (64 records, 16 shared slices and their own) are the second's, 7.9 us against 11-13."""

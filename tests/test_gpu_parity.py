@@ -648,6 +648,40 @@ def test_shared_and_private_keys_in_one_launch(B, hd, G, split):
     dm.close()
 
 
+@pytest.mark.parametrize("hkv,G,split,n,T,P,h,one,plan", [(8, 4, 1, 15, 9, 1000, 40, False, (5, 6)), (8, 3, 0, 13, 8, 1000, 30, False, (3, 8)),
+                                                          (16, 2, 0, 24, 6, 1600, 230, True, (3, 5))])
+def test_shared_prefix_in_slices_of_no_power_of_two(B, hkv, G, split, n, T, P, h, one, plan):
+    """The shared pass in 6, 8 (of 10 that would fit) and 5 slices, the last with fewer key steps or as many, alone in its launch and beside the private keys;
+    the last group of rows not full."""
+    sh = I.DecoderShape("shared", 1, 256, hkv * G, hkv, 128, 192, 512, "bf16")
+    w = I.make_weights(sh, 43)
+    prefix = I.templated_prompt(sh.vocab, 43, P)
+    dm = B.DeviceModel(sh, w, max_pos=P + 300, max_tokens=2048, pool_tokens=P + n * (h + 64), max_seqs=n, act_split=split)
+    root, root_ref = dm.new_kv(), okv(sh)
+    dm.extend(root, prefix)
+    O.forward(sh, w, prefix, root_ref)
+    kvs, refs = [], []
+    for s in range(n):
+        kv, ref = B.ax_kv_fork(root, -1), root_ref.fork()
+        t = I.zipf_tokens(sh.vocab, 43, f"h{s}", h - s % 3)
+        dm.extend(kv, t)
+        O.forward(sh, w, t, ref)
+        kvs.append(kv)
+        refs.append(ref)
+    shared, own_tiles = P // 32 * 32, n * -(-T * G // 32)
+    own = sum(-(-T * G // 32) * -(-(P + h - s % 3 + T - shared) // 32) for s in range(n))
+    cfg = B.make_config(sh, P + 300, 2048, n, split)
+    assert B.ax_dbg_split_plan(cfg, own_tiles * hkv, -(-(P + h + T - shared) // 32))[0] == (4 if one else 1)
+    assert B.ax_dbg_shared_plan(cfg, n * T, shared, own_tiles, own, one) == plan
+    news = [I.zipf_tokens(sh.vocab, 43, f"n{s}", T) for s in range(n)]
+    got = dm.extend_batch(kvs, news, B.AX_OUT_ALL_LOGITS).cpu().numpy()
+    for s in range(n):
+        check_logits(sh, got[s * T:(s + 1) * T], O.forward(sh, w, news[s], refs[s]), f"session {s}")
+    for kv in kvs + [root]:
+        B.ax_kv_free(kv)
+    dm.close()
+
+
 def test_two_resident_models_forked_sessions(B):
     """The plan-out agent's shape at a size the oracle can follow: two decoders with their own
     weights and pools resident together; per model, sessions fork one shared prefix, build
