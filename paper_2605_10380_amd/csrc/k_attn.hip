@@ -39,7 +39,9 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // is one float4 as well.
 //
 // HDT: 16-channel tiles the registers hold (head_dim <= 16 * HDT; channels past head_dim are zeros).
-// FULL: head_dim is 16 * HDT.
+// FULL: head_dim is 16 * HDT; operands of the next page are then asked for while this one's are used (AHEAD below).  Other head_dims test every load
+// against it, and the tests between the products cost more than that hides: they load a page where they use it (2 layers' attention, ahead / not:
+// head_dim 32, 16 rows over 80 / 528 keys 7.0 / 6.5 and 13.1 / 12.2 us, 96 over 576 15.1 / 14.0, 192 over 528 56.8 / 53.9).
 // OT: 16-channel tiles of the OUTPUT that the block computes (blockIdx.z: which).  A call of a few rows leaves most of the chip idle,
 // and on the one CU that its block runs on the products of 33 pages alone take 4.4 us.  With a block per 16 output channels each CU does the
 // scores again but only its part of the second product, of the V loads and of the merge.  5 rows over 517 keys: 13.3 -> 11.6 us,
@@ -89,9 +91,10 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
 
     const int r_last = min(r0 + 15, n_stacked - 1);
     const int pages = (P + r_last / G + 16) >> 4;                // up to the page of the tile's last visible key
-    // page ids of up to 64 of this wavefront's pages at a time; K of its next page is asked for behind this one's scores, V behind its output, in the
+    // AHEAD: page ids of up to 64 of this wavefront's pages at a time; K of its next page is asked for behind this one's scores, V behind its output, in the
     // same registers: one chain of loads less a page, and the loop stays one body (with a second one for a second set of operands the
     // instruction fetches cost more than the loads it hid, 12.9 -> 15.6 us)
+    constexpr bool AHEAD = FULL;
     const int mine = wave < pages ? (pages - wave + NW - 1) / NW : 0;
     int ids = 0;
     auto page_id = [&](int i) {
@@ -113,14 +116,20 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
         }
     };
     int blk = 0;
-    if (mine > 0) {
+    if (AHEAD && mine > 0) {
         blk = page_id(0);
         load_k(blk);
         load_v(blk);
     }
     for (int i = 0; i < mine; ++i) {
         const int kv0 = (wave + i * NW) * 16;
-        if (i + 1 < mine) blk = page_id(i + 1);                  // (the last page's again at the end: no branch around the loads)
+        if constexpr (!AHEAD) {
+            blk = tab[wave + i * NW];
+            load_k(blk);
+            load_v(blk);
+        } else if (i + 1 < mine) {
+            blk = page_id(i + 1);                                // (the last page's again at the end: no branch around the loads)
+        }
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};     // two chains of dependent products
 #pragma unroll
         for (int c = 0; c < HDT; ++c) {
@@ -129,9 +138,11 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
             s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][2], qf[c][2], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][3], qf[c][3], s1, 0, 0, 0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        load_k(blk);
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_k(blk);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         float mx = -INFINITY;
         f32x4 p;
 #pragma unroll
@@ -162,9 +173,11 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][i], p[i], o[c], 0, 0, 0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        load_v(blk);
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(blk);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 
     l += __shfl_xor(l, 16, 64);
@@ -1021,6 +1034,7 @@ void launch_attention(DType dt, const void* q, void* out, KVGeom kv, int layer, 
         else if (hd < 64) attn_f32_kernel<4, 4, 16, false><<<grid, 1024, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
         else if (hd == 128) attn_f32_kernel<8, 8, 8, true><<<grid, 512, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
         else if (hd < 128) attn_f32_kernel<8, 8, 8, false><<<grid, 512, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
+        else if (hd == 256) attn_f32_kernel<16, 16, 4, true><<<grid, 256, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
         else attn_f32_kernel<16, 16, 4, false><<<grid, 256, 0, s>>>(qf, of, kv, layer, sv.tile_info, sv.bt, n_q_heads, subs);
         return;
     }

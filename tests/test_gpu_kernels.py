@@ -264,10 +264,11 @@ def test_f32_model_head_dims_and_row_edges(torch_cuda, hd, d, F, P, T):
 
 
 @pytest.mark.parametrize("hd,P,T", [(64, 0, 1), (64, 17, 5), (64, 530, 33), (64, 31, 170), (64, 31, 171), (128, 0, 2), (128, 500, 6),
-                                    (128, 33, 85), (128, 33, 86)])
+                                    (128, 33, 85), (128, 33, 86), (32, 530, 33), (96, 500, 6), (192, 66, 17), (256, 0, 2), (256, 500, 6), (256, 33, 86)])
 def test_f32_attention_channel_blocks(torch_cuda, hd, P, T):
     """fp32 attention in blocks of 16 output channels and, one tile of rows further (3 query heads to a KV head: 170 rows of head_dim 64, 85 of
-    128), in whole ones: fewer pages than wavefronts and several each, a last page of one key, pool memory full of NaN patterns.  Bound: fp32
+    128), in whole ones; other head_dims (256: as 64 and 128 in whole ones; the rest load every page where they use it): fewer pages than
+    wavefronts and several each, a last page of one key, pool memory full of NaN patterns.  Bound: fp32
     products and sums of head_dim and P + T terms, 2e-5 of the largest value as for the other fp32 stages."""
     from paper_2605_10380_amd import binding as B
     sh = I.DecoderShape("f32-attn", 1, 64, 6, 2, hd, 80, 301, "f32")
