@@ -65,12 +65,13 @@ typedef struct {
     const int *row_pos, *row_slot; const float *cos, *sin;      /* ... position and slot of the rows, rotary tables [pos][head_dim / 2] */
     void *split_ws; size_t split_ws_bytes;
     int a_panels, c_panels;             /* A (and ssq, as [n_parts][M]), C16 (and ssq_out; epilogues 1 and 2) in panels of 16 rows, as calls of many
-                                           rows hold them: 8 columns of a panel's rows at a time, each row's 8 side by side */
+                                           rows hold them: 8 columns of a panel's rows at a time, each row's 8 side by side.  2: in strips, 32 columns
+                                           of all rows at a time, panel after panel of 16 rows (the last one too: C16 has room for whole panels), inside
+                                           them as panels, ssq and ssq_out as beside panels; refused without lo parts.  0: in rows */
 } ax_dbg_block_gemm;
 ax_status ax_dbg_gemm_block(ax_dbg_block_gemm *args, void *hip_stream);
 /* The same on the kernel of 17 to 256 rows (any M <= 256 here): a tile of `rows` x `cols` (SwiGLU: half of them gate, half up), refused where there is
- * no such tile; epilogues 1 to 3, slices for epilogue 1 only.  a_panels, c_panels also 2: strips, 32 columns of all rows at a time, panel after
- * panel of 16 rows (the last one too: C16 has room for whole panels), inside them as panels; ssq and ssq_out are [n_parts][M] beside strips and
+ * no such tile; epilogues 1 to 3, slices for epilogue 1 only.  Strips with or without lo parts; ssq and ssq_out are [n_parts][M] beside strips and
  * beside panels of more than 32 rows. */
 ax_status ax_dbg_gemm_regs(ax_dbg_block_gemm *args, void *hip_stream);
 

@@ -1358,7 +1358,7 @@ extern "C++" {
 // The debug GEMMs of named tiles: `built` says whether there is such a tile, `launch` runs it.
 template <class Built, class Launch>
 static ax_status dbg_gemm_tiles(ax_dbg_block_gemm* a, void* hip_stream, Built built, Launch launch) {
-    if (!a || !a->A || !a->W || a->M <= 0 || a->N <= 0 || a->K <= 0 || a->epilogue < 0 || a->epilogue > 3 || (a->ssq && a->n_parts <= 0) || a->a_panels < 0 || a->a_panels > 2 || a->c_panels < 0 || a->c_panels > 2)
+    if (!a || !a->A || !a->W || a->M <= 0 || a->N <= 0 || a->K <= 0 || a->epilogue < 0 || a->epilogue > 3 || (a->ssq && a->n_parts <= 0))
         return fail(AX_ERR_INVALID, "bad argument");
     if (a->N % 64 != 0 || a->K % 64 != 0) return fail(AX_ERR_UNSUPPORTED, "N %% 64 == 0 and K %% 64 == 0 needed");
     if (!built()) return fail(AX_ERR_INVALID, "no %d x %d block for epilogue %d", a->rows, a->cols, a->epilogue);
@@ -1389,7 +1389,8 @@ static ax_status dbg_gemm_tiles(ax_dbg_block_gemm* a, void* hip_stream, Built bu
     g.rope.kv = {a->pool, a->pool_blocks, a->n_kv_heads, a->head_dim, 16};
     g.rope.n_q_heads = a->n_q_heads; g.rope.q_out = a->C16; g.rope.row_pos = a->row_pos; g.rope.row_slot = a->row_slot;
     g.rope.cos = a->cos; g.rope.sin = a->sin;
-    g.a_layout = (ax::ActLayout)a->a_panels; g.c_layout = (ax::ActLayout)a->c_panels;
+    auto layout = [](int v) { return v == 0 ? ax::ACT_ROWS : v == 2 ? ax::ACT_STRIPS : ax::ACT_PANELS; };
+    g.a_layout = layout(a->a_panels); g.c_layout = layout(a->c_panels);
     a->n_parts_out = launch(g, s);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1402,6 +1403,7 @@ static ax_status dbg_gemm_tiles(ax_dbg_block_gemm* a, void* hip_stream, Built bu
 }
 
 ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
+    if (a && !a->a_lo && (a->a_panels == 2 || a->c_panels == 2)) return fail(AX_ERR_UNSUPPORTED, "strips need activations in hi + lo parts");
     auto built = [&] { return (a->rows == 256 && a->cols == 256) || (a->rows == 128 && (a->cols == 256 || (a->cols == 128 && a->epilogue != 2))); };
     return dbg_gemm_tiles(a, hip_stream, built, [&](const ax::GemmArgs& g, hipStream_t s) {
         return ax::launch_gemm_block_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);
@@ -1409,6 +1411,7 @@ ax_status ax_dbg_gemm_block(ax_dbg_block_gemm* a, void* hip_stream) {
 }
 
 ax_status ax_dbg_gemm_regs(ax_dbg_block_gemm* a, void* hip_stream) {
+    if (a && (a->a_panels < 0 || a->a_panels > 2 || a->c_panels < 0 || a->c_panels > 2)) return fail(AX_ERR_INVALID, "bad argument");
     auto built = [&] { return ax::gemm_regs_built((ax::Epilogue)a->epilogue, a->a_lo != 0, a->rows, a->cols, a->slices) && a->M <= 256; };
     return dbg_gemm_tiles(a, hip_stream, built, [&](const ax::GemmArgs& g, hipStream_t s) {
         return ax::launch_gemm_regs_as((ax::Epilogue)a->epilogue, g, a->rows, a->cols, a->slices, s);

@@ -171,6 +171,18 @@ def test_many_row_gemm_plan_of_measured_calls(epi, M, N, K, split, want):
     assert B.ax_dbg_gemm_plan(epi, M, N, K, split, 8 * M * 4096 * 4) == want
 
 
+def test_block_gemm_takes_strips_in_hi_and_lo_parts_only():
+    """The block kernel has no strips of plain activations (it would read them as panels and write rows): refused on the host, like layouts the
+    register kernel does not know.  (The pointers are never followed.)"""
+    base = dict(slices=1, M=64, N=192, K=64, A=64, W=64, W2=64, C=64, C16=64, gain=64, ssq_out=64)
+    for epi, layouts in ((0, dict(a_panels=2)), (1, dict(a_panels=2)), (1, dict(a_panels=1, c_panels=2)), (2, dict(c_panels=2))):
+        with pytest.raises(B.AxError):
+            B.ax_dbg_gemm_block(**base, epilogue=epi, rows=128, cols=256, **layouts)
+    for layouts in (dict(a_panels=3), dict(a_panels=-1), dict(c_panels=3)):
+        with pytest.raises(B.AxError):
+            B.ax_dbg_gemm_regs(**base, epilogue=1, rows=32, cols=32, **layouts)
+
+
 def test_extend_rejects_bad_arguments_before_any_launch():
     cfg = B.make_config(I.SHAPES["tiny"], 1024, 64)
     pool = B.ax_pool_create(cfg, 0, B.ax_pool_block_bytes(cfg) * 8)
