@@ -45,6 +45,11 @@ ax_status ax_dbg_gemm_plan(int epilogue, int M, int N, int K, int split, size_t 
 ax_status ax_dbg_panel_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, int *rows, int *cols, int *slices);
 ax_status ax_dbg_layer_panels(const ax_model_config *cfg, int rows, int *panels);
 
+/* What a layer's GEMM of 17 to 256 rows runs on (epilogues 1 to 3, arguments as ax_dbg_gemm_plan): *kernel "regs" (ax_dbg_gemm_regs) or, with split,
+ * "block" (ax_dbg_gemm_block, on strips).  Host only. */
+ax_status ax_dbg_strip_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char **kernel, int *rows, int *cols,
+                            int *slices);
+
 /* One GEMM of a bf16-weight layer on a block shape of the many-row kernel that the caller names, with everything a layer uses: hi + lo
  * activations, a pending RMSNorm of A's rows, K slices and each epilogue.  All pointers are device memory; weights row-major bf16.
  * rows x cols: 256 x 256, 128 x 256 or 128 x 128 (not for SwiGLU).  N % 64 == 0, K % 64 == 0, head_dim 64 or 128. */

@@ -96,6 +96,8 @@ def _load():
         "ax_dbg_merge_plan": (C.c_int, [C.c_int, C.c_int, C.POINTER(C.c_int)]),
         "ax_dbg_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
                                        C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+        "ax_dbg_strip_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_char_p),
+                                        C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "ax_dbg_panel_plan": (C.c_int, [C.c_int] * 5 + [C.c_size_t] + [C.POINTER(C.c_int)] * 3),
         "ax_dbg_layer_panels": (C.c_int, [C.POINTER(ax_model_config), C.c_int, C.POINTER(C.c_int)]),
         "ax_dbg_gemm_block": (C.c_int, [C.POINTER(ax_dbg_block_gemm), vp]),
@@ -421,6 +423,13 @@ def ax_dbg_gemm_plan(epilogue: int, M: int, N: int, K: int, split: bool = False,
     """(kernel, rows, cols, K slices) of a GEMM of more than 256 rows."""
     n, r, c, k = C.c_char_p(), C.c_int(), C.c_int(), C.c_int()
     _check(lib.ax_dbg_gemm_plan(epilogue, M, N, K, int(split), split_ws_bytes, C.byref(n), C.byref(r), C.byref(c), C.byref(k)))
+    return n.value.decode(), r.value, c.value, k.value
+
+
+def ax_dbg_strip_plan(epilogue: int, M: int, N: int, K: int, split: bool = False, split_ws_bytes: int = 1 << 40):
+    """(kernel, rows, cols, K slices) of a layer's GEMM of 17 to 256 rows."""
+    n, r, c, k = C.c_char_p(), C.c_int(), C.c_int(), C.c_int()
+    _check(lib.ax_dbg_strip_plan(epilogue, M, N, K, int(split), split_ws_bytes, C.byref(n), C.byref(r), C.byref(c), C.byref(k)))
     return n.value.decode(), r.value, c.value, k.value
 
 

@@ -1346,6 +1346,17 @@ ax_status ax_dbg_panel_plan(int epilogue, int M, int N, int K, int split, size_t
     return AX_OK;
 }
 
+ax_status ax_dbg_strip_plan(int epilogue, int M, int N, int K, int split, size_t split_ws_bytes, const char** kernel, int* rows, int* cols, int* slices) {
+    if (epilogue < 1 || epilogue > 3 || M <= 0 || N <= 0 || K <= 0 || !kernel || !rows || !cols || !slices) return fail(AX_ERR_INVALID, "bad argument");
+    if (M <= 16 || M > 256 || K % 64 != 0 || N % 64 != 0) return fail(AX_ERR_UNSUPPORTED, "17 to 256 rows, K %% 64 == 0, N %% 64 == 0");
+    const ax::GemmPlan p = ax::gemm_strip_plan((ax::Epilogue)epilogue, M, N, K, split != 0, split_ws_bytes);
+    *kernel = p.kernel;
+    *rows = p.rows;
+    *cols = p.cols;
+    *slices = p.slices;
+    return AX_OK;
+}
+
 ax_status ax_dbg_layer_panels(const ax_model_config* cfg, int rows, int* panels) {
     ax_status why;
     if (!config_ok(cfg, &why)) return fail(why, "model config rejected");

@@ -1255,28 +1255,21 @@ static int launch_regs_plan(Epilogue epi, const GemmArgs& g, const RegsPlan& p, 
     launch_regs_slices(gs, p.shape, s);
     return launch_residual_reduce(gs, s);
 }
-static int launch_regs(Epilogue epi, const GemmArgs& g, hipStream_t s) {
-    const bool split = g.a_lo_off != 0;
-    if (g.M > 256) {                                           // (SwiGLU of odd widths, which no layer has: 256 rows at a time)
-        for (int r0 = 0; r0 < g.M; r0 += 256) {
-            GemmArgs c = g;
-            c.M = std::min(256, g.M - r0);
-            c.A = (const f16*)g.A + (long long)r0 * g.K;
-            c.C16 = (f16*)g.C16 + (long long)r0 * g.N;
-            if (g.ssq) c.ssq = g.ssq + (long long)r0 * g.nparts;
-            launch_regs(epi, c, s);
-        }
-        return 0;
-    }
-    const size_t ws = g.split_ws ? g.split_ws_bytes : 0;
-    const RegsPlan p = plan_regs(epi, g.M, g.N, g.K, split, g.split_ws != nullptr, ws);
-    // hi + lo parts of many rows are bound by their products: 256 x 256 blocks through LDS multiply faster (~8B gate / up, 176-256 rows: 130-140 us, 100)
-    if (split && g.a_layout == ACT_STRIPS && g.N % 64 == 0) {
-        const BlockPlan b = plan_gemm_block(epi, g.M, g.N, g.K, split, true, ws);
+// Hi + lo parts in strips have the block kernel beside it, by the times that both plans expect: bound by their products, many rows multiply faster
+// through LDS (~8B gate / up at 200-256 rows 130-140 us here, 100 on 128 x 256 blocks).
+struct StripPlan { bool block; RegsPlan regs; BlockPlan tiles; };
+static StripPlan plan_strips(Epilogue epi, int M, int N, int K, bool split, bool strips, bool slices, size_t ws_bytes) {
+    StripPlan p{false, plan_regs(epi, M, N, K, split, slices, ws_bytes), {}};
+    if (split && strips && N % 64 == 0) {
+        p.tiles = plan_gemm_block(epi, M, N, K, split, true, ws_bytes);
         const int fb = env_int("AX_BLOCK", -1);
-        if (fb < 0 ? b.us < p.us && env_int("AX_REGS", -1) < 0 : fb == (epi == EPI_RESIDUAL && g.K > 2 * g.N ? 4 : epi)) return launch_gemm_block(epi, g, b, s);
+        p.block = fb < 0 ? p.tiles.us < p.regs.us && env_int("AX_REGS", -1) < 0 : fb == (epi == EPI_RESIDUAL && K > 2 * N ? 4 : epi);
     }
-    return launch_regs_plan(epi, g, p, s);
+    return p;
+}
+static int launch_regs(Epilogue epi, const GemmArgs& g, hipStream_t s) {
+    const StripPlan p = plan_strips(epi, g.M, g.N, g.K, g.a_lo_off != 0, g.a_layout == ACT_STRIPS, g.split_ws != nullptr, g.split_ws ? g.split_ws_bytes : 0);
+    return p.block ? launch_gemm_block(epi, g, p.tiles, s) : launch_regs_plan(epi, g, p.regs, s);
 }
 
 static int regs_shape(bool split, int rows, int cols) {
@@ -1303,7 +1296,7 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         launch_swiglu_stream(g, p.stream_tm, s);
         return 0;
     }
-    if (EPI != EPI_STORE_F32 && M > 16 && (M <= 256 || EPI == EPI_SWIGLU)) return launch_regs((Epilogue)EPI, g, s);
+    if (EPI != EPI_STORE_F32 && M > 16 && M <= 256) return launch_regs((Epilogue)EPI, g, s);
     const bool far_rows = g.a_rows && (unsigned long long)g.a_total_rows * K * 2 > 0xffffffffull;      // gathered rows past what the offsets below hold
     // logits of 17-32 rows: narrow ones only (wide ones on streaming blocks, see launch_lds_tile)
     if ((M <= 16 || (M <= 32 && EPI == EPI_STORE_F32 && !(N >= 256 * 256 && kLmStream))) && !far_rows) {
@@ -1322,7 +1315,7 @@ static int launch_bf16(const GemmArgs& g, hipStream_t s) {
         return EPI == EPI_RESIDUAL ? N / cols : 0;
     }
     if constexpr (EPI != EPI_SWIGLU) return launch_lds_tile<EPI>(g, s);
-    return 0;
+    return 0;                                                  // (SwiGLU: no rows are gathered, and N of a layer is a multiple of 64)
 }
 
 static GemmPlan block_plan(const BlockPlan& p) { return {"block", p.shape == 0 ? 256 : 128, p.shape == 2 ? 128 : 256, p.ks}; }
@@ -1343,6 +1336,13 @@ GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_byte
     if (epi == EPI_RESIDUAL) return many_rows_plan<EPI_RESIDUAL>(M, N, K, split, ws_bytes);
     if (epi == EPI_SWIGLU) return many_rows_plan<EPI_SWIGLU>(M, N, K, split, ws_bytes);
     return many_rows_plan<EPI_QKV>(M, N, K, split, ws_bytes);
+}
+
+GemmPlan gemm_strip_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
+    const StripPlan p = plan_strips(epi, M, N, K, split, M > kPanelRows || split, ws_bytes > 0, ws_bytes);
+    if (p.block) return block_plan(p.tiles);
+    const RegsShape& t = kRegs[split][p.regs.shape];
+    return {"regs", 16 * t.mt, 16 * t.nt, p.regs.ks};
 }
 
 GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes) {
@@ -1383,7 +1383,15 @@ void launch_gemm(DType dt, Epilogue epi, const void* A, const void* W, const voi
     g.A = A; g.W = W; g.W2 = W2; g.M = M; g.N = N; g.K = K;
     g.Cf = (float*)C;
     g.C16 = C;
-    launch_gemm_bf16(epi, g, s);
+    const bool odd = epi == EPI_SWIGLU && M > 256 && N % 64 != 0;              // no layer has these, and no kernel of more than 256 rows takes them
+    for (int r0 = 0; r0 < M; r0 += odd ? 256 : M) {
+        if (odd) {
+            g.M = std::min(256, M - r0);
+            g.A = (const f16*)A + (long long)r0 * K;
+            g.C16 = (f16*)C + (long long)r0 * N;
+        }
+        launch_gemm_bf16(epi, g, s);
+    }
 }
 
 }  // namespace ax

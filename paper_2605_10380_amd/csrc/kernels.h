@@ -138,9 +138,11 @@ int launch_gemm_bf16(Epilogue epi, const GemmArgs& g, hipStream_t s);
 struct GemmPlan { const char* kernel; int rows, cols, slices; };
 GemmPlan gemm_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
 GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);      // with A in panels
+// The plan of a layer's GEMM (not EPI_STORE_F32) of 17 to 256 rows: "regs", or in hi + lo parts "block".
+GemmPlan gemm_strip_plan(Epilogue epi, int M, int N, int K, bool split, size_t ws_bytes);
 // How the layers of a call of M rows keep their activations from kernel to kernel: all four GEMMs then run with this a_layout.  Panels up to 16 rows
 // on the few-row kernel, to 32 rows (plain activations) on the register kernel and from 257 on the block kernel, on its plan for panels; strips
-// only on the register kernel.  N of a GEMM: the layer's sizes, all multiples of 64.
+// on the register kernel and, in hi + lo parts, on the block kernel.  N of a GEMM: the layer's sizes, all multiples of 64.
 ActLayout gemm_layer_layout(int M, int d_model, int qkv, int qdim, int d_ff, bool split, size_t ws_bytes);
 // A GEMM on the block kernel with the shape and slices of `rows`, `cols`, `slices` whatever the plan would say (tests); returns as launch_gemm_bf16.
 int launch_gemm_block_as(Epilogue epi, const GemmArgs& g, int rows, int cols, int slices, hipStream_t s);

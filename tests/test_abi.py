@@ -171,6 +171,45 @@ def test_many_row_gemm_plan_of_measured_calls(epi, M, N, K, split, want):
     assert B.ax_dbg_gemm_plan(epi, M, N, K, split, 8 * M * 4096 * 4) == want
 
 
+def test_strip_gemm_plans_are_launchable():
+    """Plans of a layer's GEMMs of 17 to 256 rows: a tile of the register kernel that is built for the epilogue, K slices only of residual GEMMs, long enough and
+    within the scratch; blocks, as the block kernel has them, only for hi + lo parts."""
+    rng = np.random.default_rng(8)
+    seen = set()
+    plain = {(2, 1), (2, 2), (2, 4), (3, 2), (3, 3), (3, 4), (4, 2), (4, 3), (4, 4), (5, 4), (6, 4), (8, 4), (9, 4)} | {(m, 8) for m in range(2, 9)}
+    for _ in range(6000):
+        epi, split = int(rng.integers(1, 4)), bool(rng.integers(0, 2))
+        M, N, K = int(rng.integers(17, 257)), 64 * int(rng.integers(1, 260)), 64 * int(rng.integers(1, 260))
+        ws = int(rng.choice([0, M * N * 4, 3 * M * N * 4 - 1, 32 * M * N]))
+        kernel, rows, cols, slices = B.ax_dbg_strip_plan(epi, M, N, K, split, ws)
+        seen.add((epi, kernel, rows, cols, slices > 1))
+        assert slices == 1 or slices * M * N * 4 <= ws
+        if kernel == "block":
+            assert split and (rows, cols) in ((256, 256), (128, 256)) + (((128, 128),) if epi != 2 else ())
+            assert slices <= 4 and (slices == 1 or (epi != 2 and K % (32 * slices) == 0 and K // slices >= 512))
+        else:
+            mt, nt = rows // 16, cols // 16
+            assert kernel == "regs" and (mt, nt) in plain - ({(3, 3), (4, 3)} if split else set()) and mt <= -(-M // 16) + 1
+            assert (nt >= 2 if slices > 1 else mt <= 5 and nt <= 4) if epi == 1 else nt % 2 == 0 and slices == 1
+            assert slices in (1, 2, 4, 8) and (slices == 1 or K // 32 // slices >= 16)
+    assert len(seen) >= 60, len(seen)
+    for M, N in ((16, 2048), (257, 2048), (64, 2064)):
+        with pytest.raises(B.AxError):
+            B.ax_dbg_strip_plan(1, M, N, 2048)
+
+
+# (epilogue, rows, N, K, hi + lo parts) of decoder layers 2048, 3072 and 4096 wide
+@pytest.mark.parametrize("epi,M,N,K,split,want", [
+    (3, 17, 3072, 2048, False, ("regs", 32, 32, 1)), (2, 64, 8192, 2048, False, ("regs", 64, 64, 1)), (1, 100, 2048, 8192, False, ("regs", 64, 64, 4)),
+    (2, 256, 8192, 2048, False, ("regs", 128, 128, 1)), (1, 256, 2048, 8192, False, ("regs", 64, 128, 4)),
+    (3, 144, 5120, 3072, False, ("regs", 48, 64, 1)), (1, 144, 3072, 3072, False, ("regs", 48, 48, 1)), (2, 144, 8192, 3072, False, ("regs", 144, 64, 1)),
+    (1, 144, 3072, 8192, False, ("regs", 144, 64, 4)), (3, 17, 6144, 4096, True, ("regs", 32, 32, 1)), (2, 17, 14336, 4096, True, ("regs", 32, 128, 1)),
+    (3, 112, 6144, 4096, True, ("block", 128, 128, 4)), (2, 160, 14336, 4096, True, ("regs", 80, 128, 1)),
+    (2, 224, 14336, 4096, True, ("block", 128, 256, 1)), (1, 224, 4096, 14336, True, ("regs", 112, 128, 4))])
+def test_strip_gemm_plan_of_measured_calls(epi, M, N, K, split, want):
+    assert B.ax_dbg_strip_plan(epi, M, N, K, split, 8 * M * 4096 * 4) == want
+
+
 def test_block_gemm_takes_strips_in_hi_and_lo_parts_only():
     """The block kernel has no strips of plain activations (it would read them as panels and write rows): refused on the host, like layouts the
     register kernel does not know.  (The pointers are never followed.)"""

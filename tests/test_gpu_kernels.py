@@ -19,17 +19,17 @@ def torch_cuda():
     return torch
 
 
-# M values: skinny path (<= 16, and to 32 rows for some epilogues) and tile path (ragged); K / N pick
-# different wavefront counts in the skinny kernel and both tile shapes; 193-256 rows of wide matrices take the streaming SwiGLU
-# kernel.  More than 256 rows: N a multiple of 64 (as every model's is) goes by the plan of many-row GEMMs (see test_gpu_many_rows.py,
-# which asserts it), any other N to the tile kernel, which only these debug calls do
+# Stores: skinny path (<= 16, narrow ones to 32 rows), tiles, streaming blocks; += and SwiGLU: skinny path to 16 rows, the register kernel to
+# 256 (activations in rows; K / N pick different wavefront counts in the skinny kernel and tiles in the other).  More than 256 rows: N a
+# multiple of 64 (as every model's is) goes by the plan of many-row GEMMs (see test_gpu_many_rows.py, which asserts it), any other N to
+# the tile kernel, SwiGLU 256 rows at a time to the register kernel, which only these debug calls do
 GEMM_CASES = [(1, 64, 64), (9, 3072, 2048), (9, 2048, 8192), (17, 512, 256), (33, 128, 1024), (64, 2064, 192),
               (65, 384, 128), (100, 200 * 16, 320), (256, 3072, 2048), (300, 1024, 512), (512, 33 * 128, 256),
               (400, 1040, 1024), (384, 2048, 576), (300, 2048, 256), (230, 14336, 128), (257, 8192, 128), (640, 8192, 192), (320, 14336, 128),
               # thousands of rows: the tile kernel (N = 7712) and the block kernel
               (1600, 7712, 192), (1664, 7680, 448),
               (144, 65600, 128), (131, 65536, 192), (17, 65600, 128), (40, 65536, 192), (100, 65568, 128), (190, 65536, 128), (300, 65600, 128),   # streaming blocks for wide outputs (logits) from 17 rows
-              (144, 8192, 3072), (190, 4096, 1536), (150, 4112, 1536),  # 17-192 rows: SwiGLU over K slices (32- to 192-row blocks)
+              (144, 8192, 3072), (190, 4096, 1536), (150, 4112, 1536),  # 17-190 rows of wide matrices, columns that end inside a tile (4112)
               (40, 8192, 2048), (96, 4112, 1536), (128, 4096, 3072), (17, 8192, 2048), (30, 4112, 1536)]
 
 
@@ -110,15 +110,14 @@ def test_bf16_gemm_seeded_random_shapes(torch_cuda, M, N, K, epi):
 
 
 # the residual GEMM with the next norm's preparation, through every kernel that implements it:
-# skinny with 8 / 12 / 16 columns per block (to 16 rows, and to 32 rows when K is short), tile kernels
-# unsplit and with K slices (64- and 128-row
-# blocks), block kernel; N = 7712 and 5088 (no multiple of 64, no model's width) stay on the tile kernel at any row count
+# skinny with 8 / 12 / 16 columns per block (to 16 rows), the register kernel whole and with K slices (17-256), tile kernels unsplit and with
+# K slices (64- and 128-row blocks), block kernel; N = 7712 and 5088 (no multiple of 64, no model's width) stay on the tile kernel at any row count
 RESIDUAL_CASES = [(9, 2048, 512, False), (9, 3072, 256, False), (33, 4096, 192, False), (16, 1040, 128, False),
                   (24, 2048, 256, False), (24, 1024, 4096, True), (64, 1024, 128, False),
                   (100, 512, 256, False), (256, 2048, 2048, True), (256, 2048, 2048, False), (300, 1024, 4096, True),
                   (512, 4096, 4096, True), (520, 3072, 8192, True), (300, 4096, 14336, True), (1600, 7712, 192, True),
                   (1030, 5088, 8192, True),
-                  (144, 3072, 8192, True), (131, 2048, 8192, True), (190, 2048, 8192, True), (161, 1024, 12288, True)]   # 160- / 192-row streaming blocks, K slices
+                  (144, 3072, 8192, True), (131, 2048, 8192, True), (190, 2048, 8192, True), (161, 1024, 12288, True)]   # long K: register kernel, K slices
 
 
 @pytest.mark.parametrize("M,N,K,split", RESIDUAL_CASES)

@@ -185,7 +185,8 @@ def test_many_row_gemm_seeded_random_shapes(torch, M, N, K, epi):
 LAYERS = [
     ((256, 4, 2, 64, 320, 300, 0), ("block", "tile", "block", "tile")),
     ((384, 4, 2, 64, 2816, 257, 1), ("tile", "block", "block", "tile")), ((384, 8, 2, 64, 2816, 257, 1), ("tile", "tile", "block", "tile")),
-    ((704, 4, 2, 64, 14336, 320, 0), ("block", "tile", "stream", "tile")), ((2048, 16, 4, 128, 1088, 257, 1), ("tile", "block", "block", "block"))]
+    ((704, 4, 2, 64, 14336, 320, 0), ("block", "tile", "stream", "tile")), ((2048, 16, 4, 128, 1088, 257, 1), ("tile", "block", "block", "block")),
+    ((2048, 4, 2, 64, 10240, 270, 1), ("block", "tile", "stream", "block"))]
 PANEL_LAYERS = [
     ((256, 4, 2, 64, 320, 310, 0), ((128, 128, 1), (128, 128, 1), (128, 256, 1), (128, 128, 1))),
     ((2048, 4, 2, 64, 320, 640, 1), ((128, 128, 4), (128, 128, 1), (128, 256, 1), (128, 128, 1))),
@@ -344,8 +345,8 @@ def test_block_gemm_in_panels(torch, block, epi, split, slices, M, N, K, n_sums,
 @pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 15, 16, 17, 18, 24, 31, 32, 33])
 @pytest.mark.parametrize("hd,hkv,G,d,F", [(64, 2, 4, 256, 320), (128, 1, 8, 1024, 1600)])
 def test_layer_of_one_or_two_panels(torch, hd, hkv, G, d, F, T, split):
-    """Calls of up to 16 rows keep their activations in one panel of as many rows, plain ones of up to 32 in two (33: in rows again), on blocks
-    of 8 and 16 columns."""
+    """Calls of up to 16 rows keep their activations in one panel of as many rows, on few-row blocks of 8 and 16 columns; plain ones of up to 32 in
+    two, others in strips (33: all in strips), on the register kernel."""
     import test_gpu_kernels as K
     sh = I.DecoderShape("one-panel", 1, d, hkv * G, hkv, hd, F, 512, "bf16")
     got, ref, x, xr = K._one_layer(torch, sh, 37, T, 30 + T, 64, split)

@@ -1,10 +1,10 @@
-"""GEMMs of 17 to 256 rows: every tile of the register kernel against float64."""
+"""GEMMs of 17 to 256 rows: every tile of the register kernel, and the block kernel on strips, against float64."""
 import numpy as np
 import pytest
 
 from oracle import decoder as O
 from paper_2605_10380_amd import inputs as I
-from test_gpu_many_rows import QKV, RESIDUAL, SWIGLU, fp16_bound, operands, panels, rows_of, torch, value  # noqa: F401
+from test_gpu_many_rows import BLOCKS, QKV, RESIDUAL, SWIGLU, fp16_bound, operands, panels, rows_of, torch, value  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 ROWS, PANELS, STRIPS = 0, 1, 2
@@ -40,8 +40,24 @@ def test_register_gemm(torch, split, epi, slices, mt, nt):
     """A block of rows and a part of one in strips; whole blocks in rows with fewer chunks of K than wavefronts; a last panel of a few rows in panels.
     Columns end inside a tile (320), K (576) is no whole number of chunks a wavefront.  A pending norm of 5 and of 70 partial sums a row."""
     from paper_2605_10380_amd import binding as B
-    for M, K, hd, layout, n_sums in ((min(mt * 16 + 5, 256), 576, 64, STRIPS, 70), (mt * 16, 64 * slices, 128, ROWS, 5), (max(17, mt * 16 - 11), 320, 64, PANELS, 5)):
-        rng = np.random.default_rng(mt * 100 + nt * 10 + epi + split)
+    check_gemm(torch, B.ax_dbg_gemm_regs, split, epi, slices, 16 * mt, 16 * nt, mt * 100 + nt * 10 + epi + split,
+               ((min(mt * 16 + 5, 256), 576, 64, STRIPS, 70), (mt * 16, 64 * slices, 128, ROWS, 5), (max(17, mt * 16 - 11), 320, 64, PANELS, 5)))
+
+
+@pytest.mark.parametrize("rows,cols,epi,slices", [(r, c, epi, slices) for r, c in BLOCKS for epi in (RESIDUAL, SWIGLU, QKV) for slices in (1, 3)
+                                                  if not (epi == SWIGLU and ((r, c) == (128, 128) or slices > 1))])
+def test_block_gemm_on_strips(torch, rows, cols, epi, slices):
+    """Hi + lo parts in strips on the block kernel, which takes them at 17 to 256 rows where it multiplies faster: a block that is mostly padding,
+    a last panel of 1, 4 and 13 rows, whole panels, more rows than a block's 128."""
+    from paper_2605_10380_amd import binding as B
+    check_gemm(torch, B.ax_dbg_gemm_block, 1, epi, slices, rows, cols, rows + cols + epi, ((20, 192, 64, STRIPS, 70), (109, 576, 128, STRIPS, 5),
+                                                                                       (177, 192, 64, STRIPS, 33), (256, 576, 64, STRIPS, 64)))
+
+
+def check_gemm(torch, gemm, split, epi, slices, tile_rows, tile_cols, seed, calls):
+    """Calls of (rows, K, head_dim, layout, partial sums behind the pending norm) on one tile against float64."""
+    for M, K, hd, layout, n_sums in calls:
+        rng = np.random.default_rng(seed)
         N, Hq = (640 if hd == 128 and epi == QKV else 320), 3
         parts, a, w = operands(rng, M, N, K, split)
         dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
@@ -50,7 +66,7 @@ def test_register_gemm(torch, split, epi, slices, mt, nt):
         rows = (M + 15) // 16 * 16 if layout == STRIPS else M
         by_part = layout == STRIPS or (layout == PANELS and M > 32)
         keep = dict(A=dev(lay(parts)), W=bf(w))
-        args = dict(epilogue=epi, rows=16 * mt, cols=16 * nt, slices=slices, M=M, N=N, K=K, a_lo=rows * K if split else 0, a_panels=layout)
+        args = dict(epilogue=epi, rows=tile_rows, cols=tile_cols, slices=slices, M=M, N=N, K=K, a_lo=rows * K if split else 0, a_panels=layout)
         ref = a @ O.widen(w).T
         if epi != RESIDUAL:
             ssq = rng.uniform(0.1, 2.0, (M, n_sums)).astype(np.float32)
@@ -83,7 +99,7 @@ def test_register_gemm(torch, split, epi, slices, mt, nt):
             keep.update(pool=pool, row_pos=dev(pos), row_slot=dev(slot), cos=dev(np.cos(ang).astype(np.float32)), sin=dev(np.sin(ang).astype(np.float32)))
             args.update(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=hd, pool_blocks=n_blocks)
         torch.cuda.synchronize()
-        n_out = B.ax_dbg_gemm_regs(**args, **{k: t.data_ptr() for k, t in keep.items()})
+        n_out = gemm(**args, **{k: t.data_ptr() for k, t in keep.items()})
         what = (M, K, layout)
         if epi == RESIDUAL:
             want, got = c0 + ref, keep["C"].cpu().numpy().astype(np.float64)
@@ -122,3 +138,24 @@ def test_tiles_that_are_not_built_are_refused(torch):
         with pytest.raises(B.AxError):
             B.ax_dbg_gemm_regs(**dict(dict(slices=1, M=32, N=192, K=64, A=p, W=p, W2=p, C=p, C16=p, gain=p, ssq_out=p, split_ws=p, split_ws_bytes=1 << 17,
                                            n_q_heads=1, n_kv_heads=1, head_dim=64, pool=p, pool_blocks=1, row_pos=p, row_slot=p, cos=p, sin=p), **args))
+
+
+# one layer, hi + lo parts or not, and what its plans take for QKV, O, gate / up and down (with K slices): the register kernel whole and in slices; hi + lo
+# parts with gate / up, QKV in slices and both residual GEMMs on blocks
+LAYERS = [((256, 4, 2, 64, 320), 40, 0, ("regs", "regs", "regs", "regs")), ((512, 8, 2, 64, 8192), 48, 0, ("regs", "regs", "regs", "regs4")),
+          ((1024, 8, 4, 128, 9216), 201, 1, ("regs", "regs", "block", "regs8")), ((4096, 32, 8, 128, 320), 121, 1, ("block4", "regs4", "regs", "regs")),
+          ((9536, 4, 2, 64, 768), 249, 1, ("regs", "block", "regs", "block"))]
+
+
+@pytest.mark.parametrize("dims,rows,split,plan", LAYERS)
+def test_layer_of_17_to_256_rows(torch, dims, rows, split, plan):
+    from test_gpu_kernels import _one_layer
+    from paper_2605_10380_amd import binding as B
+    d, hq, hkv, hd, F = dims
+    qkv = (hq + 2 * hkv) * hd
+    got = [B.ax_dbg_strip_plan(e, rows, n, k, bool(split), 256 * max(8 * d, qkv) * 4) for e, n, k in ((QKV, qkv, d), (RESIDUAL, d, hq * hd), (SWIGLU, F, d), (RESIDUAL, d, F))]
+    assert tuple(k + (str(s) if s > 1 else "") for k, _, _, s in got) == plan
+    sh = I.DecoderShape("strips", 1, d, hq, hkv, hd, F, 512, "bf16")
+    attn, attn_ref, x, x_ref = _one_layer(torch, sh, 37, rows, 24, 256, split)
+    assert np.abs(attn - attn_ref).max() <= 4e-3 * np.abs(attn_ref).max()
+    assert np.abs(x - x_ref).max() <= 4e-3 * np.abs(x_ref).max()

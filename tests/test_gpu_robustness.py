@@ -140,8 +140,9 @@ SPLIT_SHAPES = {
 @pytest.mark.parametrize("which", list(SPLIT_SHAPES))
 def test_split_activations_every_kernel_family(B, which):
     """ax_model_config.act_split = 1: activations between kernels as hi + lo fp16 pairs.  Row counts
-    chosen so that every GEMM family (few-row, LDS tiles with and without K slices, streaming blocks)
-    and both attention kernels run with two-part operands, one sequence and several; against the
+    chosen so that the few-row, register, tile and block GEMMs (with and without K slices) and both
+    attention kernels run with two-part operands, one sequence and several (streaming SwiGLU and the block
+    kernel on strips need wider layers: test_gpu_many_rows.py, test_gpu_regs.py); against the
     oracle, and against the same calls on a model without the split: the split must not be worse,
     and over the run its worst error must be clearly smaller."""
     sh = SPLIT_SHAPES[which]
