@@ -123,8 +123,8 @@ Layout make_layout(const ax_model_config& c) {
     }
     L.partials = take(c.dtype == AX_BF16 ? 2 * L.max_records * ((size_t)c.head_dim * 32 + 64) * 4 : 0);
     // fp32 slabs of GEMMs that finish in a second kernel: K-slice partials of the residual GEMMs (SPLITK_MAX slabs of
-    // [T, d_model]; the SwiGLU GEMM's slices take what fits) and the raw products of the QKV GEMM from 65 rows up, which
-    // needs ONE whole [T, (Hq + 2 Hkv) hd] slab whatever the ratio of that width to d_model
+    // [T, d_model]), of QKV GEMMs on the block kernel (what fits), and the raw products of QKV GEMMs on the tile kernel, which
+    // need ONE whole [T, (Hq + 2 Hkv) hd] slab whatever the ratio of that width to d_model
     L.splitk_bytes = c.dtype == AX_BF16 ? std::max(T * c.d_model * 4 * ax::SPLITK_MAX,
                                                    T * (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * 4) : 0;
     L.splitk = take(L.splitk_bytes);

@@ -679,7 +679,7 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
     constexpr bool DUAL = COLS == 8 && NB == 1;
     const unsigned wod = (unsigned)(packed_row(min(n0 + (lr & 7), N - 1), K) - first_panel + lg * PK_KG + (lr >> 3) * PK_CHUNK) * 2u;
     auto weights = [&](const char* base, unsigned off, int k) { return (const u32x4*)(base + (long long)k * 32 + off); };
-    // A in panels (act_index): a row tile is one of them.  32 k of 9 rows are 576 bytes in a row, 4 or 5 lines instead of 9 halves.
+    // A in panels (act_index), up to 16 rows only: the row tile is the panel.  32 k of 9 rows are 576 bytes in a row, 4 or 5 lines instead of 9 halves.
     unsigned xo[MT];
     int xs[MT];                                                     // bytes per k
 #pragma unroll
@@ -687,8 +687,9 @@ void gemm_bf16_skinny_kernel(GemmArgs g) {
         const int m = min(t * 16 + lr, M - 1);
         const int row = a_rows ? a_rows[m] : m;
         const int first = t * 16, panel_rows = min(16, g.a_total_rows - first);
-        xs[t] = g.a_layout ? panel_rows * 2 : 2;
-        xo[t] = g.a_layout ? (unsigned)first * (unsigned)K * 2u + (row - first) * 16u + lg * panel_rows * 16u : (unsigned)row * (unsigned)K * 2u + lg * 16u;
+        const bool panel = MT == 1 && g.a_layout;
+        xs[t] = panel ? panel_rows * 2 : 2;
+        xo[t] = panel ? (unsigned)first * (unsigned)K * 2u + (row - first) * 16u + lg * panel_rows * 16u : (unsigned)row * (unsigned)K * 2u + lg * 16u;
     }
     auto acts = [&](int t, int part, int k) { return (const f16x8*)((const char*)(part ? X + g.a_lo_off : X) + (long long)k * xs[t] + xo[t]); };
 
@@ -1012,12 +1013,11 @@ static const int kQkvTile = env_int("AX_QKV_TILE", -1);   // experiment knobs: f
 static const int kResTile = env_int("AX_RES_TILE", -1);
 static const int kResBig = env_int("AX_RES_BIG", 256);
 static const int kQkvKs = env_int("AX_QKV_KS", 0);   // experiment knob: K slices of the QKV GEMM (1 = never split)
-// Which blocks and how many K slices the tile kernel takes for a QKV or residual GEMM (ws_bytes: room for slabs).
-// Two block shapes, both of 8 wavefronts: 64 x 128 (2 x 4 wavefronts of 32 x 32) and 128 x 128
-// (wavefront tile 64 x 32).  The larger one pulls a third fewer operand bytes per output and
-// wins wherever it still gives the chip enough blocks (measured per GEMM class below).
-// (Figures at 256 rows and fewer below are from when these blocks served such calls, now the register kernel's; the rules, of tiles and CUs, are
-// reached at 257-512 rows and by odd widths.)
+// Which blocks and how many K slices the tile kernel takes for a QKV or residual GEMM (ws_bytes: room for slabs).  Reached by layers that keep rows,
+// 257-304 rows of most widths and up to 512 of layers much wider than d_model (plan_many weighs it against the block kernel), and by widths that
+// are no multiple of 64.  Two block shapes, both of 8 wavefronts: 64 x 128 (2 x 4 wavefronts of 32 x 32) and 128 x 128 (wavefront tile 64 x 32), which
+// pulls a third fewer operand bytes per output.  At 257-304 rows of the ~1B, ~3B and ~8B layers it is 64-row blocks that stay ahead of the block
+// kernel, in us: ~1B QKV in 2 slices 12.9 (block kernel 13.1), ~3B down in 2 slices 28.4 (31.2), ~8B QKV in hi + lo parts, whole, 41.5 (43.7).
 struct TilePlan { bool big; int ks; };
 template <int EPI>
 static TilePlan plan_tile(int M, int N, int K, size_t ws_bytes) {
@@ -1027,39 +1027,33 @@ static TilePlan plan_tile(int M, int N, int K, size_t ws_bytes) {
     const bool pad_ok = (long long)((M + 127) / 128) * 128 * 100 <= (long long)((M + 63) / 64) * 64 * 115;
     const size_t slab = (size_t)M * N * sizeof(float);
     if constexpr (EPI == EPI_QKV) {
-        // 128-row blocks from 80 tiles up (~3B / ~8B at M = 256: 36 -> 29 / 43 -> 34 us); the ~1B shape at M = 256 has 48 such
-        // tiles and stays with 64 rows
+        // 128-row blocks from 80 tiles up: fewer leave too many CUs idle.  64-row blocks: two slices only while both fit one round of 256 blocks
+        // (more blocks than CUs run two to a CU and gain nothing from the cut: ~1B at 384 rows 26.8 -> 24.7 us whole, ~3B / ~8B at 320 rows
+        // 35.2 -> 32.3 / 43.0 -> 39.1 us)
         const bool big = kQkvTile >= 0 ? kQkvTile > 0 : (pad_ok && tiles128 >= 80);
-        // 64-row blocks: two slices only while both fit one round of 256 blocks (more blocks than CUs run two to a
-        // CU and gain nothing from the cut: ~1B at 384 rows 26.8 -> 24.7 us, ~3B / ~8B at 320 rows 35.2 -> 32.3 / 43.0 -> 39.1 us)
         int ks = big ? (tiles128 < 128 ? 2 : 1) : (tiles64 * 2 <= 256 ? 2 : 1);
-        // three slices where they fill the chip better than two and K divides (~3B at 193-256 rows: 80 tiles,
-        // 240 blocks instead of 160: 30.6 -> 28.8 us; four slices, 320 blocks in two rounds: 37.5 us)
+        // three slices of 128-row blocks where they fill the chip better than two and K divides (80 tiles: 240 blocks instead of 160; four, 320
+        // blocks, would be two rounds)
         if (big && ks == 2 && tiles128 * 3 <= 256 && K % (3 * 64) == 0 && K / (3 * 64) >= 8 && 3 * slab <= ws_bytes) ks = 3;
         if (kQkvKs > 0) ks = kQkvKs;
         while (ks > 1 && (K % (ks * 64) != 0 || ks * slab > ws_bytes)) ks >>= 1;
         return {big, ks};
     } else {
-        // Few output tiles (M = 256 against N = 2048 is 64 tiles of 64 x 128 for 256 CUs): cut K
-        // until there are ~256 blocks, each still with 8 or more k-steps; fp32 partial slabs go to
-        // the workspace and residual_reduce_kernel finishes.
+        // Few output tiles (320 rows against N = 2048 are 80 tiles of 64 x 128 for 256 CUs): cut K until there are ~256 blocks, each still with 8 or
+        // more k-steps; fp32 partial slabs go to the workspace and residual_reduce_kernel finishes.
         auto slices = [&](long long tiles) {
             int ks = 1;
             if (!ws_bytes || N % 64 != 0) return ks;
-            // (a cut that would overshoot one round of 256 blocks is not taken once 144 or more CUs have a block:
-            // ~3B at 193-256 rows, 96 tiles: 192 blocks instead of 384, O projection 20.6 -> 18.7 us, down projection -
-            // then on 128-row blocks, 4 slices, 192 blocks - 39.1 -> 30.7 us; ~1B at 384 rows 37.5 -> 30.2 us,
-            // ~8B O projection at 384 rows 39.3 -> 31.0 us, ~3B at 144 rows 18.5 -> 16.8 us)
+            // (a cut that would overshoot one round of 256 blocks is not taken once 144 or more CUs have a block: ~1B at 384 rows 37.5 -> 30.2 us,
+            // ~8B O projection at 384 rows 39.3 -> 31.0)
             static const int fill = env_int("AX_SLICE_FILL", 144);   // measurement switch: 256 = always cut up to a full round
             while (ks < SPLITK_MAX && tiles * ks < 256 && !(tiles * ks >= fill && tiles * ks * 2 > 256) &&
                    K % (ks * 2 * 64) == 0 && K / (ks * 2 * 64) >= 8 && ks * 2 * slab <= ws_bytes)
                 ks *= 2;
             return ks;
         };
-        // 128-row blocks: when there are plenty of tiles without any cut (or more 64-row tiles than one
-        // round of two per CU), or when K is long (down projection) and at most 4 slices give ~200 blocks or more.
-        // Measured against 64-row blocks: ~8B down projection 57 -> 49 us at M = 256, 98 -> 81 at 512;
-        // ~1B at M = 256 would need 8 slices and is no faster, so it keeps 64-row blocks.
+        // 128-row blocks: when there are plenty of tiles without any cut (or more 64-row tiles than one round of two per CU), or when K is long (down
+        // projection) and at most 4 slices give ~200 blocks or more (~8B down projection at 512 rows 98 -> 81 us).
         const int ks128 = slices(tiles128);
         const bool big = kResTile >= 0 ? kResTile > 0 : (pad_ok && (tiles128 >= kResBig || tiles64 > 256 || (K >= 4096 && ks128 <= 4 && tiles128 * ks128 >= 192)));
         return {big, big ? ks128 : slices(tiles64)};
@@ -1072,8 +1066,8 @@ static int launch_lds_tile(const GemmArgs& g, hipStream_t s) {
     if constexpr (EPI == EPI_QKV) {
         // A plain store GEMM writes fp32 products, a second kernel does the rms scaling, rotary
         // embedding and KV append: measured faster than a fused epilogue (one head per wavefront)
-        // at every size tried (M = 256 / 512, all three model shapes).  With few tiles K is cut in
-        // two slices that the second kernel adds up.
+        // at 512 rows of all three model shapes.  With few tiles K is cut in slices that the second
+        // kernel adds up.
         // (The workspace holds at least one [M, N] fp32 slab - a model's layout reserves max_tokens x N of it
         // whatever the ratio of N to d_model; a caller that brings less gets nothing launched.)
         const TilePlan t = plan_tile<EPI>(M, N, K, g.split_ws ? g.split_ws_bytes : 0);
@@ -1212,10 +1206,11 @@ static void launch_swiglu_stream(const GemmArgs& g, int tm, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------ 17-256 rows
-// The register kernel (k_gemm_regs.h): tile and K slices by the times of all tiles that are built, alone and on cold weights, for the four GEMMs
-// of the ~1B, ~3B and ~8B (hi + lo) layers at 2-16 panels of rows, 600 launches, most within 1.5 us.  A round of blocks is its first
-// round trips, sums and epilogue, and per 32 k the panels of W that no other row block has brought to the L2 and, cheaper, all others.
-// Slices cost slabs and the kernel that adds them up.  Inside models the forms chosen so are the fastest or within 2 us of it at 17-256 rows.
+// The register kernel (k_gemm_regs.h): tile and K slices by a time fitted to all tiles that are built, alone and on cold weights, for the four GEMMs
+// of the ~1B, ~3B and ~8B (hi + lo) layers at 2-16 panels of rows, 600 launches, most within 1.5 us.  A round of 256 blocks is 3.4-4.4 us of first round trips,
+// sums and epilogue and, per 32 k, 0.025 us for each panel of W that no other row block has brought to the L2 (1 KB: 41 GB/s a CU; less while few CUs
+// ask) and 0.0145 for every other panel (70 GB/s).  Slices cost slabs and the kernel that adds them up.  Inside models the forms chosen so are the fastest or
+// within 2 us of it at 17-256 rows.  More than one round is taken where it pulls less (~8B gate / up at 176 rows: 448 blocks).
 struct RegsPlan { int shape, ks; float us; };
 static RegsPlan plan_regs(Epilogue epi, int M, int N, int K, bool split, bool slices, size_t ws_bytes) {
     RegsPlan best{-1, 1, 0.f};
@@ -1349,7 +1344,9 @@ GemmPlan gemm_panel_plan(Epilogue epi, int M, int N, int K, bool split, size_t w
     return block_plan(plan_gemm_block(epi, M, N, K, split, true, ws_bytes));
 }
 
-// Up to 16 rows one panel, plain activations of up to 32 rows two; up to 256 rows strips.
+// Up to 16 rows one panel, which the few-row kernel reads in fewer lines than rows; up to 256 rows strips, except plain activations of 17-32 rows, which
+// keep panels: both are read by the register kernel, at 17-20 rows panels are ahead (us a call, panels / strips: ~1B 17 rows 937 / 954, ~3B 2066 / 2116), at
+// 24-32 strips (~1B 976 / 963 and 1020 / 974, ~3B 2153 / 2133 and 2258 / 2149).
 // More than 256 rows, by the times that the plans expect: panels make the block kernel faster at every size, but only that kernel reads them,
 // and the ones made for fewer rows are ahead of it where its third row tile is mostly padding (~8B at 257 rows: rows 11.4 ms, panels 11.8) and
 // in layers much wider than d_model.  Rows where they are expected 4 % ahead, 8 % with more than 3/8 of that tile filled: over 19 layers at 17

@@ -4,14 +4,15 @@
 // part of K, so no operand is read twice by a block, nothing is staged, and there is no barrier until the partial sums meet in LDS.  With A in
 // panels of 16 rows and W packed, every load is the 1 KB that one lane order of the 16x16x32 MFMA takes.
 //
-// What bounds it: how fast a CU is filled.  A CU takes 120 GB/s out of its XCD's L2, 27 from HBM with all CUs at work, and its loads return in
-// order, so the two add up: one round of blocks costs (bytes of W that miss) / 27 + (the rest of the operands) / 120 + about 5 us of first
-// round trips, sum over wavefronts and epilogue.  So the tile is the one that pulls the least over the whole launch while every CU has
-// at most one block (plan_regs).  Against the kernels that served these rows before - 64-row tiles in LDS or streaming blocks, with K slices and a
+// What bounds it: how fast a CU is filled.  A probe takes 120 GB/s a CU out of its XCD's L2 and 27 from HBM with all CUs at work, and loads return in
+// order, so the two add up; beside its products and its sums this kernel reaches 70 and 41 (weights that few CUs ask for at once among them),
+// and a round of blocks starts and ends for 3.4-4.4 us.  plan_regs takes the tile and the K slices with the least such time, mostly one round of 256 blocks or fewer.
+// Against the kernels that served these rows before - 64-row tiles in LDS or streaming blocks, with K slices and a
 // kernel that adds them up - in us a layer's GEMM, those kernels included: ~3B at 144 rows
-// QKV 21.8 -> 18.7, O 18.6 -> 14.4, gate / up 46.5 -> 31.5, down 28.3 -> 27.7; ~8B (hi + lo) at 17 rows 24.8 -> 18.3, 14.6 -> 13.5, 44.8 -> 35, 27.3 -> 29.8.
-// Whole calls: ~1B 48 rows 1246 -> 988, 100 rows 1424 -> 1200, 256 rows 1786 -> 1726; ~3B 64 rows 2804 -> 2558, 16 sessions of 9 rows 5185 -> 4692; ~8B
-// 24 rows 4384 -> 4148, 160 rows 9818 -> 7471.
+// QKV 21.8 -> 18.7, O 18.6 -> 14.4, gate / up 46.5 -> 31.5, down 28.3 -> 27.7; ~8B (hi + lo) at 17 rows 24.8 -> 18.3, 14.6 -> 13.5, 44.8 -> 35, 27.3 -> 29.8;
+// at 256 rows of ~1B gate / up 27.5 -> 28.4, the other three and so the call ahead.
+// Whole calls, timed in turn: ~1B 48 rows 1298 -> 1030, 100 rows 1508 -> 1281, 256 rows 1717 -> 1640 over 2048 cached keys, 1724 -> 1706 over 4096; ~3B 64 rows 2808 ->
+// 2555, 256 rows 4048 -> 4001; ~8B 24 rows 4401 -> 4075, 160 rows 10134 -> 7552, 256 rows 10213 -> 9054.
 #pragma once
 
 #include "gemm_device.h"
