@@ -682,6 +682,33 @@ def test_shared_prefix_in_slices_of_no_power_of_two(B, hkv, G, split, n, T, P, h
     dm.close()
 
 
+@pytest.mark.parametrize("T,n,split", [(24, 1, 0), (200, 1, 0), (90, 1, 1), (9, 16, 0), (9, 6, 1)])
+def test_calls_repeat_bit_for_bit(B, T, n, split):
+    """17 to 256 rows, alone and over a shared prefix: no sum depends on which wavefront or block comes first, nor on what a model ran before."""
+    sh = I.DecoderShape("again", 2, 512, 8, 2, 128, 1024, 512, "bf16")
+    w = I.make_weights(sh, 47)
+    prefix = I.templated_prompt(sh.vocab, 47, 2100)
+    news = [I.zipf_tokens(sh.vocab, 47, f"n{s}", T) for s in range(n)]
+
+    def passes(dm, times):
+        root = dm.new_kv()
+        dm.extend(root, prefix)
+        for _ in range(times):
+            kvs = [B.ax_kv_fork(root, -1) for _ in range(n)]
+            yield dm.extend_batch(kvs, news, B.AX_OUT_ALL_LOGITS).cpu().numpy()
+            for kv in kvs:
+                B.ax_kv_free(kv)
+        B.ax_kv_free(root)
+
+    first = None
+    for _ in range(2):
+        dm = B.DeviceModel(sh, w, max_pos=2500, max_tokens=2112, pool_tokens=8192, max_seqs=n + 1, act_split=split)
+        for got in passes(dm, 3):
+            first = got if first is None else first
+            assert np.array_equal(got, first)
+        dm.close()
+
+
 def test_two_resident_models_forked_sessions(B):
     """The plan-out agent's shape at a size the oracle can follow: two decoders with their own
     weights and pools resident together; per model, sessions fork one shared prefix, build
