@@ -774,8 +774,8 @@ void attn_block_kernel(AttnArgs a) {
 
 // The shared-prefix pass of a many-sequence call and the private keys of its sequences in one launch: blocks of the former first, one on every CU, the
 // latter beside them.  The pass is bound by its products and the private keys by memory (16 sessions of the ~3B shape over 6144 shared and 1024-2048
-// private keys: 21.1 and 26.8 us one after the other, 39.2 together; with half as many records of the shared keys, on blocks of 4 tiles instead of 8, the
-// merge takes 8.3 instead of 12.6).
+// private keys: 21.1 and 26.8 us one after the other, 38.9 together; with half as many records of the shared keys, on blocks of 4 tiles instead of 8, the
+// merge takes 8.2 instead of 12.6).
 template <int HD, bool QS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_shared_kernel(AttnArgs sh, AttnArgs a, int items, int tiles) {
